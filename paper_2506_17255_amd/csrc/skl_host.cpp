@@ -357,13 +357,17 @@ static void plan_prefill(const skl_desc_t *d, skl_plan *P)
     // blocks (34816 B each), a 1 KiB dummy row and the block metadata in LDS
     L.gemm_v3 = L.max_ptable_bytes <= 48 * 1024 &&
                 2ull * L.max_ptable_bytes + 2ull * 34816 + 1024 + 32ull * P->bmeta.size() + 256 <= SKL_LDS_HARD_BYTES ? 1 : 0;
-    // staged kernel: dense 16-entry steps along the channel list, four per 64-channel block; entries past
-    // the end of the list are empty steps (zero activation words)
+    // staged kernel: dense 32-entry steps along the channel list, two per 64-channel block (entries past the end of
+    // the list are empty: zero activation words), and the windows of X that the packing kernel stages
     L.gemm_kb = (L.n_packed + 63) / 64;
-    P->ssteps.clear();
-    for (uint32_t st = 0; st < 4 * L.gemm_kb; ++st) {
-        const uint32_t c0 = 16 * st;
-        P->ssteps.push_back(skl_gemm_step{std::min(c0, L.n_packed), c0 >= L.n_packed ? 0u : std::min(2u, (L.n_packed - c0) / 8)});
+    P->windows.clear();
+    for (uint32_t e0 = 0; e0 < 64 * L.gemm_kb; e0 += 32 * PO_STEPS) {
+        uint32_t lo = SKL_NO_CHANNEL, hi = 0;
+        for (uint32_t e = e0; e < std::min(e0 + 32 * PO_STEPS, L.n_packed); ++e)
+            if (P->chan[e] != SKL_NO_CHANNEL) lo = std::min(lo, P->chan[e]), hi = std::max(hi, P->chan[e] + 1);
+        skl_pack_window w{lo == SKL_NO_CHANNEL ? 0u : lo / 8 * 8, 0u};
+        if (hi > w.base && hi - w.base <= PO_WINDOW) w.n = hi - w.base;
+        P->windows.push_back(w);
     }
     // Which kernel a call takes.  Layers whose tables the fused kernel cannot keep in LDS always rebuild
     // their weights once per call.  The others do so from 513 tokens on: measured on MI355X
@@ -525,10 +529,10 @@ static skl_status_t make_plan(const skl_desc_t *user, skl_plan *P)
     uint64_t off = 4096;
     if (L.path == 1) {
         L.off_bmeta = off;  off = align_up(off + P->bmeta.size() * sizeof(skl_block_meta), 256);
-        L.off_chan = off;   off = align_up(off + P->chan.size() * sizeof(uint32_t), 256);
+        L.off_chan = off;   off = align_up(off + align_up(P->chan.size(), 32 * PO_STEPS) * sizeof(uint32_t), 256);     // read in whole windows
         L.off_ginfo = off;  off = align_up(off + P->ginfo.size() * sizeof(skl_group_info), 256);
         L.off_gsteps = off; off = align_up(off + P->gsteps.size() * sizeof(skl_gemm_step), 256);
-        L.off_ssteps = off; off = align_up(off + P->ssteps.size() * sizeof(skl_gemm_step), 256);
+        L.off_windows = off; off = align_up(off + P->windows.size() * sizeof(skl_pack_window), 256);
         if (!L.qbits) {
             L.off_tables = off; off = align_up(off + L.table_bytes, 256);
             L.off_ptables = off; off = align_up(off + L.ptable_bytes, 256);
@@ -657,9 +661,10 @@ skl_status_t sketch_linear_create(const skl_desc_t *desc, void *dev_buf, uint64_
     if (L.path == 1) {
         memcpy(img.data() + L.off_bmeta, P.bmeta.data(), P.bmeta.size() * sizeof(skl_block_meta));
         memcpy(img.data() + L.off_chan, P.chan.data(), P.chan.size() * sizeof(uint32_t));
+        for (uint64_t i = P.chan.size(); i % (32 * PO_STEPS); ++i) reinterpret_cast<uint32_t *>(img.data() + L.off_chan)[i] = SKL_NO_CHANNEL;
         memcpy(img.data() + L.off_ginfo, P.ginfo.data(), P.ginfo.size() * sizeof(skl_group_info));
         memcpy(img.data() + L.off_gsteps, P.gsteps.data(), P.gsteps.size() * sizeof(skl_gemm_step));
-        memcpy(img.data() + L.off_ssteps, P.ssteps.data(), P.ssteps.size() * sizeof(skl_gemm_step));
+        memcpy(img.data() + L.off_windows, P.windows.data(), P.windows.size() * sizeof(skl_pack_window));
         // state offset of every input channel (one group per channel)
         for (uint32_t j = 0; j < L.in; ++j) base[j + 1] = base[j] + (uint64_t)L.d * desc->group_width[j];
         if (L.qbits) {

@@ -67,6 +67,14 @@ struct skl_gemm_step {
     uint32_t n_words;      // 1 or 2
 };
 
+// Staged prefill: where in a row of X the channels of PO_STEPS consecutive steps of 32 channel-list entries lie.
+#define PO_STEPS 8u
+#define PO_WINDOW 384u         // most halfs of a window (a multiple of 128: 16 threads copy 8 halfs each at a time)
+struct skl_pack_window {
+    uint32_t base;         // first channel of the window, a multiple of 8
+    uint32_t n;            // channels in the window, at most PO_WINDOW; 0: the steps' channels are further apart
+};
+
 struct skl_layer {
     uint32_t in = 0, out = 0, tj = 0, to = 0, d = 0;
     uint32_t A[SKL_MAX_D] = {0}, C[SKL_MAX_D] = {0};
@@ -113,9 +121,9 @@ struct skl_layer {
     uint32_t gemm_v3 = 0, n_gsteps = 0;
     uint64_t off_gsteps = 0;
     // staged prefill (weights rebuilt once per call into the workspace): 64-channel blocks along the channel
-    // list, and its dense step list (4 steps of 16 list entries per block)
+    // list, and the windows of X that hold the channels of PO_STEPS steps of 32 list entries
     uint32_t gemm_staged_from = 0, gemm_kb = 0;     // calls with at least gemm_staged_from tokens are staged
-    uint64_t off_ssteps = 0;
+    uint64_t off_windows = 0;
 
     // low-bit states: only codes and scales are resident (row sketches: re-ordered into the word order of the
     // block tables); every call expands them into 16-bit tables at the end of its workspace
@@ -138,7 +146,7 @@ struct skl_plan {
     std::vector<uint32_t> bg_start;
     std::vector<skl_group_info> ginfo;
     std::vector<skl_gemm_step> gsteps;
-    std::vector<skl_gemm_step> ssteps;
+    std::vector<skl_pack_window> windows;
 };
 
 static inline bool skl_gemm_is_staged(const skl_layer *L, uint32_t tokens) { return tokens >= L->gemm_staged_from; }

@@ -24,16 +24,6 @@ namespace SKL_NS {
 #define PK_PARTS (SKL_WG / (2u * PK_STEPS))     // threads per word: each takes 32 / PK_PARTS tokens
 static_assert(2 * PK_STEPS * PK_PARTS == SKL_WG && 32 % PK_PARTS == 0, "one thread per (word, part of the row block)");
 
-__device__ __forceinline__ uint32_t neg_half_pair(uint32_t e, uint32_t x_dt)
-{
-    if (x_dt == SKL_BF16) {
-        const uint32_t lo = float_to_half_bits(__builtin_bit_cast(float, e << 16));
-        const uint32_t hi = float_to_half_bits(__builtin_bit_cast(float, e & 0xFFFF0000u));
-        e = lo | (hi << 16);
-    }
-    return e ^ 0x80008000u;
-}
-
 __global__ __launch_bounds__(SKL_WG) void k_pack_activations3(const uint16_t *__restrict__ X, uint32_t x_dt, uint32_t ldx,
                                                                uint32_t tokens, uint32_t in, const uint32_t *__restrict__ chan,
                                                                const skl_gemm_step *__restrict__ steps, uint32_t n_steps,
@@ -412,7 +402,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // adds the partials of one accumulator block of a leftover tile in workgroup order and stores it;
 // grid (8 * l_max, 16), 256 threads laid out as in the third kernel
 __global__ __launch_bounds__(256) void k_gemm3_fixup(G3Split sp, const float *__restrict__ parts, void *Y, uint32_t y_dt,
-                                                     uint32_t ldy, uint32_t tokens, uint32_t out, uint32_t tile0)
+                                                     uint32_t ldy, uint32_t tokens, uint32_t out)
 {
     const uint32_t xcd = blockIdx.x / sp.l_max, l = blockIdx.x % sp.l_max, ab = blockIdx.y;
     if (l >= sp.left(xcd)) return;
@@ -433,7 +423,7 @@ __global__ __launch_bounds__(256) void k_gemm3_fixup(G3Split sp, const float *__
         }
     }
     const uint32_t rb = ab >> 3, cb = ab & 7;
-    const uint32_t o = (tile0 + tile_n) * GM3_NT + cb * 32 + n;    // tile0: first output tile of the slab the split covers
+    const uint32_t o = tile_n * GM3_NT + cb * 32 + n;
     if (o >= out) return;
 #pragma unroll
     for (int i4 = 0; i4 < 4; ++i4) {
@@ -473,7 +463,7 @@ uint64_t skl_gemm_workspace_bytes(const skl_layer *L, uint32_t tokens)
 }
 
 // activation re-ordering for the prefill kernels
-skl_status_t skl_launch_pack(const skl_layer *L, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx, uint32_t tokens,
+static skl_status_t launch_pack(const skl_layer *L, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx, uint32_t tokens,
                              const uint32_t *chan, const skl_gemm_step *steps, uint32_t n_steps, uint4 *Xp, hipStream_t stream)
 {
     skl_status_t st = allow_lds(k_pack_activations3, PK_LDS_BYTES);
@@ -483,10 +473,10 @@ skl_status_t skl_launch_pack(const skl_layer *L, const uint16_t *X, skl_dtype_t 
     return check_launch("activation packing");
 }
 
-skl_status_t skl_launch_gemm3_fixup(const G3Split &sp, const float *parts, void *Y, skl_dtype_t y_dt, uint32_t ldy,
-                                    uint32_t tokens, uint32_t out, uint32_t tile0, hipStream_t stream)
+static skl_status_t launch_gemm3_fixup(const G3Split &sp, const float *parts, void *Y, skl_dtype_t y_dt, uint32_t ldy,
+                                    uint32_t tokens, uint32_t out, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_gemm3_fixup, dim3(8 * sp.l_max, 16), dim3(256), 0, stream, sp, parts, Y, (uint32_t)y_dt, ldy, tokens, out, tile0);
+    hipLaunchKernelGGL(k_gemm3_fixup, dim3(8 * sp.l_max, 16), dim3(256), 0, stream, sp, parts, Y, (uint32_t)y_dt, ldy, tokens, out);
     return check_launch("gemm fix-up");
 }
 
@@ -510,7 +500,7 @@ skl_status_t skl_launch_gemm(const skl_layer *L, const void *X_, skl_dtype_t x_d
         if (staged) return skl_launch_gemm_staged(L, src, X, x_dt, ldx, Y, y_dt, ldy, tokens, ws, stream);
         {
             const skl_gemm_step *steps = reinterpret_cast<const skl_gemm_step *>(L->dev + L->off_gsteps);
-            st = skl_launch_pack(L, X, x_dt, ldx, tokens, a.chan, steps, L->n_gsteps, static_cast<uint4 *>(ws), stream);
+            st = launch_pack(L, X, x_dt, ldx, tokens, a.chan, steps, L->n_gsteps, static_cast<uint4 *>(ws), stream);
             if (st != SKL_OK) return st;
             Gemm2Args g;
             g.h = a.h; g.ptables = src.ptables; g.bmeta = a.bmeta;
@@ -530,7 +520,7 @@ skl_status_t skl_launch_gemm(const skl_layer *L, const void *X_, skl_dtype_t x_d
             })
             if (st == SKL_OK) st = check_launch("gemm");
             if (st != SKL_OK || sp.l_max == 0) return st;
-            return skl_launch_gemm3_fixup(sp, g.parts, Y, y_dt, ldy, tokens, L->out, 0, stream);
+            return launch_gemm3_fixup(sp, g.parts, Y, y_dt, ldy, tokens, L->out, stream);
         }
     }
     return skl_tile_launch_gemm(L, src, X, x_dt, ldx, Y, y_dt, ldy, tokens, stream);

@@ -1,23 +1,28 @@
-// Shared by the prefill kernels: tile shapes, the activation re-ordering
-// pre-pass and the operand rebuild used by producers.
+// Shared by the prefill kernels: tile shapes, the operand rebuild used by producers and the epilogues of
+// the fused kernel.
 #pragma once
 #include "skl_device.h"
 #include "skl_split.h"
 
-struct skl_gemm_step;
-struct G3Split;
 namespace SKL_NS {
-// activation re-ordering for the second and third prefill kernels (skl_prefill.hip)
-skl_status_t skl_launch_pack(const skl_layer *L, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx, uint32_t tokens,
-                             const uint32_t *chan, const skl_gemm_step *steps, uint32_t n_steps, uint4 *Xp, hipStream_t stream);
 // staged prefill (skl_prefill_staged.hip): workspace bytes of a call (activation words, partial tiles, weight words)
 uint64_t skl_gemm_staged_bytes(const skl_layer *L, uint32_t tokens);
 skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx,
                                     void *Y, skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, void *ws, hipStream_t stream);
-// adds the partials of the leftover tiles in workgroup order and stores them (skl_prefill.hip)
-skl_status_t skl_launch_gemm3_fixup(const G3Split &sp, const float *parts, void *Y, skl_dtype_t y_dt, uint32_t ldy,
-                                    uint32_t tokens, uint32_t out, uint32_t tile0, hipStream_t stream);
 }  // namespace SKL_NS
+
+typedef float float4v __attribute__((ext_vector_type(4)));
+
+// two activations -> two binary16 values with inverted sign bits
+__device__ __forceinline__ uint32_t neg_half_pair(uint32_t e, uint32_t x_dt)
+{
+    if (x_dt == SKL_BF16) {
+        const uint32_t lo = float_to_half_bits(__builtin_bit_cast(float, e << 16));
+        const uint32_t hi = float_to_half_bits(__builtin_bit_cast(float, e & 0xFFFF0000u));
+        e = lo | (hi << 16);
+    }
+    return e ^ 0x80008000u;
+}
 
 #define GM_NT 128            // outputs per workgroup
 #define GM_THREADS 512       // four compute + four copy wavefronts
@@ -94,7 +99,7 @@ __device__ __forceinline__ void g2_build(const uint32_t (&off)[4][D], uint32_t t
 }
 
 
-// ---- 256 x 256 output tiles: shared by the fused and the staged prefill kernel ----
+// ---- 256 x 256 output tiles of the fused prefill kernel ----
 #define G3_CB_WORDS (8u * G2_ROW)
 #define G3_SLOT_BYTES (8u * G3_CB_WORDS * 16u)
 
@@ -107,9 +112,8 @@ __device__ __forceinline__ float acc_elem(float v)
     return r;
 }
 
-// RB: 32-row blocks per wavefront (2: 64 tokens x 256 outputs; 1: the half-height tiles of the staged kernel)
-template <int DT, int RB = 2>
-__device__ __forceinline__ void gemm3_store(const float16v (&acc)[8 * RB], void *Y, uint32_t ldy, uint32_t t0, uint32_t tokens,
+template <int DT>
+__device__ __forceinline__ void gemm3_store(const float16v (&acc)[16], void *Y, uint32_t ldy, uint32_t t0, uint32_t tokens,
                                             uint32_t o0, uint32_t out, uint32_t q)
 {
 #pragma unroll
@@ -117,7 +121,7 @@ __device__ __forceinline__ void gemm3_store(const float16v (&acc)[8 * RB], void 
         const uint32_t o = o0 + cb * 32;
         if (o >= out) continue;
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
+        for (int rb = 0; rb < 2; ++rb) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const uint32_t t = t0 + rb * 32 + (i >> 2) * 8 + q * 4 + (i & 3);
@@ -138,8 +142,8 @@ __device__ __forceinline__ void gemm3_store(const float16v (&acc)[8 * RB], void 
 // whole 512-byte (1 KiB for float32) rows of Y instead of 2-byte elements.  Needs 16-byte aligned rows.
 #define G3_EPI_BYTES 16896u             // per wavefront: 32 rows x (512 + 16) bytes, or 16 rows x (1024 + 16)
 static_assert(4 * G3_EPI_BYTES <= 2 * G3_SLOT_BYTES + 1024, "the epilogue areas must end below the block metadata");
-template <int DT, int RB = 2>
-__device__ __forceinline__ void gemm3_store_rows(const float16v (&acc)[8 * RB], uint32_t lds_wave, void *Y, uint32_t ldy,
+template <int DT>
+__device__ __forceinline__ void gemm3_store_rows(const float16v (&acc)[16], uint32_t lds_wave, void *Y, uint32_t ldy,
                                                  uint32_t t0, uint32_t tokens, uint32_t o_tile, uint32_t out, uint32_t lane)
 {
     constexpr uint32_t ES = DT == SKL_F32 ? 4 : 2;
@@ -148,7 +152,7 @@ __device__ __forceinline__ void gemm3_store_rows(const float16v (&acc)[8 * RB], 
     constexpr uint32_t ROWS = 32 / GROUPS, CH = 256 * ES / 16;  // rows per group, 16-byte pieces per row
     const uint32_t n = lane & 31, q = lane >> 5;
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
+    for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
         for (int gr = 0; gr < GROUPS; ++gr) {
 #pragma unroll

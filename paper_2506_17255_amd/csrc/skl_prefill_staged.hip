@@ -8,20 +8,18 @@
 //   1. k_rebuild_operands: one workgroup per (channel block, range of output tiles) stages the block's table
 //      in LDS once, runs select / gather / query / decode for all its outputs and writes the weights as
 //      16-byte matrix-core operand words, already in the order the product kernel's LDS slot has;
-//   2. k_staged_gemm: 256 tokens x 256 outputs per workgroup, one wavefront per SIMD with the 65536
-//      float32 accumulators in its registers (the shape of the fused kernel); per 64 channels a wavefront
-//      loads its own activation words straight into registers, copies a quarter of the workgroup's weight
-//      words into an LDS slot, and issues 64 MFMAs on words read back from the slot filled one block earlier.
-// The work split, partial tiles and fix-up pass are those of the fused kernel, dealt by output-tile column.
+//   2. k_staged_gemm: 256 tokens x 256 outputs per workgroup, a product of operand words that both come from
+//      memory (k_pack_operands re-orders the activations first).
+// The work split is that of the fused kernel, dealt by output-tile column.
 #include "skl_prefill_common.h"
 
 namespace SKL_NS {
 
 
-#define SG_SLOT_WORDS 2048u             // 64 channels x 256 outputs: [column block 8][row 8 = (step, half)][32 outputs] words
+#define SG_STEP_WORDS 1024u             // 32 channels x 256 outputs (or tokens): [16-wide block 16][channel group 4][16] words of eight channels
+#define SG_SLOT_WORDS (2u * SG_STEP_WORDS)
 #define SG_SLOT_BYTES (SG_SLOT_WORDS * 16u)
-static_assert(4 * G3_EPI_BYTES >= 2 * SG_SLOT_BYTES, "the epilogue areas are the larger use of LDS");
-#define SG_LDS_BYTES (4 * G3_EPI_BYTES)
+#define SG_EPI_BYTES 8704u              // epilogue, per wavefront: 32 rows x (64 float32 + 16 bytes)
 
 struct RebuildArgs {
     HashArgs h;
@@ -43,16 +41,16 @@ __device__ __forceinline__ void rebuild_body(const RebuildArgs &p, uint32_t blk,
     for (uint32_t tile = lo; tile < hi; ++tile) {
         // outputs past the end of the layer are rebuilt like the last one: their products are never stored
         const uint32_t o = min((p.tile0 + tile) * GM3_NT + threadIdx.x, p.out - 1);
-        uint4 *dst = p.Wp + (size_t)tile * p.KB * SG_SLOT_WORDS + (threadIdx.x >> 5) * 256 + (threadIdx.x & 31);
+        uint4 *dst = p.Wp + (size_t)tile * p.KB * SG_SLOT_WORDS + (threadIdx.x >> 4) * 64 + (threadIdx.x & 15);
         uint32_t off[D];
         row_offsets<D>(p.h, o, bm.K, RS, off);
 #pragma unroll
         for (int c = 0; c < NB; ++c) {
             const uint32_t w = w0 + c;
-            dst[(size_t)(w >> 3) * SG_SLOT_WORDS + (w & 7) * 32] = keys_to_neg_half8(row_query8<D>(tab, off, c));
+            dst[(size_t)(w >> 2) * SG_STEP_WORDS + (w & 3) * 16] = keys_to_neg_half8(row_query8<D>(tab, off, c));
         }
         if (pad)
-            for (uint32_t w = p.n_words; w < 8 * p.KB; ++w) dst[(size_t)(w >> 3) * SG_SLOT_WORDS + (w & 7) * 32] = make_uint4(0, 0, 0, 0);
+            for (uint32_t w = p.n_words; w < 8 * p.KB; ++w) dst[(size_t)(w >> 2) * SG_STEP_WORDS + (w & 3) * 16] = make_uint4(0, 0, 0, 0);
     }
 }
 
@@ -83,9 +81,76 @@ __global__ __launch_bounds__(SKL_WG) void k_rebuild_operands(RebuildArgs r)
     rebuild_block<D>(r, blockIdx.x);
 }
 
+// Activations to negated binary16, re-ordered into the matrix-core A words of k_staged_gemm:
+// [256-token tile][32-channel step][16-token block][channel group 4][16 tokens], a word being eight entries of the
+// channel list for one token.  A workgroup takes 16 tokens x PO_STEPS steps: it copies the window of X that holds
+// the steps' channels into LDS in its own order (whole aligned 16-byte pieces, coalesced) and builds the words from
+// 2-byte LDS reads, so that the channels which the width order moved away cost nothing (fetching every word that
+// spans such a gap channel by channel from memory took 5 of 15 us on layers with one percent of wide channels).
+// Steps whose channels are far apart (the wide channels themselves) have no window and are fetched from memory.
+// 2048 tokens x 4096 channels of such a layer, 16.8 MB in and out: 10 us, 15 before (5.1 TB/s would be 6.6).
+// grid (ceil(tokens / 16), ceil(steps / PO_STEPS))
+#define PO_STRIDE (PO_WINDOW + 8u)      // halfs per LDS row: 16-byte aligned rows on different banks
+__global__ __launch_bounds__(SKL_WG) void k_pack_operands(const uint16_t *__restrict__ X, uint32_t x_dt, uint32_t ldx, uint32_t tokens,
+                                                           uint32_t in, const uint32_t *__restrict__ chan,
+                                                           const skl_pack_window *__restrict__ windows, uint32_t n_steps,
+                                                           uint4 *__restrict__ Xp)
+{
+    __shared__ __align__(16) uint16_t rows[16 * PO_STRIDE];
+    const uint32_t t0 = blockIdx.x * 16, g = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t row = lane & 15, kg = lane >> 4;
+    const skl_pack_window win = windows[g];
+    constexpr uint32_t N = PO_STEPS / (SKL_WG / 64);            // steps per wavefront
+    u32x4v ch[N][2];                                            // this lane's channels (the list is padded to whole groups of steps)
+#pragma unroll
+    for (uint32_t i = 0; i < N; ++i) {
+        const u32x4v *c = reinterpret_cast<const u32x4v *>(chan + (g * PO_STEPS + wave + 4 * i) * 32 + kg * 8);
+        ch[i][0] = c[0];
+        ch[i][1] = c[1];
+    }
+    if (win.n) {
+        const uint32_t r = threadIdx.x >> 4;                    // 16 threads copy one token's row
+        const uint16_t *src = X + (size_t)min(t0 + r, tokens - 1) * ldx + win.base;
+        const bool vec = (ldx & 7u) == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;        // (base is a multiple of 8)
+#pragma unroll
+        for (uint32_t i = 0; i < PO_WINDOW / 128; ++i) {
+            const uint32_t c = ((threadIdx.x & 15) + 16 * i) * 8;
+            if (c < win.n) {
+                u32x4v v = {0, 0, 0, 0};
+                if (vec && win.base + c + 8 <= in) {
+                    v = *reinterpret_cast<const u32x4v *>(src + c);
+                } else {
+#pragma unroll
+                    for (uint32_t k = 0; k < 8; ++k)
+                        if (win.base + c + k < in) v[k >> 1] |= (uint32_t)src[c + k] << ((k & 1) * 16);
+                }
+                *reinterpret_cast<u32x4v *>(rows + r * PO_STRIDE + c) = v;
+            }
+        }
+    }
+    __syncthreads();
+    const uint16_t *far = X + (size_t)min(t0 + row, tokens - 1) * ldx;     // rows past the end repeat the last one: their products are never stored
+    const uint16_t *near = rows + row * PO_STRIDE;
+#pragma unroll
+    for (uint32_t i = 0; i < N; ++i) {
+        const uint32_t step = g * PO_STEPS + wave + 4 * i;
+        if (step >= n_steps) continue;
+        uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k) {
+            const uint32_t c = ch[i][k >> 2][k & 3];
+            uint32_t e = 0;
+            if (c != SKL_NO_CHANNEL && skl_in_range(c, in, SKL_DBG_CHANNEL)) e = win.n ? near[c - win.base] : far[c];
+            w[k >> 1] |= e << ((k & 1) * 16);
+        }
+        Xp[((size_t)(t0 / GM_MT) * n_steps + step) * SG_STEP_WORDS + (t0 % GM_MT) / 16 * 64 + lane] =
+            make_uint4(neg_half_pair(w[0], x_dt), neg_half_pair(w[1], x_dt), neg_half_pair(w[2], x_dt), neg_half_pair(w[3], x_dt));
+    }
+}
+
 struct StagedArgs {
-    const uint4 *Xp;                    // activation words: [token tile][step][8 row blocks][64 lanes]
-    const uint4 *Wp;                    // weight words: [output tile][64-channel block][SG_SLOT_WORDS]
+    const uint4 *Xp;                    // activation words: [256-token tile][32-channel step][SG_STEP_WORDS]
+    const uint4 *Wp;                    // weight words: [output tile][32-channel step][SG_STEP_WORDS]
     void *Y;
     float *parts;
     uint32_t KB, tokens, out, y_dt, ldy, rows_aligned;
@@ -93,117 +158,238 @@ struct StagedArgs {
     G3Split sp;
 };
 
-// RB: 32-token row blocks per wavefront: 2 (256 x 256 tiles) or 1 (128 x 256 tiles, the single-round mode of the split)
-template <int RB>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_staged_gemm(StagedArgs p)
+// The wavefront's results (RB x 4 blocks of 16 tokens x 16 outputs) turned round in a private LDS area, 32 rows at
+// a time, and stored in 16-byte pieces: every store instruction writes whole 128-byte (256 for float32) row pieces.
+template <int DT, int RB>
+__device__ __forceinline__ void staged_store_rows(const float4v (&acc)[RB][4], uint32_t lds_wave, void *Y, uint32_t ldy, uint32_t t0,
+                                                  uint32_t tokens, uint32_t o0, uint32_t out, uint32_t lane)
 {
+    constexpr uint32_t ES = DT == SKL_F32 ? 4 : 2, ROWB = 64 * ES + 16, CH = 64 * ES / 16;      // bytes per LDS row (padded), pieces per row
+    static_assert(32 * ROWB <= SG_EPI_BYTES, "32 rows have to fit the wavefront's area");
+    const uint32_t n = lane & 15, q = lane >> 4;
+#pragma unroll
+    for (int r = 0; r < RB; r += 2) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t addr = lds_wave + (h * 16 + q * 4 + i) * ROWB + (c * 16 + n) * ES;
+                    const float v = acc[r + h][c][i];
+                    if (DT == SKL_F32) *(__attribute__((address_space(3))) float *)(uintptr_t)addr = v;
+                    else *(__attribute__((address_space(3))) uint16_t *)(uintptr_t)addr = DT == SKL_F16 ? float_to_half_bits(v) : float_to_bf16_bits(v);
+                }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (uint32_t it = 0; it < 32 * CH / 64; ++it) {
+            const uint32_t idx = it * 64 + lane, row = idx / CH, c = idx % CH;
+            const uint4 w = lds_word_at(lds_wave + row * ROWB + c * 16);
+            const uint32_t t = t0 + r * 16 + row, o = o0 + c * (16 / ES);
+            if (t < tokens && o < out) {
+                char *dst = static_cast<char *>(Y) + ((size_t)t * ldy + o) * ES;
+                if (o + 16 / ES <= out) {
+                    *reinterpret_cast<uint4 *>(dst) = w;
+                } else {                                    // ragged last piece of the layer
+                    const uint32_t e[4] = {w.x, w.y, w.z, w.w};
+                    for (uint32_t b = 0; b < (out - o) * ES; b += 2)
+                        *reinterpret_cast<uint16_t *>(dst + b) = (uint16_t)(e[b >> 2] >> ((b & 2) * 8));
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// Y = X W on re-ordered operands, RB * 32 tokens x 256 outputs per workgroup (RB 8, or 4 in the single-round mode of
+// the split).  Eight wavefronts, two per SIMD, so that one has matrix instructions to issue while the other waits;
+// each owns RB * 16 tokens x 64 outputs (RB x 4 accumulator blocks).
+// Bound by the chip's power: a loop of nothing but matrix instructions on random operands runs at 1.78 PFLOP/s in
+// the 32x32x16 form and at 2.05 in the 16x16x32 form (half the accumulator traffic per product), hence the latter.
+// Both operands go global -> LDS without passing through registers (both are stored in operand order, so that a
+// copy is a contiguous KiB and an LDS read is free of bank conflicts), a stage of 32 channels at a time.  All but
+// two of the stages in LDS are on their way while one is multiplied from registers and one is being read.  The
+// copies are issued between the matrix instructions one by one: as a burst they queue at the address unit and hold
+// the wavefronts up before the barrier.  One barrier per stage; the words of a stage are read during the stage
+// before, so that no matrix instruction waits for an LDS read issued after a barrier.
+// 2048 tokens x 8192 x 28672: 718 us = 1.34 PFLOP/s, 801 us with one wavefront per SIMD in the 32x32x16 form; of the
+// difference to a loop without LDS reads and copies (525 us) the reads are about 80 us and the copies 120, and on
+// all-zero data (clock not held back) the copies alone set the time: 7.6 GB through the L2s, 1.7 GB from behind
+// them, in 570 us.  4096 x 11008: 185 us (200), 4096 x 4096 in half-height tiles: 65 us (74).
+#define SG_STAGES(rb) ((rb) == 8 ? 5u : 6u)
+#define SG_STAGE_BYTES(rb) ((rb) * 2048u + 16384u)      // (rb * 32) tokens x 32 channels, 32 channels x 256 outputs
+template <int RB>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_staged_gemm(StagedArgs p)
+{
+    constexpr uint32_t A_BYTES = RB * 2048, ST_BYTES = SG_STAGE_BYTES(RB), NS = SG_STAGES(RB);
     const uint32_t xcd = blockIdx.x & 7, wg = blockIdx.x >> 3;
     const G3Split sp = p.sp;
     uint32_t round = 0, u_next = sp.share_begin(xcd, wg);
     if (sp.rounds(xcd) == 0 && u_next >= sp.share_begin(xcd, wg + 1)) return;
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void *)smem;
-    const uint32_t n = lane & 31, q = lane >> 5;
-    const uint32_t b_lane = lds0 + (q * 32 + n) * 16;           // this lane's operand word of (column block 0, step 0)
-    // where this lane's eight copied words go inside a slot (+ 64 i); native vectors, so that the words in flight stay in registers
-    u32x4v *const copy_w = reinterpret_cast<u32x4v *>(smem) + wave * 512 + lane;
-    const uint32_t last_kb = p.KB - 1;
-    float16v acc[8 * RB];                                       // [row block][column block]
+    const uint32_t wm = wave >> 2, wn = wave & 3;               // token half and 64-output quarter of this wavefront
+    const uint32_t a_lane = lds0 + wm * (RB * 1024) + lane * 16, b_lane = lds0 + A_BYTES + wn * 4096 + lane * 16;
+    const uint32_t lds_wave = lds0 + wave * 1024, copy_off[2] = {wave * 1024 + lane * 16, (wave + 8) * 1024 + lane * 16};
+    float4v acc[RB][4];
     for (;;) {
         G3Split::Seg sg;
         if (!sp.next(xcd, wg, round, u_next, sg)) break;
-        const uint32_t k0 = sg.k0, k1 = sg.k1;
-        const bool whole = sg.whole != 0;
-        const size_t part_slot = sg.part_slot;
         uint32_t tile_m, tile_n;
         sp.tile_of(xcd, sg.k, tile_m, tile_n);
-        const uint32_t t0 = tile_m * (128 * RB) + wave * (32 * RB);
-        const uint32_t o_tile = (p.tile0 + tile_n) * GM3_NT;        // first output of the tile in the layer
-        // activation words of the wavefront's first row block (step st: + 512 st; second row block: + 64); the
-        // words are laid out by 256-token tiles of eight row blocks, a half-height tile is four of them
-        const uint4 *xa = RB == 2 ? p.Xp + ((size_t)tile_m * p.KB * 32 + wave * 2) * 64 + lane
-                                  : p.Xp + ((size_t)(tile_m >> 1) * p.KB * 32 + (tile_m & 1) * 4 + wave) * 64 + lane;
-        const u32x4v *wb = reinterpret_cast<const u32x4v *>(p.Wp) + (size_t)tile_n * p.KB * SG_SLOT_WORDS + wave * 512 + lane;    // block kb: + 2048 kb; word i: + 64 i
+        const uint32_t n_st = __builtin_amdgcn_readfirstlane((sg.k1 - sg.k0) * 2);      // stages of the segment
+        // the activation words are laid out by 256-token tiles of sixteen blocks; a half-height tile is eight of them
+        const char *const xa = uniform_address(p.Xp + ((size_t)(RB == 8 ? tile_m : tile_m >> 1) * p.KB + sg.k0) * SG_SLOT_WORDS + (RB == 8 ? 0 : (tile_m & 1) * 512));
+        const char *const wb = uniform_address(p.Wp + ((size_t)tile_n * p.KB + sg.k0) * SG_SLOT_WORDS);
+        constexpr int PER = RB / 4 + 2;                         // copies of a wavefront per stage: of the activations, then of the weights
+        auto next_buf = [](uint32_t buf) { return buf + ST_BYTES == NS * ST_BYTES ? 0 : buf + ST_BYTES; };
+        // Copy I of the wavefront's share of a stage, into the LDS buffer at offset buf.  Two source pointers step
+        // through the stages, a constant lane offset per copy does the rest: with addresses formed per copy the
+        // scalar instructions between the matrix instructions held up both wavefronts of a SIMD at once.
+        const char *pa = xa, *pb = wb;
+        auto copy_piece = [&](uint32_t buf, auto piece) {
+            constexpr uint32_t I = decltype(piece)::value, J = I < RB / 4 ? I : I - RB / 4;
+            lds_dma_16_offset<(I < RB / 4 ? 0 : A_BYTES) + J * 8192>(I < RB / 4 ? pa : pb, copy_off[J], lds_wave + buf);
+        };
+        // to the next stage of the segment (past its end: the last one again, never multiplied)
+        auto next_stage = [&](uint32_t st) {
+            const uint32_t step = st + 1 < n_st ? SG_STEP_WORDS * 16 : 0;
+            pa += step;
+            pb += step;
+        };
 #pragma unroll
-        for (int i = 0; i < 8 * RB; ++i) acc[i] = (float16v){0.f};
-        uint4 a[4][RB];
-        u32x4v tb[8];
-        {
-            const u32x4v *w0 = wb + (size_t)k0 * SG_SLOT_WORDS;
+        for (int r = 0; r < RB; ++r)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) tb[i] = w0[i * 64];
+            for (int c = 0; c < 4; ++c) acc[r][c] = (float4v){0.f, 0.f, 0.f, 0.f};
+        uint4 a[2][RB], b[2][4];
+        const std::integral_constant<uint32_t, 0> c0;
+        const std::integral_constant<uint32_t, 1> c1;
+        const std::integral_constant<uint32_t, 2> c2;
+        const std::integral_constant<uint32_t, 3> c3;
+        auto read_b = [&](uint32_t buf, auto set) {             // operand words of the stage in buffer buf
+            constexpr uint32_t H = decltype(set)::value;
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
+            for (int c = 0; c < 4; ++c) b[H][c] = lds_word_at(b_lane + buf + c * 1024);
+        };
+        auto read_a = [&](uint32_t buf, auto set, int r) {
+            constexpr uint32_t H = decltype(set)::value;
+            a[H][r] = lds_word_at(a_lane + buf + r * 1024);
+        };
+        auto multiply_row = [&](auto set, int r) {
+            constexpr uint32_t H = decltype(set)::value;
 #pragma unroll
-                for (int r = 0; r < RB; ++r) a[s][r] = xa[(size_t)(k0 * 4 + s) * 512 + r * 64];
-            u32x4v *dst = copy_w + (k0 & 1) * SG_SLOT_WORDS;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) dst[i * 64] = tb[i];
-            const u32x4v *w1 = wb + (size_t)min(k0 + 1, last_kb) * SG_SLOT_WORDS;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) tb[i] = w1[i * 64];
+            for (int c = 0; c < 4; ++c)
+                acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, a[H][r]), __builtin_bit_cast(half8v, b[H][c]), acc[r][c], 0, 0, 0);
+        };
+        uint32_t buf = 0;
+        for (uint32_t st = 0; st < NS; ++st) {
+            copy_piece(buf, c0);
+            copy_piece(buf, c1);
+            copy_piece(buf, c2);
+            if constexpr (PER == 4) copy_piece(buf, c3);
+            next_stage(st);
+            buf += ST_BYTES;
         }
-        __syncthreads();                                        // weight words of block k0 are in their slot
-        for (uint32_t kb = k0; kb < k1; ++kb) {
-            const uint32_t baddr = b_lane + (kb & 1) * SG_SLOT_BYTES;
-            u32x4v *const nxt = copy_w + ((kb & 1) ^ 1) * SG_SLOT_WORDS;
-            const uint4 *xn = xa + (size_t)min(kb + 1, last_kb) * 2048;                         // next block's activation words (the last block again past the end)
-            const u32x4v *w2 = wb + (size_t)min(kb + 2, last_kb) * SG_SLOT_WORDS;
-            uint4 bw[8];
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * PER) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        read_b(0, c0);
 #pragma unroll
-            for (int cb = 0; cb < 8; ++cb) bw[cb] = lds_word_at(baddr + cb * 4096);
+        for (int r = 0; r < RB; ++r) read_a(0, c0, r);
+        uint32_t from = 0;                                      // buffer of the stage in registers
+        // stage st is in register set H; stage st + 1 is read into the other one, stage st + NS takes its buffer
+        auto stage = [&](uint32_t st, auto set) {
+            constexpr uint32_t H = decltype(set)::value;
+            const std::integral_constant<uint32_t, H ^ 1> other;
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * PER) : "memory");    // stage st + 1 has arrived, stage st is read
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            const uint32_t nxt = next_buf(from);
+            read_b(nxt, other);
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int r = 0; r < RB; ++r) {
+                read_a(nxt, other, r);
                 __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int cb = 0; cb < 8; ++cb) {
-#pragma unroll
-                    for (int r = 0; r < RB; ++r)
-                        acc[8 * r + cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                            __builtin_bit_cast(half8v, a[s][r]), __builtin_bit_cast(half8v, bw[cb]), acc[8 * r + cb], 0, 0, 0);
-                    if (s < 3) bw[cb] = lds_word_at(baddr + cb * 4096 + (s + 1) * 1024);
-                    if (cb == 3) {                  // two of the next block's weight words into the other slot, their successors requested
-                        nxt[(2 * s) * 64] = tb[2 * s];
-                        nxt[(2 * s + 1) * 64] = tb[2 * s + 1];
-                    }
-                    if (cb == 5) {
-                        tb[2 * s] = w2[(2 * s) * 64];
-                        tb[2 * s + 1] = w2[(2 * s + 1) * 64];
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                // next block's activation words into the registers just used
-#pragma unroll
-                for (int r = 0; r < RB; ++r) a[s][r] = xn[s * 512 + r * 64];
+                multiply_row(set, r);
+                if (r == 0) copy_piece(from, c0);
+                if (r == RB / 4) copy_piece(from, c1);
+                if (r == RB / 2) copy_piece(from, c2);
+                if constexpr (PER == 4)
+                    if (r == 3 * RB / 4) copy_piece(from, c3);
+                if (r == RB - 1) next_stage(st + NS);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __syncthreads();                                    // everyone is done with this block's slot; the other one is complete
+            from = nxt;
+        };
+        for (uint32_t st = 0; st < n_st; st += 2) {             // (n_st is even: two stages per 64-channel block)
+            stage(st, c0);
+            stage(st + 1, c1);
         }
-        // the addresses of the epilogue are formed from a lane number the compiler cannot trace back, so that
-        // they are not kept in registers (or scratch memory) across the block loop
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __syncthreads();                                        // nothing on its way into LDS, nobody reads it: the epilogue may use it
+        // the addresses of the epilogue are formed from a lane number the compiler cannot trace back, so that they are
+        // not kept in registers across the loop above
         uint32_t ln = lane;
-        asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+v"(ln));       // also: the last MFMA has left the pipeline
-        if (whole && p.rows_aligned) {
-            const uint32_t lw = lds0 + wave * G3_EPI_BYTES;
-            if (p.y_dt == SKL_F32) gemm3_store_rows<SKL_F32, RB>(acc, lw, p.Y, p.ldy, t0, p.tokens, o_tile, p.out, ln);
-            else if (p.y_dt == SKL_F16) gemm3_store_rows<SKL_F16, RB>(acc, lw, p.Y, p.ldy, t0, p.tokens, o_tile, p.out, ln);
-            else gemm3_store_rows<SKL_BF16, RB>(acc, lw, p.Y, p.ldy, t0, p.tokens, o_tile, p.out, ln);
-        } else if (whole) {
-            const uint32_t ne = ln & 31, qe = ln >> 5;
-            if (p.y_dt == SKL_F32) gemm3_store<SKL_F32, RB>(acc, p.Y, p.ldy, t0, p.tokens, o_tile + ne, p.out, qe);
-            else if (p.y_dt == SKL_F16) gemm3_store<SKL_F16, RB>(acc, p.Y, p.ldy, t0, p.tokens, o_tile + ne, p.out, qe);
-            else gemm3_store<SKL_BF16, RB>(acc, p.Y, p.ldy, t0, p.tokens, o_tile + ne, p.out, qe);
-        } else if constexpr (RB == 2) {         // (the single-round mode of the half-height tiles has no partial tiles)
-            // partial tile: [wavefront][accumulator block][4 elements][lane], whole 1 KiB rows per store
-            float4 *dst = reinterpret_cast<float4 *>(p.parts + part_slot * G3_SLOT_FLOATS) + (size_t)wave * 4096 + ln;
+        asm volatile("" : "+v"(ln));
+        const uint32_t t0 = tile_m * (RB * 32) + wm * (RB * 16), o0 = (p.tile0 + tile_n) * GM3_NT + wn * 64;
+        if (sg.whole && p.rows_aligned) {
+            const uint32_t lw = lds0 + wave * SG_EPI_BYTES;
+            if (p.y_dt == SKL_F32) staged_store_rows<SKL_F32, RB>(acc, lw, p.Y, p.ldy, t0, p.tokens, o0, p.out, ln);
+            else if (p.y_dt == SKL_F16) staged_store_rows<SKL_F16, RB>(acc, lw, p.Y, p.ldy, t0, p.tokens, o0, p.out, ln);
+            else staged_store_rows<SKL_BF16, RB>(acc, lw, p.Y, p.ldy, t0, p.tokens, o0, p.out, ln);
+        } else if (sg.whole) {
 #pragma unroll
-            for (int ab = 0; ab < 16; ++ab)
+            for (int r = 0; r < RB; ++r)
 #pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4)
-                    dst[(ab * 4 + i4) * 64] = make_float4(acc_elem(acc[ab][4 * i4]), acc_elem(acc[ab][4 * i4 + 1]),
-                                                          acc_elem(acc[ab][4 * i4 + 2]), acc_elem(acc[ab][4 * i4 + 3]));
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint32_t t = t0 + r * 16 + (ln >> 4) * 4 + i, o = o0 + c * 16 + (ln & 15);
+                        if (t < p.tokens && o < p.out) store_out(p.Y, p.y_dt, (size_t)t * p.ldy + o, acc[r][c][i]);
+                    }
+        } else if constexpr (RB == 8) {         // (the single-round mode of the half-height tiles has no partial tiles)
+            // partial tile: [token block 16][output block 16][lane] x 4 tokens, whole 1 KiB rows per store
+            float4v *dst = reinterpret_cast<float4v *>(p.parts + sg.part_slot * G3_SLOT_FLOATS) + ln;
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) dst[(size_t)((wm * 8 + r) * 16 + wn * 4 + c) * 64] = acc[r][c];
         }
         __syncthreads();                                        // the epilogue's LDS areas are free again
     }
+}
+
+// Adds the partials of 16 tokens of a leftover tile in workgroup order, turns them round in LDS and stores rows;
+// grid (8 * l_max, 16)
+__global__ __launch_bounds__(256) void k_staged_fixup(G3Split sp, const float *__restrict__ parts, void *Y, uint32_t y_dt, uint32_t ldy,
+                                                      uint32_t tokens, uint32_t out, uint32_t tile0)
+{
+    __shared__ float rows[16][GM3_NT + 1];
+    const uint32_t xcd = blockIdx.x / sp.l_max, l = blockIdx.x % sp.l_max, rb = blockIdx.y;
+    if (l >= sp.left(xcd)) return;
+    uint32_t tile_m, tile_n;
+    sp.tile_of(xcd, sp.rounds(xcd) * sp.gx + l, tile_m, tile_n);
+    const uint32_t t0 = tile_m * GM_MT + rb * 16;
+    if (t0 >= tokens) return;
+    const uint32_t n_parts = sp.parts(xcd, l), lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const float4v *src = reinterpret_cast<const float4v *>(parts + sp.slot(xcd, l, 0) * G3_SLOT_FLOATS) + (rb * 16 + wave * 4) * 64 + lane;
+    float4v v[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = src[c * 64];
+    for (uint32_t part = 1; part < n_parts; ++part) {           // the slots of a tile are neighbours
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] += src[(size_t)part * (G3_SLOT_FLOATS / 4) + c * 64];
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rows[(lane >> 4) * 4 + i][(wave * 4 + c) * 16 + (lane & 15)] = v[c][i];
+    __syncthreads();
+    const uint32_t o = (tile0 + tile_n) * GM3_NT + threadIdx.x;     // tile0: first output tile of the slab the split covers
+    if (o >= out) return;
+    for (uint32_t t = 0; t < 16 && t0 + t < tokens; ++t) store_out(Y, y_dt, (size_t)(t0 + t) * ldy + o, rows[t][threadIdx.x]);
 }
 
 // ========================================================================
@@ -228,7 +414,7 @@ static uint32_t staged_slab_cols(const skl_layer *L, uint32_t tokens)
 static uint64_t staged_pack_bytes(const skl_layer *L, uint32_t tokens)
 {
     const uint64_t m_tiles = (tokens + GM_MT - 1) / GM_MT;
-    return m_tiles * L->gemm_kb * 4 * 8192ull;                  // 8 row blocks of 64 lanes x 16 bytes per (token tile, step)
+    return m_tiles * L->gemm_kb * 2 * SG_STEP_WORDS * 16ull;
 }
 
 static uint64_t staged_part_bytes(const skl_layer *L, uint32_t tokens)
@@ -262,8 +448,10 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
     uint4 *Wp = reinterpret_cast<uint4 *>(area);
     const uint32_t KB = L->gemm_kb, n_col = (L->out + GM3_NT - 1) / GM3_NT, slab_cols = staged_slab_cols(L, tokens);
 
-    const skl_gemm_step *steps = reinterpret_cast<const skl_gemm_step *>(L->dev + L->off_ssteps);
-    skl_status_t st = skl_launch_pack(L, X, x_dt, ldx, tokens, a.chan, steps, 4 * KB, Xp, stream);
+    const skl_pack_window *windows = reinterpret_cast<const skl_pack_window *>(L->dev + L->off_windows);
+    hipLaunchKernelGGL(k_pack_operands, dim3((tokens + 15) / 16, (2 * KB + PO_STEPS - 1) / PO_STEPS), dim3(SKL_WG), 0, stream, X, (uint32_t)x_dt,
+                       ldx, tokens, L->in, a.chan, windows, 2 * KB, Xp);
+    skl_status_t st = check_launch("activation packing");
     if (st != SKL_OK) return st;
     for (uint32_t tile0 = 0; tile0 < n_col; tile0 += slab_cols) {
         const uint32_t cols = std::min(slab_cols, n_col - tile0);
@@ -290,19 +478,23 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
         g.rows_aligned = ((size_t)ldy * (y_dt == SKL_F32 ? 4 : 2)) % 16 == 0;
         g.tile0 = tile0;
         g.sp = skl_make_split(cols * GM3_NT, KB, tokens, true);
+        constexpr size_t lds8 = SG_STAGES(8) * SG_STAGE_BYTES(8), lds4 = SG_STAGES(4) * SG_STAGE_BYTES(4);
+        static_assert(lds4 >= 8 * SG_EPI_BYTES, "the epilogue has to fit the stages' LDS");
         if (g.sp.mt == GM_MT) {
-            st = allow_lds(k_staged_gemm<2>, SG_LDS_BYTES);
+            st = allow_lds(k_staged_gemm<8>, lds8);
             if (st != SKL_OK) return st;
-            hipLaunchKernelGGL(k_staged_gemm<2>, dim3(8 * g.sp.gx), dim3(256), SG_LDS_BYTES, stream, g);
+            hipLaunchKernelGGL(k_staged_gemm<8>, dim3(8 * g.sp.gx), dim3(512), lds8, stream, g);
         } else {
-            st = allow_lds(k_staged_gemm<1>, SG_LDS_BYTES);
+            st = allow_lds(k_staged_gemm<4>, lds4);
             if (st != SKL_OK) return st;
-            hipLaunchKernelGGL(k_staged_gemm<1>, dim3(8 * g.sp.gx), dim3(256), SG_LDS_BYTES, stream, g);
+            hipLaunchKernelGGL(k_staged_gemm<4>, dim3(8 * g.sp.gx), dim3(512), lds4, stream, g);
         }
         st = check_launch("staged gemm");
         if (st != SKL_OK) return st;
         if (g.sp.l_max) {
-            st = skl_launch_gemm3_fixup(g.sp, parts, Y, y_dt, ldy, tokens, L->out, tile0, stream);
+            hipLaunchKernelGGL(k_staged_fixup, dim3(8 * g.sp.l_max, 16), dim3(256), 0, stream, g.sp, parts, Y, (uint32_t)y_dt, ldy, tokens,
+                               L->out, tile0);
+            st = check_launch("staged gemm fix-up");
             if (st != SKL_OK) return st;
         }
     }

@@ -4,7 +4,9 @@ import numpy as np
 import pytest
 
 import oracle
-from skl_harness import build_states_on_gpu
+import paper_2506_17255_amd as skl
+import workloads as wk
+from skl_harness import GpuLayer, build_states_on_gpu, rel_fro
 
 pytestmark = pytest.mark.gpu
 
@@ -30,3 +32,28 @@ def test_row_sketch_construction(in_f, out_f, d, widths):
     A, C = hash_params(rng, d)
     got = build_states_on_gpu(W, 1, out_f, d, A, C, K)
     assert np.array_equal(got, oracle.update(W, 1, out_f, d, A, C, K).states)
+
+
+def row_layer(seed, in_f, out_f, d, widths):
+    rng = np.random.default_rng(seed)
+    W = (rng.standard_normal((in_f, out_f)) * 0.02).astype(np.float16)
+    A, C = hash_params(rng, d)
+    return oracle.update(W, 1, out_f, d, A, C, np.asarray(widths, dtype=np.uint32))
+
+
+# float32 result of float32 sums of at most 1030 exact products: relative error below sqrt(1030) * 2^-24 = 2e-6
+SUM_TOL = 2e-6
+
+
+@pytest.mark.parametrize("wide_share", [0.01, 0.3, 1.0])
+@pytest.mark.parametrize("in_f,tokens,ldx_pad", [(1030, 17, 2), (1030, 300, 0), (264, 1, 0), (520, 257, 3)])
+def test_activation_packing_of_the_staged_prefill(in_f, tokens, ldx_pad, wide_share):
+    """Channels near each other (windows of X in LDS), scattered (fetched one by one) and in their own order; rows of
+    X on 16-byte boundaries and not; token counts around the 16-token blocks and 256-token tiles."""
+    rng = np.random.default_rng(in_f + tokens)
+    sk = row_layer(5, in_f, 264, 3, np.where(rng.random(in_f) < wide_share, 20, 9))
+    X = wk.f32_to_bf16_bits(rng.standard_normal((tokens, in_f)).astype(np.float32))
+    ref = oracle.linear(oracle.query(sk), X, x_kind="bf16")
+    with GpuLayer(sk, skl.FLAG_STAGED_PREFILL) as g:
+        y = g.gemm(X, "bf16", "f32", ldx=in_f + ldx_pad)
+    assert rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
