@@ -129,7 +129,9 @@ typedef struct {
     uint32_t block_classes;    /* path 1: bit i set when some channel block has 2^i 16-byte words per
                                   state row (8 * 2^i input channels per block) */
     uint32_t prefill_kernel;   /* what sketch_linear_gemm runs on calls with fewer than
-                                  prefill_staged_from tokens: SKL_PREFILL_* */
+                                  prefill_staged_from tokens: SKL_PREFILL_*.  Short prompts
+                                  (at most 128 tokens) of row sketches are staged whatever this
+                                  says, unless the descriptor asks for the fused kernel */
     uint32_t n_blocks;         /* path 1: channel blocks */
     uint32_t prefill_staged_from; /* row sketches: calls with at least this many tokens take
                                   SKL_PREFILL_STAGED (0: every call, 0xFFFFFFFF: none) */
@@ -143,7 +145,7 @@ typedef struct {
                                        between the matrix instructions of a 256 x 256 tile */
 #define SKL_PREFILL_STAGED 4u       /* row sketches with larger tables, and long calls: weights rebuilt once per
                                        call into a cache-sized slab of the workspace, then a 256 x 256-tile
-                                       product */
+                                       product (tiles of 64 or 128 tokens for short prompts) */
 
 /* Bytes of device memory create() needs for this description.
  * Validates the whole description (Sec. 3.1 states must be finite). */

@@ -9,7 +9,7 @@
 //      in LDS once, runs select / gather / query / decode for all its outputs and writes the weights as
 //      16-byte matrix-core operand words, already in the order the product kernel's LDS slot has;
 //   2. k_staged_gemm: 256 tokens x 256 outputs per workgroup, a product of operand words that both come from
-//      memory (k_pack_operands re-orders the activations first).
+//      memory (the workgroups of the first launch that do not rebuild re-order the activations).
 // The work split is that of the fused kernel, dealt by output-tile column.
 #include "skl_prefill_common.h"
 
@@ -74,13 +74,6 @@ __device__ __forceinline__ void rebuild_block(const RebuildArgs &p, uint32_t idx
     }
 }
 
-// grid (channel blocks x output segments)
-template <int D>
-__global__ __launch_bounds__(SKL_WG) void k_rebuild_operands(RebuildArgs r)
-{
-    rebuild_block<D>(r, blockIdx.x);
-}
-
 // Activations to negated binary16, re-ordered into the matrix-core A words of k_staged_gemm:
 // [256-token tile][32-channel step][16-token block][channel group 4][16 tokens], a word being eight entries of the
 // channel list for one token.  A workgroup takes 16 tokens x PO_STEPS steps: it copies the window of X that holds
@@ -89,15 +82,25 @@ __global__ __launch_bounds__(SKL_WG) void k_rebuild_operands(RebuildArgs r)
 // spans such a gap channel by channel from memory took 5 of 15 us on layers with one percent of wide channels).
 // Steps whose channels are far apart (the wide channels themselves) have no window and are fetched from memory.
 // 2048 tokens x 4096 channels of such a layer, 16.8 MB in and out: 10 us, 15 before (5.1 TB/s would be 6.6).
-// grid (ceil(tokens / 16), ceil(steps / PO_STEPS))
 #define PO_STRIDE (PO_WINDOW + 8u)      // halfs per LDS row: 16-byte aligned rows on different banks
-__global__ __launch_bounds__(SKL_WG) void k_pack_operands(const uint16_t *__restrict__ X, uint32_t x_dt, uint32_t ldx, uint32_t tokens,
-                                                           uint32_t in, const uint32_t *__restrict__ chan,
-                                                           const skl_pack_window *__restrict__ windows, uint32_t n_steps,
-                                                           uint4 *__restrict__ Xp)
+#define PO_LDS_BYTES (16u * PO_STRIDE * 2u)
+struct PackArgs {
+    const uint16_t *X;
+    const uint32_t *chan;
+    const skl_pack_window *windows;
+    uint4 *Xp;
+    uint32_t x_dt, ldx, tokens, in, n_steps;
+};
+// tokens t0 .. t0 + 15, group g of PO_STEPS steps; LDS: PO_LDS_BYTES at smem
+__device__ __forceinline__ void pack_group(const PackArgs &p, uint32_t t0, uint32_t g)
 {
-    __shared__ __align__(16) uint16_t rows[16 * PO_STRIDE];
-    const uint32_t t0 = blockIdx.x * 16, g = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint16_t *rows = reinterpret_cast<uint16_t *>(smem);
+    const uint16_t *__restrict__ X = p.X;
+    const uint32_t *__restrict__ chan = p.chan;
+    const skl_pack_window *__restrict__ windows = p.windows;
+    uint4 *__restrict__ Xp = p.Xp;
+    const uint32_t x_dt = p.x_dt, ldx = p.ldx, tokens = p.tokens, in = p.in, n_steps = p.n_steps;
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t row = lane & 15, kg = lane >> 4;
     const skl_pack_window win = windows[g];
     constexpr uint32_t N = PO_STEPS / (SKL_WG / 64);            // steps per wavefront
@@ -148,6 +151,19 @@ __global__ __launch_bounds__(SKL_WG) void k_pack_operands(const uint16_t *__rest
     }
 }
 
+// Both in one launch: a short prompt has too few activations to fill the chip and too little work for a launch of its
+// own (4096 x 4096, 100 tokens, whole call: 34 -> 29 us; 1024 x 2048: 22 -> 18; 2048 tokens: 80 -> 78).  The first n_pack workgroups re-order the activations, the others rebuild;
+// 16-token rows x step groups + channel blocks x output segments workgroups, over two grid dimensions (a dimension holds
+// 2^32 threads)
+template <int D>
+__global__ __launch_bounds__(SKL_WG) void k_rebuild_operands(RebuildArgs r, PackArgs k, uint32_t n_pack)
+{
+    const uint32_t n_rows = (k.tokens + 15) / 16, idx = blockIdx.y * gridDim.x + blockIdx.x;
+    if (idx < n_pack) pack_group(k, idx % n_rows * 16, idx / n_rows);
+    else if (idx < n_pack + r.n_blocks * r.n_oseg) rebuild_block<D>(r, idx - n_pack);
+}
+
+template <class Split>
 struct StagedArgs {
     const uint4 *Xp;                    // activation words: [256-token tile][32-channel step][SG_STEP_WORDS]
     const uint4 *Wp;                    // weight words: [output tile][32-channel step][SG_STEP_WORDS]
@@ -155,7 +171,7 @@ struct StagedArgs {
     float *parts;
     uint32_t KB, tokens, out, y_dt, ldy, rows_aligned;
     uint32_t tile0;                     // first output tile of the slab (Wp and the split are slab-relative)
-    G3Split sp;
+    Split sp;
 };
 
 // The wavefront's results (RB x 4 blocks of 16 tokens x 16 outputs) turned round in a private LDS area, 32 rows at
@@ -214,25 +230,31 @@ __device__ __forceinline__ void staged_store_rows(const float4v (&acc)[RB][4], u
 // copies are issued between the matrix instructions one by one: as a burst they queue at the address unit and hold
 // the wavefronts up before the barrier.  One barrier per stage; the words of a stage are read during the stage
 // before, so that no matrix instruction waits for an LDS read issued after a barrier.
+// Short prompts (ShortSplit) take it with RB 2 or 4 for one token tile of 64 or 128 tokens: bound by the weight words,
+// each read once, and by the partials; 4096 x 11008 at 100 tokens 22 us (56 us in the fused kernel, which multiplies a
+// 256-token tile and rebuilds its weights beside it).
 // 2048 tokens x 8192 x 28672: 718 us = 1.34 PFLOP/s, 801 us with one wavefront per SIMD in the 32x32x16 form; of the
 // difference to a loop without LDS reads and copies (525 us) the reads are about 80 us and the copies 120, and on
 // all-zero data (clock not held back) the copies alone set the time: 7.6 GB through the L2s, 1.7 GB from behind
 // them, in 570 us.  4096 x 11008: 185 us (200), 4096 x 4096 in half-height tiles: 65 us (74).
-#define SG_STAGES(rb) ((rb) == 8 ? 5u : 6u)
+#define SG_STAGES(rb) ((rb) == 8 ? 5u : (rb) == 4 ? 6u : 7u)
 #define SG_STAGE_BYTES(rb) ((rb) * 2048u + 16384u)      // (rb * 32) tokens x 32 channels, 32 channels x 256 outputs
-template <int RB>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_staged_gemm(StagedArgs p)
+template <int RB, class Split>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_staged_gemm(StagedArgs<Split> p)
 {
     constexpr uint32_t A_BYTES = RB * 2048, ST_BYTES = SG_STAGE_BYTES(RB), NS = SG_STAGES(RB);
+    constexpr bool PARTS = RB == 8 || std::is_same<Split, ShortSplit>::value;   // (the single-round mode of the half-height tiles has no partial tiles)
     const uint32_t xcd = blockIdx.x & 7, wg = blockIdx.x >> 3;
-    const G3Split sp = p.sp;
+    const Split sp = p.sp;
+    if (sp.empty(xcd, wg)) return;
     uint32_t round = 0, u_next = sp.share_begin(xcd, wg);
-    if (sp.rounds(xcd) == 0 && u_next >= sp.share_begin(xcd, wg + 1)) return;
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void *)smem;
     const uint32_t wm = wave >> 2, wn = wave & 3;               // token half and 64-output quarter of this wavefront
     const uint32_t a_lane = lds0 + wm * (RB * 1024) + lane * 16, b_lane = lds0 + A_BYTES + wn * 4096 + lane * 16;
     const uint32_t lds_wave = lds0 + wave * 1024, copy_off[2] = {wave * 1024 + lane * 16, (wave + 8) * 1024 + lane * 16};
+    // 64 tokens are half a KiB per wavefront: both halves of the workgroup copy the same four KiB
+    const uint32_t a_wave = RB == 2 ? lds0 + (wave & 3) * 1024 : lds_wave, a_off = RB == 2 ? (wave & 3) * 1024 + lane * 16 : copy_off[0];
     float4v acc[RB][4];
     for (;;) {
         G3Split::Seg sg;
@@ -241,17 +263,20 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         sp.tile_of(xcd, sg.k, tile_m, tile_n);
         const uint32_t n_st = __builtin_amdgcn_readfirstlane((sg.k1 - sg.k0) * 2);      // stages of the segment
         // the activation words are laid out by 256-token tiles of sixteen blocks; a half-height tile is eight of them
+        // (RB 2: the short-prompt mode, whose only token tile is the first)
         const char *const xa = uniform_address(p.Xp + ((size_t)(RB == 8 ? tile_m : tile_m >> 1) * p.KB + sg.k0) * SG_SLOT_WORDS + (RB == 8 ? 0 : (tile_m & 1) * 512));
         const char *const wb = uniform_address(p.Wp + ((size_t)tile_n * p.KB + sg.k0) * SG_SLOT_WORDS);
-        constexpr int PER = RB / 4 + 2;                         // copies of a wavefront per stage: of the activations, then of the weights
+        constexpr uint32_t NA = RB >= 4 ? RB / 4 : 1;
+        constexpr int PER = NA + 2;                             // copies of a wavefront per stage: of the activations, then of the weights
         auto next_buf = [](uint32_t buf) { return buf + ST_BYTES == NS * ST_BYTES ? 0 : buf + ST_BYTES; };
         // Copy I of the wavefront's share of a stage, into the LDS buffer at offset buf.  Two source pointers step
         // through the stages, a constant lane offset per copy does the rest: with addresses formed per copy the
         // scalar instructions between the matrix instructions held up both wavefronts of a SIMD at once.
         const char *pa = xa, *pb = wb;
         auto copy_piece = [&](uint32_t buf, auto piece) {
-            constexpr uint32_t I = decltype(piece)::value, J = I < RB / 4 ? I : I - RB / 4;
-            lds_dma_16_offset<(I < RB / 4 ? 0 : A_BYTES) + J * 8192>(I < RB / 4 ? pa : pb, copy_off[J], lds_wave + buf);
+            constexpr uint32_t I = decltype(piece)::value, J = I < NA ? I : I - NA;
+            if constexpr (I == 0) lds_dma_16_offset<0>(pa, a_off, a_wave + buf);
+            else lds_dma_16_offset<(I < NA ? 0 : A_BYTES) + J * 8192>(I < NA ? pa : pb, copy_off[J], lds_wave + buf);
         };
         // to the next stage of the segment (past its end: the last one again, never multiplied)
         auto next_stage = [&](uint32_t st) {
@@ -349,47 +374,66 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                         const uint32_t t = t0 + r * 16 + (ln >> 4) * 4 + i, o = o0 + c * 16 + (ln & 15);
                         if (t < p.tokens && o < p.out) store_out(p.Y, p.y_dt, (size_t)t * p.ldy + o, acc[r][c][i]);
                     }
-        } else if constexpr (RB == 8) {         // (the single-round mode of the half-height tiles has no partial tiles)
-            // partial tile: [token block 16][output block 16][lane] x 4 tokens, whole 1 KiB rows per store
-            float4v *dst = reinterpret_cast<float4v *>(p.parts + sg.part_slot * G3_SLOT_FLOATS) + ln;
+        } else if constexpr (PARTS) {
+            // partial tile: [token block][output block 16][lane] x 4 tokens, whole 1 KiB rows per store
+            float4v *dst = reinterpret_cast<float4v *>(p.parts + sg.part_slot * (RB * 32 * GM3_NT)) + ln;
 #pragma unroll
-            for (int r = 0; r < RB; ++r)
+            for (int r = 0; r < RB; ++r) {
+                if (RB < 8 && t0 + r * 16 >= p.tokens) continue;        // blocks of tokens past the end: nobody reads them
 #pragma unroll
-                for (int c = 0; c < 4; ++c) dst[(size_t)((wm * 8 + r) * 16 + wn * 4 + c) * 64] = acc[r][c];
+                for (int c = 0; c < 4; ++c) dst[(size_t)((wm * RB + r) * 16 + wn * 4 + c) * 64] = acc[r][c];
+            }
         }
         __syncthreads();                                        // the epilogue's LDS areas are free again
     }
 }
 
-// Adds the partials of 16 tokens of a leftover tile in workgroup order, turns them round in LDS and stores rows;
-// grid (8 * l_max, 16)
-__global__ __launch_bounds__(256) void k_staged_fixup(G3Split sp, const float *__restrict__ parts, void *Y, uint32_t y_dt, uint32_t ldy,
-                                                      uint32_t tokens, uint32_t out, uint32_t tile0)
+// Adds n_parts partials of 16 tokens x 256 outputs (the first at src, part_floats apart) in order, turns them round in
+// LDS and stores rows.
+__device__ __forceinline__ void fixup_rows(const float *first, uint32_t part_floats, uint32_t n_parts, void *Y, uint32_t y_dt, uint32_t ldy,
+                                           uint32_t t0, uint32_t tokens, uint32_t o0, uint32_t out)
 {
     __shared__ float rows[16][GM3_NT + 1];
-    const uint32_t xcd = blockIdx.x / sp.l_max, l = blockIdx.x % sp.l_max, rb = blockIdx.y;
-    if (l >= sp.left(xcd)) return;
-    uint32_t tile_m, tile_n;
-    sp.tile_of(xcd, sp.rounds(xcd) * sp.gx + l, tile_m, tile_n);
-    const uint32_t t0 = tile_m * GM_MT + rb * 16;
-    if (t0 >= tokens) return;
-    const uint32_t n_parts = sp.parts(xcd, l), lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const float4v *src = reinterpret_cast<const float4v *>(parts + sp.slot(xcd, l, 0) * G3_SLOT_FLOATS) + (rb * 16 + wave * 4) * 64 + lane;
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const float4v *src = reinterpret_cast<const float4v *>(first) + (wave * 4) * 64 + lane;
     float4v v[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) v[c] = src[c * 64];
     for (uint32_t part = 1; part < n_parts; ++part) {           // the slots of a tile are neighbours
 #pragma unroll
-        for (int c = 0; c < 4; ++c) v[c] += src[(size_t)part * (G3_SLOT_FLOATS / 4) + c * 64];
+        for (int c = 0; c < 4; ++c) v[c] += src[(size_t)part * (part_floats / 4) + c * 64];
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
         for (int i = 0; i < 4; ++i) rows[(lane >> 4) * 4 + i][(wave * 4 + c) * 16 + (lane & 15)] = v[c][i];
     __syncthreads();
-    const uint32_t o = (tile0 + tile_n) * GM3_NT + threadIdx.x;     // tile0: first output tile of the slab the split covers
+    const uint32_t o = o0 + threadIdx.x;
     if (o >= out) return;
     for (uint32_t t = 0; t < 16 && t0 + t < tokens; ++t) store_out(Y, y_dt, (size_t)(t0 + t) * ldy + o, rows[t][threadIdx.x]);
+}
+
+// the leftover tiles of a call; grid (8 * l_max, 16)
+__global__ __launch_bounds__(256) void k_staged_fixup(G3Split sp, const float *__restrict__ parts, void *Y, uint32_t y_dt, uint32_t ldy,
+                                                      uint32_t tokens, uint32_t out, uint32_t tile0)
+{
+    const uint32_t xcd = blockIdx.x / sp.l_max, l = blockIdx.x % sp.l_max, rb = blockIdx.y;
+    if (l >= sp.left(xcd)) return;
+    uint32_t tile_m, tile_n;
+    sp.tile_of(xcd, sp.rounds(xcd) * sp.gx + l, tile_m, tile_n);
+    const uint32_t t0 = tile_m * GM_MT + rb * 16;
+    if (t0 >= tokens) return;
+    fixup_rows(parts + sp.slot(xcd, l, 0) * G3_SLOT_FLOATS + rb * 16 * GM3_NT, G3_SLOT_FLOATS, sp.parts(xcd, l), Y, y_dt, ldy, t0, tokens,
+               (tile0 + tile_n) * GM3_NT, out);            // tile0: first output tile of the slab the split covers
+}
+
+// the shared tiles of a short prompt; grid (tiles, ceil(tokens / 16))
+__global__ __launch_bounds__(256) void k_short_fixup(ShortSplit sp, uint32_t part_floats, const float *__restrict__ parts, void *Y, uint32_t y_dt,
+                                                     uint32_t ldy, uint32_t tokens, uint32_t out, uint32_t tile0)
+{
+    const uint32_t tile = blockIdx.x, rb = blockIdx.y;
+    fixup_rows(parts + (size_t)tile * sp.P * part_floats + rb * 16 * GM3_NT, part_floats, sp.P, Y, y_dt, ldy, rb * 16, tokens,
+               (tile0 + tile) * GM3_NT, out);
 }
 
 // ========================================================================
@@ -417,8 +461,18 @@ static uint64_t staged_pack_bytes(const skl_layer *L, uint32_t tokens)
     return m_tiles * L->gemm_kb * 2 * SG_STEP_WORDS * 16ull;
 }
 
+// short prompts: tokens per tile
+static uint32_t short_mt(uint32_t tokens) { return tokens <= 64 ? 64 : 128; }
+
 static uint64_t staged_part_bytes(const skl_layer *L, uint32_t tokens)
 {
+    if (tokens <= SKL_SHORT_TOKENS) {
+        const uint32_t n_col = (L->out + GM3_NT - 1) / GM3_NT, cols = staged_slab_cols(L, tokens);
+        // (the last slab may be narrower, and its tiles cut into more shares)
+        const ShortSplit sp = skl_make_short_split(cols * GM3_NT, L->gemm_kb), last = skl_make_short_split((n_col % cols ? n_col % cols : cols) * GM3_NT, L->gemm_kb);
+        const uint64_t most = std::max<uint64_t>(sp.P > 1 ? (uint64_t)sp.T * sp.P : 0, last.P > 1 ? (uint64_t)last.T * last.P : 0);
+        return most * short_mt(tokens) * GM3_NT * sizeof(float);
+    }
     // the widest slab has the most leftover tiles
     const G3Split sp = skl_make_split(staged_slab_cols(L, tokens) * GM3_NT, L->gemm_kb, tokens, true);
     uint64_t most = 8ull * sp.l_max * sp.p_cap;
@@ -436,6 +490,17 @@ uint64_t skl_gemm_staged_bytes(const skl_layer *L, uint32_t tokens)
            (uint64_t)staged_slab_cols(L, tokens) * L->gemm_kb * SG_SLOT_BYTES;
 }
 
+template <int RB, class Split>
+static skl_status_t launch_product(const StagedArgs<Split> &g, uint32_t grid, hipStream_t stream)
+{
+    constexpr size_t lds = SG_STAGES(RB) * SG_STAGE_BYTES(RB);
+    static_assert(lds >= 8 * SG_EPI_BYTES && lds <= SKL_LDS_HARD_BYTES, "the epilogue has to fit the stages' LDS");
+    const skl_status_t st = allow_lds(k_staged_gemm<RB, Split>, lds);
+    if (st != SKL_OK) return st;
+    hipLaunchKernelGGL((k_staged_gemm<RB, Split>), dim3(grid), dim3(512), lds, stream, g);
+    return check_launch("staged gemm");
+}
+
 skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx,
                                     void *Y, skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, void *ws, hipStream_t stream)
 {
@@ -449,10 +514,8 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
     const uint32_t KB = L->gemm_kb, n_col = (L->out + GM3_NT - 1) / GM3_NT, slab_cols = staged_slab_cols(L, tokens);
 
     const skl_pack_window *windows = reinterpret_cast<const skl_pack_window *>(L->dev + L->off_windows);
-    hipLaunchKernelGGL(k_pack_operands, dim3((tokens + 15) / 16, (2 * KB + PO_STEPS - 1) / PO_STEPS), dim3(SKL_WG), 0, stream, X, (uint32_t)x_dt,
-                       ldx, tokens, L->in, a.chan, windows, 2 * KB, Xp);
-    skl_status_t st = check_launch("activation packing");
-    if (st != SKL_OK) return st;
+    const PackArgs k{X, a.chan, windows, Xp, (uint32_t)x_dt, ldx, tokens, L->in, 2 * KB};
+    skl_status_t st = SKL_OK;
     for (uint32_t tile0 = 0; tile0 < n_col; tile0 += slab_cols) {
         const uint32_t cols = std::min(slab_cols, n_col - tile0);
         RebuildArgs r;
@@ -464,32 +527,42 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
         // workgroups, and every segment at least one tile column.
         const uint32_t few = (1024 + L->n_blocks - 1) / L->n_blocks, many = (4096 + L->n_blocks - 1) / L->n_blocks;
         r.n_oseg = std::max(1u, std::min(cols, std::max(few, std::min(cols / 12, many))));
-        const size_t lds = L->max_table_bytes;
+        const size_t lds = std::max<size_t>(L->max_table_bytes, PO_LDS_BYTES);
+        const uint32_t n_pack = tile0 ? 0 : (tokens + 15) / 16 * ((2 * KB + PO_STEPS - 1) / PO_STEPS);     // (with the first slab)
+        const uint32_t n_wg = n_pack + L->n_blocks * r.n_oseg, row = std::min(n_wg, 1u << 22);
+        const dim3 grid(row, (n_wg + row - 1) / row);
         DISPATCH_D(L->d, {
             st = allow_lds(k_rebuild_operands<D>, lds);
-            if (st == SKL_OK) hipLaunchKernelGGL((k_rebuild_operands<D>), dim3(L->n_blocks * r.n_oseg), dim3(SKL_WG), lds, stream, r);
+            if (st == SKL_OK) hipLaunchKernelGGL((k_rebuild_operands<D>), grid, dim3(SKL_WG), lds, stream, r, k, n_pack);
         })
         if (st == SKL_OK) st = check_launch("operand rebuild");
         if (st != SKL_OK) return st;
 
-        StagedArgs g;
-        g.Xp = Xp; g.Wp = Wp; g.Y = Y; g.parts = parts;
-        g.KB = KB; g.tokens = tokens; g.out = L->out; g.y_dt = (uint32_t)y_dt; g.ldy = ldy;
-        g.rows_aligned = ((size_t)ldy * (y_dt == SKL_F32 ? 4 : 2)) % 16 == 0;
-        g.tile0 = tile0;
-        g.sp = skl_make_split(cols * GM3_NT, KB, tokens, true);
-        constexpr size_t lds8 = SG_STAGES(8) * SG_STAGE_BYTES(8), lds4 = SG_STAGES(4) * SG_STAGE_BYTES(4);
-        static_assert(lds4 >= 8 * SG_EPI_BYTES, "the epilogue has to fit the stages' LDS");
-        if (g.sp.mt == GM_MT) {
-            st = allow_lds(k_staged_gemm<8>, lds8);
+        auto fill = [&](auto &g) {
+            g.Xp = Xp; g.Wp = Wp; g.Y = Y; g.parts = parts;
+            g.KB = KB; g.tokens = tokens; g.out = L->out; g.y_dt = (uint32_t)y_dt; g.ldy = ldy;
+            g.rows_aligned = ((size_t)ldy * (y_dt == SKL_F32 ? 4 : 2)) % 16 == 0;
+            g.tile0 = tile0;
+        };
+        if (tokens <= SKL_SHORT_TOKENS) {
+            StagedArgs<ShortSplit> g;
+            fill(g);
+            g.sp = skl_make_short_split(cols * GM3_NT, KB);
+            const uint32_t mt = short_mt(tokens), n_grid = (g.sp.T * g.sp.P + 7) / 8 * 8;
+            st = mt == 64 ? launch_product<2>(g, n_grid, stream) : launch_product<4>(g, n_grid, stream);
             if (st != SKL_OK) return st;
-            hipLaunchKernelGGL(k_staged_gemm<8>, dim3(8 * g.sp.gx), dim3(512), lds8, stream, g);
-        } else {
-            st = allow_lds(k_staged_gemm<4>, lds4);
-            if (st != SKL_OK) return st;
-            hipLaunchKernelGGL(k_staged_gemm<4>, dim3(8 * g.sp.gx), dim3(512), lds4, stream, g);
+            if (g.sp.P > 1) {
+                hipLaunchKernelGGL(k_short_fixup, dim3(g.sp.T, (tokens + 15) / 16), dim3(256), 0, stream, g.sp, mt * GM3_NT, parts, Y,
+                                   (uint32_t)y_dt, ldy, tokens, L->out, tile0);
+                st = check_launch("short-prompt fix-up");
+                if (st != SKL_OK) return st;
+            }
+            continue;
         }
-        st = check_launch("staged gemm");
+        StagedArgs<G3Split> g;
+        fill(g);
+        g.sp = skl_make_split(cols * GM3_NT, KB, tokens, true);
+        st = g.sp.mt == GM_MT ? launch_product<8>(g, 8 * g.sp.gx, stream) : launch_product<4>(g, 8 * g.sp.gx, stream);
         if (st != SKL_OK) return st;
         if (g.sp.l_max) {
             hipLaunchKernelGGL(k_staged_fixup, dim3(8 * g.sp.l_max, 16), dim3(256), 0, stream, g.sp, parts, Y, (uint32_t)y_dt, ldy, tokens,

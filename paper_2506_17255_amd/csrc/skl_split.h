@@ -69,6 +69,7 @@ struct G3Split {
     }
     __host__ __device__ uint32_t parts(uint32_t x, uint32_t l) const { return owner(x, (l + 1) * nb - 1) - owner(x, l * nb) + 1; }
     __host__ __device__ size_t slot(uint32_t x, uint32_t l, uint32_t part) const { return ((size_t)x * l_max + l) * p_cap + part; }
+    __host__ __device__ bool empty(uint32_t x, uint32_t wg) const { return rounds(x) == 0 && share_begin(x, wg) >= share_begin(x, wg + 1); }
     // next segment of workgroup wg of XCD x: blocks [k0, k1) of the XCD's k-th tile.  round and u_next
     // carry the position (start: 0 and share_begin(x, wg)); false when the workgroup is done.
     struct Seg { uint32_t k, k0, k1, whole; size_t part_slot; };
@@ -96,6 +97,41 @@ struct G3Split {
     }
 };
 #define G3_SLOT_FLOATS 65536u           // one 256 x 256 partial
+
+// Work split of the short-prompt product (one token tile): an output tile's 64-channel blocks are cut into P equal
+// contiguous shares, one workgroup each.  Every weight word is read by exactly one workgroup, so nothing is gained from
+// keeping a tile on one XCD.  P > 1: every share leaves a float32 partial in slot [tile][share], added up in share order.
+struct ShortSplit {
+    uint32_t T, nb, P;                  // output tiles, blocks per tile, shares per tile
+    __host__ __device__ bool empty(uint32_t xcd, uint32_t wg) const { return wg * 8 + xcd >= T * P; }
+    __host__ __device__ uint32_t share_begin(uint32_t, uint32_t) const { return 0; }
+    __host__ __device__ void tile_of(uint32_t, uint32_t k, uint32_t &tile_m, uint32_t &tile_n) const { tile_m = 0; tile_n = k; }
+    // a workgroup's only segment
+    __host__ __device__ bool next(uint32_t xcd, uint32_t wg, uint32_t &round, uint32_t &, G3Split::Seg &sg) const
+    {
+        if (round++) return false;
+        const uint32_t w = wg * 8 + xcd, part = w % P;
+        sg.k = w / P;
+        sg.k0 = part * nb / P;
+        sg.k1 = (part + 1) * nb / P;
+        sg.whole = P == 1;
+        sg.part_slot = w;
+        return true;
+    }
+};
+
+// 128 workgroups or a little more, but shares of at least four blocks.  More shares stream the weights no faster and
+// write more partials (4096 x 11008, 100 tokens, whole call by workgroups: 43 75.5 us, 86 60.7, 129 55.4, 172 56.2,
+// 215 58.5; 4096 x 4096: 64 38.2, 128 33.9, 256 40.8); shares that ran on into the next tile, 62 us, added a partial
+// and a second start-up to most workgroups.
+static inline ShortSplit skl_make_short_split(uint32_t out, uint32_t nb)
+{
+    ShortSplit sp;
+    sp.T = (out + GM3_NT - 1) / GM3_NT;
+    sp.nb = nb;
+    sp.P = std::max(1u, std::min((127 + sp.T) / sp.T, nb / 4));
+    return sp;
+}
 
 // The split of a call: nb blocks per tile, 256 CUs = 32 workgroups per XCD (fewer when the busiest XCD's
 // share of the work is under four blocks per workgroup).  grouped: deal tiles in units of several token

@@ -57,3 +57,28 @@ def test_activation_packing_of_the_staged_prefill(in_f, tokens, ldx_pad, wide_sh
     with GpuLayer(sk, skl.FLAG_STAGED_PREFILL) as g:
         y = g.gemm(X, "bf16", "f32", ldx=in_f + ldx_pad)
     assert rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
+
+
+@pytest.mark.parametrize("tokens", [1, 16, 17, 64, 65, 100, 128, 129])
+@pytest.mark.parametrize("in_f,out_f,ldy_pad,y_dt", [
+    (256, 300, 0, "f32"),       # shares of fewer than eight blocks: one per tile, stored without partials; ragged outputs
+    (1030, 264, 3, "bf16"),     # four shares per tile, rows of Y not on 16-byte boundaries, ragged last block
+    (2048, 1024, 0, "f16"),     # eight shares per tile
+    (520, 520, 8, "f32"),       # two shares of four and five blocks
+])
+def test_short_prompts(in_f, out_f, ldy_pad, y_dt, tokens):
+    """Calls of at most 128 tokens (tiles of 64 and of 128 tokens) against the fused kernel, which other calls of
+    these layers take, and the oracle; 129 tokens: the first call of the other path."""
+    rng = np.random.default_rng(in_f + out_f + tokens)
+    sk = row_layer(6, in_f, out_f, 4, np.where(rng.random(in_f) < 0.02, 20, 9))
+    X = wk.f32_to_bf16_bits(rng.standard_normal((tokens, in_f)).astype(np.float32))
+    ref = oracle.linear(oracle.query(sk), X, x_kind="bf16")
+    # one rounding of the result: half a unit of the last place, at most 2^-9 (bf16) and 2^-12 (f16) relative
+    tol = {"f32": SUM_TOL, "f16": 2.0**-11, "bf16": 2.0**-8}[y_dt]
+    with GpuLayer(sk) as g, GpuLayer(sk, skl.FLAG_FUSED_PREFILL) as f:
+        assert g.info["prefill_kernel"] == skl.SKL_PREFILL_FUSED
+        y, other = (h.gemm(X, "bf16", y_dt, ldy=out_f + ldy_pad) for h in (g, f))
+        assert np.array_equal(y, g.gemm(X, "bf16", y_dt, ldy=out_f + ldy_pad))
+    assert y.shape == ref.shape
+    for v in (y, other):
+        assert rel_fro(v, ref) <= tol, rel_fro(v, ref)
