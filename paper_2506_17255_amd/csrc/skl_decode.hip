@@ -769,6 +769,8 @@ skl_status_t skl_launch_gemv(const skl_layer *L, const void *x_, uint32_t ldx, v
             })
         }
     } else {
+        if (with_reduction && skl_tile_gemv_is_small(L, batch))
+            return skl_tile_launch_gemv_small(L, src, x, ldx, batch, y, y_dt, ldy, stream);
         st = skl_tile_launch_gemv(L, src, x, ldx, batch, partial, stream);
     }
     if (st != SKL_OK) return st;

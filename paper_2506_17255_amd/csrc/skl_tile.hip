@@ -16,9 +16,20 @@ struct TileArgs {
     uint32_t in, out, tj, to, n_ob, jc_rows, n_jc;
 };
 
-__device__ __forceinline__ void stage_keys(uint16_t *dst, const uint16_t *src, uint32_t n)
+// a group's table to LDS by `stride` threads, this one number t: in pieces of 16 or 4 bytes where it starts on such
+// a boundary (the widths before it decide), key by key elsewhere and at its end
+__device__ __forceinline__ void stage_keys(uint16_t *dst, const uint16_t *src, uint32_t n, uint32_t t, uint32_t stride)
 {
-    for (uint32_t i = threadIdx.x; i < n; i += SKL_WG) dst[i] = src[i];
+    const uintptr_t at = reinterpret_cast<uintptr_t>(src);
+    uint32_t done = 0;
+    if ((at & 15u) == 0) {
+        done = n & ~7u;
+        for (uint32_t i = t; i < n / 8; i += stride) reinterpret_cast<uint4 *>(dst)[i] = reinterpret_cast<const uint4 *>(src)[i];
+    } else if ((at & 3u) == 0) {
+        done = n & ~1u;
+        for (uint32_t i = t; i < n / 2; i += stride) reinterpret_cast<uint32_t *>(dst)[i] = reinterpret_cast<const uint32_t *>(src)[i];
+    }
+    for (uint32_t i = done + t; i < n; i += stride) dst[i] = src[i];
 }
 
 struct TileUnit {
@@ -72,7 +83,7 @@ __global__ __launch_bounds__(SKL_WG) void k_tile_reconstruct(TileArgs p, uint16_
 {
     uint16_t *tab = reinterpret_cast<uint16_t *>(smem);
     const TileUnit u = tile_unit(p, blockIdx.x);
-    stage_keys(tab, p.keys + u.key_off, D * u.K);
+    stage_keys(tab, p.keys + u.key_off, D * u.K, threadIdx.x, SKL_WG);
     __syncthreads();
     const uint32_t ol = blockIdx.y * SKL_WG + threadIdx.x;
     if (ol >= p.to) return;
@@ -93,7 +104,7 @@ __global__ __launch_bounds__(SKL_WG) void k_tile_gemv(TileArgs p, const uint16_t
     uint16_t *tab = reinterpret_cast<uint16_t *>(smem);
     float *xs = reinterpret_cast<float *>(smem + key_words);   // [BT][jc_rows]
     const TileUnit u = tile_unit(p, blockIdx.x);
-    stage_keys(tab, p.keys + u.key_off, D * u.K);
+    stage_keys(tab, p.keys + u.key_off, D * u.K, threadIdx.x, SKL_WG);
     const uint32_t b0 = blockIdx.z * BT;
     const uint32_t rows = u.j_hi - u.j_lo;
     for (uint32_t i = threadIdx.x; i < BT * rows; i += SKL_WG) {
@@ -110,6 +121,8 @@ __global__ __launch_bounds__(SKL_WG) void k_tile_gemv(TileArgs p, const uint16_t
     float acc[BT];
 #pragma unroll
     for (int b = 0; b < BT; ++b) acc[b] = 0.f;
+    // four rows' gathers in flight: a chunk is a chain of rows, each a dependent LDS read otherwise
+#pragma unroll 4
     for (uint32_t jr = 0; jr < rows; ++jr) {
         const float w = half_bits_to_float(key_to_half_bits(th.query(tab, u.K, Kq)));
 #pragma unroll
@@ -120,6 +133,77 @@ __global__ __launch_bounds__(SKL_WG) void k_tile_gemv(TileArgs p, const uint16_t
     for (int b = 0; b < BT; ++b)
         if (b0 + b < batch)
             partial[((size_t)unit * batch + b0 + b) * p.out + u.ob * p.to + ol] = acc[b];
+}
+
+// Decode GEMV of a small layer in one launch.  Bound by latency: the work is under a microsecond, and the partial
+// sums and the second launch of a split reduction took longer.  A workgroup owns 16 outputs and every input row:
+// the tables above these outputs all sit in LDS, each staged by wavefronts of its own at the same time; the 64
+// threads of an output take every 64th row of a table, and their sums are added in LDS in a fixed order.  grid z
+// walks the batch, BT rows per pass.
+// Whole call, split -> one launch: 256 x 256, batch 1 6.4-8.1 -> 4.1-4.6 us, batch 16 8.2 -> 4.5; 1024 x 1024 in groups
+// of 256, batch 1 8.9 -> 5.5, in groups of 128, batch 16 14.9 -> 8.1; 1024 x 2048 in groups of 128, batch 1 8.2 -> 6.6.
+#define TS_O 16
+#define TS_SLICES 64
+#define TS_MAX_IN 1024
+
+template <int D, int BT>
+__global__ __launch_bounds__(TS_O * TS_SLICES) void k_tile_gemv_small(TileArgs p, const uint16_t *__restrict__ x, uint32_t ldx,
+                                                                       uint32_t batch, void *__restrict__ y, uint32_t y_dt,
+                                                                       uint32_t ldy, uint32_t key_words)
+{
+    const uint32_t n_jb = p.in / p.tj;
+    const uint32_t n_oc = (p.to + TS_O - 1) / TS_O;                 // 16-wide output chunks per group column
+    const uint32_t ob = blockIdx.x / n_oc, oc = blockIdx.x - ob * n_oc;
+    float *xs = reinterpret_cast<float *>(smem + n_jb * key_words);          // [BT][in]
+    float *red = xs + (size_t)BT * p.in;                                      // [BT][TS_SLICES][TS_O]
+    __shared__ uint32_t width[TS_MAX_IN / TS_SLICES];
+    const uint32_t b0 = blockIdx.z * BT;
+    // a wavefront or more to a table, all tables at once (one after the other, eight tables took 8.6 us a call, now 6.6)
+    uint32_t tables = 1;                                             // side by side: n_jb rounded up to a power of two
+    while (tables < n_jb) tables *= 2;
+    const uint32_t per_table = TS_O * TS_SLICES / tables;
+    const uint32_t my_jb = threadIdx.x / per_table;
+    if (my_jb < n_jb) {
+        const skl_group_meta gm = p.gmeta[my_jb * p.n_ob + ob];
+        const uint32_t t = threadIdx.x & (per_table - 1);
+        if (t == 0) width[my_jb] = gm.K;
+        stage_keys(reinterpret_cast<uint16_t *>(smem + my_jb * key_words), p.keys + gm.key_off, D * gm.K, t, per_table);
+    }
+#pragma unroll
+    for (int b = 0; b < BT; ++b)
+        for (uint32_t j = threadIdx.x; j < p.in; j += TS_O * TS_SLICES)
+            xs[b * p.in + j] = b0 + b < batch ? half_bits_to_float(x[(size_t)(b0 + b) * ldx + j]) : 0.f;
+    __syncthreads();
+    const uint32_t n = threadIdx.x & (TS_O - 1), slice = threadIdx.x / TS_O;
+    const uint32_t ol = min(oc * TS_O + n, p.to - 1);               // a lane past the group repeats its last output
+    float acc[BT];
+#pragma unroll
+    for (int b = 0; b < BT; ++b) acc[b] = 0.f;
+    for (uint32_t jb = 0; jb < n_jb; ++jb) {
+        const uint16_t *tab = reinterpret_cast<const uint16_t *>(smem + jb * key_words);
+        const uint32_t K = __builtin_amdgcn_readfirstlane(width[jb]), Kq = K << 8;
+        TileHash<D> th;
+        th.init(p.h, slice * p.to + ol, TS_SLICES * p.to);
+#pragma unroll 4
+        for (uint32_t jl = slice; jl < p.tj; jl += TS_SLICES) {
+            const float w = half_bits_to_float(key_to_half_bits(th.query(tab, K, Kq)));
+#pragma unroll
+            for (int b = 0; b < BT; ++b) acc[b] = fmaf(w, xs[b * p.in + jb * p.tj + jl], acc[b]);
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < BT; ++b) red[(b * TS_SLICES + slice) * TS_O + n] = acc[b];
+    __syncthreads();
+    // 16 x 4 threads per batch row: four quarters of the slices, then across the quarters
+    const uint32_t b = threadIdx.x >> 6, q = (threadIdx.x >> 4) & 3u;
+    if (b >= BT) return;
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < TS_SLICES / 4; ++i) t += red[(b * TS_SLICES + q * (TS_SLICES / 4) + i) * TS_O + n];
+    t += __shfl_xor(t, 16);
+    t += __shfl_xor(t, 32);
+    if (q == 0 && oc * TS_O + n < p.to && b0 + b < batch)
+        store_out(y, y_dt, (size_t)(b0 + b) * ldy + ob * p.to + ol, t);
 }
 
 // prefill GEMM on path 0: 64 tokens x 64 outputs per workgroup; per 16 input
@@ -149,7 +233,7 @@ __global__ __launch_bounds__(SKL_WG) void k_tile_gemm(TileArgs p, const uint16_t
     for (uint32_t jb = 0; jb < n_jb; ++jb) {
         const skl_group_meta gm = p.gmeta[jb * p.n_ob + ob];
         __syncthreads();
-        stage_keys(tab, p.keys + gm.key_off, D * gm.K);
+        stage_keys(tab, p.keys + gm.key_off, D * gm.K, threadIdx.x, SKL_WG);
         __syncthreads();
         const uint32_t Kq = gm.K << 8;
         for (uint32_t j0 = 0; j0 < p.tj; j0 += 16) {
@@ -248,6 +332,48 @@ skl_status_t skl_tile_launch_gemv(const skl_layer *L, const TableSrc &src, const
         });
     }
     return st;
+}
+
+// Where one launch is taken: groups of at least 64 rows (fewer leave threads idle), at most 1024 input rows (the gain,
+// 3.5 us at 256 rows, is down to 1.6 there: every workgroup walks all rows), tables that leave room for two workgroups on
+// a compute unit, and no more workgroups than that one round (512 of them: 512 x 2048, batch 16, 13.3 -> 7.3 us); beyond, each table
+// would be staged by workgroups that wait for their turn.
+static inline size_t tile_small_lds(const skl_layer *L, uint32_t bt)
+{
+    return (size_t)L->n_jb * tile_key_words(L) * 16 + (size_t)bt * (L->in + TS_SLICES * TS_O) * sizeof(float);
+}
+
+bool skl_tile_gemv_is_small(const skl_layer *L, uint32_t batch)
+{
+    const uint64_t wgs = (uint64_t)L->n_ob * ((L->to + TS_O - 1) / TS_O) * (batch == 1 ? 1 : (batch + 3) / 4);
+    return L->tj >= TS_SLICES && L->in <= TS_MAX_IN && wgs <= 512 && tile_small_lds(L, batch == 1 ? 1 : 4) <= 65536;
+}
+
+skl_status_t skl_tile_launch_gemv_small(const skl_layer *L, const TableSrc &src, const uint16_t *x, uint32_t ldx, uint32_t batch,
+                                        void *y, skl_dtype_t y_dt, uint32_t ldy, hipStream_t stream)
+{
+    skl_status_t st = SKL_OK;
+    const TileArgs a = make_tile_args(L, src);
+    const uint32_t kw = (uint32_t)tile_key_words(L);
+    const uint32_t n_oc = (L->to + TS_O - 1) / TS_O;
+    if (batch == 1) {
+        const size_t lds = tile_small_lds(L, 1);
+        DISPATCH_D(L->d, {
+            st = allow_lds(k_tile_gemv_small<D, 1>, lds);
+            if (st == SKL_OK)
+                hipLaunchKernelGGL((k_tile_gemv_small<D, 1>), dim3(L->n_ob * n_oc), dim3(TS_O * TS_SLICES), lds, stream, a, x, ldx,
+                                   batch, y, (uint32_t)y_dt, ldy, kw);
+        });
+    } else {
+        const size_t lds = tile_small_lds(L, 4);
+        DISPATCH_D(L->d, {
+            st = allow_lds(k_tile_gemv_small<D, 4>, lds);
+            if (st == SKL_OK)
+                hipLaunchKernelGGL((k_tile_gemv_small<D, 4>), dim3(L->n_ob * n_oc, 1, (batch + 3) / 4), dim3(TS_O * TS_SLICES), lds,
+                                   stream, a, x, ldx, batch, y, (uint32_t)y_dt, ldy, kw);
+        });
+    }
+    return st == SKL_OK ? check_launch("gemv") : st;
 }
 
 skl_status_t skl_tile_launch_gemm(const skl_layer *L, const TableSrc &src, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx,

@@ -82,3 +82,39 @@ def test_short_prompts(in_f, out_f, ldy_pad, y_dt, tokens):
     assert y.shape == ref.shape
     for v in (y, other):
         assert rel_fro(v, ref) <= tol, rel_fro(v, ref)
+
+
+@pytest.mark.parametrize("batch", [1, 2, 4, 5, 16])
+@pytest.mark.parametrize("in_f,out_f,tile_in,tile_out,d", [
+    (64, 24, 64, 24, 2),         # the smallest rows of a group; the last 16 outputs of a group are eight
+    (300, 70, 100, 35, 3),       # rows and outputs of a group that fill no step; tables off 16-byte boundaries
+    (63, 32, 63, 32, 2),         # one row less than the one-launch kernel's lane groups: split
+    (1024, 64, 128, 16, 4),      # the most input rows
+    (1088, 64, 64, 32, 4),       # beyond: split
+    (64, 8208, 64, 16, 2),       # 513 workgroups and more: split at batch 1, too
+])
+def test_small_group_decode(in_f, out_f, tile_in, tile_out, d, batch):
+    """2-D groups on both sides of the line between one launch and a split reduction, groups of unequal width."""
+    rng = np.random.default_rng(in_f + out_f + batch)
+    W = (rng.standard_normal((in_f, out_f)) * 0.02).astype(np.float16)
+    A, C = hash_params(rng, d)
+    K = rng.integers(9, 200, size=(in_f // tile_in) * (out_f // tile_out)).astype(np.uint32)
+    sk = oracle.update(W, tile_in, tile_out, d, A, C, K)
+    x = rng.standard_normal((batch, in_f)).astype(np.float16)
+    ref = oracle.linear(oracle.query(sk), x)
+    with GpuLayer(sk) as g:
+        y = g.gemv(x, "f32")
+    assert rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
+
+
+@pytest.mark.parametrize("batch", [2, 5, 16])
+@pytest.mark.parametrize("out_f", [260, 261, 1027])
+def test_batched_decode_stores(out_f, batch):
+    """Rows of partial sums on 16-byte boundaries (whole words) and not, a last unit of a few outputs."""
+    rng = np.random.default_rng(out_f + batch)
+    sk = row_layer(7, 520, out_f, 4, np.where(rng.random(520) < 0.02, 40, 17))
+    x = rng.standard_normal((batch, 520)).astype(np.float16)
+    ref = oracle.linear(oracle.query(sk), x)
+    with GpuLayer(sk) as g:
+        y = g.gemv(x, "f32")
+    assert rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
