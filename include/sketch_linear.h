@@ -131,7 +131,8 @@ typedef struct {
     uint32_t prefill_kernel;   /* what sketch_linear_gemm runs on calls with fewer than
                                   prefill_staged_from tokens: SKL_PREFILL_*.  Short prompts
                                   (at most 128 tokens) of row sketches are staged whatever this
-                                  says, unless the descriptor asks for the fused kernel */
+                                  says, unless the descriptor asks for the fused kernel or the
+                                  workspace only holds that one's need */
     uint32_t n_blocks;         /* path 1: channel blocks */
     uint32_t prefill_staged_from; /* row sketches: calls with at least this many tokens take
                                   SKL_PREFILL_STAGED (0: every call, 0xFFFFFFFF: none) */
@@ -177,7 +178,14 @@ SKL_API skl_status_t sketch_linear_plan(const skl_desc_t *desc, uint32_t segment
  * (op = 1, n = tokens) or reconstruct (op = 2, n ignored).  The workspace
  * holds the partial sums of the split reduction (gemv), the re-ordered fp16
  * activations and partial tiles (gemm) and, for layers with low-bit states,
- * the 16-bit tables expanded for the call; its contents are scratch. */
+ * the 16-bit tables expanded for the call; its contents are scratch.
+ * The need of gemm does not grow with n throughout.  Staged calls
+ * (SKL_PREFILL_STAGED) hold the layer's dense weights on top, so that a short
+ * prompt (n <= 128) may need more than one of 129 to prefill_staged_from - 1
+ * tokens.  A short prompt that is handed less than its need takes the fused
+ * kernel if that fits: on layers whose prefill_kernel is SKL_PREFILL_FUSED the
+ * need of a layer created with flag bit 2 is enough.  The two kernels add in
+ * different orders. */
 SKL_API skl_status_t sketch_linear_workspace_bytes(const skl_layer_t *layer, uint32_t op, uint32_t n,
                                            uint64_t *bytes);
 

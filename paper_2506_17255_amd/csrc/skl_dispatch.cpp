@@ -13,9 +13,9 @@
     skl_status_t skl_launch_gemv(const skl_layer *L, const void *x, uint32_t ldx, void *y, skl_dtype_t y_dt, uint32_t ldy,       \
                                  uint32_t batch, void *ws, void *stream, bool with_reduction);                                   \
     skl_status_t skl_launch_gemm(const skl_layer *L, const void *X, skl_dtype_t x_dt, uint32_t ldx, void *Y, skl_dtype_t y_dt,   \
-                                 uint32_t ldy, uint32_t tokens, void *ws, void *stream);                                         \
+                                 uint32_t ldy, uint32_t tokens, bool staged, void *ws, void *stream);                            \
     uint64_t skl_gemv_workspace_bytes(const skl_layer *L, uint32_t batch);                                                       \
-    uint64_t skl_gemm_workspace_bytes(const skl_layer *L, uint32_t tokens);                                                      \
+    uint64_t skl_gemm_workspace_bytes(const skl_layer *L, uint32_t tokens, bool staged);                                         \
     uint64_t skl_gemv_group_workspace_bytes(const skl_layer *const *layers, uint32_t n, uint32_t batch);                         \
     skl_status_t skl_launch_gemv_group(const skl_layer *const *layers, uint32_t n, const void *x, uint32_t ldx,                  \
                                        void *const *ys, skl_dtype_t y_dt, uint32_t ldy, uint32_t batch, void *ws, void *stream,  \
@@ -54,9 +54,9 @@ skl_status_t skl_launch_gemv_static(const skl_layer *L, const void *x, uint32_t 
 }
 
 skl_status_t skl_launch_gemm(const skl_layer *L, const void *X, skl_dtype_t x_dt, uint32_t ldx, void *Y, skl_dtype_t y_dt,
-                             uint32_t ldy, uint32_t tokens, void *ws, void *stream)
+                             uint32_t ldy, uint32_t tokens, bool staged, void *ws, void *stream)
 {
-    return BY_MODE(L, skl_launch_gemm(L, X, x_dt, ldx, Y, y_dt, ldy, tokens, ws, stream));
+    return BY_MODE(L, skl_launch_gemm(L, X, x_dt, ldx, Y, y_dt, ldy, tokens, staged, ws, stream));
 }
 
 skl_status_t skl_launch_gemv_group(const skl_layer *const *layers, uint32_t n, const void *x, uint32_t ldx, void *const *ys,
@@ -72,7 +72,7 @@ skl_status_t skl_launch_gemv_group(const skl_layer *const *layers, uint32_t n, c
 
 uint64_t skl_reconstruct_workspace_bytes(const skl_layer *L) { return skl_qm0::skl_reconstruct_workspace_bytes(L); }
 uint64_t skl_gemv_workspace_bytes(const skl_layer *L, uint32_t batch) { return skl_qm0::skl_gemv_workspace_bytes(L, batch); }
-uint64_t skl_gemm_workspace_bytes(const skl_layer *L, uint32_t tokens) { return skl_qm0::skl_gemm_workspace_bytes(L, tokens); }
+uint64_t skl_gemm_workspace_bytes(const skl_layer *L, uint32_t tokens, bool staged) { return skl_qm0::skl_gemm_workspace_bytes(L, tokens, staged); }
 uint64_t skl_gemv_group_workspace_bytes(const skl_layer *const *layers, uint32_t n, uint32_t batch)
 {
     return skl_qm0::skl_gemv_group_workspace_bytes(layers, n, batch);

@@ -783,7 +783,7 @@ skl_status_t sketch_linear_workspace_bytes(const skl_layer_t *L, uint32_t op, ui
         *bytes = skl_gemv_workspace_bytes(L, n);
     } else if (op == 1) {
         if (n < 1) FAIL(SKL_ERR_INVALID_ARG, "tokens must be positive");
-        *bytes = skl_gemm_workspace_bytes(L, n);
+        *bytes = skl_gemm_workspace_bytes(L, n, skl_gemm_is_staged(L, n));
     } else if (op == 2) {
         *bytes = skl_reconstruct_workspace_bytes(L);
     } else {
@@ -883,10 +883,15 @@ skl_status_t sketch_linear_gemm(const skl_layer_t *L, const void *X, skl_dtype_t
     // grid limits of the kernels behind this call, checked before anything is enqueued
     if (L->path == 1 && tokens > 8191u * 256u) FAIL(SKL_ERR_UNSUPPORTED, "more than %u tokens in one call through a row-sketch layer", 8191u * 256u);
     if (L->path == 0 && tokens > 65535u * 64u) FAIL(SKL_ERR_UNSUPPORTED, "more than %u tokens in one call through the per-weight path", 65535u * 64u);
-    skl_status_t st = check_io(L, X, ldx, 2, Y, ldy, dtype_size(y_dt), tokens, ws, ws_bytes,
-                               skl_gemm_workspace_bytes(L, tokens));
+    bool staged = skl_gemm_is_staged(L, tokens);
+    uint64_t need = skl_gemm_workspace_bytes(L, tokens, staged);
+    if (ws_bytes < need && staged && skl_gemm_may_be_fused(L, tokens)) {
+        const uint64_t fused = skl_gemm_workspace_bytes(L, tokens, false);
+        if (fused < need) staged = false, need = fused;
+    }
+    skl_status_t st = check_io(L, X, ldx, 2, Y, ldy, dtype_size(y_dt), tokens, ws, ws_bytes, need);
     if (st != SKL_OK) return st;
-    return skl_launch_gemm(L, X, x_dt, ldx, Y, y_dt, ldy, tokens, ws, stream);
+    return skl_launch_gemm(L, X, x_dt, ldx, Y, y_dt, ldy, tokens, staged, ws, stream);
 }
 
 // ---- several layers on the same activations, one launch --------------------

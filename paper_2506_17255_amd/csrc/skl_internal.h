@@ -157,6 +157,9 @@ static inline bool skl_gemm_is_staged(const skl_layer *L, uint32_t tokens)
 {
     return tokens >= L->gemm_staged_from || (tokens <= SKL_SHORT_TOKENS && L->gemm_staged_from != 0xFFFFFFFFu);
 }
+// A short prompt needs room for the layer's dense weights when it is staged; on a layer that can run the fused kernel a
+// smaller workspace is no error: the call takes that kernel in it.
+static inline bool skl_gemm_may_be_fused(const skl_layer *L, uint32_t tokens) { return tokens < L->gemm_staged_from; }
 
 // error text of the calling thread
 void skl_set_error(const char *fmt, ...);
@@ -191,14 +194,14 @@ skl_status_t skl_launch_gemv(const skl_layer *L, const void *x, uint32_t ldx, vo
                              skl_dtype_t y_dt, uint32_t ldy, uint32_t batch, void *ws, void *stream,
                              bool with_reduction);
 skl_status_t skl_launch_gemm(const skl_layer *L, const void *X, skl_dtype_t x_dt, uint32_t ldx,
-                             void *Y, skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, void *ws,
-                             void *stream);
+                             void *Y, skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, bool staged, void *ws,
+                             void *stream);      // staged: ignored on the per-weight path
 uint64_t skl_gemv_workspace_bytes(const skl_layer *L, uint32_t batch);
 // decode with the library's static device array as workspace (at most skl_static_scratch_bytes())
 uint64_t skl_static_scratch_bytes();
 skl_status_t skl_launch_gemv_static(const skl_layer *L, const void *x, uint32_t ldx, void *y, skl_dtype_t y_dt, uint32_t ldy,
                                     uint32_t batch, void *stream);
-uint64_t skl_gemm_workspace_bytes(const skl_layer *L, uint32_t tokens);
+uint64_t skl_gemm_workspace_bytes(const skl_layer *L, uint32_t tokens, bool staged);
 // decode of 1..4 row-sketch layers of one shape that share x; gate_up: n = 2 (gate, up), ys[0] receives SiLU(gate) * up
 uint64_t skl_gemv_group_workspace_bytes(const skl_layer *const *layers, uint32_t n, uint32_t batch);
 skl_status_t skl_launch_gemv_group(const skl_layer *const *layers, uint32_t n, const void *x, uint32_t ldx, void *const *ys,

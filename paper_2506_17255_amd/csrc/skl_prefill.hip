@@ -448,17 +448,17 @@ static uint64_t gemm_pack_bytes(const skl_layer *L, uint32_t tokens)
     return m_tiles * L->n_gsteps * 8192ull;      // 8 row blocks of 64 lanes x 16 bytes per (token tile, step)
 }
 
-static uint64_t gemm_own_bytes(const skl_layer *L, uint32_t tokens)
+static uint64_t gemm_own_bytes(const skl_layer *L, uint32_t tokens, bool staged)
 {
     if (L->path != 1) return 0;
-    if (skl_gemm_is_staged(L, tokens)) return skl_gemm_staged_bytes(L, tokens);
+    if (staged) return skl_gemm_staged_bytes(L, tokens);
     const G3Split sp = gemm3_split(L, tokens);
     return gemm_pack_bytes(L, tokens) + 8ull * sp.l_max * sp.p_cap * G3_SLOT_FLOATS * sizeof(float);      // + partial tiles
 }
 
-uint64_t skl_gemm_workspace_bytes(const skl_layer *L, uint32_t tokens)
+uint64_t skl_gemm_workspace_bytes(const skl_layer *L, uint32_t tokens, bool staged)
 {
-    const uint64_t own = gemm_own_bytes(L, tokens);
+    const uint64_t own = gemm_own_bytes(L, tokens, staged);
     return L->qbits ? round256(own) + skl_dequant_bytes(L) : own;
 }
 
@@ -481,13 +481,12 @@ static skl_status_t launch_gemm3_fixup(const G3Split &sp, const float *parts, vo
 }
 
 skl_status_t skl_launch_gemm(const skl_layer *L, const void *X_, skl_dtype_t x_dt, uint32_t ldx, void *Y,
-                             skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, void *ws, void *stream_)
+                             skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, bool staged, void *ws, void *stream_)
 {
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     const uint16_t *X = static_cast<const uint16_t *>(X_);
-    const bool staged = L->path == 1 && skl_gemm_is_staged(L, tokens);      // the rebuild kernel reads the padded tables, the fused kernel the unpadded ones
-    TableSrc src;
-    skl_status_t st = skl_table_source(L, static_cast<char *>(ws) + round256(gemm_own_bytes(L, tokens)),
+    TableSrc src;       // the rebuild kernel reads the padded tables, the fused kernel the unpadded ones
+    skl_status_t st = skl_table_source(L, static_cast<char *>(ws) + round256(gemm_own_bytes(L, tokens, staged)),
                                    L->path == 1 && staged, L->path == 1 && !staged, stream, &src);
     if (st != SKL_OK) return st;
     if (L->path == 1) {

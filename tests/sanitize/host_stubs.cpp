@@ -17,7 +17,7 @@ skl_status_t skl_launch_gemv(const skl_layer *, const void *, uint32_t, void *, 
 {
     return no_device("gemv");
 }
-skl_status_t skl_launch_gemm(const skl_layer *, const void *, skl_dtype_t, uint32_t, void *, skl_dtype_t, uint32_t, uint32_t, void *,
+skl_status_t skl_launch_gemm(const skl_layer *, const void *, skl_dtype_t, uint32_t, void *, skl_dtype_t, uint32_t, uint32_t, bool, void *,
                              void *)
 {
     return no_device("gemm");
@@ -28,7 +28,7 @@ skl_status_t skl_launch_gemv_static(const skl_layer *, const void *, uint32_t, v
 {
     return no_device("gemv");
 }
-uint64_t skl_gemm_workspace_bytes(const skl_layer *, uint32_t) { return 0; }
+uint64_t skl_gemm_workspace_bytes(const skl_layer *, uint32_t, bool) { return 0; }
 uint64_t skl_gemv_group_workspace_bytes(const skl_layer *const *, uint32_t, uint32_t) { return 0; }
 skl_status_t skl_launch_gemv_group(const skl_layer *const *, uint32_t, const void *, uint32_t, void *const *, skl_dtype_t, uint32_t,
                                    uint32_t, void *, void *, bool)

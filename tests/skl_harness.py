@@ -128,7 +128,8 @@ class GpuLayer:
             assert np.all(np.isnan(y[:, self.sk.out_features:].astype(np.float32))), "wrote past out_features"
         return y[:, :self.sk.out_features]
 
-    def gemm(self, X_bits: np.ndarray, x_dtype: str = "bf16", y_dtype: str = "f32", ldx=None, ldy=None) -> np.ndarray:
+    def gemm(self, X_bits: np.ndarray, x_dtype: str = "bf16", y_dtype: str = "f32", ldx=None, ldy=None, ws_bytes=None) -> np.ndarray:
+        """ws_bytes: hand the call a workspace of that size (whose end is checked) instead of one of the size it asks for."""
         t = self.torch
         tokens, in_f = X_bits.shape
         ldx = ldx or in_f
@@ -139,9 +140,13 @@ class GpuLayer:
         ydt = {"f32": t.float32, "f16": t.float16, "bf16": t.bfloat16}[y_dtype]
         yd = t.full((tokens, ldy), float("nan"), dtype=ydt, device=self.dev)
         ws, need = self.workspace(1, tokens)
+        if ws_bytes is not None:
+            ws = t.full((ws_bytes + 4096,), 0xA5, dtype=t.uint8, device=self.dev)
         skl.sketch_linear_gemm(self.handle, xd.data_ptr(), DT[x_dtype], ldx, yd.data_ptr(), DT[y_dtype], ldy,
-                               tokens, ws.data_ptr(), ws.numel(), self.stream())
+                               tokens, ws.data_ptr(), ws.numel() if ws_bytes is None else ws_bytes, self.stream())
         t.cuda.synchronize()
+        if ws_bytes is not None:
+            assert bool((ws[ws_bytes:] == 0xA5).all()), "wrote past the workspace"
         y = yd.float().cpu().numpy() if y_dtype == "bf16" else yd.cpu().numpy()
         if ldy > self.sk.out_features:
             assert np.all(np.isnan(y[:, self.sk.out_features:].astype(np.float32))), "wrote past out_features"

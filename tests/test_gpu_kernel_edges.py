@@ -84,6 +84,28 @@ def test_short_prompts(in_f, out_f, ldy_pad, y_dt, tokens):
         assert rel_fro(v, ref) <= tol, rel_fro(v, ref)
 
 
+@pytest.mark.parametrize("bits", [16, 4])
+@pytest.mark.parametrize("tokens", [1, 64, 100, 128])
+def test_short_prompts_in_a_workspace_of_the_fused_kernel(tokens, bits):
+    """A workspace that holds the fused kernel's need but not the dense weights: the call is accepted, and is the fused
+    kernel's bit for bit; one byte less is refused; the full need gives the staged result."""
+    rng = np.random.default_rng(tokens + bits)
+    sk = row_layer(8, 264, 776, 3, np.where(rng.random(264) < 0.02, 20, 9))
+    if bits < 16:
+        sk = oracle.quantize(sk, bits)
+    X = wk.f32_to_bf16_bits(rng.standard_normal((tokens, 264)).astype(np.float32))
+    with GpuLayer(sk) as g, GpuLayer(sk, skl.FLAG_FUSED_PREFILL) as f:
+        need, fused = (skl.sketch_linear_workspace_bytes(h.handle, 1, tokens) for h in (g, f))
+        assert fused < need
+        want = f.gemm(X, "bf16", "f32")
+        for n in (fused, need - 1):
+            assert np.array_equal(g.gemm(X, "bf16", "f32", ws_bytes=n), want)
+        assert np.array_equal(g.gemm(X, "bf16", "f32", ws_bytes=need), g.gemm(X, "bf16", "f32"))
+        with pytest.raises(skl.SketchLinearError) as e:
+            g.gemm(X, "bf16", "f32", ws_bytes=fused - 1)
+        assert e.value.status == skl.SKL_ERR_BUFFER_TOO_SMALL
+
+
 @pytest.mark.parametrize("batch", [1, 2, 4, 5, 16])
 @pytest.mark.parametrize("in_f,out_f,tile_in,tile_out,d", [
     (64, 24, 64, 24, 2),         # the smallest rows of a group; the last 16 outputs of a group are eight
