@@ -130,9 +130,10 @@ typedef struct {
                                   state row (8 * 2^i input channels per block) */
     uint32_t prefill_kernel;   /* what sketch_linear_gemm runs on calls with fewer than
                                   prefill_staged_from tokens: SKL_PREFILL_*.  Short prompts
-                                  (at most 128 tokens) of row sketches are staged whatever this
-                                  says, unless the descriptor asks for the fused kernel or the
-                                  workspace only holds that one's need */
+                                  (at most 128 tokens) of row sketches may be staged all the same:
+                                  where the dense weights stay below 240 MiB or the channel
+                                  blocks are narrow, unless the descriptor asks for the fused
+                                  kernel or the workspace only holds that one's need */
     uint32_t n_blocks;         /* path 1: channel blocks */
     uint32_t prefill_staged_from; /* row sketches: calls with at least this many tokens take
                                   SKL_PREFILL_STAGED (0: every call, 0xFFFFFFFF: none) */

@@ -375,6 +375,15 @@ static void plan_prefill(const skl_desc_t *d, skl_plan *P)
     // is a single round of tiles either way, and the staged one is 10 % faster at 1024 tokens and 25 % at
     // 2048.  flags bit 1: always staged; bit 2: fused whenever the tables allow.
     L.gemm_staged_from = !L.gemm_v3 || (d->flags & 2u) ? 0u : (d->flags & 4u) ? 0xFFFFFFFFu : 513u;
+    // Short prompts are staged too, as long as the memory-side cache (256 MiB) holds the rebuilt weights between the
+    // two launches.  Whole call, 17 / 128 tokens, fused -> staged, d = 4, blocks of eight words: 4096 x 4096 54 / 56 ->
+    // 29 / 29 us, 8192 x 8192 82 / 83 -> 55 / 62, 14336 x 8192 (224 MiB) 112 / 114 -> 83 / 98; but 16384 x 8192 (256 MiB)
+    // 122 / 125 -> 129 / 147, 28672 x 8192 193 / 192 -> 232 / 246.  Where the blocks are narrow the fused kernel pays
+    // for the empty half of its matrix instructions and staging wins at every size: d = 3, four words, 8192 x 16384
+    // 185 / 187 -> 132 / 151, 8192 x 28672 306 / 307 -> 219 / 224.
+    const uint64_t weight_bytes = (uint64_t)((L.out + 255) / 256) * L.gemm_kb * 32768;
+    const bool narrow = 2ull * L.n_blocks > 3ull * L.gemm_kb;
+    L.gemm_short_to = L.gemm_staged_from == 513u && (narrow || weight_bytes <= 240ull << 20) ? SKL_SHORT_TOKENS : 0u;
 }
 
 // Row-sketch plan.  Returns false when some width is too large for any block

@@ -122,7 +122,8 @@ struct skl_layer {
     uint64_t off_gsteps = 0;
     // staged prefill (weights rebuilt once per call into the workspace): 64-channel blocks along the channel
     // list, and the windows of X that hold the channels of PO_STEPS steps of 32 list entries
-    uint32_t gemm_staged_from = 0, gemm_kb = 0;     // calls with at least gemm_staged_from tokens are staged
+    uint32_t gemm_staged_from = 0, gemm_kb = 0;     // calls with at least gemm_staged_from tokens are staged,
+    uint32_t gemm_short_to = 0;                     // and those with at most gemm_short_to
     uint64_t off_windows = 0;
 
     // low-bit states: only codes and scales are resident (row sketches: re-ordered into the word order of the
@@ -149,14 +150,9 @@ struct skl_plan {
     std::vector<skl_pack_window> windows;
 };
 
-// Short prompts are staged with tiles of 64 or 128 tokens (unless the fused kernel is asked for): up to one 128-token
-// tile.  Whole call, fused / this: 4096 x 11008, 17 tokens 85 / 45 us, 100 tokens 87 / 52, 128 tokens 87 / 54;
-// 4096 x 4096 55 / 29, 56 / 29, 56 / 30; 1024 x 2048 38 / 15, 39 / 18, 39 / 18.
+// Short prompts, up to one 128-token tile: staged calls take tiles of 64 or 128 tokens.
 #define SKL_SHORT_TOKENS 128u
-static inline bool skl_gemm_is_staged(const skl_layer *L, uint32_t tokens)
-{
-    return tokens >= L->gemm_staged_from || (tokens <= SKL_SHORT_TOKENS && L->gemm_staged_from != 0xFFFFFFFFu);
-}
+static inline bool skl_gemm_is_staged(const skl_layer *L, uint32_t tokens) { return tokens >= L->gemm_staged_from || tokens <= L->gemm_short_to; }
 // A short prompt needs room for the layer's dense weights when it is staged; on a layer that can run the fused kernel a
 // smaller workspace is no error: the call takes that kernel in it.
 static inline bool skl_gemm_may_be_fused(const skl_layer *L, uint32_t tokens) { return tokens < L->gemm_staged_from; }

@@ -84,6 +84,28 @@ def test_short_prompts(in_f, out_f, ldy_pad, y_dt, tokens):
         assert rel_fro(v, ref) <= tol, rel_fro(v, ref)
 
 
+@pytest.mark.parametrize("in_f,out_f,d,staged", [
+    (15360, 8192, 2, True),     # 240 MiB of dense weights
+    (15424, 8192, 2, False),    # 64 channels more
+    (15424, 8192, 7, True),     # blocks of four words (seven rows leave no room for eight)
+])
+def test_short_prompts_of_layers_around_the_cache_size(in_f, out_f, d, staged):
+    """Which way a short prompt goes, told by the workspace it asks for; the fused way is the fused kernel's bit for bit."""
+    rng = np.random.default_rng(in_f + d)
+    A, C = hash_params(rng, d)
+    K = np.full(in_f, 4, dtype=np.uint32)
+    states = (rng.standard_normal(in_f * d * 4) * 0.02).astype(np.float16).view(np.uint16)
+    sk = oracle.Sketch(in_f, out_f, 1, out_f, d, A, C, K, states)
+    X = wk.f32_to_bf16_bits(rng.standard_normal((20, in_f)).astype(np.float32))
+    with GpuLayer(sk) as g, GpuLayer(sk, skl.FLAG_FUSED_PREFILL) as f:
+        assert g.info["prefill_kernel"] == skl.SKL_PREFILL_FUSED
+        need, fused = (skl.sketch_linear_workspace_bytes(h.handle, 1, 20) for h in (g, f))
+        assert (need > in_f * out_f * 2) == staged and (need == fused) != staged
+        y, other = (h.gemm(X, "bf16", "f32") for h in (g, f))
+    assert rel_fro(y, other) <= (2 * in_f) ** 0.5 * 2.0**-24        # two float32 sums of in_f exact products each
+    assert staged or np.array_equal(y, other)
+
+
 @pytest.mark.parametrize("bits", [16, 4])
 @pytest.mark.parametrize("tokens", [1, 64, 100, 128])
 def test_short_prompts_in_a_workspace_of_the_fused_kernel(tokens, bits):
