@@ -284,7 +284,13 @@ SKL_API skl_status_t sketch_linear_gemm(const skl_layer_t *layer, const void *X,
  * XCDs balanced.  Tiles are 256 tokens high, except in staged calls whose
  * 128-token tiles number between 225 and 256 (2048 tokens x 4096 outputs):
  * there every workgroup takes one whole tile of 128 tokens and nothing is left
- * over.
+ * over; and in staged calls of at most 128 tokens, which have one tile of 64 or
+ * 128 tokens per 256 outputs: the blocks of a tile are cut into equal shares
+ * (shape word 2 of them, whole tiles if 0), tile t's share s runs on workgroup
+ * t * shares + s of all, dealt to XCD 0..7 in turn, and leaves slot
+ * t * shares + s.  A slot holds the tokens of a tile x 256 outputs.  Staged
+ * layers of more than 1 GiB of weight words are worked off in slabs of output
+ * tiles, each split by itself.
  * *n_segments receives the number of segments (also when it exceeds
  * `capacity`; then only the first `capacity` are written).  `shape` (HOST,
  * 6 words, may be NULL) receives workgroups per XCD, partial tiles per XCD,

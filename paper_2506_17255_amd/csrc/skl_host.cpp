@@ -572,14 +572,13 @@ static skl_status_t make_plan(const skl_desc_t *user, skl_plan *P)
 // ---------------------------------------------------------- prefill split
 // every segment of the split, eight words each: xcd, workgroup, token tile, output tile, first block,
 // end block, whole-tile flag, partial slot; returns the number of segments (writes at most cap of them)
-uint64_t skl_gemm3_segments(uint32_t out, uint32_t n_blocks, uint32_t tokens, bool grouped, uint32_t *segs, uint64_t cap,
-                            uint32_t *shape)
+template <class Split>
+static uint64_t list_segments(const Split &sp, uint32_t gx, uint32_t *segs, uint64_t cap)
 {
-    const G3Split sp = skl_make_split(out, n_blocks, tokens, grouped);
-    if (shape) { shape[0] = sp.gx; shape[1] = sp.l_max; shape[2] = sp.p_cap; shape[3] = sp.T; shape[4] = sp.mu; shape[5] = sp.mt; }
     uint64_t n = 0;
     for (uint32_t x = 0; x < 8; ++x)
-        for (uint32_t wg = 0; wg < sp.gx; ++wg) {
+        for (uint32_t wg = 0; wg < gx; ++wg) {
+            if (sp.empty(x, wg)) continue;
             uint32_t round = 0, u_next = sp.share_begin(x, wg);
             G3Split::Seg sg;
             while (sp.next(x, wg, round, u_next, sg)) {
@@ -587,12 +586,25 @@ uint64_t skl_gemm3_segments(uint32_t out, uint32_t n_blocks, uint32_t tokens, bo
                     uint32_t *o = segs + 8 * n;
                     o[0] = x; o[1] = wg;
                     sp.tile_of(x, sg.k, o[2], o[3]);
-                    o[4] = sg.k0; o[5] = sg.k1; o[6] = sg.whole; o[7] = (uint32_t)sg.part_slot;
+                    o[4] = sg.k0; o[5] = sg.k1; o[6] = sg.whole; o[7] = sg.whole ? 0 : (uint32_t)sg.part_slot;
                 }
                 ++n;
             }
         }
     return n;
+}
+
+uint64_t skl_prefill_segments(uint32_t out, uint32_t n_blocks, uint32_t tokens, bool staged, uint32_t *segs, uint64_t cap, uint32_t *shape)
+{
+    if (staged && tokens <= SKL_SHORT_TOKENS) {
+        const ShortSplit sp = skl_make_short_split(out, n_blocks);
+        const uint32_t gx = (sp.T * sp.P + 7) / 8;
+        if (shape) { shape[0] = gx; shape[1] = sp.P > 1 ? (sp.T + 7) / 8 : 0; shape[2] = sp.P > 1 ? sp.P : 0; shape[3] = sp.T; shape[4] = 1; shape[5] = skl_short_mt(tokens); }
+        return list_segments(sp, gx, segs, cap);
+    }
+    const G3Split sp = skl_make_split(out, n_blocks, tokens, staged);
+    if (shape) { shape[0] = sp.gx; shape[1] = sp.l_max; shape[2] = sp.p_cap; shape[3] = sp.T; shape[4] = sp.mu; shape[5] = sp.mt; }
+    return list_segments(sp, sp.gx, segs, cap);
 }
 
 // ---------------------------------------------------------- debug build
@@ -1021,7 +1033,7 @@ skl_status_t sketch_linear_prefill_split(uint32_t kernel, uint32_t out_features,
     if (!segments && capacity) FAIL(SKL_ERR_INVALID_ARG, "segments is NULL with a non-zero capacity");
     if (out_features < 1 || n_blocks < 1 || tokens < 1) FAIL(SKL_ERR_INVALID_ARG, "out_features, n_blocks and tokens must be positive");
     if (tokens > (1u << 24)) FAIL(SKL_ERR_UNSUPPORTED, "more than 2^24 tokens in one call");
-    *n_segments = skl_gemm3_segments(out_features, n_blocks, tokens, kernel == SKL_PREFILL_STAGED, segments, capacity, shape);
+    *n_segments = skl_prefill_segments(out_features, n_blocks, tokens, kernel == SKL_PREFILL_STAGED, segments, capacity, shape);
     return SKL_OK;
 }
 

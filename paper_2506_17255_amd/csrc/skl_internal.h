@@ -150,8 +150,6 @@ struct skl_plan {
     std::vector<skl_pack_window> windows;
 };
 
-// Short prompts, up to one 128-token tile: staged calls take tiles of 64 or 128 tokens.
-#define SKL_SHORT_TOKENS 128u
 static inline bool skl_gemm_is_staged(const skl_layer *L, uint32_t tokens) { return tokens >= L->gemm_staged_from || tokens <= L->gemm_short_to; }
 // A short prompt needs room for the layer's dense weights when it is staged; on a layer that can run the fused kernel a
 // smaller workspace is no error: the call takes that kernel in it.
@@ -209,5 +207,5 @@ skl_status_t skl_launch_build(const skl_desc_t *d, uint64_t n_groups, const uint
 uint64_t skl_microbench_work(uint32_t kind, uint32_t iters, uint64_t ws_bytes);
 skl_status_t skl_launch_microbench(uint32_t kind, uint32_t iters, void *ws, uint64_t ws_bytes, void *stream);
 skl_status_t skl_launch_debug_selftest(uint32_t value, uint32_t limit, void *stream);
-uint64_t skl_gemm3_segments(uint32_t out, uint32_t n_blocks, uint32_t tokens, bool by_col, uint32_t *segs, uint64_t cap,
-                            uint32_t *shape);
+uint64_t skl_prefill_segments(uint32_t out, uint32_t n_blocks, uint32_t tokens, bool staged, uint32_t *segs, uint64_t cap,
+                              uint32_t *shape);

@@ -18,7 +18,7 @@ namespace SKL_NS {
 
 #define SG_STEP_WORDS 1024u             // 32 channels x 256 outputs (or tokens): [16-wide block 16][channel group 4][16] words of eight channels
 #define SG_SLOT_WORDS (2u * SG_STEP_WORDS)
-#define SG_SLOT_BYTES (SG_SLOT_WORDS * 16u)
+static_assert(SG_SLOT_BYTES == SG_SLOT_WORDS * 16u, "weight words of a 64-channel block of an output tile");
 #define SG_EPI_BYTES 8704u              // epilogue, per wavefront: 32 rows x (64 float32 + 16 bytes)
 
 struct RebuildArgs {
@@ -439,21 +439,7 @@ __global__ __launch_bounds__(256) void k_short_fixup(ShortSplit sp, uint32_t par
 // ========================================================================
 // Launcher
 // ========================================================================
-// Output-tile columns per slab.  The weight words of a slab (KB x 32 KiB per column) are rebuilt, multiplied
-// and released before the next slab is touched, which bounds the workspace for very large layers; up to
-// 1 GiB of weight words the layer is one slab (measured on the 8192 x 28672 layer: four slabs of 134 MB
-// cost 8 % -- every slab stages all tables again -- and the product kernel gained nothing from finding its
-// words in the memory-side cache).  Slabs are whole rounds of the product kernel (32 columns x 8 token
-// tiles = one tile per workgroup at 2048 tokens).
-static uint32_t staged_slab_cols(const skl_layer *L, uint32_t tokens)
-{
-    const uint32_t n_col = (L->out + GM3_NT - 1) / GM3_NT, m_tiles = (tokens + GM_MT - 1) / GM_MT;
-    const uint64_t col_bytes = (uint64_t)L->gemm_kb * SG_SLOT_BYTES;
-    if (n_col * col_bytes <= (1ull << 30)) return n_col;
-    const uint32_t round_cols = std::max(1u, 256 / std::max(1u, m_tiles));      // columns of one tile per workgroup
-    const uint32_t cols = round_cols * (uint32_t)std::max<uint64_t>(1, (512ull << 20) / (round_cols * col_bytes));
-    return std::min(n_col, cols);
-}
+static uint32_t staged_slab_cols(const skl_layer *L, uint32_t tokens) { return skl_staged_slab_cols(L->out, L->gemm_kb, tokens); }
 
 static uint64_t staged_pack_bytes(const skl_layer *L, uint32_t tokens)
 {
@@ -461,27 +447,9 @@ static uint64_t staged_pack_bytes(const skl_layer *L, uint32_t tokens)
     return m_tiles * L->gemm_kb * 2 * SG_STEP_WORDS * 16ull;
 }
 
-// short prompts: tokens per tile
-static uint32_t short_mt(uint32_t tokens) { return tokens <= 64 ? 64 : 128; }
-
 static uint64_t staged_part_bytes(const skl_layer *L, uint32_t tokens)
 {
-    if (tokens <= SKL_SHORT_TOKENS) {
-        const uint32_t n_col = (L->out + GM3_NT - 1) / GM3_NT, cols = staged_slab_cols(L, tokens);
-        // (the last slab may be narrower, and its tiles cut into more shares)
-        const ShortSplit sp = skl_make_short_split(cols * GM3_NT, L->gemm_kb), last = skl_make_short_split((n_col % cols ? n_col % cols : cols) * GM3_NT, L->gemm_kb);
-        const uint64_t most = std::max<uint64_t>(sp.P > 1 ? (uint64_t)sp.T * sp.P : 0, last.P > 1 ? (uint64_t)last.T * last.P : 0);
-        return most * short_mt(tokens) * GM3_NT * sizeof(float);
-    }
-    // the widest slab has the most leftover tiles
-    const G3Split sp = skl_make_split(staged_slab_cols(L, tokens) * GM3_NT, L->gemm_kb, tokens, true);
-    uint64_t most = 8ull * sp.l_max * sp.p_cap;
-    const uint32_t n_col = (L->out + GM3_NT - 1) / GM3_NT, cols = staged_slab_cols(L, tokens);
-    if (n_col % cols) {
-        const G3Split last = skl_make_split((n_col % cols) * GM3_NT, L->gemm_kb, tokens, true);
-        most = std::max<uint64_t>(most, 8ull * last.l_max * last.p_cap);
-    }
-    return most * G3_SLOT_FLOATS * sizeof(float);
+    return skl_staged_part_floats(L->out, L->gemm_kb, tokens) * sizeof(float);
 }
 
 uint64_t skl_gemm_staged_bytes(const skl_layer *L, uint32_t tokens)
@@ -548,7 +516,7 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
             StagedArgs<ShortSplit> g;
             fill(g);
             g.sp = skl_make_short_split(cols * GM3_NT, KB);
-            const uint32_t mt = short_mt(tokens), n_grid = (g.sp.T * g.sp.P + 7) / 8 * 8;
+            const uint32_t mt = skl_short_mt(tokens), n_grid = (g.sp.T * g.sp.P + 7) / 8 * 8;
             st = mt == 64 ? launch_product<2>(g, n_grid, stream) : launch_product<4>(g, n_grid, stream);
             if (st != SKL_OK) return st;
             if (g.sp.P > 1) {

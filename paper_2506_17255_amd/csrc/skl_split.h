@@ -98,6 +98,10 @@ struct G3Split {
 };
 #define G3_SLOT_FLOATS 65536u           // one 256 x 256 partial
 
+// Short prompts: staged calls of at most SKL_SHORT_TOKENS tokens are one token tile of 64 or 128 tokens.
+#define SKL_SHORT_TOKENS 128u
+static inline uint32_t skl_short_mt(uint32_t tokens) { return tokens <= 64 ? 64 : 128; }
+
 // Work split of the short-prompt product (one token tile): an output tile's 64-channel blocks are cut into P equal
 // contiguous shares, one workgroup each.  Every weight word is read by exactly one workgroup, so nothing is gained from
 // keeping a tile on one XCD.  P > 1: every share leaves a float32 partial in slot [tile][share], added up in share order.
@@ -120,10 +124,11 @@ struct ShortSplit {
     }
 };
 
-// 128 workgroups or a little more, but shares of at least four blocks.  More shares stream the weights no faster and
-// write more partials (4096 x 11008, 100 tokens, whole call by workgroups: 43 75.5 us, 86 60.7, 129 55.4, 172 56.2,
-// 215 58.5; 4096 x 4096: 64 38.2, 128 33.9, 256 40.8); shares that ran on into the next tile, 62 us, added a partial
-// and a second start-up to most workgroups.
+// The fewest equal shares per tile that make 128 workgroups, but shares of at least four blocks.  More shares stream the
+// weights no faster and write more partials (while the split was chosen, 4096 x 11008, 100 tokens, whole call by
+// workgroups: 43 75.5 us, 86 60.7, 129 55.4, 172 56.2, 215 58.5; 4096 x 4096: 64 38.2, 128 33.9, 256 40.8); shares that
+// ran on into the next tile, 62 us, added a partial and a second start-up to most workgroups.  (65 to 127 tiles need two
+// shares each, up to 254 workgroups: one share would leave half the chip without work.)
 static inline ShortSplit skl_make_short_split(uint32_t out, uint32_t nb)
 {
     ShortSplit sp;
@@ -182,4 +187,41 @@ static inline G3Split skl_make_split(uint32_t out, uint32_t nb, uint32_t tokens,
         for (uint32_t l = 0; l < sp.left(x); ++l) sp.p_cap = std::max(sp.p_cap, sp.parts(x, l));
     }
     return sp;
+}
+
+// ---- staged calls: slabs and partial tiles ----
+#define SG_SLOT_BYTES 32768u            // weight words of one 64-channel block of an output tile (64 channels x 256 outputs)
+
+// Output-tile columns per slab.  The weight words of a slab (kb x 32 KiB per column) are rebuilt, multiplied and released
+// before the next slab is touched, which bounds the workspace for very large layers; up to 1 GiB of weight words the
+// layer is one slab (measured on the 8192 x 28672 layer: four slabs of 134 MB cost 8 % -- every slab stages all tables
+// again -- and the product kernel gained nothing from finding its words in the memory-side cache).  Slabs are whole
+// rounds of the product kernel (32 columns x 8 token tiles = one tile per workgroup at 2048 tokens).
+static inline uint32_t skl_staged_slab_cols(uint32_t out, uint32_t kb, uint32_t tokens)
+{
+    const uint32_t n_col = (out + GM3_NT - 1) / GM3_NT, m_tiles = (tokens + GM_MT - 1) / GM_MT;
+    const uint64_t col_bytes = (uint64_t)kb * SG_SLOT_BYTES;
+    if (n_col * col_bytes <= (1ull << 30)) return n_col;
+    const uint32_t round_cols = std::max(1u, 256 / std::max(1u, m_tiles));      // columns of one tile per workgroup
+    const uint32_t cols = round_cols * (uint32_t)std::max<uint64_t>(1, (512ull << 20) / (round_cols * col_bytes));
+    return std::min(n_col, cols);
+}
+
+// Room for the partial tiles of a staged call: the most of any slab (the last one may be narrower, and its tiles be cut
+// into more shares).
+static inline uint64_t skl_staged_part_floats(uint32_t out, uint32_t kb, uint32_t tokens)
+{
+    const uint32_t n_col = (out + GM3_NT - 1) / GM3_NT, cols = skl_staged_slab_cols(out, kb, tokens);
+    uint64_t most = 0;
+    for (const uint32_t width : {cols, n_col % cols}) {
+        if (!width) continue;
+        if (tokens <= SKL_SHORT_TOKENS) {
+            const ShortSplit sp = skl_make_short_split(width * GM3_NT, kb);
+            if (sp.P > 1) most = std::max(most, (uint64_t)sp.T * sp.P * skl_short_mt(tokens) * GM3_NT);
+        } else {
+            const G3Split sp = skl_make_split(width * GM3_NT, kb, tokens, true);
+            most = std::max(most, (uint64_t)sp.l_max * 8 * sp.p_cap * G3_SLOT_FLOATS);
+        }
+    }
+    return most;
 }

@@ -7,11 +7,14 @@ leave float32 partials in numbered slots.  These tests enumerate the split
 through the C ABI and check the properties the kernels rely on.
 """
 import itertools
+import os
+import subprocess
 
 import pytest
 
 import paper_2506_17255_amd as skl
 
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 KERNELS = [skl.SKL_PREFILL_FUSED, skl.SKL_PREFILL_STAGED]
 
@@ -60,10 +63,11 @@ SHAPES = [
     (65536, 5, 4096),
     (256 * 33, 64, 2048), # one tile more than a whole round on one XCD
 ]
+# Staged calls of at most 128 tokens have a split of their own (below); these are of the general one.
+CASES = [(*shape, kernel) for kernel in KERNELS for shape in SHAPES if kernel != skl.SKL_PREFILL_STAGED or shape[2] > 128]
 
 
-@pytest.mark.parametrize("kernel", KERNELS)
-@pytest.mark.parametrize("out_features,n_blocks,tokens", SHAPES)
+@pytest.mark.parametrize("out_features,n_blocks,tokens,kernel", CASES)
 def test_every_block_of_every_tile_is_multiplied_once(out_features, n_blocks, tokens, kernel):
     segs, (gx, l_max, p_cap, n_tiles, mu, mt) = split(out_features, n_blocks, tokens, kernel)
     assert mt in (128, 256) and (mt == 256 or kernel == skl.SKL_PREFILL_STAGED)
@@ -92,8 +96,7 @@ def test_every_block_of_every_tile_is_multiplied_once(out_features, n_blocks, to
     assert len(seen) == n_tiles * n_blocks
 
 
-@pytest.mark.parametrize("kernel", KERNELS)
-@pytest.mark.parametrize("out_features,n_blocks,tokens", SHAPES)
+@pytest.mark.parametrize("out_features,n_blocks,tokens,kernel", CASES)
 def test_partial_slots_are_distinct_dense_and_in_workgroup_order(out_features, n_blocks, tokens, kernel):
     segs, (gx, l_max, p_cap, n_tiles, mu, mt) = split(out_features, n_blocks, tokens, kernel)
     by_tile = {}
@@ -119,8 +122,7 @@ def test_partial_slots_are_distinct_dense_and_in_workgroup_order(out_features, n
             assert e == b
 
 
-@pytest.mark.parametrize("kernel", KERNELS)
-@pytest.mark.parametrize("out_features,n_blocks,tokens", SHAPES)
+@pytest.mark.parametrize("out_features,n_blocks,tokens,kernel", CASES)
 def test_workgroups_get_equal_work(out_features, n_blocks, tokens, kernel):
     segs, (gx, l_max, p_cap, n_tiles, mu, mt) = split(out_features, n_blocks, tokens, kernel)
     load = {}
@@ -197,8 +199,8 @@ def check_fixup_reads_only_written_slots(out_features, n_blocks, tokens, kernel=
             assert (tm, tn) not in written
 
 
-@pytest.mark.parametrize("kernel", KERNELS)
-@pytest.mark.parametrize("out_features,n_blocks,tokens", SHAPES + [(7936, 16, 2048), (256 * 57, 1, 256), (4864, 1, 768)])
+@pytest.mark.parametrize("out_features,n_blocks,tokens,kernel",
+                         CASES + [(*s, k) for k in KERNELS for s in [(7936, 16, 2048), (256 * 57, 1, 256), (4864, 1, 768)]])
 def test_fixup_reads_only_written_slots(out_features, n_blocks, tokens, kernel):
     check_fixup_reads_only_written_slots(out_features, n_blocks, tokens, kernel)
 
@@ -225,6 +227,33 @@ def test_half_height_tiles_are_used_where_they_fill_the_chip_once():
             assert len({(s[0], s[1]) for s in segs}) == n_tiles     # one tile per workgroup
     segs, shape = split(4096, 64, 2048, skl.SKL_PREFILL_FUSED)
     assert shape[5] == 256
+
+
+@pytest.mark.parametrize("tokens", [1, 17, 64, 65, 128])
+@pytest.mark.parametrize("n_tiles_out,n_blocks", [(1, 1), (1, 3), (3, 8), (16, 64), (43, 64), (64, 7), (100, 64), (127, 9), (128, 64),
+                                                  (129, 448), (300, 16)])
+def test_short_prompts_are_listed_as_they_run(n_tiles_out, n_blocks, tokens):
+    """One token tile; a tile's blocks in equal shares, one workgroup each, dealt to the XCDs in turn."""
+    segs, (gx, l_max, p_cap, n_tiles, mu, mt) = split(256 * n_tiles_out - 5, n_blocks, tokens, skl.SKL_PREFILL_STAGED)
+    assert (n_tiles, mu, mt) == (n_tiles_out, 1, 64 if tokens <= 64 else 128)
+    shares = p_cap or 1
+    assert shares == max(1, min(-(-128 // n_tiles), n_blocks // 4))      # the fewest that make 128, of four blocks or more
+    assert len(segs) == n_tiles * shares and gx == -(-len(segs) // 8)
+    done = [0] * n_tiles
+    for i, (xcd, wg, tm, tn, k0, k1, whole, slot) in enumerate(sorted(segs, key=lambda s: s[1] * 8 + s[0])):
+        assert wg * 8 + xcd == i and (tm, tn) == (0, i // shares)
+        assert k0 == done[tn] < k1 <= n_blocks and abs((k1 - k0) * shares - n_blocks) < shares
+        done[tn] = k1
+        assert whole == (shares == 1) and slot == (0 if whole else i) and (whole or slot < 8 * l_max * p_cap)
+    assert done == [n_blocks] * n_tiles
+
+
+def test_slabs_of_staged_calls_and_the_room_for_their_partials(tmp_path):
+    exe = tmp_path / "staged_slabs"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "paper_2506_17255_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "sanitize", "staged_slabs.cpp"), "-o", str(exe)])
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout
 
 
 def test_argument_errors():
