@@ -57,7 +57,8 @@ __device__ __forceinline__ Key build_key(uint32_t w, uint32_t o)
     return sizeof(Key) == 4 ? (Key)((w & 0x7FFFu) << 17 | o << 1 | w >> 15) : (Key)((uint64_t)(w & 0x7FFFu) << 25 | (uint64_t)o << 1 | w >> 15);
 }
 
-// grid ceil(in / channels per workgroup); LDS: channels x d x (largest width) keys
+// grid ceil(in / channels per workgroup); LDS: channels x d x (largest width) keys, then a sum per wavefront
+#define BR_SUMS_BYTES (BR_THREADS / 64 * 4)
 template <int D, typename Key>
 __global__ __launch_bounds__(BR_THREADS) void k_build_rows(BuildArgs p, uint16_t *__restrict__ states)
 {
@@ -123,7 +124,7 @@ __global__ __launch_bounds__(BR_THREADS) void k_build_rows(BuildArgs p, uint16_t
     uint32_t before = 0;
     for (uint32_t i = threadIdx.x; i < j0; i += BR_THREADS) before += p.width[i];
     for (int m = 32; m; m >>= 1) before += __shfl_xor(before, m);
-    __shared__ uint32_t part[BR_THREADS / 64];
+    uint32_t *part = reinterpret_cast<uint32_t *>(S + (p.max_states << lg));
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = before;
     __syncthreads();
     before = 0;
@@ -182,11 +183,13 @@ skl_status_t skl_launch_build(const skl_desc_t *d, uint64_t n_groups, const uint
         while (a.lg_ch && ((ch_lds << a.lg_ch) > 64 * 1024 || ((a.in + (1u << a.lg_ch) - 1) >> a.lg_ch) < SKL_N_CU)) --a.lg_ch;
         a.max_states = d->d * max_K;
         const dim3 grid((a.in + (1u << a.lg_ch) - 1) >> a.lg_ch);
-        const size_t lds = (size_t)(ch_lds << a.lg_ch);
+        const size_t lds = (size_t)(ch_lds << a.lg_ch) + BR_SUMS_BYTES;
         DISPATCH_D(d->d, {
-            if (key32) hipLaunchKernelGGL((k_build_rows<D, uint32_t>), grid, dim3(BR_THREADS), lds, stream, a, states);
-            else hipLaunchKernelGGL((k_build_rows<D, unsigned long long>), grid, dim3(BR_THREADS), lds, stream, a, states);
+            st = key32 ? allow_lds(k_build_rows<D, uint32_t>, lds) : allow_lds(k_build_rows<D, unsigned long long>, lds);
+            if (st == SKL_OK && key32) hipLaunchKernelGGL((k_build_rows<D, uint32_t>), grid, dim3(BR_THREADS), lds, stream, a, states);
+            else if (st == SKL_OK) hipLaunchKernelGGL((k_build_rows<D, unsigned long long>), grid, dim3(BR_THREADS), lds, stream, a, states);
         })
+        if (st != SKL_OK) return st;
     } else {
         const uint32_t sweep = (uint32_t)std::min<uint64_t>((d->n_states + SKL_WG - 1) / SKL_WG, 4096);
         hipLaunchKernelGGL(k_build_clear, dim3(sweep), dim3(SKL_WG), 0, stream, a.keys, d->n_states);

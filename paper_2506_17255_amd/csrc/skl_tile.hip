@@ -145,6 +145,7 @@ __global__ __launch_bounds__(SKL_WG) void k_tile_gemv(TileArgs p, const uint16_t
 #define TS_O 16
 #define TS_SLICES 64
 #define TS_MAX_IN 1024
+#define TS_WIDTHS (TS_MAX_IN / TS_SLICES)       // most tables above an output
 
 template <int D, int BT>
 __global__ __launch_bounds__(TS_O * TS_SLICES) void k_tile_gemv_small(TileArgs p, const uint16_t *__restrict__ x, uint32_t ldx,
@@ -156,7 +157,7 @@ __global__ __launch_bounds__(TS_O * TS_SLICES) void k_tile_gemv_small(TileArgs p
     const uint32_t ob = blockIdx.x / n_oc, oc = blockIdx.x - ob * n_oc;
     float *xs = reinterpret_cast<float *>(smem + n_jb * key_words);          // [BT][in]
     float *red = xs + (size_t)BT * p.in;                                      // [BT][TS_SLICES][TS_O]
-    __shared__ uint32_t width[TS_MAX_IN / TS_SLICES];
+    uint32_t *width = reinterpret_cast<uint32_t *>(red + BT * TS_SLICES * TS_O);    // [n_jb]
     const uint32_t b0 = blockIdx.z * BT;
     // a wavefront or more to a table, all tables at once (one after the other, eight tables took 8.6 us a call, now 6.6)
     uint32_t tables = 1;                                             // side by side: n_jb rounded up to a power of two
@@ -357,7 +358,7 @@ skl_status_t skl_tile_launch_gemv_small(const skl_layer *L, const TableSrc &src,
     const uint32_t kw = (uint32_t)tile_key_words(L);
     const uint32_t n_oc = (L->to + TS_O - 1) / TS_O;
     if (batch == 1) {
-        const size_t lds = tile_small_lds(L, 1);
+        const size_t lds = tile_small_lds(L, 1) + TS_WIDTHS * sizeof(uint32_t);
         DISPATCH_D(L->d, {
             st = allow_lds(k_tile_gemv_small<D, 1>, lds);
             if (st == SKL_OK)
@@ -365,7 +366,7 @@ skl_status_t skl_tile_launch_gemv_small(const skl_layer *L, const TableSrc &src,
                                    batch, y, (uint32_t)y_dt, ldy, kw);
         });
     } else {
-        const size_t lds = tile_small_lds(L, 4);
+        const size_t lds = tile_small_lds(L, 4) + TS_WIDTHS * sizeof(uint32_t);
         DISPATCH_D(L->d, {
             st = allow_lds(k_tile_gemv_small<D, 4>, lds);
             if (st == SKL_OK)

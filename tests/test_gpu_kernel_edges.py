@@ -22,6 +22,8 @@ def hash_params(rng, d):
     (515, 96, 8, (250, 3)),          # tables that leave room for fewer channels per workgroup
     (3, 65536, 2, (500,)),           # the most outputs a 32-bit key can number
     (3, 65544, 2, (500,)),           # one step beyond: 64-bit keys
+    (2048, 96, 4, (512, 100)),       # the most LDS: eight channels' keys fill 64 KiB
+    (5, 96, 4, (4096, 100)),         # the same with one channel per workgroup
 ])
 def test_row_sketch_construction(in_f, out_f, d, widths):
     """Bit-identical to the oracle's sequential update (integers: no tolerance)."""
@@ -136,6 +138,7 @@ def test_short_prompts_in_a_workspace_of_the_fused_kernel(tokens, bits):
     (1024, 64, 128, 16, 4),      # the most input rows
     (1088, 64, 64, 32, 4),       # beyond: split
     (64, 8208, 64, 16, 2),       # 513 workgroups and more: split at batch 1, too
+    (1024, 32, 128, 16, 4),      # (with the widths below) the most LDS at batch 1: tables, rows and sums fill 64 KiB
 ])
 def test_small_group_decode(in_f, out_f, tile_in, tile_out, d, batch):
     """2-D groups on both sides of the line between one launch and a split reduction, groups of unequal width."""
@@ -143,6 +146,8 @@ def test_small_group_decode(in_f, out_f, tile_in, tile_out, d, batch):
     W = (rng.standard_normal((in_f, out_f)) * 0.02).astype(np.float16)
     A, C = hash_params(rng, d)
     K = rng.integers(9, 200, size=(in_f // tile_in) * (out_f // tile_out)).astype(np.uint32)
+    if (in_f, out_f, tile_in) == (1024, 32, 128):
+        K[0] = (65536 - 4 * (1024 + 1024)) // 8 // (2 * d)
     sk = oracle.update(W, tile_in, tile_out, d, A, C, K)
     x = rng.standard_normal((batch, in_f)).astype(np.float16)
     ref = oracle.linear(oracle.query(sk), x)
