@@ -10,7 +10,7 @@
 struct BuildArgs {
     HashArgs h;
     const uint16_t *W;
-    const uint64_t *base;       // state offset of every group
+    const uint64_t *base;       // state offset of every group (row sketches: null where the kernel sums the widths)
     const uint32_t *width;
     unsigned long long *keys;
     uint32_t in, out, tj, to, n_ob, d;
@@ -59,20 +59,20 @@ __device__ __forceinline__ Key build_key(uint32_t w, uint32_t o)
 
 // grid ceil(in / channels per workgroup); LDS: channels x d x (largest width) keys, then a sum per wavefront
 #define BR_SUMS_BYTES (BR_THREADS / 64 * 4)
-template <int D, typename Key>
-__global__ __launch_bounds__(BR_THREADS) void k_build_rows(BuildArgs p, uint16_t *__restrict__ states)
+template <int D, typename Key, uint32_t T>
+__global__ __launch_bounds__(T) void k_build_rows(BuildArgs p, uint16_t *__restrict__ states)
 {
     constexpr uint32_t KEY_SHIFT = sizeof(Key) == 4 ? 17 : 25;
     Key *S = reinterpret_cast<Key *>(smem);
     const uint32_t lg = p.lg_ch, ch = 1u << lg, j0 = blockIdx.x << lg;
     const uint32_t c = threadIdx.x & (ch - 1);                  // this thread's channel
     const uint32_t j = min(j0 + c, p.in - 1), K = p.width[j];
-    for (uint32_t i = threadIdx.x; i < (p.max_states << lg); i += BR_THREADS) S[i] = (Key)~(Key)0;
+    for (uint32_t i = threadIdx.x; i < (p.max_states << lg); i += T) S[i] = (Key)~(Key)0;
     __syncthreads();
     const uint16_t *row = p.W + (size_t)j * p.out;
     // LDS byte address of (row r, state 0, channel c), and log2 of the bytes per state
     const uint32_t sh = lg + (sizeof(Key) == 4 ? 2 : 3), Kq = K << 8;
-    const uint32_t out = p.out, step = (BR_THREADS >> lg) * 8;
+    const uint32_t out = p.out, step = (T >> lg) * 8;
     uint32_t Sr[D], A[D], A_next[D];                            // A_next: from a thread's eighth output to the first of its next eight
 #pragma unroll
     for (int r = 0; r < D; ++r) A[r] = p.h.A[r], A_next[r] = (step - 8) * p.h.A[r];
@@ -119,20 +119,26 @@ __global__ __launch_bounds__(BR_THREADS) void k_build_rows(BuildArgs p, uint16_t
             for (int r = 0; r < D; ++r) t[r] += A_next[r];      // (only the last piece may be short)
         }
     }
-    // the states of the channels before this workgroup's: summed here (a few loads per thread) so that the widths
-    // are all the host has to send
-    uint32_t before = 0;
-    for (uint32_t i = threadIdx.x; i < j0; i += BR_THREADS) before += p.width[i];
-    for (int m = 32; m; m >>= 1) before += __shfl_xor(before, m);
-    uint32_t *part = reinterpret_cast<uint32_t *>(S + (p.max_states << lg));
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = before;
-    __syncthreads();
-    before = 0;
-    for (uint32_t i = 0; i < BR_THREADS / 64; ++i) before += part[i];
-    uint16_t *dst = states + (size_t)before * D;
+    // the states of the channels before this workgroup's: summed here where that is a few loads per thread, so that the
+    // widths are all the host has to send
+    uint16_t *dst = states;
+    if (p.base) {
+        __syncthreads();
+        dst += p.base[j0];
+    } else {
+        uint32_t before = 0;
+        for (uint32_t i = threadIdx.x; i < j0; i += T) before += p.width[i];
+        for (int m = 32; m; m >>= 1) before += __shfl_xor(before, m);
+        uint32_t *part = reinterpret_cast<uint32_t *>(S + (p.max_states << lg));
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = before;
+        __syncthreads();
+        before = 0;
+        for (uint32_t i = 0; i < T / 64; ++i) before += part[i];
+        dst += (size_t)before * D;
+    }
     for (uint32_t cc = 0; cc < ch && j0 + cc < p.in; ++cc) {
         const uint32_t n = D * p.width[j0 + cc];
-        for (uint32_t i = threadIdx.x; i < n; i += BR_THREADS) {
+        for (uint32_t i = threadIdx.x; i < n; i += T) {
             const Key k = S[(i << lg) + cc];
             dst[i] = k == (Key)~(Key)0 ? (uint16_t)0 : (uint16_t)(((k & 1) << 15) | (k >> KEY_SHIFT));
         }
@@ -162,32 +168,46 @@ skl_status_t skl_launch_build(const skl_desc_t *d, uint64_t n_groups, const uint
     uint64_t *base_dev = reinterpret_cast<uint64_t *>(area);
     area += round256((n_groups + 1) * 8);
     uint32_t *width_dev = reinterpret_cast<uint32_t *>(area);
-    a.base = base_dev; a.width = width_dev;
+    a.width = width_dev;
     a.in = d->in_features; a.out = d->out_features; a.tj = d->tile_in; a.to = d->tile_out;
     a.n_ob = d->out_features / d->tile_out; a.d = d->d;
     const bool key32 = d->tile_out <= 65536;
     uint32_t max_K = 0;
     for (uint64_t g = 0; g < n_groups; ++g) max_K = std::max(max_K, d->group_width[g]);
     const uint64_t ch_lds = (uint64_t)d->d * max_K * (key32 ? 4 : 8);       // row sketches: LDS bytes per channel
-    const bool rows = d->tile_in == 1 && d->tile_out == d->out_features && ch_lds <= 64 * 1024;
+    bool rows = d->tile_in == 1 && d->tile_out == d->out_features && ch_lds <= 64 * 1024;
+    if (rows) {
+        // eight channels per workgroup, fewer where their keys exceed 64 KiB or the chip would not be filled
+        a.lg_ch = 3;
+        while (a.lg_ch && ((ch_lds << a.lg_ch) > 64 * 1024 || ((a.in + (1u << a.lg_ch) - 1) >> a.lg_ch) < SKL_N_CU)) --a.lg_ch;
+        a.max_states = d->d * max_K;
+        rows = ((a.in + (1u << a.lg_ch) - 1) >> a.lg_ch) < (1ull << 32) / BR_THREADS;      // a grid dimension holds 2^32 threads
+    }
+    // Many channels: every workgroup would sum the widths of half of them on the average, which grows with the square of
+    // their number, so the host sends the offsets (8 bytes per channel); and short rows then want small workgroups.
+    // Whole call, summed / sent: 16384 x 4096 85 / 90 us, 24576 x 4096 124 / 130, 32768 x 4096 151 / 138, 65536 x 4096
+    // 320 / 242.  Rows of 256 outputs, summed by 1024 threads / sent to 256: 24576 73 / 66, 65536 197 / 120.
+    const bool short_rows = d->out_features <= 256 && d->in_features > 16384;
+    const bool send_base = !rows || short_rows || d->in_features > 24576;
+    a.base = send_base ? base_dev : nullptr;
     hipError_t e = hipMemcpyAsync(width_dev, d->group_width, n_groups * 4, hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess && !rows) e = hipMemcpyAsync(base_dev, group_base, (n_groups + 1) * 8, hipMemcpyHostToDevice, stream);
+    if (e == hipSuccess && send_base) e = hipMemcpyAsync(base_dev, group_base, (n_groups + 1) * 8, hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) {
         skl_set_error("copy of the group widths failed: %s", hipGetErrorString(e));
         return SKL_ERR_HIP;
     }
     skl_status_t st = SKL_OK;
     if (rows) {
-        // eight channels per workgroup, fewer where their keys exceed 64 KiB or the chip would not be filled
-        a.lg_ch = 3;
-        while (a.lg_ch && ((ch_lds << a.lg_ch) > 64 * 1024 || ((a.in + (1u << a.lg_ch) - 1) >> a.lg_ch) < SKL_N_CU)) --a.lg_ch;
-        a.max_states = d->d * max_K;
         const dim3 grid((a.in + (1u << a.lg_ch) - 1) >> a.lg_ch);
         const size_t lds = (size_t)(ch_lds << a.lg_ch) + BR_SUMS_BYTES;
+        auto launch = [&](auto kernel, uint32_t threads) {
+            st = allow_lds(kernel, lds);
+            if (st == SKL_OK) hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, stream, a, states);
+        };
         DISPATCH_D(d->d, {
-            st = key32 ? allow_lds(k_build_rows<D, uint32_t>, lds) : allow_lds(k_build_rows<D, unsigned long long>, lds);
-            if (st == SKL_OK && key32) hipLaunchKernelGGL((k_build_rows<D, uint32_t>), grid, dim3(BR_THREADS), lds, stream, a, states);
-            else if (st == SKL_OK) hipLaunchKernelGGL((k_build_rows<D, unsigned long long>), grid, dim3(BR_THREADS), lds, stream, a, states);
+            if (!key32) launch(k_build_rows<D, unsigned long long, BR_THREADS>, BR_THREADS);
+            else if (!short_rows) launch(k_build_rows<D, uint32_t, BR_THREADS>, BR_THREADS);
+            else launch(k_build_rows<D, uint32_t, BR_THREADS / 4>, BR_THREADS / 4);
         })
         if (st != SKL_OK) return st;
     } else {
@@ -198,7 +218,7 @@ skl_status_t skl_launch_build(const skl_desc_t *d, uint64_t n_groups, const uint
     }
     st = check_launch("sketch construction");
     if (st != SKL_OK) return st;
-    e = hipStreamSynchronize(stream);          // the host arrays behind the two copies may go away now
+    e = hipStreamSynchronize(stream);          // the host arrays behind the copies may go away now
     if (e != hipSuccess) {
         skl_set_error("sketch construction failed: %s", hipGetErrorString(e));
         return SKL_ERR_HIP;

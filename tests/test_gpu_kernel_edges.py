@@ -24,6 +24,8 @@ def hash_params(rng, d):
     (3, 65544, 2, (500,)),           # one step beyond: 64-bit keys
     (2048, 96, 4, (512, 100)),       # the most LDS: eight channels' keys fill 64 KiB
     (5, 96, 4, (4096, 100)),         # the same with one channel per workgroup
+    (16385, 256, 2, (8, 33)),        # many short rows: workgroups of 256 threads, offsets from the host
+    (24577, 264, 3, (8, 33)),        # many rows
 ])
 def test_row_sketch_construction(in_f, out_f, d, widths):
     """Bit-identical to the oracle's sequential update (integers: no tolerance)."""
@@ -34,6 +36,18 @@ def test_row_sketch_construction(in_f, out_f, d, widths):
     A, C = hash_params(rng, d)
     got = build_states_on_gpu(W, 1, out_f, d, A, C, K)
     assert np.array_equal(got, oracle.update(W, 1, out_f, d, A, C, K).states)
+
+
+def test_row_sketch_construction_of_more_channels_than_a_grid_holds_workgroups():
+    """2^22 + 3 channels, one of them so wide that a workgroup has room for a single channel."""
+    in_f, out_f = (1 << 22) + 3, 8
+    rng = np.random.default_rng(22)
+    W = rng.integers(0, 0x7C00, size=(in_f, out_f), dtype=np.uint16).view(np.float16)
+    K = np.ones(in_f, dtype=np.uint32)
+    K[7] = 16384
+    A, C = hash_params(rng, 1)
+    got = build_states_on_gpu(W, 1, out_f, 1, A, C, K)
+    assert np.array_equal(got, oracle.update(W, 1, out_f, 1, A, C, K).states)
 
 
 def row_layer(seed, in_f, out_f, d, widths):
