@@ -170,6 +170,29 @@ def test_small_group_decode(in_f, out_f, tile_in, tile_out, d, batch):
     assert rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
 
 
+@pytest.mark.parametrize("d,widths", [
+    (1, (255, 257, 256, 4095, 4096, 4097, 8191, 8192, 9003, 1, 8, 300)),        # lengths around the batches, any alignment
+    (2, (128, 129, 2048, 2049, 4096, 4100, 5, 4, 2047, 700, 1024, 4095)),
+    (3, (85, 86, 683, 1366, 2731, 1365, 2730, 3, 2733, 99, 682, 101)),
+])
+def test_table_staging_of_2d_groups(d, widths):
+    """Tables that start on boundaries of 16, 4 and 2 bytes and end inside a piece: weights bit for bit, then the
+    other kernels that stage them."""
+    for n_in, n_out in ((192, 256), (768, 64)):
+        rng = np.random.default_rng(d + n_in)
+        W = (rng.standard_normal((n_in, n_out)) * 0.02).astype(np.float16)
+        A, C = hash_params(rng, d)
+        sk = oracle.update(W, 64, 64, d, A, C, np.asarray(widths, dtype=np.uint32))
+        W_hat = oracle.query(sk)
+        x = rng.standard_normal((70, n_in)).astype(np.float16)
+        ref = oracle.linear(W_hat, x)
+        with GpuLayer(sk) as g:
+            assert np.array_equal(g.reconstruct(), W_hat)
+            for batch in (1, 5):
+                assert rel_fro(g.gemv(x[:batch], "f32"), ref[:batch]) <= SUM_TOL
+            assert rel_fro(g.gemm(x.view(np.uint16), "f16", "f32"), ref) <= SUM_TOL
+
+
 @pytest.mark.parametrize("batch", [2, 5, 16])
 @pytest.mark.parametrize("out_f", [260, 261, 1027])
 def test_batched_decode_stores(out_f, batch):
