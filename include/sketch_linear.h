@@ -118,7 +118,9 @@ typedef struct {
                                   1 = row sketches (tile_in = 1, tile_out = d_out):
                                       index depends on the output channel only */
     uint32_t n_units;          /* channel blocks (path 1) or group chunks (path 0): the
-                                  number of partial sums per output in the split reduction */
+                                  number of partial sums per output in the split reduction
+                                  (which decode calls through small 2-D groups do without:
+                                  they take one launch) */
     uint32_t max_table_bytes;  /* largest LDS-resident table of one workgroup */
     uint64_t table_bytes;      /* bytes of sketch tables (or of codes and scales) resident in dev_buf */
     uint64_t n_weights;        /* in_features * out_features */
@@ -146,8 +148,9 @@ typedef struct {
 #define SKL_PREFILL_FUSED 3u        /* row sketches, tables of two blocks resident in LDS: weights rebuilt
                                        between the matrix instructions of a 256 x 256 tile */
 #define SKL_PREFILL_STAGED 4u       /* row sketches with larger tables, and long calls: weights rebuilt once per
-                                       call into a cache-sized slab of the workspace, then a 256 x 256-tile
-                                       product (tiles of 64 or 128 tokens for short prompts) */
+                                       call into the workspace (layers of more than 1 GiB of them slab by
+                                       slab), then a 256 x 256-tile product (tiles of 64 or 128 tokens for
+                                       short prompts) */
 
 /* Bytes of device memory create() needs for this description.
  * Validates the whole description (Sec. 3.1 states must be finite). */
@@ -194,9 +197,10 @@ SKL_API skl_status_t sketch_linear_workspace_bytes(const skl_layer_t *layer, uin
  *   x  DEVICE, binary16, [batch][ldx], ldx >= in_features  (x_dtype must be SKL_F16)
  *   y  DEVICE, binary16 or float32, [batch][ldy], ldy >= out_features
  * Products are exact, accumulation is float32, the result is rounded to
- * nearest-even once.  The summation order is fixed: results are
- * bit-identical from run to run.  (Sec. 3 inference flow: decompress then
- * compute, here fused; Eq. 5 and Eq. 1/2.) */
+ * nearest-even once.  The summation order is fixed for a layer and a batch:
+ * results are bit-identical from run to run, but a row of x may be summed in
+ * another order at another batch size (other kernels or splits run).  (Sec. 3
+ * inference flow: decompress then compute, here fused; Eq. 5 and Eq. 1/2.) */
 SKL_API skl_status_t sketch_linear_gemv(const skl_layer_t *layer, const void *x, skl_dtype_t x_dtype,
                                 uint32_t ldx, void *y, skl_dtype_t y_dtype, uint32_t ldy,
                                 uint32_t batch, void *workspace, uint64_t workspace_bytes,
@@ -246,7 +250,10 @@ SKL_API skl_status_t sketch_linear_gemv_gate_up(const skl_layer_t *gate, const s
 /* Diagnostic: only the first of the two kernels behind sketch_linear_gemv
  * (query, Eq. 5, fused with the products; one partial sum per output and
  * block group left in workspace), without the reduction that produces y.
- * For timing that kernel by itself; same argument rules as gemv. */
+ * For timing that kernel by itself; same argument rules as gemv.  Calls that
+ * sketch_linear_gemv makes in one launch (2-D groups of at least 64 rows in
+ * layers of at most 1024, while there are few outputs and batch rows) have no
+ * such kernel: here they run the first kernel of the split form. */
 SKL_API skl_status_t sketch_linear_gemv_partials(const skl_layer_t *layer, const void *x, skl_dtype_t x_dtype,
                                          uint32_t ldx, uint32_t batch, void *workspace,
                                          uint64_t workspace_bytes, void *hip_stream);

@@ -1,5 +1,5 @@
 // Staged prefill over row sketches (Sec. 3 inference flow: decompress the layer, compute, release -- here at
-// the granularity of one call, through a cache-sized part of the workspace; W_hat of Sec. 3.1 Eq. 5, the
+// the granularity of one call, through the workspace; W_hat of Sec. 3.1 Eq. 5, the
 // product Y = X W_hat of Sec. 2.1).
 //
 // For layers whose block tables are too large for the fused kernel (wide sketches put few input channels

@@ -193,10 +193,11 @@ static inline G3Split skl_make_split(uint32_t out, uint32_t nb, uint32_t tokens,
 #define SG_SLOT_BYTES 32768u            // weight words of one 64-channel block of an output tile (64 channels x 256 outputs)
 
 // Output-tile columns per slab.  The weight words of a slab (kb x 32 KiB per column) are rebuilt, multiplied and released
-// before the next slab is touched, which bounds the workspace for very large layers; up to 1 GiB of weight words the
-// layer is one slab (measured on the 8192 x 28672 layer: four slabs of 134 MB cost 8 % -- every slab stages all tables
-// again -- and the product kernel gained nothing from finding its words in the memory-side cache).  Slabs are whole
-// rounds of the product kernel (32 columns x 8 token tiles = one tile per workgroup at 2048 tokens).
+// before the next slab is touched; up to 1 GiB of weight words the layer is one slab (measured on the 8192 x 28672 layer:
+// four slabs of 134 MB cost 8 % -- every slab stages all tables again -- and the product kernel gained nothing from
+// finding its words in the memory-side cache).  Slabs are whole rounds of the product kernel (32 columns x 8 token tiles =
+// one tile per workgroup at 2048 tokens): about 512 MiB, but never less than one round, which with one token tile is 256
+// columns (2 GiB for a layer of 16384 channels).
 static inline uint32_t skl_staged_slab_cols(uint32_t out, uint32_t kb, uint32_t tokens)
 {
     const uint32_t n_col = (out + GM3_NT - 1) / GM3_NT, m_tiles = (tokens + GM_MT - 1) / GM_MT;
