@@ -31,23 +31,44 @@ __device__ __forceinline__ void copy_words(Word *dst, const Word *src, uint32_t 
     for (; i < n; i += stride) dst[i] = src[i];
 }
 
-// A group's table to LDS by `stride` threads, this one number t: in pieces of 16 or 4 bytes where it starts on such
-// a boundary (the widths before it decide), key by key elsewhere, where a thread has one key only, and at its end.
-// Bound by the latency of the loads, hence several in flight.  1024 x 8192 in groups of 64 x 8192 (tables of 32 to 64 KiB),
-// d = 4: batch 16 46.9 us key by key, 48.5 with the same pieces one at a time, 41.5 so; 100 tokens 89.3, 103.2, 78.4.
+// a group's table to LDS by `stride` threads, this one number t: in pieces of 16 or 4 bytes where it starts on such
+// a boundary (the widths before it decide), key by key elsewhere and at its end
 __device__ __forceinline__ void stage_keys(uint16_t *dst, const uint16_t *src, uint32_t n, uint32_t t, uint32_t stride)
 {
     const uintptr_t at = reinterpret_cast<uintptr_t>(src);
-    if (n <= stride) {
+    uint32_t done = 0;
+    if ((at & 15u) == 0) {
+        done = n & ~7u;
+        for (uint32_t i = t; i < n / 8; i += stride) reinterpret_cast<uint4 *>(dst)[i] = reinterpret_cast<const uint4 *>(src)[i];
+    } else if ((at & 3u) == 0) {
+        done = n & ~1u;
+        for (uint32_t i = t; i < n / 2; i += stride) reinterpret_cast<uint32_t *>(dst)[i] = reinterpret_cast<const uint32_t *>(src)[i];
+    }
+    for (uint32_t i = done + t; i < n; i += stride) dst[i] = src[i];
+}
+
+// The same by a workgroup, tables of more than two 16-byte pieces per thread with several loads in flight (bound by
+// their latency) and key by key where they lie off 4-byte boundaries (a plain loop, which the compiler unrolls).  1024 x
+// 8192 in groups of 64 x 8192 (tables of 32 KiB), d = 4: batch 16 46.9 us with all keys one by one, 48.5 with pieces one at a
+// time, 41.5 so; 100 tokens 89.3, 103.2, 78.4.  Smaller tables gain nothing and would pay for the longer code (1 %),
+// the smallest even for the choice of a piece (2048 x 512 in groups of 32 x 32, 100 tokens: 134 us, 141).
+__device__ __forceinline__ void stage_table(uint16_t *dst, const uint16_t *src, uint32_t n)
+{
+    const uint32_t t = threadIdx.x;
+    if (n <= SKL_WG) {
         if (t < n) dst[t] = src[t];
-    } else if ((at & 15u) == 0) {
-        copy_words<4>(reinterpret_cast<uint4 *>(dst), reinterpret_cast<const uint4 *>(src), n / 8, t, stride);
+        return;
+    }
+    if (n <= 16 * SKL_WG) return stage_keys(dst, src, n, t, SKL_WG);
+    const uintptr_t at = reinterpret_cast<uintptr_t>(src);
+    if ((at & 15u) == 0) {
+        copy_words<4>(reinterpret_cast<uint4 *>(dst), reinterpret_cast<const uint4 *>(src), n / 8, t, SKL_WG);
         if (t < (n & 7u)) dst[(n & ~7u) + t] = src[(n & ~7u) + t];
     } else if ((at & 3u) == 0) {
-        copy_words<8>(reinterpret_cast<uint32_t *>(dst), reinterpret_cast<const uint32_t *>(src), n / 2, t, stride);
+        copy_words<8>(reinterpret_cast<uint32_t *>(dst), reinterpret_cast<const uint32_t *>(src), n / 2, t, SKL_WG);
         if (t < (n & 1u)) dst[n - 1] = src[n - 1];
     } else {
-        for (uint32_t i = t; i < n; i += stride) dst[i] = src[i];
+        for (uint32_t i = t; i < n; i += SKL_WG) dst[i] = src[i];
     }
 }
 
@@ -102,7 +123,7 @@ __global__ __launch_bounds__(SKL_WG) void k_tile_reconstruct(TileArgs p, uint16_
 {
     uint16_t *tab = reinterpret_cast<uint16_t *>(smem);
     const TileUnit u = tile_unit(p, blockIdx.x);
-    stage_keys(tab, p.keys + u.key_off, D * u.K, threadIdx.x, SKL_WG);
+    stage_table(tab, p.keys + u.key_off, D * u.K);
     __syncthreads();
     const uint32_t ol = blockIdx.y * SKL_WG + threadIdx.x;
     if (ol >= p.to) return;
@@ -123,7 +144,7 @@ __global__ __launch_bounds__(SKL_WG) void k_tile_gemv(TileArgs p, const uint16_t
     uint16_t *tab = reinterpret_cast<uint16_t *>(smem);
     float *xs = reinterpret_cast<float *>(smem + key_words);   // [BT][jc_rows]
     const TileUnit u = tile_unit(p, blockIdx.x);
-    stage_keys(tab, p.keys + u.key_off, D * u.K, threadIdx.x, SKL_WG);
+    stage_table(tab, p.keys + u.key_off, D * u.K);
     const uint32_t b0 = blockIdx.z * BT;
     const uint32_t rows = u.j_hi - u.j_lo;
     for (uint32_t i = threadIdx.x; i < BT * rows; i += SKL_WG) {
@@ -176,7 +197,7 @@ __global__ __launch_bounds__(TS_O * TS_SLICES) void k_tile_gemv_small(TileArgs p
     const uint32_t ob = blockIdx.x / n_oc, oc = blockIdx.x - ob * n_oc;
     float *xs = reinterpret_cast<float *>(smem + n_jb * key_words);          // [BT][in]
     float *red = xs + (size_t)BT * p.in;                                      // [BT][TS_SLICES][TS_O]
-    uint32_t *width = reinterpret_cast<uint32_t *>(red + BT * TS_SLICES * TS_O);    // [n_jb]
+    __shared__ uint32_t width[TS_WIDTHS];                            // (a fixed address: 0.1 us less than behind the sums)
     const uint32_t b0 = blockIdx.z * BT;
     // a wavefront or more to a table, all tables at once (one after the other, eight tables took 8.6 us a call, now 6.6)
     uint32_t tables = 1;                                             // side by side: n_jb rounded up to a power of two
@@ -253,7 +274,7 @@ __global__ __launch_bounds__(SKL_WG) void k_tile_gemm(TileArgs p, const uint16_t
     for (uint32_t jb = 0; jb < n_jb; ++jb) {
         const skl_group_meta gm = p.gmeta[jb * p.n_ob + ob];
         __syncthreads();
-        stage_keys(tab, p.keys + gm.key_off, D * gm.K, threadIdx.x, SKL_WG);
+        stage_table(tab, p.keys + gm.key_off, D * gm.K);
         __syncthreads();
         const uint32_t Kq = gm.K << 8;
         for (uint32_t j0 = 0; j0 < p.tj; j0 += 16) {
@@ -377,17 +398,17 @@ skl_status_t skl_tile_launch_gemv_small(const skl_layer *L, const TableSrc &src,
     const uint32_t kw = (uint32_t)tile_key_words(L);
     const uint32_t n_oc = (L->to + TS_O - 1) / TS_O;
     if (batch == 1) {
-        const size_t lds = tile_small_lds(L, 1) + TS_WIDTHS * sizeof(uint32_t);
+        const size_t lds = tile_small_lds(L, 1);
         DISPATCH_D(L->d, {
-            st = allow_lds(k_tile_gemv_small<D, 1>, lds);
+            st = allow_lds(k_tile_gemv_small<D, 1>, lds + TS_WIDTHS * sizeof(uint32_t));
             if (st == SKL_OK)
                 hipLaunchKernelGGL((k_tile_gemv_small<D, 1>), dim3(L->n_ob * n_oc), dim3(TS_O * TS_SLICES), lds, stream, a, x, ldx,
                                    batch, y, (uint32_t)y_dt, ldy, kw);
         });
     } else {
-        const size_t lds = tile_small_lds(L, 4) + TS_WIDTHS * sizeof(uint32_t);
+        const size_t lds = tile_small_lds(L, 4);
         DISPATCH_D(L->d, {
-            st = allow_lds(k_tile_gemv_small<D, 4>, lds);
+            st = allow_lds(k_tile_gemv_small<D, 4>, lds + TS_WIDTHS * sizeof(uint32_t));
             if (st == SKL_OK)
                 hipLaunchKernelGGL((k_tile_gemv_small<D, 4>), dim3(L->n_ob * n_oc, 1, (batch + 3) / 4), dim3(TS_O * TS_SLICES), lds,
                                    stream, a, x, ldx, batch, y, (uint32_t)y_dt, ldy, kw);
