@@ -49,7 +49,7 @@ __global__ __launch_bounds__(SKL_WG) void k_build_scatter(BuildArgs p)
 // at 64 random states of one channel (the layout this kernel had before), 11.7 for 32-bit ones, 4.6 for 32-bit
 // ones in rows of eight channels, 4.1 if nothing collides.  Hence eight channels, and 32-bit keys wherever a
 // group has at most 2^16 weights: magnitude (15 bits) | output (16) | sign.
-// 4096 x 11008, d = 4: the kernel takes 31 us (78 us with one channel and 64-bit keys per workgroup); the calls' time is 46 us, 92 us before.
+// 4096 x 11008, d = 4: the kernel takes 31 us (78 us with one channel and 64-bit keys per workgroup); the whole call 47 us, 95 to 98 before.
 #define BR_THREADS 1024u
 template <typename Key>
 __device__ __forceinline__ Key build_key(uint32_t w, uint32_t o)

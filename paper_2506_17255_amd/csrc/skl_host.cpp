@@ -370,10 +370,13 @@ static void plan_prefill(const skl_desc_t *d, skl_plan *P)
         P->windows.push_back(w);
     }
     // Which kernel a call takes.  Layers whose tables the fused kernel cannot keep in LDS always rebuild
-    // their weights once per call.  The others do so from 513 tokens on: measured on MI355X
-    // (4096 x 4096 and 4096 x 11008, 0.5 bit/weight) the two kernels tie up to 512 tokens, where a call
-    // is a single round of tiles either way, and the staged one is 10 % faster at 1024 tokens and 25 % at
-    // 2048.  flags bit 1: always staged; bit 2: fused whenever the tables allow.
+    // their weights once per call.  The others do so from 513 tokens on, where staging is faster on every layer
+    // measured (whole call, fused / staged, 768 tokens, 0.5 bit/weight: 4096 x 4096 83 / 69 us, 4096 x 11008 141 / 110,
+    // 28672 x 8192 509 / 490).  From 129 to 512 tokens it is faster on most layers too (129, 256, 512 tokens: 4096 x 4096
+    // 55 / 43, 55 / 47, 65 / 52; 4096 x 11008 84 / 73, 84 / 78, 113 / 99; 1024 x 2048 39 / 23, 40 / 23, 47 / 32), level on
+    // some (11008 x 4096 75 / 69, 73 / 73, 100 / 85) and slower beyond the memory-side cache (28672 x 8192 192 / 242,
+    // 191 / 251, 344 / 328); but it needs room for the dense weights, which calls of that size have never asked for.
+    // flags bit 1: always staged; bit 2: fused whenever the tables allow.
     L.gemm_staged_from = !L.gemm_v3 || (d->flags & 2u) ? 0u : (d->flags & 4u) ? 0xFFFFFFFFu : 513u;
     // Short prompts are staged too, as long as the memory-side cache (256 MiB) holds the rebuilt weights between the
     // two launches.  Whole call, 17 / 128 tokens, fused -> staged, d = 4, blocks of eight words: 4096 x 4096 54 / 56 ->

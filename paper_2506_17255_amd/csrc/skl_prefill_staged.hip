@@ -2,15 +2,15 @@
 // the granularity of one call, through the workspace; W_hat of Sec. 3.1 Eq. 5, the
 // product Y = X W_hat of Sec. 2.1).
 //
-// For layers whose block tables are too large for the fused kernel (wide sketches put few input channels
-// behind one table: a 256-output workgroup would have to stream tables that cover all outputs, several
+// For long prompts, short ones, and layers whose block tables are too large for the fused kernel (wide sketches put few
+// input channels behind one table: a 256-output workgroup would have to stream tables that cover all outputs, several
 // times the bytes of the dense weights of its tile), every weight is rebuilt exactly once per call:
 //   1. k_rebuild_operands: one workgroup per (channel block, range of output tiles) stages the block's table
 //      in LDS once, runs select / gather / query / decode for all its outputs and writes the weights as
 //      16-byte matrix-core operand words, already in the order the product kernel's LDS slot has;
 //   2. k_staged_gemm: 256 tokens x 256 outputs per workgroup, a product of operand words that both come from
 //      memory (the workgroups of the first launch that do not rebuild re-order the activations).
-// The work split is that of the fused kernel, dealt by output-tile column.
+// The work split is that of the fused kernel, dealt by output-tile column; short prompts have one of their own.
 #include "skl_prefill_common.h"
 
 namespace SKL_NS {
@@ -233,10 +233,10 @@ __device__ __forceinline__ void staged_store_rows(const float4v (&acc)[RB][4], u
 // Short prompts (ShortSplit) take it with RB 2 or 4 for one token tile of 64 or 128 tokens: bound by the weight words,
 // each read once, and by the partials; 4096 x 11008 at 100 tokens 22 us (56 us in the fused kernel, which multiplies a
 // 256-token tile and rebuilds its weights beside it).
-// 2048 tokens x 8192 x 28672: 718 us = 1.34 PFLOP/s, 801 us with one wavefront per SIMD in the 32x32x16 form; of the
+// 2048 tokens x 8192 x 28672: 718 to 726 us at best = 1.32 to 1.34 PFLOP/s, 801 us with one wavefront per SIMD in the 32x32x16 form; of the
 // difference to a loop without LDS reads and copies (525 us) the reads are about 80 us and the copies 120, and on
 // all-zero data (clock not held back) the copies alone set the time: 7.6 GB through the L2s, 1.7 GB from behind
-// them, in 570 us.  4096 x 11008: 185 us (200), 4096 x 4096 in half-height tiles: 65 us (74).
+// them, in 570 us.  4096 x 11008: 186 us (200), 4096 x 4096 in half-height tiles: 63 us (74).
 #define SG_STAGES(rb) ((rb) == 8 ? 5u : (rb) == 4 ? 6u : 7u)
 #define SG_STAGE_BYTES(rb) ((rb) * 2048u + 16384u)      // (rb * 32) tokens x 32 channels, 32 channels x 256 outputs
 template <int RB, class Split>
