@@ -359,6 +359,7 @@ __global__ __launch_bounds__(MAXW * 64) void k_row_gemv1_group(GroupArgs m, cons
 // 32 channels it gathers/queries/decodes four operand words and issues four
 // MFMAs.  The sums stay in registers for the whole block group.
 typedef float float4v __attribute__((ext_vector_type(4)));
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));       // the same on any 4-byte boundary
 
 template <int D, int NB>
 __device__ __forceinline__ void gn_offsets(const HashArgs &h, uint32_t o_base, uint32_t out, uint32_t K, uint32_t lane,
@@ -477,7 +478,7 @@ __device__ __forceinline__ void gn_run(const StreamArgs &p, const StreamCtx &c, 
 
 #define SKL_GN_FIXED_LDS (SKL_MAX_GROUP_BLOCKS * 32)
 
-template <int D>
+template <int D, bool PAST>
 __device__ __forceinline__ void gemvN_body(const StreamArgs &p, const uint16_t *__restrict__ x, uint32_t ldx, uint32_t batch,
                                            uint32_t xs_stride, float *__restrict__ partial)
 {
@@ -536,20 +537,20 @@ __device__ __forceinline__ void gemvN_body(const StreamArgs &p, const uint16_t *
         }
         if (w.wave_live) {
             // acc[j][i]: batch row 4 * (lane / 16) + i, output o_base + 4 * (lane % 16) + j.  A lane's four
-            // sub-blocks are neighbouring outputs, so that a row of 64 outputs leaves as 16 lanes x 16 bytes
-            // and through the L2, where the reduction behind this kernel reads it (with four-byte non-temporal
-            // stores a gate/up pair of 4096 x 11008, batch 16, took 44.6 us, now 43.9; 11008 x 4096, batch 8: 18.8, no
-            // difference).
+            // sub-blocks are neighbouring outputs, so that a row of 64 outputs leaves as 16 lanes x 16 bytes.  (Four
+            // stores of 4 bytes per row, 16 outputs apart and past the caches: 8192 x 28672 116 us, 111 so, and up to 13 %
+            // on other shapes; of 4 bytes each where 4 does not divide out: 11008 x 4097, batch 16, 27.8 us, 23.8 so.)
             float *pblk = partial + (size_t)c.g * batch * p.r.out;
             const uint32_t o = w.o_base + 4 * (w.lane & 15);
-            const bool vec = (p.r.out & 3u) == 0;       // rows of `partial` are 16-byte aligned
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const uint32_t m = 4 * (w.lane >> 4) + i;
                 if (m < batch) {
                     float *row = pblk + (size_t)m * p.r.out + o;
-                    if (vec) {
-                        if (o < c.o_hi) *reinterpret_cast<float4v *>(row) = (float4v){acc[0][i], acc[1][i], acc[2][i], acc[3][i]};
+                    if (o + 3 < c.o_hi) {       // (rows of `partial` are on 4-byte boundaries only where 4 does not divide out)
+                        const float4u v = {acc[0][i], acc[1][i], acc[2][i], acc[3][i]};
+                        if constexpr (PAST) __builtin_nontemporal_store(v, reinterpret_cast<float4u *>(row));
+                        else *reinterpret_cast<float4u *>(row) = v;
                     } else {
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
@@ -561,19 +562,19 @@ __device__ __forceinline__ void gemvN_body(const StreamArgs &p, const uint16_t *
     }
 }
 
-template <int D>
+template <int D, bool PAST>
 __global__ __launch_bounds__(SKL_SWG) void k_row_gemvN(StreamArgs p, const uint16_t *__restrict__ x, uint32_t ldx,
                                                         uint32_t batch, uint32_t xs_stride, float *__restrict__ partial)
 {
-    gemvN_body<D>(p, x, ldx, batch, xs_stride, partial);
+    gemvN_body<D, PAST>(p, x, ldx, batch, xs_stride, partial);
 }
 
 // the batched kernel for a group of layers on the same activations: grid row y runs layer y
-template <int D>
+template <int D, bool PAST>
 __global__ __launch_bounds__(SKL_SWG) void k_row_gemvN_group(GroupArgs m, const uint16_t *__restrict__ x, uint32_t ldx,
                                                               uint32_t batch, float *__restrict__ partial)
 {
-    gemvN_body<D>(m.a[blockIdx.y], x, ldx, batch, m.xs_stride[blockIdx.y], partial + blockIdx.y * m.partial_stride);
+    gemvN_body<D, PAST>(m.a[blockIdx.y], x, ldx, batch, m.xs_stride[blockIdx.y], partial + blockIdx.y * m.partial_stride);
 }
 
 
@@ -738,6 +739,17 @@ static skl_status_t launch_gemv1(uint32_t d, uint32_t waves, uint32_t upw, dim3 
                        : launch_gemv1_as<16, 2>(d, waves, grid, lds, stream, a, x, partial);
 }
 
+// Whether the batched kernel stores its partial sums past the caches (a kernel of its own: decided inside, it cost 0.3
+// us).  The reduction behind it reads them from the L2 if they went through it; but many of them (more than eight rows, or
+// rows off 16-byte boundaries, whose ends share lines) are then still on their way out when the kernel ends, unless the
+// layer is so wide that they left meanwhile.  Means of six layers of a shape, through / past: 4096 x 4096 pair, batch 16,
+// 25.1 / 22.7 us, batch 8 20.6 / 20.6; 4096 x 11008, batch 16, 22.1 / 21.5, pair 39.5 / 39.4, gate/up 42.9 / 43.6, batch 8
+// 19.8 / 19.85; 2048 x 14336, batch 16, 20.2 / 20.6; 4096 x 5001 pair, batch 8, 23.4 / 22.2; 4096 x 11007, batch 16, 25.4 / 24.2.
+static bool partials_past_cache(uint32_t out, uint32_t batch, bool gate_up)
+{
+    return out <= (gate_up ? 8192u : 12288u) && batch > (out % 4 ? 4u : 8u);
+}
+
 skl_status_t skl_launch_gemv(const skl_layer *L, const void *x_, uint32_t ldx, void *y, skl_dtype_t y_dt,
                              uint32_t ldy, uint32_t batch, void *ws, void *stream_, bool with_reduction)
 {
@@ -771,11 +783,12 @@ skl_status_t skl_launch_gemv(const skl_layer *L, const void *x_, uint32_t ldx, v
             a.tab_bytes = L->tab_bytes;
             a.buf_flag = 2;
             const size_t lds = (size_t)L->tab_bytes + SKL_GN_FIXED_LDS + (size_t)16 * xs_stride * sizeof(uint16_t);
-            DISPATCH_D(L->d, {
-                st = allow_lds(k_row_gemvN<D>, lds);
-                if (st == SKL_OK)
-                    hipLaunchKernelGGL((k_row_gemvN<D>), grid, dim3(64 * waves), lds, stream, a, x, ldx, batch, xs_stride, partial);
-            })
+            auto launch = [&](auto kernel) {
+                st = allow_lds(kernel, lds);
+                if (st == SKL_OK) hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), lds, stream, a, x, ldx, batch, xs_stride, partial);
+            };
+            const bool past = partials_past_cache(L->out, batch, false);
+            DISPATCH_D(L->d, { past ? launch(k_row_gemvN<D, true>) : launch(k_row_gemvN<D, false>); })
         }
     } else {
         if (with_reduction && skl_tile_gemv_is_small(L, batch))
@@ -889,11 +902,12 @@ skl_status_t skl_launch_gemv_group(const skl_layer *const *layers, uint32_t n, c
     skl_status_t st = SKL_OK;
     const dim3 grid(grid_x, n);
     if (!one) {
-        DISPATCH_D(F->d, {
-            st = allow_lds(k_row_gemvN_group<D>, lds);
-            if (st == SKL_OK)
-                hipLaunchKernelGGL((k_row_gemvN_group<D>), grid, dim3(64 * waves), lds, stream, m, x, ldx, batch, partial);
-        })
+        auto launch = [&](auto kernel) {
+            st = allow_lds(kernel, lds);
+            if (st == SKL_OK) hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), lds, stream, m, x, ldx, batch, partial);
+        };
+        const bool past = partials_past_cache(F->out, batch, gate_up);
+        DISPATCH_D(F->d, { past ? launch(k_row_gemvN_group<D, true>) : launch(k_row_gemvN_group<D, false>); })
     } else {
         st = launch_gemv1_group(F->d, waves, F->decode_upw, grid, lds, stream, m, x, partial);
     }

@@ -202,9 +202,10 @@ def test_table_staging_of_2d_groups(d, widths):
 
 
 @pytest.mark.parametrize("batch", [2, 5, 16])
-@pytest.mark.parametrize("out_f", [260, 261, 1027])
+@pytest.mark.parametrize("out_f", [260, 261, 262, 1027, 12287, 12288, 12289, 12292])
 def test_batched_decode_stores(out_f, batch):
-    """Rows of partial sums on 16-byte boundaries (whole words) and not, a last unit of a few outputs."""
+    """Rows of partial sums on 16-byte boundaries and not, a last unit of a few outputs; stores through the caches (few
+    rows, or more than 12288 outputs) and past them."""
     rng = np.random.default_rng(out_f + batch)
     sk = row_layer(7, 520, out_f, 4, np.where(rng.random(520) < 0.02, 40, 17))
     x = rng.standard_normal((batch, 520)).astype(np.float16)
