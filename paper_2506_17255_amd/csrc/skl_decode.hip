@@ -740,14 +740,17 @@ static skl_status_t launch_gemv1(uint32_t d, uint32_t waves, uint32_t upw, dim3 
 }
 
 // Whether the batched kernel stores its partial sums past the caches (a kernel of its own: decided inside, it cost 0.3
-// us).  The reduction behind it reads them from the L2 if they went through it; but many of them (more than eight rows, or
-// rows off 16-byte boundaries, whose ends share lines) are then still on their way out when the kernel ends, unless the
-// layer is so wide that they left meanwhile.  Means of six layers of a shape, through / past: 4096 x 4096 pair, batch 16,
-// 25.1 / 22.7 us, batch 8 20.6 / 20.6; 4096 x 11008, batch 16, 22.1 / 21.5, pair 39.5 / 39.4, gate/up 42.9 / 43.6, batch 8
-// 19.8 / 19.85; 2048 x 14336, batch 16, 20.2 / 20.6; 4096 x 5001 pair, batch 8, 23.4 / 22.2; 4096 x 11007, batch 16, 25.4 / 24.2.
-static bool partials_past_cache(uint32_t out, uint32_t batch, bool gate_up)
+// us).  The reduction behind it reads them from the L2 if they went through it, but from some megabytes on (fewer where
+// rows off 16-byte boundaries share lines) many of them are still on their way out when the kernel ends; those of wide
+// layers leave meanwhile.  Through / past, means of four to six layers of a shape: one layer 4.2 MB (4096 x 4096, batch 8)
+// 12.4 / 12.85 us, 6.8 MB (2048 x 8192, batch 13) 13.7 / 13.5, 11.3 MB (4096 x 11008, batch 16) 22.4 / 21.7, 7.3 MB of 14336
+// outputs 20.2 / 20.6; pairs 6.6 MB (1200 x 10424, d = 2, batch 10) 20.1 / 20.4, 8.1 (3904 x 3968, d = 3, batch 8) 19.1 /
+// 18.2, 8.4 (4096 x 4096, batch 8) 20.5 / 20.5, 16.8 25.1 / 22.8; gate/up, whose reduction has more to read per output,
+// 10.5 MB 22.5 / 22.5, 16.8 27.15 / 25.7, 22.5 MB of 11008 outputs 43.5 / 44.3; 11008 x 4097, batch 8, 4.2 MB 22.0 / 21.3.
+static bool partials_past_cache(uint64_t bytes, uint32_t out, uint32_t n_layers, bool gate_up)
 {
-    return out <= (gate_up ? 8192u : 12288u) && batch > (out % 4 ? 4u : 8u);
+    const uint64_t least = gate_up ? 10000000 : n_layers > 1 ? 8000000 : 6500000;
+    return out <= (gate_up ? 8192u : 12288u) && bytes * (out % 4 ? 8 : 5) >= least * 5;
 }
 
 skl_status_t skl_launch_gemv(const skl_layer *L, const void *x_, uint32_t ldx, void *y, skl_dtype_t y_dt,
@@ -787,7 +790,7 @@ skl_status_t skl_launch_gemv(const skl_layer *L, const void *x_, uint32_t ldx, v
                 st = allow_lds(kernel, lds);
                 if (st == SKL_OK) hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), lds, stream, a, x, ldx, batch, xs_stride, partial);
             };
-            const bool past = partials_past_cache(L->out, batch, false);
+            const bool past = partials_past_cache(gemv_partial_bytes(L, batch), L->out, 1, false);
             DISPATCH_D(L->d, { past ? launch(k_row_gemvN<D, true>) : launch(k_row_gemvN<D, false>); })
         }
     } else {
@@ -906,7 +909,9 @@ skl_status_t skl_launch_gemv_group(const skl_layer *const *layers, uint32_t n, c
             st = allow_lds(kernel, lds);
             if (st == SKL_OK) hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), lds, stream, m, x, ldx, batch, partial);
         };
-        const bool past = partials_past_cache(F->out, batch, gate_up);
+        uint64_t bytes = 0;
+        for (uint32_t i = 0; i < n; ++i) bytes += gemv_partial_bytes(layers[i], batch);
+        const bool past = partials_past_cache(bytes, F->out, n, gate_up);
         DISPATCH_D(F->d, { past ? launch(k_row_gemvN_group<D, true>) : launch(k_row_gemvN_group<D, false>); })
     } else {
         st = launch_gemv1_group(F->d, waves, F->decode_upw, grid, lds, stream, m, x, partial);

@@ -202,13 +202,15 @@ def test_table_staging_of_2d_groups(d, widths):
 
 
 @pytest.mark.parametrize("batch", [2, 5, 16])
-@pytest.mark.parametrize("out_f", [260, 261, 262, 1027, 12287, 12288, 12289, 12292])
-def test_batched_decode_stores(out_f, batch):
-    """Rows of partial sums on 16-byte boundaries and not, a last unit of a few outputs; stores through the caches (few
-    rows, or more than 12288 outputs) and past them."""
+@pytest.mark.parametrize("in_f,out_f", [(520, 260), (520, 261), (520, 262), (520, 1027),
+                                         (520, 12287), (520, 12288), (520, 12289),      # batch 16: 7.1 MB past the caches, but for the last
+                                         (2048, 4098), (2048, 4100)])                   # batch 16: 6.3 MB, past them only where rows are not aligned
+def test_batched_decode_stores(in_f, out_f, batch):
+    """Rows of partial sums on 16-byte boundaries and not, a last unit of a few outputs; stores through the caches and,
+    where a call leaves megabytes of them, past."""
     rng = np.random.default_rng(out_f + batch)
-    sk = row_layer(7, 520, out_f, 4, np.where(rng.random(520) < 0.02, 40, 17))
-    x = rng.standard_normal((batch, 520)).astype(np.float16)
+    sk = row_layer(7, in_f, out_f, 4, np.where(rng.random(in_f) < 0.02, 40, 17))
+    x = rng.standard_normal((batch, in_f)).astype(np.float16)
     ref = oracle.linear(oracle.query(sk), x)
     with GpuLayer(sk) as g:
         y = g.gemv(x, "f32")
