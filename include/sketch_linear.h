@@ -135,7 +135,11 @@ typedef struct {
                                   (at most 128 tokens) of row sketches may be staged all the same:
                                   where the dense weights stay below 240 MiB or the channel
                                   blocks are narrow, unless the descriptor asks for the fused
-                                  kernel or the workspace only holds that one's need */
+                                  kernel or the workspace only holds that one's need.  Where flag
+                                  bits 1 and 2 are clear, calls of up to 512 tokens of either
+                                  kernel may run a third one instead, which rebuilds the weights
+                                  of up to 128 tokens in one pass without storing them, in the
+                                  same workspace (not where fewer than 129 tokens would be fused) */
     uint32_t n_blocks;         /* path 1: channel blocks */
     uint32_t prefill_staged_from; /* row sketches: calls with at least this many tokens take
                                   SKL_PREFILL_STAGED (0: every call, 0xFFFFFFFF: none) */

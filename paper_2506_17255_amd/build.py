@@ -19,7 +19,7 @@ DEBUG_LIB = os.path.join(HERE, "libsketch_linear_debug.so")
 # compiled once
 COMMON_SOURCES = ["skl_host.cpp", "skl_file.cpp", "skl_dispatch.cpp", "skl_lowbit.hip", "skl_build.hip", "skl_microbench.hip"]
 # compiled once per query mode (-DSKL_QM=0 / 1): their kernels and launchers live in a namespace per mode
-MODE_SOURCES = ["skl_prefill.hip", "skl_decode.hip", "skl_prefill_staged.hip", "skl_reconstruct.hip", "skl_tile.hip",
+MODE_SOURCES = ["skl_prefill.hip", "skl_decode.hip", "skl_prefill_staged.hip", "skl_prefill_short.hip", "skl_reconstruct.hip", "skl_tile.hip",
                 "skl_naive.hip"]
 SOURCES = COMMON_SOURCES + MODE_SOURCES
 

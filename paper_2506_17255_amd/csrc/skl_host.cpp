@@ -387,6 +387,9 @@ static void plan_prefill(const skl_desc_t *d, skl_plan *P)
     const uint64_t weight_bytes = (uint64_t)((L.out + 255) / 256) * L.gemm_kb * 32768;
     const bool narrow = 2ull * L.n_blocks > 3ull * L.gemm_kb;
     L.gemm_short_to = L.gemm_staged_from == 513u && (narrow || weight_bytes <= 240ull << 20) ? SKL_SHORT_TOKENS : 0u;
+    L.gemm_prompt = !(d->flags & 6u) && L.max_table_bytes <= SKL_PBUF_DIST;
+    L.gemm_steps32 = 0;
+    for (const skl_block_meta &bm : P->bmeta) L.gemm_steps32 += (bm.nb + 3) / 4;
 }
 
 // Row-sketch plan.  Returns false when some width is too large for any block

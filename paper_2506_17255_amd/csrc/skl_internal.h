@@ -125,6 +125,9 @@ struct skl_layer {
     uint32_t gemm_staged_from = 0, gemm_kb = 0;     // calls with at least gemm_staged_from tokens are staged,
     uint32_t gemm_short_to = 0;                     // and those with at most gemm_short_to
     uint64_t off_windows = 0;
+    // prompts in one pass: allowed (the library chooses the kernel, and every padded table fits a table buffer); 32-channel
+    // steps of all blocks
+    uint32_t gemm_prompt = 0, gemm_steps32 = 0;
 
     // low-bit states: only codes and scales are resident (row sketches: re-ordered into the word order of the
     // block tables); every call expands them into 16-bit tables at the end of its workspace

@@ -462,6 +462,34 @@ uint64_t skl_gemm_workspace_bytes(const skl_layer *L, uint32_t tokens, bool stag
     return L->qbits ? round256(own) + skl_dequant_bytes(L) : own;
 }
 
+// Whether a call the library may choose the kernel for takes the one-pass kernel (`plan`) instead of the staged or the
+// fused one, in the room those ask for: by the estimated times.  The other two are lines through measured whole calls: a
+// staged one by the MB of dense weights it writes and reads (dearer beyond the caches) and its tokens, a fused one 44 us +
+// 2.6 us per channel block of the busiest workgroup.  Layers that stay fused at up to SKL_SHORT_TOKENS tokens (workspaces without room for the dense weights,
+// eight-word layers beyond the memory-side cache) stay so.  One pass / the other, us: 4096 x 11008, d = 4: 17 tokens 27 / 45
+// (staged), 64 31 / 46, 100 38 / 50, 256 66 / 85 (fused), 512 112 / 115; 4096 x 4096: 17 / 25, 20 / 25, 24 / 28, 31 / 55,
+// 42 / 64; 8192 x 8192: 33 / 76, 38 / 77, 46 / 84, 74 / 85, 131 / 127; four-word blocks (4096 x 11008, 0.75 bit): 32 / 43,
+// 36 / 44, 48 / 48, 85 / 112, 145 / 169; two-word (8192 x 28672, d = 3): 180 / 229, 198 / 233, 320 / 234, 626 / 265.
+static bool takes_prompt_kernel(const skl_layer *L, uint32_t tokens, bool staged, PromptPlan &plan)
+{
+    if (!L->gemm_prompt || tokens > SKL_PROMPT_MAX_TOKENS || (!staged && tokens <= SKL_SHORT_TOKENS)) return false;
+    plan = skl_make_prompt_plan(PromptLayer{L->out, L->d, L->n_blocks, L->gemm_kb, L->gemm_steps32, L->table_bytes}, tokens,
+                                gemm_own_bytes(L, tokens, staged));
+    if (!plan.P) return false;
+    double other;
+    if (staged) {
+        const double mb = 2e-6 * L->in * L->out;                // dense weights
+        other = 13.0 + 0.36 * std::min(mb, 100.0) + 0.5 * std::max(mb - 100.0, 0.0) + 0.03 * std::min(tokens, SKL_SHORT_TOKENS);
+        if (tokens > SKL_SHORT_TOKENS) other += 20.0 + 1.25e-4 * tokens * mb;
+    } else {
+        const G3Split sp = gemm3_split(L, tokens);
+        uint32_t blocks = 0;
+        for (uint32_t x = 0; x < 8; ++x) blocks = std::max(blocks, sp.rounds(x) * sp.nb + (sp.units(x) + sp.gx - 1) / sp.gx);
+        other = 44.0 + 2.6 * blocks;
+    }
+    return plan.cost_us * 1.02 < other;
+}
+
 // activation re-ordering for the prefill kernels
 static skl_status_t launch_pack(const skl_layer *L, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx, uint32_t tokens,
                              const uint32_t *chan, const skl_gemm_step *steps, uint32_t n_steps, uint4 *Xp, hipStream_t stream)
@@ -485,10 +513,13 @@ skl_status_t skl_launch_gemm(const skl_layer *L, const void *X_, skl_dtype_t x_d
 {
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     const uint16_t *X = static_cast<const uint16_t *>(X_);
-    TableSrc src;       // the rebuild kernel reads the padded tables, the fused kernel the unpadded ones
+    TableSrc src;       // the rebuild kernel and the one-pass kernel read the padded tables, the fused kernel the unpadded ones
+    PromptPlan prompt{};
+    const bool one_pass = L->path == 1 && takes_prompt_kernel(L, tokens, staged, prompt);
     skl_status_t st = skl_table_source(L, static_cast<char *>(ws) + round256(gemm_own_bytes(L, tokens, staged)),
-                                   L->path == 1 && staged, L->path == 1 && !staged, stream, &src);
+                                   L->path == 1 && (staged || one_pass), L->path == 1 && !staged && !one_pass, stream, &src);
     if (st != SKL_OK) return st;
+    if (one_pass) return skl_launch_gemm_prompt(L, src, prompt, X, x_dt, ldx, Y, y_dt, ldy, tokens, ws, stream);
     if (L->path == 1) {
         const RowArgs a = make_row_args(L, src);
         const uint32_t m_tiles = (tokens + GM_MT - 1) / GM_MT;

@@ -9,6 +9,9 @@ namespace SKL_NS {
 uint64_t skl_gemm_staged_bytes(const skl_layer *L, uint32_t tokens);
 skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx,
                                     void *Y, skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, void *ws, hipStream_t stream);
+// short prompts in one pass (skl_prefill_short.hip)
+skl_status_t skl_launch_gemm_prompt(const skl_layer *L, const TableSrc &src, const PromptPlan &s, const uint16_t *X, skl_dtype_t x_dt,
+                                    uint32_t ldx, void *Y, skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, void *ws, hipStream_t stream);
 }  // namespace SKL_NS
 
 typedef float float4v __attribute__((ext_vector_type(4)));
@@ -22,6 +25,84 @@ __device__ __forceinline__ uint32_t neg_half_pair(uint32_t e, uint32_t x_dt)
         e = lo | (hi << 16);
     }
     return e ^ 0x80008000u;
+}
+
+// Activations to negated binary16, re-ordered into matrix-core A words, a word being eight entries of the channel list
+// for one token: lane l of a wavefront builds the word of token l % 16 and channel group l / 16 of a 32-channel step,
+// and place(step) says where in the caller's layout it goes.  A workgroup takes 16 tokens x PO_STEPS steps: it copies the window of X that holds
+// the steps' channels into LDS in its own order (whole aligned 16-byte pieces, coalesced) and builds the words from
+// 2-byte LDS reads, so that the channels which the width order moved away cost nothing (fetching every word that
+// spans such a gap channel by channel from memory took 5 of 15 us on layers with one percent of wide channels).
+// Steps whose channels are far apart (the wide channels themselves) have no window and are fetched from memory.
+// 2048 tokens x 4096 channels of such a layer, 16.8 MB in and out: 10 us, 15 before (5.1 TB/s would be 6.6).
+#define PO_STRIDE (PO_WINDOW + 8u)      // halfs per LDS row: 16-byte aligned rows on different banks
+#define PO_LDS_BYTES (16u * PO_STRIDE * 2u)
+struct PackArgs {
+    const uint16_t *X;
+    const uint32_t *chan;
+    const skl_pack_window *windows;
+    uint4 *Xp;
+    uint32_t x_dt, ldx, tokens, in, n_steps;
+};
+// tokens t0 .. t0 + 15, group g of PO_STEPS steps; LDS: PO_LDS_BYTES at smem
+template <class Place>
+__device__ __forceinline__ void pack_group(const PackArgs &p, uint32_t t0, uint32_t g, Place place)
+{
+    uint16_t *rows = reinterpret_cast<uint16_t *>(smem);
+    const uint16_t *__restrict__ X = p.X;
+    const uint32_t *__restrict__ chan = p.chan;
+    const skl_pack_window *__restrict__ windows = p.windows;
+    uint4 *__restrict__ Xp = p.Xp;
+    const uint32_t x_dt = p.x_dt, ldx = p.ldx, tokens = p.tokens, in = p.in, n_steps = p.n_steps;
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t row = lane & 15, kg = lane >> 4;
+    const skl_pack_window win = windows[g];
+    constexpr uint32_t N = PO_STEPS / (SKL_WG / 64);            // steps per wavefront
+    u32x4v ch[N][2];                                            // this lane's channels (the list is padded to whole groups of steps)
+#pragma unroll
+    for (uint32_t i = 0; i < N; ++i) {
+        const u32x4v *c = reinterpret_cast<const u32x4v *>(chan + (g * PO_STEPS + wave + 4 * i) * 32 + kg * 8);
+        ch[i][0] = c[0];
+        ch[i][1] = c[1];
+    }
+    if (win.n) {
+        const uint32_t r = threadIdx.x >> 4;                    // 16 threads copy one token's row
+        const uint16_t *src = X + (size_t)min(t0 + r, tokens - 1) * ldx + win.base;
+        const bool vec = (ldx & 7u) == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;        // (base is a multiple of 8)
+#pragma unroll
+        for (uint32_t i = 0; i < PO_WINDOW / 128; ++i) {
+            const uint32_t c = ((threadIdx.x & 15) + 16 * i) * 8;
+            if (c < win.n) {
+                u32x4v v = {0, 0, 0, 0};
+                if (vec && win.base + c + 8 <= in) {
+                    v = *reinterpret_cast<const u32x4v *>(src + c);
+                } else {
+#pragma unroll
+                    for (uint32_t k = 0; k < 8; ++k)
+                        if (win.base + c + k < in) v[k >> 1] |= (uint32_t)src[c + k] << ((k & 1) * 16);
+                }
+                *reinterpret_cast<u32x4v *>(rows + r * PO_STRIDE + c) = v;
+            }
+        }
+    }
+    __syncthreads();
+    const uint16_t *far = X + (size_t)min(t0 + row, tokens - 1) * ldx;     // rows past the end repeat the last one: their products are never stored
+    const uint16_t *near = rows + row * PO_STRIDE;
+#pragma unroll
+    for (uint32_t i = 0; i < N; ++i) {
+        const uint32_t step = g * PO_STEPS + wave + 4 * i;
+        if (step >= n_steps) continue;
+        uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k) {
+            const uint32_t c = ch[i][k >> 2][k & 3];
+            uint32_t e = 0;
+            if (c != SKL_NO_CHANNEL && skl_in_range(c, in, SKL_DBG_CHANNEL)) e = win.n ? near[c - win.base] : far[c];
+            w[k >> 1] |= e << ((k & 1) * 16);
+        }
+        Xp[place(step)] =
+            make_uint4(neg_half_pair(w[0], x_dt), neg_half_pair(w[1], x_dt), neg_half_pair(w[2], x_dt), neg_half_pair(w[3], x_dt));
+    }
 }
 
 #define GM_NT 128            // outputs per workgroup

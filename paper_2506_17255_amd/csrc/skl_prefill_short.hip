@@ -1,0 +1,337 @@
+// Prefill of short prompts over row sketches in one pass (Sec. 3.1 Eq. 5 fused with Y = X W, Sec. 2.1): no weight
+// leaves the compute unit that rebuilt it.
+//   1. k_prompt_pack: activations to negated binary16, re-ordered into matrix-core operand words;
+//   2. k_prompt_gemm: a workgroup owns all tokens x a tile of outputs over a group of consecutive channel blocks; it
+//      streams the blocks' tables and activation words through LDS and leaves float32 partial sums;
+//   3. k_prompt_reduce: adds the partial sums of a tile in group order and stores Y.
+#include "skl_prefill_common.h"
+
+//
+// The staged kernels write and read the dense weights once per call; here they exist only between the LDS gathers and the
+// matrix instructions of one wavefront.  The kernel is that of the batched decode with up to 128 tokens instead of 16:
+// lanes are outputs, a wavefront rebuilds the operand words of 32 outputs and multiplies them with all tokens of its
+// tile, whose activation words arrive in LDS beside the table (two buffers each).
+// Bound by none of its units alone: 4096 x 11008, d = 4, 100 tokens, 250 workgroups of seven wavefronts, main kernel 28
+// us; with the copies left out 24, with the arithmetic left out 20, with neither 7 (LDS busy 0.3 of the time, matrix cores
+// 0.2, vector issue 0.25): two wavefronts per SIMD meet at a barrier per block and wait for LDS together.  What helped:
+// copies issued one by one between the arithmetic instead of as a burst behind the barrier (39 -> 33, it holds the
+// wavefronts up), chunks without bounds checks (33 -> 28), the products of a pair beside the query of the next one.
+// Whole call (packing 4 us, reduction 6): 17 tokens 45 -> 28 us, 64 46 -> 31, 100 50 -> 38 (59 -> 36 on inputs that are
+// not in the caches), 256 85 -> 64; 8192 x 8192 76 -> 34, 77 -> 38, 84 -> 45, 85 -> 72; 4096 x 4096 25 -> 18, 26 -> 21, 28
+// -> 24, 55 -> 31.
+namespace SKL_NS {
+
+struct PromptArgs {
+    HashArgs h;
+    const skl_block_meta *bmeta;
+    const uint4 *tables;                // padded block tables, [r][k][rs] words
+    const uint4 *Xq;                    // activation words: [word of the channel list][RB * 16 tokens]
+    float *parts;                       // [tile][group][16-token block][16-output block][64 lanes] x 4 tokens
+    uint32_t out, n_blocks;
+    uint32_t T, M, P, per_xcd;          // output tiles, token tiles, block groups, workgroups per XCD
+    uint32_t rows, n_words;             // 16-token blocks per partial tile, words of the channel list
+};
+
+// [token tile][word of the channel list][RB * 16 tokens]: the words of a block are contiguous, so that its copy into LDS is
+// one piece and the matrix-core operand reads are free of bank conflicts.
+template <int RB>
+__global__ __launch_bounds__(SKL_WG) void k_prompt_pack(PackArgs k, uint32_t n_rows)
+{
+    const uint32_t t0 = blockIdx.x % n_rows * 16, lane = threadIdx.x & 63;
+    pack_group(k, t0, blockIdx.x / n_rows, [&](uint32_t step) {
+        return ((size_t)(t0 / (RB * 16)) * k.n_steps * 4 + step * 4 + (lane >> 4)) * (RB * 16) + t0 % (RB * 16) + (lane & 15);
+    });
+}
+
+#define PG_X0 (2u * SKL_PBUF_DIST)      // LDS: two table buffers, two activation buffers
+#define PG_LDS(rb) (PG_X0 + 2u * (rb) * 2048u)
+
+// A copy of n16 words into LDS, 1 KiB chunks dealt to the wavefronts in turn and issued one by one between the
+// arithmetic.  The last chunk starts early enough to end with the source (a source shorter than a chunk repeats its last
+// word), so that no lane needs a bounds check and nothing past the end is read.
+struct PromptCopy {
+    const char *src;
+    uint32_t off, last, lds, step, lane_bytes;
+    __device__ __forceinline__ void start(const uint4 *from, uint32_t n16, uint32_t lds_addr, uint32_t wave, uint32_t nw, uint32_t lane)
+    {
+        src = uniform_address(from);
+        n16 = __builtin_amdgcn_readfirstlane(n16);
+        last = n16 > 64 ? n16 * 16 - 1024 : 0;
+        off = wave * 1024;
+        if (n16 <= wave * 64) off = 0xFFFFFFFFu;
+        step = nw * 1024;
+        lds = lds_addr;
+        lane_bytes = min(lane, n16 - 1) * 16;
+    }
+    __device__ __forceinline__ bool more() const { return off < last + 1024; }
+    __device__ __forceinline__ void issue()
+    {
+        const uint32_t o = min(off, last);
+        lds_dma_16_uniform(src + o, lane_bytes, lds + o);
+        off += step;
+    }
+    __device__ __forceinline__ void some(int n)
+    {
+#pragma unroll
+        for (int i = 0; i < n; ++i)
+            if (more()) issue();
+    }
+};
+
+template <int D, int RB>
+struct PromptWalk {
+    uint32_t b, b1, buf;                // next block, end of the group, its buffers
+    skl_block_meta bm, nx;              // metadata of block b and the one after it
+    uint32_t lane, wave, nw, o_base, lds0, tile_m;
+    float4v acc[RB][2];
+};
+
+template <int D, int RB>
+__device__ __forceinline__ void prompt_copies(const PromptArgs &p, const PromptWalk<D, RB> &w, const skl_block_meta &bm, uint32_t buf, PromptCopy &tab, PromptCopy &x)
+{
+    tab.start(p.tables + bm.table_off16, D * bm.K * bm.rs, w.lds0 + buf * SKL_PBUF_DIST, w.wave, w.nw, w.lane);
+    x.start(p.Xq + ((size_t)w.tile_m * p.n_words + (bm.chan_off >> 3)) * (RB * 16), bm.nb * (RB * 16), w.lds0 + PG_X0 + buf * (RB * 2048), w.wave, w.nw, w.lane);
+}
+
+// A run of consecutive blocks of one width class (NB words per state row): NB / 4 (at least one) steps of 32 channels
+// x two 16-output sub-blocks per block.
+template <int D, int RB, int NB>
+__device__ __forceinline__ void prompt_run(const PromptArgs &p, PromptWalk<D, RB> &w)
+{
+    constexpr uint32_t RS = NB == 1 ? 1 : NB + 1;
+    constexpr int NH = NB == 8 ? 2 : 1, NP = 2 * NH, RING = D <= 4 || (D == 5 && RB < 8) ? 3 : 2;      // pairs whose gathers are in registers or on their way
+    const uint32_t n = w.lane & 15, kg = w.lane >> 4;
+    const uint32_t word = min(kg, (uint32_t)NB - 1);       // classes with fewer than 4 words: lanes past the last word re-read it, their activations count as zero
+    const bool x_live = NB >= 4 || kg < (uint32_t)NB;
+    uint32_t off[2][D], K_prev = 0;
+    uint4 q[RING][D], a[NH][RB], wd[2];
+    bool carried = false;
+    do {
+        wait_async_copies();
+        __syncthreads();                                        // block b has arrived, nobody reads the other buffers any more
+        const bool more = w.b + 1 < w.b1;
+        PromptCopy ct, cx;
+        prompt_copies<D, RB>(p, w, w.nx, w.buf ^ 1, ct, cx);
+        if (!more) ct.off = cx.off = 0xFFFFFFFFu;
+        const skl_block_meta n2 = p.bmeta[min(w.b + 2, w.b1 - 1)];
+        if (w.bm.K != K_prev) {
+            const uint32_t K = w.bm.K, Kq = K << 8;
+            uint32_t ob = w.o_base;
+            asm volatile("" : "+v"(ob));
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const uint32_t o = min(ob + 16 * j + n, p.out - 1);
+#pragma unroll
+                for (int r = 0; r < D; ++r) {
+                    const uint32_t t = __umul24(p.h.A[r], o) + p.h.C[r];
+                    off[j][r] = w.lds0 + w.buf * SKL_PBUF_DIST + ((r * K + select_index(t, Kq)) * RS + word) * 16;
+                }
+            }
+            K_prev = K;
+        } else {                                                // the other buffer
+            const uint32_t to = w.buf ? SKL_PBUF_DIST : 0u - SKL_PBUF_DIST;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < D; ++r) off[j][r] += to;
+        }
+        const uint32_t xa = w.lds0 + PG_X0 + w.buf * (RB * 2048) + word * (RB * 256) + n * 16;
+        auto gather = [&](int pr) {
+#pragma unroll
+            for (int r = 0; r < D; ++r) q[pr % RING][r] = lds_word_at(off[pr & 1][r] + (pr >> 1) * 64);
+        };
+        auto read_a = [&](int h) {
+#pragma unroll
+            for (int i = 0; i < RB; ++i) a[h][i] = lds_word_at(xa + h * (RB * 1024) + i * 256);
+        };
+        auto query = [&](int pr) {
+            uint4 m = q[pr % RING][0];
+#pragma unroll
+            for (int r = 1; r < D; ++r) m = pk_max_u16x8(m, q[pr % RING][r]);
+            wd[pr & 1].x = keys_to_neg_half2_mad(m.x); wd[pr & 1].y = keys_to_neg_half2_mad(m.y);
+            wd[pr & 1].z = keys_to_neg_half2_mad(m.z); wd[pr & 1].w = keys_to_neg_half2_mad(m.w);
+        };
+        auto multiply = [&](int pr) {
+#pragma unroll
+            for (int i = 0; i < RB; ++i) {
+                const uint4 ai = NB >= 4 ? a[pr >> 1][i] : keep_if(x_live, a[pr >> 1][i]);
+                w.acc[i][pr & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, ai), __builtin_bit_cast(half8v, wd[pr & 1]), w.acc[i][pr & 1], 0, 0, 0);
+            }
+        };
+        gather(0);
+        if (RING > 2) gather(1);
+        read_a(0);
+        cx.some(1);
+        ct.some(2);
+        __builtin_amdgcn_sched_barrier(0);
+        if (NH == 2 && carried) multiply(NP - 1);               // of the block before
+        __builtin_amdgcn_sched_barrier(0);
+        query(0);
+        if (RING == 2) gather(1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int pr = 1; pr < NP; ++pr) {
+            if (RING > 2 && pr + 1 < NP) gather(pr + 1);
+            if (NH == 2 && pr == 1) read_a(1);
+            if (pr == 1) cx.some(1);
+            ct.some(2);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(pr - 1);
+            query(pr);
+            if (RING == 2 && pr + 1 < NP) gather(pr + 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        while (ct.more()) ct.issue();
+        while (cx.more()) cx.issue();
+        if (NH == 1) multiply(NP - 1);
+        carried = true;
+        w.bm = w.nx;
+        w.nx = n2;
+        w.buf ^= 1;
+        ++w.b;
+    } while (w.b < w.b1 && w.bm.rs == RS);
+    if (NH == 2) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+            w.acc[i][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, a[NH - 1][i]), __builtin_bit_cast(half8v, wd[1]), w.acc[i][1], 0, 0, 0);
+    }
+}
+
+// One workgroup per (block group, token tile, output tile), in that order over the XCDs: the workgroups of an XCD stage
+// the same tables, which enter its L2 once.  Up to twelve wavefronts (eight where 96 or 128 tokens of accumulators and
+// activation words want 256 registers per lane).
+template <int D, int RB>
+__global__ __launch_bounds__(RB >= 6 ? 512 : 768) void k_prompt_gemm(PromptArgs p)
+{
+    const uint32_t q = (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);
+    if (q >= p.T * p.M * p.P) return;
+    const uint32_t g = q / (p.T * p.M), tm = q - g * p.T * p.M, tile_m = tm / p.T, tile = tm - tile_m * p.T;
+    const uint32_t b0 = g * p.n_blocks / p.P;
+    PromptWalk<D, RB> w;
+    w.b = b0;
+    w.b1 = (g + 1) * p.n_blocks / p.P;
+    w.buf = 0;
+    w.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    w.nw = blockDim.x >> 6;
+    w.lds0 = (uint32_t)(uintptr_t)(lds_void *)smem;
+    w.lane = threadIdx.x & 63;
+    w.o_base = (tile * w.nw + w.wave) * 32;
+    w.tile_m = tile_m;
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) w.acc[i][j] = (float4v){0.f, 0.f, 0.f, 0.f};
+    w.bm = p.bmeta[b0];
+    w.nx = p.bmeta[min(b0 + 1, w.b1 - 1)];
+    {
+        PromptCopy ct, cx;
+        prompt_copies<D, RB>(p, w, w.bm, 0, ct, cx);
+        while (ct.more()) ct.issue();
+        while (cx.more()) cx.issue();
+    }
+    while (w.b < w.b1) {
+        switch (w.bm.rs) {
+        case 9: if constexpr (D <= 6) { prompt_run<D, RB, 8>(p, w); break; }
+        case 5: prompt_run<D, RB, 4>(p, w); break;
+        case 3: prompt_run<D, RB, 2>(p, w); break;
+        default: prompt_run<D, RB, 1>(p, w); break;
+        }
+    }
+    float4v *dst = reinterpret_cast<float4v *>(p.parts) + ((size_t)(tm * p.P + g) * p.rows * 2 * w.nw + w.wave * 2) * 64 + w.lane;
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+        if ((uint32_t)i >= p.rows) break;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) dst[((size_t)i * 2 * w.nw + j) * 64] = w.acc[i][j];
+    }
+}
+
+// y = the sum of the P partials of every output, in group order: a wavefront adds one 16 x 16 block, four partials in
+// flight, and the workgroup's 16 x 64 outputs are turned round in LDS to leave as 8- or 16-byte pieces.  Grid (ceil(out /
+// 64), 16-token blocks).
+__global__ __launch_bounds__(256) void k_prompt_reduce(const float *__restrict__ parts, uint32_t T, uint32_t P, uint32_t nw, uint32_t rows, void *Y, uint32_t y_dt,
+                                                       uint32_t ldy, uint32_t tokens, uint32_t out)
+{
+    __shared__ __align__(16) float sm[16][68];
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, rb = blockIdx.y;
+    const uint32_t cb = blockIdx.x * 4 + wave, tile = cb / (2 * nw), c = cb - tile * 2 * nw, tm = rb / rows * T + tile;
+    const size_t stride = (size_t)rows * 2 * nw * 64;           // float4v per group
+    float4v s = {0.f, 0.f, 0.f, 0.f};
+    if (cb * 16 < out) {
+        const float4v *src = reinterpret_cast<const float4v *>(parts) + (size_t)tm * P * stride + ((size_t)(rb % rows) * 2 * nw + c) * 64 + lane;
+        uint32_t g = 0;
+        for (; g + 4 <= P; g += 4) {
+            float4v v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = src[(size_t)(g + k) * stride];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) s += v[k];
+        }
+        for (; g < P; ++g) s += src[(size_t)g * stride];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sm[(lane >> 4) * 4 + i][wave * 16 + (lane & 15)] = s[i];
+    __syncthreads();
+    const uint32_t row = threadIdx.x >> 4, o = blockIdx.x * 64 + (threadIdx.x & 15) * 4, t = rb * 16 + row;
+    if (t >= tokens || o >= out) return;
+    const float4 v = *reinterpret_cast<const float4 *>(&sm[row][(threadIdx.x & 15) * 4]);
+    const size_t at = (size_t)t * ldy + o;
+    if ((ldy & 3u) == 0 && o + 4 <= out) {                      // (Y starts on a 16-byte boundary)
+        if (y_dt == SKL_F32) {
+            *reinterpret_cast<float4 *>(static_cast<float *>(Y) + at) = v;
+        } else {
+            uint16_t e[4];
+            const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) e[i] = y_dt == SKL_F16 ? float_to_half_bits(f[i]) : float_to_bf16_bits(f[i]);
+            *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(Y) + at) = make_uint2(e[0] | (uint32_t)e[1] << 16, e[2] | (uint32_t)e[3] << 16);
+        }
+        return;
+    }
+    store_out(Y, y_dt, at, v.x);
+    if (o + 1 < out) store_out(Y, y_dt, at + 1, v.y);
+    if (o + 2 < out) store_out(Y, y_dt, at + 2, v.z);
+    if (o + 3 < out) store_out(Y, y_dt, at + 3, v.w);
+}
+
+// ========================================================================
+// Launcher
+// ========================================================================
+skl_status_t skl_launch_gemm_prompt(const skl_layer *L, const TableSrc &src, const PromptPlan &s, const uint16_t *X, skl_dtype_t x_dt,
+                                    uint32_t ldx, void *Y, skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, void *ws, hipStream_t stream)
+{
+    const RowArgs a = make_row_args(L, src);
+    PromptArgs g;
+    g.h = a.h; g.bmeta = a.bmeta; g.tables = src.tables;
+    g.Xq = static_cast<uint4 *>(ws);
+    g.parts = reinterpret_cast<float *>(static_cast<char *>(ws) + s.pack_bytes);
+    g.out = L->out; g.n_blocks = L->n_blocks;
+    g.T = s.T; g.M = s.M; g.P = s.P; g.rows = s.rows; g.n_words = 8 * L->gemm_kb;
+    g.per_xcd = (s.T * s.M * s.P + 7) / 8;
+    const PackArgs k{X, a.chan, reinterpret_cast<const skl_pack_window *>(L->dev + L->off_windows), static_cast<uint4 *>(ws),
+                     (uint32_t)x_dt, ldx, tokens, L->in, 2 * L->gemm_kb};
+    const uint32_t n_rows = (tokens + 15) / 16, n_pack = n_rows * ((k.n_steps + PO_STEPS - 1) / PO_STEPS);
+    skl_status_t st = SKL_OK;
+    auto launch = [&](auto rb_tag, auto kernel) {
+        constexpr int RB = decltype(rb_tag)::value;
+        static_assert(PG_LDS(RB) <= SKL_LDS_HARD_BYTES, "two tables and two activation buffers");
+        st = allow_lds(kernel, PG_LDS(RB));
+        if (st != SKL_OK) return;
+        hipLaunchKernelGGL((k_prompt_pack<RB>), dim3(n_pack), dim3(SKL_WG), PO_LDS_BYTES, stream, k, n_rows);
+        st = check_launch("prompt packing");
+        if (st == SKL_OK) hipLaunchKernelGGL(kernel, dim3(8 * g.per_xcd), dim3(64 * s.nw), PG_LDS(RB), stream, g);
+    };
+    DISPATCH_D(L->d, {
+        if (s.rb == 2) launch(std::integral_constant<int, 2>(), k_prompt_gemm<D, 2>);
+        else if (s.rb == 4) launch(std::integral_constant<int, 4>(), k_prompt_gemm<D, 4>);
+        else if (s.rb == 6) launch(std::integral_constant<int, 6>(), k_prompt_gemm<D, 6>);
+        else launch(std::integral_constant<int, 8>(), k_prompt_gemm<D, 8>);
+    })
+    if (st == SKL_OK) st = check_launch("prompt gemm");
+    if (st != SKL_OK) return st;
+    hipLaunchKernelGGL(k_prompt_reduce, dim3((L->out + 63) / 64, n_rows), dim3(256), 0, stream, g.parts, s.T, s.P, s.nw, s.rows, Y, (uint32_t)y_dt,
+                       ldy, tokens, L->out);
+    return check_launch("prompt reduction");
+}
+
+}  // namespace SKL_NS

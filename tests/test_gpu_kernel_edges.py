@@ -6,7 +6,7 @@ import pytest
 import oracle
 import paper_2506_17255_amd as skl
 import workloads as wk
-from skl_harness import GpuLayer, build_states_on_gpu, rel_fro
+from skl_harness import GpuLayer, build_states_on_gpu, matmul_f64, rel_fro
 
 pytestmark = pytest.mark.gpu
 
@@ -144,6 +144,51 @@ def test_short_prompts_in_a_workspace_of_the_fused_kernel(tokens, bits):
         with pytest.raises(skl.SketchLinearError) as e:
             g.gemm(X, "bf16", "f32", ws_bytes=fused - 1)
         assert e.value.status == skl.SKL_ERR_BUFFER_TOO_SMALL
+
+
+@pytest.mark.parametrize("in_f,out_f,d,widths,bits,tokens,x_dt,y_dt,ldy_pad", [
+    (777, 3001, 4, (9, 24), 16, 1, "bf16", "f32", 0),               # ragged rows of Y, a last tile of few outputs
+    (777, 3001, 4, (9, 24), 16, 16, "f16", "f16", 3),               # tiles of 32 tokens
+    (777, 3001, 4, (9, 200, 330, 1000), 16, 17, "bf16", "bf16", 0),     # wide channels in blocks of four, two and one words
+    (1030, 4000, 3, (9, 250), 16, 33, "bf16", "f32", 0),            # tiles of 64 tokens
+    (777, 3001, 2, (9, 2000), 16, 64, "f16", "f32", 4),
+    (777, 3001, 1, (9, 500), 16, 65, "bf16", "f32", 0),             # one row; tiles of 96 tokens
+    (900, 3001, 5, (60, 90), 16, 96, "bf16", "bf16", 3),            # five rows: fewer gathers in flight
+    (2048, 5001, 6, (40, 70), 16, 97, "f16", "f16", 0),             # tiles of 128 tokens
+    (1500, 6000, 8, (30, 100), 16, 20, "bf16", "f32", 0),           # eight rows: blocks of four words
+    (1500, 9000, 7, (1, 2), 16, 20, "bf16", "f32", 0),              # tables shorter than a copy
+    (2048, 6050, 4, (33, 113), 16, 113, "bf16", "f32", 0),          # the largest eight-word table (65088 bytes)
+    (900, 3001, 4, (9, 24), 8, 40, "bf16", "f32", 0),               # low-bit states: tables in the workspace
+    (900, 1100, 3, (9, 24), 16, 129, "bf16", "f32", 0),             # two token tiles
+    (900, 1100, 2, (9, 24), 4, 300, "bf16", "f16", 4),              # three
+    (520, 777, 4, (9, 24), 16, 512, "f16", "f32", 0),               # four, all full
+])
+def test_prompts_in_one_pass(in_f, out_f, d, widths, bits, tokens, x_dt, y_dt, ldy_pad):
+    """Against the oracle and the staged kernel, twice bit for bit.  Up to 128 tokens the way the call goes shows in the
+    workspace: the weight words that the staged kernel would leave at its end are not written."""
+    rng = np.random.default_rng(in_f + out_f + tokens)
+    A, C = hash_params(rng, d)
+    K = np.where(rng.random(in_f) < 0.03, rng.choice(widths[1:], in_f), widths[0]).astype(np.uint32)
+    states = (rng.standard_normal(int(K.sum()) * d) * 0.02).astype(np.float16).view(np.uint16)
+    sk = oracle.Sketch(in_f, out_f, 1, out_f, d, A, C, K, states)
+    if bits < 16:
+        sk = oracle.quantize(sk, bits)
+    x = rng.standard_normal((tokens, in_f)).astype(np.float32)
+    X = wk.f32_to_bf16_bits(x) if x_dt == "bf16" else x.astype(np.float16).view(np.uint16)
+    W_hat = oracle.query(sk)
+    ref = matmul_f64(W_hat, X if x_dt == "bf16" else X.view(np.float16), x_dt)
+    # float32 sums of in_f exact products, then one rounding to the output type
+    tol = SUM_TOL + {"f32": 0.0, "f16": 2.0**-11, "bf16": 2.0**-8}[y_dt]
+    with GpuLayer(sk) as g, GpuLayer(sk, skl.FLAG_STAGED_PREFILL) as st:
+        ws, need = g.workspace(1, tokens)
+        ws.fill_(0xA5)
+        y = g.gemm(X, x_dt, y_dt, ldy=out_f + ldy_pad)
+        if tokens <= 128 and bits == 16:
+            assert bool((ws[need - 4096:need] == 0xA5).all())
+        assert np.array_equal(y, g.gemm(X, x_dt, y_dt, ldy=out_f + ldy_pad))
+        other = st.gemm(X, x_dt, y_dt, ldy=out_f + ldy_pad)
+    for v in (y, other):
+        assert np.isfinite(v.astype(np.float32)).all() and rel_fro(v, ref) <= tol, rel_fro(v, ref)
 
 
 @pytest.mark.parametrize("batch", [1, 2, 4, 5, 16])
