@@ -45,7 +45,7 @@ struct PackArgs {
     uint32_t x_dt, ldx, tokens, in, n_steps;
 };
 // tokens t0 .. t0 + 15, group g of PO_STEPS steps; LDS: PO_LDS_BYTES at smem
-template <class Place>
+template <uint32_t NT, class Place>
 __device__ __forceinline__ void pack_group(const PackArgs &p, uint32_t t0, uint32_t g, Place place)
 {
     uint16_t *rows = reinterpret_cast<uint16_t *>(smem);
@@ -57,21 +57,21 @@ __device__ __forceinline__ void pack_group(const PackArgs &p, uint32_t t0, uint3
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t row = lane & 15, kg = lane >> 4;
     const skl_pack_window win = windows[g];
-    constexpr uint32_t N = PO_STEPS / (SKL_WG / 64);            // steps per wavefront
+    constexpr uint32_t WAVES = NT / 64, N = PO_STEPS / WAVES, PER_ROW = NT / 16;            // steps per wavefront
     u32x4v ch[N][2];                                            // this lane's channels (the list is padded to whole groups of steps)
 #pragma unroll
     for (uint32_t i = 0; i < N; ++i) {
-        const u32x4v *c = reinterpret_cast<const u32x4v *>(chan + (g * PO_STEPS + wave + 4 * i) * 32 + kg * 8);
+        const u32x4v *c = reinterpret_cast<const u32x4v *>(chan + (g * PO_STEPS + wave + WAVES * i) * 32 + kg * 8);
         ch[i][0] = c[0];
         ch[i][1] = c[1];
     }
     if (win.n) {
-        const uint32_t r = threadIdx.x >> 4;                    // 16 threads copy one token's row
+        const uint32_t r = threadIdx.x / PER_ROW;               // PER_ROW threads copy one token's row
         const uint16_t *src = X + (size_t)min(t0 + r, tokens - 1) * ldx + win.base;
         const bool vec = (ldx & 7u) == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;        // (base is a multiple of 8)
 #pragma unroll
-        for (uint32_t i = 0; i < PO_WINDOW / 128; ++i) {
-            const uint32_t c = ((threadIdx.x & 15) + 16 * i) * 8;
+        for (uint32_t i = 0; i < (PO_WINDOW + 8 * PER_ROW - 1) / (8 * PER_ROW); ++i) {
+            const uint32_t c = (threadIdx.x % PER_ROW + PER_ROW * i) * 8;
             if (c < win.n) {
                 u32x4v v = {0, 0, 0, 0};
                 if (vec && win.base + c + 8 <= in) {
@@ -90,7 +90,7 @@ __device__ __forceinline__ void pack_group(const PackArgs &p, uint32_t t0, uint3
     const uint16_t *near = rows + row * PO_STRIDE;
 #pragma unroll
     for (uint32_t i = 0; i < N; ++i) {
-        const uint32_t step = g * PO_STEPS + wave + 4 * i;
+        const uint32_t step = g * PO_STEPS + wave + WAVES * i;
         if (step >= n_steps) continue;
         uint32_t w[4] = {0, 0, 0, 0};
 #pragma unroll

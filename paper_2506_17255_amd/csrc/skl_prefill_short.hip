@@ -38,7 +38,7 @@ template <int RB>
 __global__ __launch_bounds__(SKL_WG) void k_prompt_pack(PackArgs k, uint32_t n_rows)
 {
     const uint32_t t0 = blockIdx.x % n_rows * 16, lane = threadIdx.x & 63;
-    pack_group(k, t0, blockIdx.x / n_rows, [&](uint32_t step) {
+    pack_group<SKL_WG>(k, t0, blockIdx.x / n_rows, [&](uint32_t step) {
         return ((size_t)(t0 / (RB * 16)) * k.n_steps * 4 + step * 4 + (lane >> 4)) * (RB * 16) + t0 % (RB * 16) + (lane & 15);
     });
 }

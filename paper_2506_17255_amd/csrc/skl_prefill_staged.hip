@@ -21,6 +21,7 @@ namespace SKL_NS {
 static_assert(SG_SLOT_BYTES == SG_SLOT_WORDS * 16u, "weight words of a 64-channel block of an output tile");
 #define SG_EPI_BYTES 8704u              // epilogue, per wavefront: 32 rows x (64 float32 + 16 bytes)
 
+#define SG_REBUILD_WG 512u              // threads per workgroup of the rebuild launch
 struct RebuildArgs {
     HashArgs h;
     const skl_block_meta *bmeta;
@@ -38,10 +39,11 @@ __device__ __forceinline__ void rebuild_body(const RebuildArgs &p, uint32_t blk,
     const uint32_t hi = (uint32_t)(((uint64_t)(seg + 1) * p.n_col) / p.n_oseg);
     const uint32_t w0 = bm.chan_off >> 3;                       // first operand word of the block along the channel list
     const bool pad = blk + 1 == p.n_blocks;                     // the last block also fills the words up to the end of the last 64-channel block
-    for (uint32_t tile = lo; tile < hi; ++tile) {
+    const uint32_t sub = threadIdx.x & 255;
+    for (uint32_t tile = lo + (threadIdx.x >> 8); tile < hi; tile += SG_REBUILD_WG / 256) {
         // outputs past the end of the layer are rebuilt like the last one: their products are never stored
-        const uint32_t o = min((p.tile0 + tile) * GM3_NT + threadIdx.x, p.out - 1);
-        uint4 *dst = p.Wp + (size_t)tile * p.KB * SG_SLOT_WORDS + (threadIdx.x >> 4) * 64 + (threadIdx.x & 15);
+        const uint32_t o = min((p.tile0 + tile) * GM3_NT + sub, p.out - 1);
+        uint4 *dst = p.Wp + (size_t)tile * p.KB * SG_SLOT_WORDS + (sub >> 4) * 64 + (sub & 15);
         uint32_t off[D];
         row_offsets<D>(p.h, o, bm.K, RS, off);
 #pragma unroll
@@ -63,7 +65,7 @@ __device__ __forceinline__ void rebuild_block(const RebuildArgs &p, uint32_t idx
     if (!skl_in_range(blk, p.n_blocks, SKL_DBG_BLOCK) || !skl_in_range(seg, p.n_oseg, SKL_DBG_OUTPUT)) return;
     const skl_block_meta bm = p.bmeta[blk];
     // global -> LDS without passing through registers: all of a wavefront's chunks are in flight at once
-    copy_words_to_lds_async(smem, p.tables + bm.table_off16, D * bm.K * bm.rs, SKL_WG / 64);
+    copy_words_to_lds_async(smem, p.tables + bm.table_off16, D * bm.K * bm.rs, SG_REBUILD_WG / 64);
     wait_async_copies();
     __syncthreads();
     switch (bm.rs) {
@@ -75,21 +77,27 @@ __device__ __forceinline__ void rebuild_block(const RebuildArgs &p, uint32_t idx
 }
 
 // Both in one launch: a short prompt has too few activations to fill the chip and too little work for a launch of its
-// own (4096 x 4096, 100 tokens, whole call: 34 -> 29 us; 1024 x 2048: 22 -> 18; 2048 tokens: 80 -> 78).  The first n_pack workgroups re-order the activations, the others rebuild;
-// 16-token rows x step groups + channel blocks x output segments workgroups, over two grid dimensions (a dimension holds
+// own (4096 x 4096, 100 tokens, whole call: 34 -> 29 us; 1024 x 2048: 22 -> 18; 2048 tokens: 80 -> 78).  The rebuilding
+// workgroups come first: they wait for tables and write the weights while the many short ones that re-order the
+// activations fill the compute units around them.  512 threads, so that six wavefronts per SIMD gather from the three
+// tables a compute unit has room for.  4096 x 11008, 2048 tokens, 0.5 bit, 256 threads and the activations first 39.7 us, now
+// 28 (the weights alone 19; their 90 MB take a fill 13); 8192 x 28672 131 -> 106 (470 MB, a fill 69; the gathers cost
+// nothing, without the stores 79); 4096 x 4096 19.7 -> 15.3.
+// Channel blocks x output segments + 16-token rows x step groups workgroups, over two grid dimensions (a dimension holds
 // 2^32 threads)
 template <int D>
-__global__ __launch_bounds__(SKL_WG) void k_rebuild_operands(RebuildArgs r, PackArgs k, uint32_t n_pack)
+__global__ __launch_bounds__(SG_REBUILD_WG) void k_rebuild_operands(RebuildArgs r, PackArgs k, uint32_t n_pack)
 {
     const uint32_t n_rows = (k.tokens + 15) / 16, idx = blockIdx.y * gridDim.x + blockIdx.x;
-    if (idx < n_pack) {
+    if (idx < r.n_blocks * r.n_oseg) {
+        rebuild_block<D>(r, idx);
+    } else if (idx < r.n_blocks * r.n_oseg + n_pack) {
         // [256-token tile][32-channel step][16-token block][channel group 4][16 tokens]
-        const uint32_t t0 = idx % n_rows * 16;
-        pack_group(k, t0, idx / n_rows, [&](uint32_t step) {
+        const uint32_t i = idx - r.n_blocks * r.n_oseg, t0 = i % n_rows * 16;
+        pack_group<SG_REBUILD_WG>(k, t0, i / n_rows, [&](uint32_t step) {
             return ((size_t)(t0 / GM_MT) * k.n_steps + step) * SG_STEP_WORDS + (t0 % GM_MT) / 16 * 64 + (threadIdx.x & 63);
         });
     }
-    else if (idx < n_pack + r.n_blocks * r.n_oseg) rebuild_block<D>(r, idx - n_pack);
 }
 
 template <class Split>
@@ -419,18 +427,18 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
         r.h = a.h; r.bmeta = a.bmeta; r.tables = src.tables; r.Wp = Wp;
         r.out = L->out; r.n_blocks = L->n_blocks; r.KB = KB; r.n_words = L->n_packed / 8;
         r.tile0 = tile0; r.n_col = cols;
-        // Output segments per channel block: a workgroup stages its block's table once (as many bytes as
-        // the weight words of one or two tiles), so it should rebuild a dozen tiles; but at least ~1024
-        // workgroups, and every segment at least one tile column.
-        const uint32_t few = (1024 + L->n_blocks - 1) / L->n_blocks, many = (4096 + L->n_blocks - 1) / L->n_blocks;
-        r.n_oseg = std::max(1u, std::min(cols, std::max(few, std::min(cols / 12, many))));
+        // Output segments per channel block: two, or as many as make 128 workgroups.  More segments stage every table
+        // more often and gain nothing (the activation workgroups behind them fill the rest of the chip): launch time by
+        // segments, 2048 tokens, 4096 x 11008 (67 blocks) 2 28.2 us, 4 29.6, 8 31.5; 8192 x 28672 (518) 2 105.8, 4
+        // 111.8, 8 120.4; 4096 x 4096 (66) 2 15.3, 4 17.1; 2048 x 5632, 1500 tokens (33) 1 19.1, 2 12.6, 4 12.4.
+        r.n_oseg = std::min(cols, std::max(2u, (127 + L->n_blocks) / L->n_blocks));
         const size_t lds = std::max<size_t>(L->max_table_bytes, PO_LDS_BYTES);
         const uint32_t n_pack = tile0 ? 0 : (tokens + 15) / 16 * ((2 * KB + PO_STEPS - 1) / PO_STEPS);     // (with the first slab)
         const uint32_t n_wg = n_pack + L->n_blocks * r.n_oseg, row = std::min(n_wg, 1u << 22);
         const dim3 grid(row, (n_wg + row - 1) / row);
         DISPATCH_D(L->d, {
             st = allow_lds(k_rebuild_operands<D>, lds);
-            if (st == SKL_OK) hipLaunchKernelGGL((k_rebuild_operands<D>), grid, dim3(SKL_WG), lds, stream, r, k, n_pack);
+            if (st == SKL_OK) hipLaunchKernelGGL((k_rebuild_operands<D>), grid, dim3(SG_REBUILD_WG), lds, stream, r, k, n_pack);
         })
         if (st == SKL_OK) st = check_launch("operand rebuild");
         if (st != SKL_OK) return st;
