@@ -46,38 +46,6 @@ __global__ __launch_bounds__(SKL_WG) void k_prompt_pack(PackArgs k, uint32_t n_r
 #define PG_X0 (2u * SKL_PBUF_DIST)      // LDS: two table buffers, two activation buffers
 #define PG_LDS(rb) (PG_X0 + 2u * (rb) * 2048u)
 
-// A copy of n16 words into LDS, 1 KiB chunks dealt to the wavefronts in turn and issued one by one between the
-// arithmetic.  The last chunk starts early enough to end with the source (a source shorter than a chunk repeats its last
-// word), so that no lane needs a bounds check and nothing past the end is read.
-struct PromptCopy {
-    const char *src;
-    uint32_t off, last, lds, step, lane_bytes;
-    __device__ __forceinline__ void start(const uint4 *from, uint32_t n16, uint32_t lds_addr, uint32_t wave, uint32_t nw, uint32_t lane)
-    {
-        src = uniform_address(from);
-        n16 = __builtin_amdgcn_readfirstlane(n16);
-        last = n16 > 64 ? n16 * 16 - 1024 : 0;
-        off = wave * 1024;
-        if (n16 <= wave * 64) off = 0xFFFFFFFFu;
-        step = nw * 1024;
-        lds = lds_addr;
-        lane_bytes = min(lane, n16 - 1) * 16;
-    }
-    __device__ __forceinline__ bool more() const { return off < last + 1024; }
-    __device__ __forceinline__ void issue()
-    {
-        const uint32_t o = min(off, last);
-        lds_dma_16_uniform(src + o, lane_bytes, lds + o);
-        off += step;
-    }
-    __device__ __forceinline__ void some(int n)
-    {
-#pragma unroll
-        for (int i = 0; i < n; ++i)
-            if (more()) issue();
-    }
-};
-
 template <int D, int RB>
 struct PromptWalk {
     uint32_t b, b1, buf;                // next block, end of the group, its buffers
@@ -87,7 +55,7 @@ struct PromptWalk {
 };
 
 template <int D, int RB>
-__device__ __forceinline__ void prompt_copies(const PromptArgs &p, const PromptWalk<D, RB> &w, const skl_block_meta &bm, uint32_t buf, PromptCopy &tab, PromptCopy &x)
+__device__ __forceinline__ void prompt_copies(const PromptArgs &p, const PromptWalk<D, RB> &w, const skl_block_meta &bm, uint32_t buf, ChunkCopy &tab, ChunkCopy &x)
 {
     tab.start(p.tables + bm.table_off16, D * bm.K * bm.rs, w.lds0 + buf * SKL_PBUF_DIST, w.wave, w.nw, w.lane);
     x.start(p.Xq + ((size_t)w.tile_m * p.n_words + (bm.chan_off >> 3)) * (RB * 16), bm.nb * (RB * 16), w.lds0 + PG_X0 + buf * (RB * 2048), w.wave, w.nw, w.lane);
@@ -110,7 +78,7 @@ __device__ __forceinline__ void prompt_run(const PromptArgs &p, PromptWalk<D, RB
         wait_async_copies();
         __syncthreads();                                        // block b has arrived, nobody reads the other buffers any more
         const bool more = w.b + 1 < w.b1;
-        PromptCopy ct, cx;
+        ChunkCopy ct, cx;
         prompt_copies<D, RB>(p, w, w.nx, w.buf ^ 1, ct, cx);
         if (!more) ct.off = cx.off = 0xFFFFFFFFu;
         const skl_block_meta n2 = p.bmeta[min(w.b + 2, w.b1 - 1)];
@@ -181,8 +149,8 @@ __device__ __forceinline__ void prompt_run(const PromptArgs &p, PromptWalk<D, RB
             if (RING == 2 && pr + 1 < NP) gather(pr + 1);
             __builtin_amdgcn_sched_barrier(0);
         }
-        while (ct.more()) ct.issue();
-        while (cx.more()) cx.issue();
+        ct.rest();
+        cx.rest();
         if (NH == 1) multiply(NP - 1);
         carried = true;
         w.bm = w.nx;
@@ -224,10 +192,10 @@ __global__ __launch_bounds__(RB >= 6 ? 512 : 768) void k_prompt_gemm(PromptArgs 
     w.bm = p.bmeta[b0];
     w.nx = p.bmeta[min(b0 + 1, w.b1 - 1)];
     {
-        PromptCopy ct, cx;
+        ChunkCopy ct, cx;
         prompt_copies<D, RB>(p, w, w.bm, 0, ct, cx);
-        while (ct.more()) ct.issue();
-        while (cx.more()) cx.issue();
+        ct.rest();
+        cx.rest();
     }
     while (w.b < w.b1) {
         switch (w.bm.rs) {
