@@ -260,3 +260,32 @@ def test_batched_decode_stores(in_f, out_f, batch):
     with GpuLayer(sk) as g:
         y = g.gemv(x, "f32")
     assert rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
+
+
+@pytest.mark.parametrize("out_f,batch,ldh_pad,h_dt", [
+    (4096, 15, 0, "f32"),       # 240 wavefronts of the row reduction: the other one
+    (4096, 16, 0, "f16"),       # 256: the first
+    (4097, 16, 3, "f32"),       # partial sums and rows of h on 4-byte boundaries, one output in the last piece
+    (4098, 16, 2, "f16"),
+    (16390, 4, 2, "f32"),       # 65 x 4; rows of h on 16-byte boundaries, a last piece of two outputs
+])
+def test_gate_up_reductions(out_f, batch, ldh_pad, h_dt):
+    """Both reductions of the gate/up pair around the line between them; layers with unlike numbers of block groups."""
+    t = __import__("torch")
+    rng = np.random.default_rng(out_f + batch)
+    x = rng.standard_normal((batch, 200)).astype(np.float16)
+    A, C = hash_params(rng, 2)
+    skg, sku = (oracle.Sketch(200, out_f, 1, out_f, 2, A, C, K, (rng.standard_normal(2 * int(K.sum())) * 0.02).astype(np.float16).view(np.uint16))
+                for K in (np.full(200, 9, dtype=np.uint32), rng.integers(2, 40, size=200).astype(np.uint32)))
+    ref = oracle.gate_up(oracle.linear(oracle.query(skg), x), oracle.linear(oracle.query(sku), x))
+    with GpuLayer(skg) as g, GpuLayer(sku) as u:
+        xd = t.from_numpy(x.view(np.int16)).cuda()
+        h = t.full((batch, out_f + ldh_pad), float("nan"), dtype={"f32": t.float32, "f16": t.float16}[h_dt], device="cuda")
+        ws = t.empty(skl.sketch_linear_gemv_group_workspace_bytes([g.handle, u.handle], batch), dtype=t.uint8, device="cuda")
+        skl.sketch_linear_gemv_gate_up(g.handle, u.handle, xd.data_ptr(), skl.SKL_F16, 200, h.data_ptr(),
+                                       {"f32": skl.SKL_F32, "f16": skl.SKL_F16}[h_dt], out_f + ldh_pad, batch, ws.data_ptr(), ws.numel(), g.stream())
+        got = h.float().cpu().numpy()
+    assert np.isnan(got[:, out_f:]).all()
+    # SiLU and the product pass the sums' relative errors on at most doubled, expf adds a few units of the last place
+    tol = 4 * SUM_TOL + (2.0**-11 if h_dt == "f16" else 0.0)
+    assert rel_fro(got[:, :out_f], ref) <= tol, rel_fro(got[:, :out_f], ref)
