@@ -302,6 +302,10 @@ SKL_API skl_status_t sketch_linear_gemm(const skl_layer_t *layer, const void *X,
  * t * shares + s.  A slot holds the tokens of a tile x 256 outputs.  Staged
  * layers of more than 1 GiB of weight words are worked off in slabs of output
  * tiles, each split by itself.
+ * Staged calls of more than 128 tokens in one slab take whole tiles of another
+ * width (256 tokens x 128 to 352 outputs) instead where those fit the chip
+ * better; this listing then shows the split that such a call would have with
+ * tiles of 256 outputs.
  * *n_segments receives the number of segments (also when it exceeds
  * `capacity`; then only the first `capacity` are written).  `shape` (HOST,
  * 6 words, may be NULL) receives workgroups per XCD, partial tiles per XCD,

@@ -28,7 +28,8 @@ struct RebuildArgs {
     const uint4 *tables;                // padded block tables, [r][k][rs] words
     uint4 *Wp;                          // [output tile of the slab][64-channel block][SG_SLOT_WORDS]
     uint32_t out, n_blocks, KB, n_words;
-    uint32_t tile0, n_col, n_oseg;      // the slab: first output tile, output tiles, output segments
+    uint32_t tile0, n_col, n_oseg;      // the slab: first output tile (of 256), pieces of 256 outputs, output segments
+    uint32_t tb, n_tb;                  // 16-output blocks per tile of the product kernel, blocks of the slab
 };
 
 template <int D, int RS>
@@ -43,16 +44,18 @@ __device__ __forceinline__ void rebuild_body(const RebuildArgs &p, uint32_t blk,
     for (uint32_t tile = lo + (threadIdx.x >> 8); tile < hi; tile += SG_REBUILD_WG / 256) {
         // outputs past the end of the layer are rebuilt like the last one: their products are never stored
         const uint32_t o = min((p.tile0 + tile) * GM3_NT + sub, p.out - 1);
-        uint4 *dst = p.Wp + (size_t)tile * p.KB * SG_SLOT_WORDS + (sub >> 4) * 64 + (sub & 15);
+        const uint32_t ob = tile * 16 + (sub >> 4), wide = ob / p.tb, step_words = p.tb * 64;
+        if (ob >= p.n_tb) continue;
+        uint4 *dst = p.Wp + (size_t)wide * p.KB * 2 * step_words + (ob - wide * p.tb) * 64 + (sub & 15);
         uint32_t off[D];
         row_offsets<D>(p.h, o, bm.K, RS, off);
 #pragma unroll
         for (int c = 0; c < NB; ++c) {
             const uint32_t w = w0 + c;
-            dst[(size_t)(w >> 2) * SG_STEP_WORDS + (w & 3) * 16] = keys_to_neg_half8(row_query8<D>(tab, off, c));
+            dst[(size_t)(w >> 2) * step_words + (w & 3) * 16] = keys_to_neg_half8(row_query8<D>(tab, off, c));
         }
         if (pad)
-            for (uint32_t w = p.n_words; w < 8 * p.KB; ++w) dst[(size_t)(w >> 2) * SG_STEP_WORDS + (w & 3) * 16] = make_uint4(0, 0, 0, 0);
+            for (uint32_t w = p.n_words; w < 8 * p.KB; ++w) dst[(size_t)(w >> 2) * step_words + (w & 3) * 16] = make_uint4(0, 0, 0, 0);
     }
 }
 
@@ -113,11 +116,11 @@ struct StagedArgs {
 
 // The wavefront's results (RB x 4 blocks of 16 tokens x 16 outputs) turned round in a private LDS area, 32 rows at
 // a time, and stored in 16-byte pieces: every store instruction writes whole 128-byte (256 for float32) row pieces.
-template <int DT, int RB>
-__device__ __forceinline__ void staged_store_rows(const float4v (&acc)[RB][4], uint32_t lds_wave, void *Y, uint32_t ldy, uint32_t t0,
+template <int DT, int RB, int CB = 4, int C0 = 0, int NC = 4>
+__device__ __forceinline__ void staged_store_rows(const float4v (&acc)[RB][CB], uint32_t lds_wave, void *Y, uint32_t ldy, uint32_t t0,
                                                   uint32_t tokens, uint32_t o0, uint32_t out, uint32_t lane)
 {
-    constexpr uint32_t ES = DT == SKL_F32 ? 4 : 2, ROWB = 64 * ES + 16, CH = 64 * ES / 16;      // bytes per LDS row (padded), pieces per row
+    constexpr uint32_t ES = DT == SKL_F32 ? 4 : 2, ROWB = 64 * ES + 16, CH = NC * 16 * ES / 16;      // bytes per LDS row (padded), pieces per row
     static_assert(32 * ROWB <= SG_EPI_BYTES, "32 rows have to fit the wavefront's area");
     const uint32_t n = lane & 15, q = lane >> 4;
 #pragma unroll
@@ -125,11 +128,11 @@ __device__ __forceinline__ void staged_store_rows(const float4v (&acc)[RB][4], u
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
+            for (int c = 0; c < NC; ++c)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const uint32_t addr = lds_wave + (h * 16 + q * 4 + i) * ROWB + (c * 16 + n) * ES;
-                    const float v = acc[r + h][c][i];
+                    const float v = acc[r + h][C0 + c][i];
                     if (DT == SKL_F32) *(__attribute__((address_space(3))) float *)(uintptr_t)addr = v;
                     else *(__attribute__((address_space(3))) uint16_t *)(uintptr_t)addr = DT == SKL_F16 ? float_to_half_bits(v) : float_to_bf16_bits(v);
                 }
@@ -325,6 +328,152 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 }
 
+// Y = X W on re-ordered operands, whole tiles of 256 tokens x 32 * CB outputs (the split is skl_make_wide_split).  A tile
+// that fits the chip in whole rounds needs no partial tiles: 4096 x 11008 at 2048 tokens is 256 tiles of 352 outputs instead
+// of 344 of 256, 88 of which went through 90 MB of float32 partials and a fix-up launch (product 185 us + fix-up 17 -> 131;
+// whole call 219 -> 172).
+// As k_staged_gemm, but the eight wavefronts own 64 tokens x 16 * CB outputs each: up to 176 accumulator registers, so that
+// of a stage only the activation words are held twice; weight words are read two or three columns (of 16 outputs) ahead of
+// their products, into registers that the column before has left.  A stage's buffer is therefore read until its last
+// column, and the copies issued during a stage go to the buffer of the stage before it.
+struct WideArgs {
+    const uint4 *Xp;                    // activation words: [256-token tile][32-channel step][SG_STEP_WORDS]
+    const uint4 *Wp;                    // weight words: [output tile][32-channel step][2 * CB blocks of 16 outputs][64]
+    void *Y;
+    uint32_t KB, tokens, out, y_dt, ldy, rows_aligned;
+    G3Split sp;
+};
+
+#define SW_STAGE_BYTES(cb) (16384u + (cb) * 2048u)
+#define SW_STAGES(cb) ((cb) <= 8 ? 5u : 4u)
+template <int DT, int CB, int C0>
+__device__ __forceinline__ void wide_store(const float4v (&acc)[4][CB], uint32_t lds_wave, void *Y, uint32_t ldy, uint32_t t0, uint32_t tokens,
+                                           uint32_t o0, uint32_t out, uint32_t lane)
+{
+    if constexpr (C0 < CB) {
+        staged_store_rows<DT, 4, CB, C0, (CB - C0 < 4 ? CB - C0 : 4)>(acc, lds_wave, Y, ldy, t0, tokens, o0 + C0 * 16, out, lane);
+        wide_store<DT, CB, C0 + 4>(acc, lds_wave, Y, ldy, t0, tokens, o0, out, lane);
+    }
+}
+
+template <int CB>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_staged_wide(WideArgs p)
+{
+    constexpr uint32_t A_BYTES = 16384, ST_BYTES = SW_STAGE_BYTES(CB), NS = SW_STAGES(CB), LOOK = CB % 4 == 2 ? 2 : 3;     // (words of the next columns in registers)
+    constexpr int PER = (16 + 2 * CB + 7) / 8;
+    static_assert(CB % 4 == 0 || CB % 4 == (int)LOOK, "the words read ahead of the next stage land in free registers");
+    const uint32_t xcd = blockIdx.x & 7, wg = blockIdx.x >> 3;
+    const G3Split sp = p.sp;
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void *)smem;
+    const uint32_t wm = wave >> 1, wn = wave & 1;
+    const uint32_t a_lane = lds0 + wm * 4096 + lane * 16, b_lane = lds0 + A_BYTES + wn * (CB * 1024) + lane * 16;
+    const uint32_t lds_wave = lds0 + wave * 1024, a_off = wave * 1024 + lane * 16;
+    // the last copy of a stage repeats its last KiB where the pieces do not divide out
+    const uint32_t last_b = min(wave + 8 * (PER - 3), 2u * CB - 1) * 1024;
+    float4v acc[4][CB];
+    for (uint32_t k = wg; k < sp.tiles_of(xcd); k += 32) {
+        uint32_t tile_m, tile_n;
+        sp.tile_of(xcd, k, tile_m, tile_n);
+        const uint32_t n_st = __builtin_amdgcn_readfirstlane(p.KB * 2);
+        const char *pa = uniform_address(p.Xp + (size_t)tile_m * p.KB * SG_SLOT_WORDS);
+        const char *pb = uniform_address(p.Wp + (size_t)tile_n * p.KB * 2 * (CB * 128));
+        auto next_buf = [](uint32_t buf) { return buf + ST_BYTES == NS * ST_BYTES ? 0 : buf + ST_BYTES; };
+        auto copy_piece = [&](uint32_t buf, auto piece) {
+            constexpr int I = decltype(piece)::value;
+            if constexpr (I < 2) lds_dma_16_offset<I * 8192>(pa + I * 8192, a_off, lds_wave + buf);
+            else if constexpr (I + 1 < PER) lds_dma_16_offset<A_BYTES + (I - 2) * 8192>(pb + (I - 2) * 8192, a_off, lds_wave + buf);
+            else lds_dma_16_offset<A_BYTES>(pb + last_b, lane * 16, lds0 + last_b + buf);
+        };
+        auto next_stage = [&](uint32_t st) {
+            const bool more = st + 1 < n_st;
+            pa += more ? SG_STEP_WORDS * 16 : 0;
+            pb += more ? CB * 2048 : 0;
+        };
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < CB; ++c) acc[r][c] = (float4v){0.f, 0.f, 0.f, 0.f};
+        uint4 a[2][4], b[4];
+        const std::integral_constant<int, 0> c0;
+        const std::integral_constant<int, 1> c1;
+        const std::integral_constant<int, 2> c2;
+        const std::integral_constant<int, 3> c3;
+        const std::integral_constant<int, 4> c4;
+        uint32_t buf = 0;
+        for (uint32_t st = 0; st + 1 < NS; ++st) {
+            copy_piece(buf, c0);
+            copy_piece(buf, c1);
+            copy_piece(buf, c2);
+            if constexpr (PER > 3) copy_piece(buf, c3);
+            if constexpr (PER > 4) copy_piece(buf, c4);
+            next_stage(st);
+            buf += ST_BYTES;
+        }
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * PER) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[0][r] = lds_word_at(a_lane + r * 1024);
+#pragma unroll
+        for (uint32_t c = 0; c < LOOK; ++c) b[c] = lds_word_at(b_lane + c * 1024);
+        uint32_t from = 0, into = (NS - 1) * ST_BYTES;          // buffer of the stage being multiplied; of the stage before it
+        auto stage = [&](uint32_t st, auto set) {
+            constexpr int H = decltype(set)::value;
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 3) * PER) : "memory");     // stage st + 1 has arrived
+            __builtin_amdgcn_s_barrier();                       // nobody reads the stage before any more
+            asm volatile("" ::: "memory");
+            const uint32_t nxt = next_buf(from);
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                if (c + (int)LOOK < CB && LOOK == 3) b[(c + 3) & 3] = lds_word_at(b_lane + from + (c + 3) * 1024);
+                if (c + (int)LOOK < CB && LOOK == 2) b[(c + 2) & 3] = lds_word_at(b_lane + from + (c + 2) * 1024);
+                if (c < 4) a[H ^ 1][c] = lds_word_at(a_lane + nxt + c * 1024);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, a[H][r]), __builtin_bit_cast(half8v, b[c & 3]), acc[r][c], 0, 0, 0);
+                if (c == 0) copy_piece(into, c0);
+                if (c == 1) copy_piece(into, c1);
+                if (c == 2) copy_piece(into, c2);
+                if constexpr (PER > 3) { if (c == 3) copy_piece(into, c3); }
+                if constexpr (PER > 4) { if (c == 4) copy_piece(into, c4); }
+                if (c == (CB > 5 ? 5 : CB - 1)) next_stage(st + NS - 1);
+                __builtin_amdgcn_sched_barrier(0);
+                if (c + (int)LOOK >= CB) b[c + LOOK - CB] = lds_word_at(b_lane + nxt + (c + LOOK - CB) * 1024);
+            }
+            into = from;
+            from = nxt;
+        };
+        for (uint32_t st = 0; st < n_st; st += 2) {             // (n_st is even: two stages per 64-channel block)
+            stage(st, c0);
+            stage(st + 1, c1);
+        }
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __syncthreads();                                        // nothing on its way into LDS, nobody reads it: the epilogue may use it
+        uint32_t ln = lane;
+        asm volatile("" : "+v"(ln));
+        const uint32_t t0 = tile_m * GM_MT + wm * 64, o0 = tile_n * (CB * 32) + wn * (CB * 16);
+        if (p.rows_aligned) {
+            const uint32_t lw = lds0 + wave * SG_EPI_BYTES;
+            if (p.y_dt == SKL_F32) wide_store<SKL_F32, CB, 0>(acc, lw, p.Y, p.ldy, t0, p.tokens, o0, p.out, ln);
+            else if (p.y_dt == SKL_F16) wide_store<SKL_F16, CB, 0>(acc, lw, p.Y, p.ldy, t0, p.tokens, o0, p.out, ln);
+            else wide_store<SKL_BF16, CB, 0>(acc, lw, p.Y, p.ldy, t0, p.tokens, o0, p.out, ln);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int c = 0; c < CB; ++c)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint32_t t = t0 + r * 16 + (ln >> 4) * 4 + i, o = o0 + c * 16 + (ln & 15);
+                        if (t < p.tokens && o < p.out) store_out(p.Y, p.y_dt, (size_t)t * p.ldy + o, acc[r][c][i]);
+                    }
+        }
+        __syncthreads();                                        // the epilogue's LDS areas are free again
+    }
+}
+
 // Adds n_parts partials of 16 tokens x 256 outputs (the first at src, part_floats apart) in order, turns them round in
 // LDS and stores rows.
 __device__ __forceinline__ void fixup_rows(const float *first, uint32_t part_floats, uint32_t n_parts, void *Y, uint32_t y_dt, uint32_t ldy,
@@ -406,6 +555,17 @@ static skl_status_t launch_product(const StagedArgs<Split> &g, uint32_t grid, hi
     return check_launch("staged gemm");
 }
 
+template <int CB>
+static skl_status_t launch_wide(const WideArgs &g, hipStream_t stream)
+{
+    constexpr size_t lds = SW_STAGES(CB) * SW_STAGE_BYTES(CB);
+    static_assert(lds >= 8 * SG_EPI_BYTES && lds <= SKL_LDS_HARD_BYTES, "the epilogue has to fit the stages' LDS");
+    const skl_status_t st = allow_lds(k_staged_wide<CB>, lds);
+    if (st != SKL_OK) return st;
+    hipLaunchKernelGGL((k_staged_wide<CB>), dim3(256), dim3(512), lds, stream, g);
+    return check_launch("staged gemm, whole tiles");
+}
+
 skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx,
                                     void *Y, skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, void *ws, hipStream_t stream)
 {
@@ -421,12 +581,18 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
     const skl_pack_window *windows = reinterpret_cast<const skl_pack_window *>(L->dev + L->off_windows);
     const PackArgs k{X, a.chan, windows, Xp, (uint32_t)x_dt, ldx, tokens, L->in, 2 * KB};
     skl_status_t st = SKL_OK;
+    // (all output tiles in one slab; the split is the call's only one then)
+    const uint64_t w_room = staged_part_bytes(L, tokens) + (uint64_t)slab_cols * KB * SG_SLOT_BYTES;
+    G3Split wide{};
+    const uint32_t wide_cb = tokens > SKL_SHORT_TOKENS && slab_cols == n_col ? skl_make_wide_split(L->out, KB, tokens, w_room, wide) : 0;
+    if (wide_cb) Wp = reinterpret_cast<uint4 *>(static_cast<char *>(ws) + round256(staged_pack_bytes(L, tokens)));      // no partial tiles: their room holds weight words
     for (uint32_t tile0 = 0; tile0 < n_col; tile0 += slab_cols) {
-        const uint32_t cols = std::min(slab_cols, n_col - tile0);
+        const uint32_t cols = wide_cb ? (wide.n_col * wide_cb + 7) / 8 : std::min(slab_cols, n_col - tile0);
         RebuildArgs r;
         r.h = a.h; r.bmeta = a.bmeta; r.tables = src.tables; r.Wp = Wp;
         r.out = L->out; r.n_blocks = L->n_blocks; r.KB = KB; r.n_words = L->n_packed / 8;
         r.tile0 = tile0; r.n_col = cols;
+        r.tb = wide_cb ? 2 * wide_cb : 16; r.n_tb = wide_cb ? wide.n_col * 2 * wide_cb : 16 * cols;
         // Output segments per channel block: two, or as many as make 128 workgroups.  More segments stage every table
         // more often and gain nothing (the activation workgroups behind them fill the rest of the chip): launch time by
         // segments, 2048 tokens, 4096 x 11008 (67 blocks) 2 28.2 us, 4 29.6, 8 31.5; 8192 x 28672 (518) 2 105.8, 4
@@ -443,6 +609,11 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
         if (st == SKL_OK) st = check_launch("operand rebuild");
         if (st != SKL_OK) return st;
 
+        if (wide_cb) {
+            const WideArgs g{Xp, Wp, Y, KB, tokens, L->out, (uint32_t)y_dt, ldy, ((size_t)ldy * (y_dt == SKL_F32 ? 4 : 2)) % 16 == 0, wide};
+            return wide_cb == 6 ? launch_wide<6>(g, stream) : wide_cb == 7 ? launch_wide<7>(g, stream) : wide_cb == 8 ? launch_wide<8>(g, stream)
+                 : wide_cb == 10 ? launch_wide<10>(g, stream) : wide_cb == 4 ? launch_wide<4>(g, stream) : launch_wide<11>(g, stream);
+        }
         auto fill = [&](auto &g) {
             g.Xp = Xp; g.Wp = Wp; g.Y = Y; g.parts = parts;
             g.KB = KB; g.tokens = tokens; g.out = L->out; g.y_dt = (uint32_t)y_dt; g.ldy = ldy;

@@ -227,6 +227,52 @@ static inline uint64_t skl_staged_part_floats(uint32_t out, uint32_t kb, uint32_
     return most;
 }
 
+// Whole tiles of another width instead: 256 tokens x 32 * cb outputs, one tile after another per workgroup (the k-th of XCD
+// x by workgroup k % 32), no partial tiles, no fix-up.  Returns cb, or 0 where the split above is estimated to be no slower
+// or the weight words do not fit `room`.  The estimates, in us: a 64-channel block of a 256 x 256 tile on every CU takes 1.52
+// (f[cb] per such area; narrow tiles read more operand words from LDS per product), a round of tiles 5 to 8 more for its
+// start and its stores, a partial tile 0.12 to write and read; a round that leaves CUs idle runs at a higher clock.  Whole
+// calls, split above / tiles by cb (2048 tokens unless said): 4096 x 11008 212 us / 4 188, 6 182, 8 198, 11 165; 4096 x 4096
+// 81 / 4 74.5; 2048 x 5632 104 / 4 66, 6 55, 8 58; 3000 x 7001 164 / 7 90, 8 97; 1024 x 2048 41 / 4 22; 8192 x 28672 830 / 4
+// 900, 7 829, 8 835, 10 801, 11 834; 4096 x 11008, 777 tokens, 164 / 6 95, 8 99; 8192 x 3000, 1300 tokens, 143 / 4 110.
+static inline uint32_t skl_make_wide_split(uint32_t out, uint32_t nb, uint32_t tokens, uint64_t room, G3Split &best)
+{
+    const G3Split old = skl_make_split(out, nb, tokens, true);
+    double blocks = 0;
+    uint32_t slots = 0, rounds = 1;
+    for (uint32_t x = 0; x < 8; ++x) {
+        blocks = std::max(blocks, old.rounds(x) * nb * (old.mt < GM_MT ? 0.6 : 1.0) + (double)old.units(x) / old.gx);
+        rounds = std::max(rounds, old.rounds(x));
+        for (uint32_t l = 0; l < old.left(x); ++l) slots += old.parts(x, l);
+    }
+    double limit = 1.52 * blocks + 8.0 * rounds + (slots ? 10.0 + 0.12 * slots : 0.0);
+    uint32_t pick = 0;
+    const struct { uint32_t cb; double f; } widths[] = {{11, 1.486}, {10, 1.49}, {8, 1.52}, {7, 1.59}, {6, 1.62}, {4, 1.77}};
+    for (const auto &w : widths) {
+        G3Split sp{};
+        sp.n_col = (out + 32 * w.cb - 1) / (32 * w.cb);
+        sp.nb = nb; sp.mt = GM_MT; sp.single = 1; sp.gx = 32;
+        sp.m_tiles = (tokens + GM_MT - 1) / GM_MT;
+        sp.T = sp.m_tiles * sp.n_col;
+        if ((uint64_t)sp.n_col * nb * w.cb * 4096 > room) continue;
+        rounds = ((sp.T + 7) / 8 + 31) / 32;
+        for (uint32_t mu = sp.m_tiles; mu >= 1; mu /= 2) {      // the largest dealing unit that needs no further round
+            if (sp.m_tiles % mu) continue;
+            sp.mu = mu;
+            uint32_t most = 0;
+            for (uint32_t x = 0; x < 8; ++x) most = std::max(most, sp.tiles_of(x));
+            if ((most + 31) / 32 <= rounds) break;
+        }
+        const double t = (0.6 * rounds + 0.4 * sp.T / 256.0) * nb * w.cb / 8.0 * w.f + 5.0 * rounds;
+        if (t < limit) {
+            limit = t;
+            best = sp;
+            pick = w.cb;
+        }
+    }
+    return pick;
+}
+
 // ---- short prompts in one pass ----
 // The plan of such a call: tiles of 32 * nw outputs (nw wavefronts) x 16 * rb tokens, the layer's channel blocks cut into P
 // groups of consecutive blocks; one workgroup per (output tile, token tile, group).

@@ -6,7 +6,7 @@ import pytest
 import oracle
 import paper_2506_17255_amd as skl
 import workloads as wk
-from skl_harness import GpuLayer, build_states_on_gpu, matmul_f64, rel_fro
+from skl_harness import GpuLayer, build_states_on_gpu, matmul_f64, rel_fro, worst_tile_rel_fro
 
 pytestmark = pytest.mark.gpu
 
@@ -189,6 +189,33 @@ def test_prompts_in_one_pass(in_f, out_f, d, widths, bits, tokens, x_dt, y_dt, l
         other = st.gemm(X, x_dt, y_dt, ldy=out_f + ldy_pad)
     for v in (y, other):
         assert np.isfinite(v.astype(np.float32)).all() and rel_fro(v, ref) <= tol, rel_fro(v, ref)
+
+
+@pytest.mark.parametrize("in_f,out_f,tokens,x_dt,y_dt,ldy_pad", [
+    (64, 600, 300, "bf16", "f32", 0),           # tiles of 128 outputs; one 64-channel block: fewer stages than the pipeline holds
+    (264, 3001, 600, "bf16", "bf16", 0),        # of 128; rows of Y not on 16-byte boundaries, ragged last tile and token tile
+    (200, 5700, 2000, "f16", "f16", 4),         # of 192
+    (128, 28672, 300, "bf16", "bf16", 0),       # of 224
+    (100, 20000, 520, "bf16", "f32", 0),        # of 256
+    (200, 8200, 2000, "bf16", "bf16", 0),       # of 320
+    (200, 11008, 2048, "bf16", "f32", 0),       # of 352: every CU one tile
+    (200, 12000, 2048, "f16", "bf16", 8),       # of 192, two tiles per workgroup
+])
+def test_whole_tiles_of_staged_prompts(in_f, out_f, tokens, x_dt, y_dt, ldy_pad):
+    """Every width of the whole-tile product, twice bit for bit, all outputs against a product in 64 bits."""
+    rng = np.random.default_rng(in_f + out_f + tokens)
+    A, C = hash_params(rng, 3)
+    K = np.where(rng.random(in_f) < 0.03, 24, 9).astype(np.uint32)
+    sk = oracle.Sketch(in_f, out_f, 1, out_f, 3, A, C, K, (rng.standard_normal(3 * int(K.sum())) * 0.02).astype(np.float16).view(np.uint16))
+    x = rng.standard_normal((tokens, in_f)).astype(np.float32)
+    X = wk.f32_to_bf16_bits(x) if x_dt == "bf16" else x.astype(np.float16).view(np.uint16)
+    ref = matmul_f64(oracle.query(sk), X if x_dt == "bf16" else X.view(np.float16), x_dt)
+    tol = SUM_TOL + {"f32": 0.0, "f16": 2.0**-11, "bf16": 2.0**-8}[y_dt]
+    with GpuLayer(sk, skl.FLAG_STAGED_PREFILL) as g:
+        y = g.gemm(X, x_dt, y_dt, ldy=out_f + ldy_pad)
+        assert np.array_equal(y, g.gemm(X, x_dt, y_dt, ldy=out_f + ldy_pad))
+    assert np.isfinite(y).all() and worst_tile_rel_fro(y, ref) <= 2 * tol, worst_tile_rel_fro(y, ref)
+    assert rel_fro(y, ref) <= tol, rel_fro(y, ref)
 
 
 @pytest.mark.parametrize("batch", [1, 2, 4, 5, 16])

@@ -256,10 +256,11 @@ def test_slabs_of_staged_calls_and_the_room_for_their_partials(tmp_path):
     assert r.returncode == 0, r.stdout
 
 
-def test_plans_of_one_pass_prompts(tmp_path):
-    exe = tmp_path / "prompt_plans"
+@pytest.mark.parametrize("name", ["prompt_plans", "wide_tiles"])
+def test_plans_of_one_pass_prompts_and_whole_tiles(name, tmp_path):
+    exe = tmp_path / name
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "paper_2506_17255_amd", "csrc"),
-                           os.path.join(ROOT, "tests", "sanitize", "prompt_plans.cpp"), "-o", str(exe)])
+                           os.path.join(ROOT, "tests", "sanitize", name + ".cpp"), "-o", str(exe)])
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout
 
