@@ -17,8 +17,8 @@
 // copies issued one by one between the arithmetic instead of as a burst behind the barrier (39 -> 33, it holds the
 // wavefronts up), chunks without bounds checks (33 -> 28), the products of a pair beside the query of the next one.
 // Whole call (packing 4 us, reduction 6): 17 tokens 45 -> 28 us, 64 46 -> 31, 100 50 -> 38 (59 -> 36 on inputs that are
-// not in the caches), 256 85 -> 64; 8192 x 8192 76 -> 34, 77 -> 38, 84 -> 45, 85 -> 72; 4096 x 4096 25 -> 18, 26 -> 21, 28
-// -> 24, 55 -> 31.
+// not in the caches), 256 88 -> 77; 8192 x 8192 17 tokens 76 -> 34, 64 77 -> 38, 100 84 -> 45; 4096 x 4096 25 -> 18, 26 -> 21,
+// 28 -> 24, 512 tokens 67 -> 56; 1024 x 2048, 300 tokens, 43 -> 20.
 namespace SKL_NS {
 
 struct PromptArgs {

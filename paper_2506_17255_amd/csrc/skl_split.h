@@ -293,7 +293,8 @@ struct PromptLayer {
 // 13 layer shapes (2 to 8 words per state row, d = 2 to 4) x 10 token counts; 5 % rms, and the plan it picks is 2 % slower
 // than the fastest one measured on average, 12 % at worst.  A block costs the larger of its copy into LDS and its
 // arithmetic plus 0.38 of the smaller; fewer than six wavefronts do not hide each other's latency.
-static inline PromptPlan skl_make_prompt_plan(const PromptLayer &L, uint32_t tokens, uint64_t room)
+// least: fewest block groups (the products of a group are one chain of float32 sums).
+static inline PromptPlan skl_make_prompt_plan(const PromptLayer &L, uint32_t tokens, uint64_t room, uint32_t least = 1)
 {
     PromptPlan best{};
     const uint32_t blocks16 = (tokens + 15) / 16;
@@ -306,8 +307,8 @@ static inline PromptPlan skl_make_prompt_plan(const PromptLayer &L, uint32_t tok
     for (uint32_t nw = 3; nw <= (rb >= 6 ? 8u : 12u); ++nw) {
         const uint32_t T = (units + nw - 1) / nw;
         const uint32_t one = 256 / (T * M);                      // groups that fill the chip once
-        for (const uint32_t P : {one, one * 2 / 3, one / 8 * 8, 512 / (T * M), 768 / (T * M), 1u}) {
-            if (P < 1 || P > std::min(L.n_blocks, 64u)) continue;
+        for (const uint32_t P : {one, one * 2 / 3, one / 8 * 8, 512 / (T * M), 768 / (T * M), least}) {
+            if (P < least || P > std::min(L.n_blocks, 64u)) continue;
             const uint64_t part = (uint64_t)M * T * P * rows * 2 * nw * 1024;
             if (pack + part > room) continue;
             const uint32_t per_group = (L.n_blocks + P - 1) / P, rounds = (T * M * P + 255) / 256;
