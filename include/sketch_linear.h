@@ -302,7 +302,7 @@ SKL_API skl_status_t sketch_linear_gemm(const skl_layer_t *layer, const void *X,
  * t * shares + s.  A slot holds the tokens of a tile x 256 outputs.  Staged
  * layers of more than 1 GiB of weight words are worked off in slabs of output
  * tiles, each split by itself.
- * Staged calls of more than 128 tokens in one slab take whole tiles of another
+ * Staged calls of more than 128 tokens in one slab may take whole tiles of another
  * width (256 tokens x 128 to 352 outputs) instead where those fit the chip
  * better; this listing then shows the split that such a call would have with
  * tiles of 256 outputs.

@@ -336,11 +336,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // of a stage only the activation words are held twice; weight words are read two or three columns (of 16 outputs) ahead of
 // their products, into registers that the column before has left.  A stage's buffer is therefore read until its last
 // column, and the copies issued during a stage go to the buffer of the stage before it.
+// CHAINS: the products of an output go through several chains of float32 sums, one after the other, where shared tiles would
+// have had as many.  Narrow tiles keep the sum of the earlier chains in as many registers as the accumulators, wider ones,
+// which have none left, write the first chain of some columns to the workspace and read it back at the end: 4096 x 11008, 5 of
+// 11 columns, 167 -> 176 us for the whole call, 8192 x 28672, 2 of 10, 812 -> 827.
 struct WideArgs {
     const uint4 *Xp;                    // activation words: [256-token tile][32-channel step][SG_STEP_WORDS]
     const uint4 *Wp;                    // weight words: [output tile][32-channel step][2 * CB blocks of 16 outputs][64]
     void *Y;
+    float *parts;                       // [workgroup][wavefront][column][64-token quarter][64 lanes] x 4: first chains
     uint32_t KB, tokens, out, y_dt, ldy, rows_aligned;
+    uint32_t chains, split, body;       // of skl_make_wide_split
     G3Split sp;
 };
 
@@ -356,9 +362,10 @@ __device__ __forceinline__ void wide_store(const float4v (&acc)[4][CB], uint32_t
     }
 }
 
-template <int CB>
+template <int CB, bool CHAINS>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_staged_wide(WideArgs p)
 {
+    constexpr bool HELD = CHAINS && CB <= (int)SW_HELD_CB;
     constexpr uint32_t A_BYTES = 16384, ST_BYTES = SW_STAGE_BYTES(CB), NS = SW_STAGES(CB), LOOK = CB % 4 == 2 ? 2 : 3;     // (words of the next columns in registers)
     constexpr int PER = (16 + 2 * CB + 7) / 8;
     static_assert(CB % 4 == 0 || CB % 4 == (int)LOOK, "the words read ahead of the next stage land in free registers");
@@ -371,7 +378,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const uint32_t lds_wave = lds0 + wave * 1024, a_off = wave * 1024 + lane * 16;
     // the last copy of a stage repeats its last KiB where the pieces do not divide out
     const uint32_t last_b = min(wave + 8 * (PER - 3), 2u * CB - 1) * 1024;
-    float4v acc[4][CB];
+    float4v acc[4][CB], sum[HELD ? 4 : 1][HELD ? CB : 1];
+    float4v *const part = CHAINS && !HELD ? reinterpret_cast<float4v *>(p.parts) + (size_t)(blockIdx.x * 8 + wave) * p.split * 256 : nullptr;
     for (uint32_t k = wg; k < sp.tiles_of(xcd); k += 32) {
         uint32_t tile_m, tile_n;
         sp.tile_of(xcd, k, tile_m, tile_n);
@@ -445,14 +453,54 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             into = from;
             from = nxt;
         };
-        for (uint32_t st = 0; st < n_st; st += 2) {             // (n_st is even: two stages per 64-channel block)
-            stage(st, c0);
-            stage(st + 1, c1);
+        if constexpr (!CHAINS) {
+            for (uint32_t st = 0; st < n_st; st += 2) {         // (n_st is even: two stages per 64-channel block)
+                stage(st, c0);
+                stage(st + 1, c1);
+            }
+        } else {
+            uint32_t st = 0;
+            for (uint32_t i = 1; i <= p.chains + HELD; ++i) {
+                for (const uint32_t end = i <= p.chains ? i * p.body / p.chains * 2 : n_st; st < end; st += 2) {
+                    stage(st, c0);
+                    stage(st + 1, c1);
+                }
+                if constexpr (HELD) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int c = 0; c < CB; ++c) {
+                            if (i <= p.chains) sum[r][c] = i == 1 ? acc[r][c] : sum[r][c] + acc[r][c];
+                            if (i < p.chains) acc[r][c] = (float4v){0.f, 0.f, 0.f, 0.f};
+                            if (i == p.chains) acc[r][c] = sum[r][c];
+                        }
+                } else if (i < p.chains) {                      // (the stores only make the next waits for copies longer)
+                    uint32_t ln = lane;
+                    asm volatile("" : "+v"(ln));
+#pragma unroll
+                    for (int c = 0; c < CB; ++c)
+                        if ((uint32_t)c < p.split) {
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                part[(c * 4 + r) * 64 + ln] = acc[r][c];
+                                acc[r][c] = (float4v){0.f, 0.f, 0.f, 0.f};
+                            }
+                        }
+                }
+            }
         }
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __syncthreads();                                        // nothing on its way into LDS, nobody reads it: the epilogue may use it
         uint32_t ln = lane;
         asm volatile("" : "+v"(ln));
+        if constexpr (CHAINS && !HELD) {
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+                if ((uint32_t)c < p.split) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[r][c] += part[(c * 4 + r) * 64 + ln];
+                }
+        }
         const uint32_t t0 = tile_m * GM_MT + wm * 64, o0 = tile_n * (CB * 32) + wn * (CB * 16);
         if (p.rows_aligned) {
             const uint32_t lw = lds0 + wave * SG_EPI_BYTES;
@@ -560,10 +608,13 @@ static skl_status_t launch_wide(const WideArgs &g, hipStream_t stream)
 {
     constexpr size_t lds = SW_STAGES(CB) * SW_STAGE_BYTES(CB);
     static_assert(lds >= 8 * SG_EPI_BYTES && lds <= SKL_LDS_HARD_BYTES, "the epilogue has to fit the stages' LDS");
-    const skl_status_t st = allow_lds(k_staged_wide<CB>, lds);
-    if (st != SKL_OK) return st;
-    hipLaunchKernelGGL((k_staged_wide<CB>), dim3(256), dim3(512), lds, stream, g);
-    return check_launch("staged gemm, whole tiles");
+    auto launch = [&](auto kernel) {
+        const skl_status_t st = allow_lds(kernel, lds);
+        if (st != SKL_OK) return st;
+        hipLaunchKernelGGL(kernel, dim3(256), dim3(512), lds, stream, g);
+        return check_launch("staged gemm, whole tiles");
+    };
+    return g.chains > 1 ? launch(k_staged_wide<CB, true>) : launch(k_staged_wide<CB, false>);
 }
 
 skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx,
@@ -583,16 +634,18 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
     skl_status_t st = SKL_OK;
     // (all output tiles in one slab; the split is the call's only one then)
     const uint64_t w_room = staged_part_bytes(L, tokens) + (uint64_t)slab_cols * KB * SG_SLOT_BYTES;
-    G3Split wide{};
-    const uint32_t wide_cb = tokens > SKL_SHORT_TOKENS && slab_cols == n_col ? skl_make_wide_split(L->out, KB, tokens, w_room, wide) : 0;
-    if (wide_cb) Wp = reinterpret_cast<uint4 *>(static_cast<char *>(ws) + round256(staged_pack_bytes(L, tokens)));      // no partial tiles: their room holds weight words
+    WideSplit wide{};
+    if (tokens > SKL_SHORT_TOKENS && slab_cols == n_col) wide = skl_make_wide_split(L->out, KB, tokens, w_room);
+    const uint32_t wide_cb = wide.cb;
+    // no partial tiles: their room holds the first chains and weight words
+    if (wide_cb) Wp = reinterpret_cast<uint4 *>(static_cast<char *>(ws) + round256(staged_pack_bytes(L, tokens)) + skl_wide_part_bytes(wide));
     for (uint32_t tile0 = 0; tile0 < n_col; tile0 += slab_cols) {
-        const uint32_t cols = wide_cb ? (wide.n_col * wide_cb + 7) / 8 : std::min(slab_cols, n_col - tile0);
+        const uint32_t cols = wide_cb ? (wide.sp.n_col * wide_cb + 7) / 8 : std::min(slab_cols, n_col - tile0);
         RebuildArgs r;
         r.h = a.h; r.bmeta = a.bmeta; r.tables = src.tables; r.Wp = Wp;
         r.out = L->out; r.n_blocks = L->n_blocks; r.KB = KB; r.n_words = L->n_packed / 8;
         r.tile0 = tile0; r.n_col = cols;
-        r.tb = wide_cb ? 2 * wide_cb : 16; r.n_tb = wide_cb ? wide.n_col * 2 * wide_cb : 16 * cols;
+        r.tb = wide_cb ? 2 * wide_cb : 16; r.n_tb = wide_cb ? wide.sp.n_col * 2 * wide_cb : 16 * cols;
         // Output segments per channel block: two, or as many as make 128 workgroups.  More segments stage every table
         // more often and gain nothing (the activation workgroups behind them fill the rest of the chip): launch time by
         // segments, 2048 tokens, 4096 x 11008 (67 blocks) 2 28.2 us, 4 29.6, 8 31.5; 8192 x 28672 (518) 2 105.8, 4
@@ -610,7 +663,8 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
         if (st != SKL_OK) return st;
 
         if (wide_cb) {
-            const WideArgs g{Xp, Wp, Y, KB, tokens, L->out, (uint32_t)y_dt, ldy, ((size_t)ldy * (y_dt == SKL_F32 ? 4 : 2)) % 16 == 0, wide};
+            const WideArgs g{Xp, Wp, Y, parts, KB, tokens, L->out, (uint32_t)y_dt, ldy, ((size_t)ldy * (y_dt == SKL_F32 ? 4 : 2)) % 16 == 0,
+                             wide.chains, wide.split, wide.body, wide.sp};
             return wide_cb == 6 ? launch_wide<6>(g, stream) : wide_cb == 7 ? launch_wide<7>(g, stream) : wide_cb == 8 ? launch_wide<8>(g, stream)
                  : wide_cb == 10 ? launch_wide<10>(g, stream) : wide_cb == 4 ? launch_wide<4>(g, stream) : launch_wide<11>(g, stream);
         }

@@ -227,35 +227,127 @@ static inline uint64_t skl_staged_part_floats(uint32_t out, uint32_t kb, uint32_
     return most;
 }
 
+// ---- rounding of float32 sums ----
+// A chain of l blocks rounds a sum of 1, 2 .. 2 l products (of 32 channels), and adding up chains rounds their sums so far:
+// the variance of an output's error, over that of rounding its last product, is about the sum of l^2 over the chains, plus
+// the blocks summed so far per addition, over the blocks of the tile.  This is the mean over the outputs of a split, for
+// products of like size; its root is within 4 % of the errors measured on channels of equal width.
+static inline double skl_split_chain(const G3Split &sp)
+{
+    double total = 0, shared = 0;
+    for (uint32_t x = 0; x < 8; ++x) {
+        const uint32_t left = sp.left(x);
+        total += (double)(sp.tiles_of(x) - left) * sp.nb * sp.nb;
+        if (!x || left != sp.left(x - 1)) {                     // (neighbours mostly share alike)
+            shared = 0;
+            for (uint32_t j = 0; left && j < sp.sharers(x); ++j)
+                for (uint32_t u = sp.share_begin(x, j), end = sp.share_begin(x, j + 1); u < end;) {
+                    const uint32_t k = u % sp.nb, n = std::min(end - u, sp.nb - k);
+                    shared += (double)n * n + (k ? k + n : 0);
+                    u += n;
+                }
+        }
+        total += shared;
+    }
+    return total / ((double)sp.T * sp.nb);
+}
+// Blocks past the last addition of chains where a whole tile is made of several: the channels of the widest sketches, which
+// carry most of the result, come last, and an addition behind them would round the whole of it.
+static inline uint32_t skl_wide_tail(uint32_t nb) { return (nb + 63) / 64; }
+// The same measure for n equal chains in a row over all but the last blocks, which the sum of them goes through.
+static inline double skl_wide_chain(uint32_t nb, uint32_t n, uint32_t tail)
+{
+    const uint32_t body = nb - tail;
+    double total = (double)tail * (2 * body + tail);
+    for (uint32_t i = 0; i < n; ++i) {
+        const uint32_t end = (i + 1) * body / n, l = end - i * body / n;
+        total += (double)l * l + (i ? end : 0);
+    }
+    return total / nb;
+}
+
 // Whole tiles of another width instead: 256 tokens x 32 * cb outputs, one tile after another per workgroup (the k-th of XCD
-// x by workgroup k % 32), no partial tiles, no fix-up.  Returns cb, or 0 where the split above is estimated to be no slower
-// or the weight words do not fit `room`.  The estimates, in us: a 64-channel block of a 256 x 256 tile on every CU takes 1.52
-// (f[cb] per such area; narrow tiles read more operand words from LDS per product), a round of tiles 5 to 8 more for its
-// start and its stores, a partial tile 0.12 to write and read; a round that leaves CUs idle runs at a higher clock.  Whole
-// calls, split above / tiles by cb (2048 tokens unless said): 4096 x 11008 212 us / 4 188, 6 182, 8 198, 11 165; 4096 x 4096
-// 81 / 4 74.5; 2048 x 5632 104 / 4 66, 6 55, 8 58; 3000 x 7001 164 / 7 90, 8 97; 1024 x 2048 41 / 4 22; 8192 x 28672 830 / 4
-// 900, 7 829, 8 835, 10 801, 11 834; 4096 x 11008, 777 tokens, 164 / 6 95, 8 99; 8192 x 3000, 1300 tokens, 143 / 4 110.
-static inline uint32_t skl_make_wide_split(uint32_t out, uint32_t nb, uint32_t tokens, uint64_t room, G3Split &best)
+// x by workgroup k % 32), no partial tiles, no fix-up.  An output of a shared tile is the sum of several chains of products,
+// one of a whole tile would be a single chain with up to three times the rounding error (4096 x 2048, 600 tokens, channels
+// of equal width: 1.4e-7 in eleven chains, 4.1e-7 in one).  So the first `split` of a wavefront's cb columns of outputs
+// go through `chains` chains, one after the other, as many as keep the measure above at that of the shared tiles.
+// Where those are whole as well, one chain does.
+struct WideSplit {
+    G3Split sp;
+    uint32_t cb, chains, split;         // cb 0: shared tiles
+    uint32_t body;                      // blocks that the chains divide; their sum goes through the rest
+    double us;                          // estimated time of the product
+};
+#define SW_HELD_CB 6u                   // up to this width the sums of the earlier chains are held in registers
+// Bytes of workspace for the first chains of `split` columns, wider tiles: 256 workgroups x 8 wavefronts x 4 KiB each.
+static inline uint64_t skl_wide_part_bytes(const WideSplit &w) { return w.cb > SW_HELD_CB ? (uint64_t)w.split << 23 : 0; }
+
+// cb is 0 where the split above is estimated to be no slower, or weight words and first chains do not fit `room`.
+// The estimates of the product, in us: a 64-channel block of a 256 x 256 tile on every CU takes 1.52 (f[cb] per such area;
+// narrow tiles read more operand words from LDS per product), 2.2 in a share of a tile; a round of tiles 5 to 8 more for its
+// start and its stores; a partial tile 0.05 to write and read; a further chain 0.16 per column held in registers, 1 per
+// column and 2 per round through memory; a round that leaves CUs idle runs at a higher clock.
+// Whole calls, shared tiles / whole ones by cb, in one chain, then as they run (2048 tokens unless said): 4096 x 11008 224 /
+// 4 188, 6 182, 8 198, 11 167, 172 us; 4096 x 4096 81 / 4 76; 2048 x 5632, 1500 tokens, 75 / 6 53, 57; 1024 x 2048 42 / 4 28, 30;
+// 3000 x 7001, 1024 tokens, 95 / 4 60, 64; 8192 x 28672 852 / 4 900, 6 829, 8 835, 10 812, 827, 11 834; 4096 x 11008, 777
+// tokens, 164 / 6 102, 105; 8192 x 3000, 1300 tokens, 136 / 4 110, 111; 4096 x 2048, 600 tokens, 49 / 4 53, 61 in twelve chains.
+static inline WideSplit skl_make_wide_split(uint32_t out, uint32_t nb, uint32_t tokens, uint64_t room)
 {
     const G3Split old = skl_make_split(out, nb, tokens, true);
-    double blocks = 0;
+    const double longest = skl_split_chain(old) * (1 + 1e-9);
+    double whole = 0, shared = 0;
     uint32_t slots = 0, rounds = 1;
     for (uint32_t x = 0; x < 8; ++x) {
-        blocks = std::max(blocks, old.rounds(x) * nb * (old.mt < GM_MT ? 0.6 : 1.0) + (double)old.units(x) / old.gx);
+        whole = std::max(whole, old.rounds(x) * nb * (old.mt < GM_MT ? 0.6 : 1.0));
+        shared = std::max(shared, (double)old.units(x) / old.gx);
         rounds = std::max(rounds, old.rounds(x));
         for (uint32_t l = 0; l < old.left(x); ++l) slots += old.parts(x, l);
     }
-    double limit = 1.52 * blocks + 8.0 * rounds + (slots ? 10.0 + 0.12 * slots : 0.0);
-    uint32_t pick = 0;
+    WideSplit best{};
+    best.us = 1.52 * whole + 2.2 * shared + 8.0 * rounds + (slots ? 6.0 + 0.05 * slots : 0.0);
     const struct { uint32_t cb; double f; } widths[] = {{11, 1.486}, {10, 1.49}, {8, 1.52}, {7, 1.59}, {6, 1.62}, {4, 1.77}};
     for (const auto &w : widths) {
-        G3Split sp{};
+        WideSplit c{};
+        G3Split &sp = c.sp;
+        c.cb = w.cb;
         sp.n_col = (out + 32 * w.cb - 1) / (32 * w.cb);
         sp.nb = nb; sp.mt = GM_MT; sp.single = 1; sp.gx = 32;
         sp.m_tiles = (tokens + GM_MT - 1) / GM_MT;
         sp.T = sp.m_tiles * sp.n_col;
-        if ((uint64_t)sp.n_col * nb * w.cb * 4096 > room) continue;
         rounds = ((sp.T + 7) / 8 + 31) / 32;
+        c.chains = 1;
+        c.body = nb;
+        double more = 0;
+        if (nb <= longest) {
+        } else if (w.cb <= SW_HELD_CB) {
+            // (where every tile is shared, all outputs have had an addition behind the last block)
+            bool found = false;
+            for (const uint32_t tail : {skl_wide_tail(nb), 0u}) {
+                if (found || (!tail && whole > 0)) break;
+                c.body = nb - tail;
+                double before = nb;
+                for (c.chains = 2; c.chains <= c.body; ++c.chains) {
+                    const double now = skl_wide_chain(nb, c.chains, tail);
+                    found = now <= longest;
+                    if (found || now >= before) break;          // (past the least the additions outweigh what they shorten)
+                    before = now;
+                }
+            }
+            if (!found) continue;
+            c.split = w.cb;
+            more = 0.16 * w.cb * c.chains * rounds;
+        } else {
+            // The two chains are added at the end, where that rounds the whole result: counted like five products, and
+            // only where the chains are long (512 x 28672, 2048 tokens, nine blocks, one percent of wide channels: 3.58e-8
+            // in two chains, 3.43e-8 in one; shared tiles 3.54e-8).
+            if (nb < 32) continue;
+            const double one = nb, two = skl_wide_chain(nb, 2, 0) + 4.0;
+            c.chains = 2;
+            c.split = (uint32_t)(w.cb * (one - longest) / (one - two)) + 1;
+            if (c.split > w.cb) continue;
+            more = (2.0 + c.split) * rounds;
+        }
+        if ((uint64_t)sp.n_col * nb * w.cb * 4096 + skl_wide_part_bytes(c) > room) continue;
         for (uint32_t mu = sp.m_tiles; mu >= 1; mu /= 2) {      // the largest dealing unit that needs no further round
             if (sp.m_tiles % mu) continue;
             sp.mu = mu;
@@ -263,14 +355,10 @@ static inline uint32_t skl_make_wide_split(uint32_t out, uint32_t nb, uint32_t t
             for (uint32_t x = 0; x < 8; ++x) most = std::max(most, sp.tiles_of(x));
             if ((most + 31) / 32 <= rounds) break;
         }
-        const double t = (0.6 * rounds + 0.4 * sp.T / 256.0) * nb * w.cb / 8.0 * w.f + 5.0 * rounds;
-        if (t < limit) {
-            limit = t;
-            best = sp;
-            pick = w.cb;
-        }
+        c.us = (0.6 * rounds + 0.4 * sp.T / 256.0) * nb * w.cb / 8.0 * w.f + 5.0 * rounds + more;
+        if (c.us < best.us) best = c;
     }
-    return pick;
+    return best;
 }
 
 // ---- short prompts in one pass ----

@@ -1,5 +1,6 @@
 // Whole-tile splits of staged calls over random layers, token counts and workspaces: every tile of the call belongs to one
-// workgroup and round, the tiles cover the outputs and their weight words fit the room.  Host only; prints the first violation.
+// workgroup and round, the tiles cover the outputs, their weight words and first chains fit the room, and the float32 sums
+// are rounded no more than those of the shared tiles they replace.  Host only; prints the first violation.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -14,19 +15,63 @@
         }                                                                                                                    \
     } while (0)
 
+// Squares of the roundings' sizes of one output, in products, over the last one's: chains of the given blocks (two products
+// each), added up in order after `tail` further blocks have gone into the last chain, or before them (merged).
+static double roundings(const std::vector<uint32_t> &chains, uint32_t tail, uint32_t nb)
+{
+    double sum = 0, so_far = 0;
+    for (size_t i = 0; i < chains.size(); ++i) {
+        for (uint32_t k = 1; k <= 2 * chains[i]; ++k) sum += k;
+        so_far += 2 * chains[i];
+        if (i) sum += so_far;
+    }
+    for (uint32_t k = 1; k <= 2 * tail; ++k) sum += so_far + k;
+    return sum / (2.0 * nb);
+}
+
+// The mean over the outputs of the shared-tile split, by walking it as the kernel does.
+static double shared_roundings(const G3Split &sp)
+{
+    std::vector<std::vector<uint32_t>> tiles(sp.T);
+    for (uint32_t x = 0; x < 8; ++x)
+        for (uint32_t wg = 0; wg < sp.gx; ++wg) {
+            uint32_t round = 0, u = sp.share_begin(x, wg);
+            G3Split::Seg sg;
+            while (sp.next(x, wg, round, u, sg)) {
+                uint32_t tm, tn;
+                sp.tile_of(x, sg.k, tm, tn);
+                tiles[(size_t)tn * sp.m_tiles + tm].push_back(sg.k1 - sg.k0);
+            }
+        }
+    double sum = 0;
+    for (const auto &t : tiles) sum += roundings(t, 0, sp.nb);
+    return sum / sp.T;
+}
+
 int main()
 {
-    uint64_t s = 88172645463325252ull, seen[12] = {};
+    uint64_t s = 88172645463325252ull, seen[12] = {}, divided[12] = {};
     auto rnd = [&](uint32_t lo, uint32_t hi) { s ^= s << 13; s ^= s >> 7; s ^= s << 17; return lo + (uint32_t)(s % (hi - lo + 1)); };
     for (uint32_t n = 0; n < 20000; ++n) {
         const uint32_t out = rnd(0, 3) ? rnd(1, 12000) : rnd(1, 60000), nb = rnd(1, 200), tokens = rnd(129, 4200);
         const uint64_t room = rnd(0, 3) ? ~0ull : (uint64_t)rnd(1, 60000) << rnd(0, 14);
-        G3Split sp{};
-        const uint32_t cb = skl_make_wide_split(out, nb, tokens, room, sp);
+        const WideSplit w = skl_make_wide_split(out, nb, tokens, room);
+        const G3Split &sp = w.sp;
+        const uint32_t cb = w.cb;
         CHECK(cb == 0 || cb == 4 || cb == 6 || cb == 7 || cb == 8 || cb == 10 || cb == 11);
         ++seen[cb];
         if (!cb) continue;
-        CHECK((uint64_t)sp.n_col * nb * cb * 4096 <= room);
+        CHECK((uint64_t)sp.n_col * nb * cb * 4096 + skl_wide_part_bytes(w) <= room);
+        CHECK(w.chains >= 1 && w.chains <= w.body && w.body <= nb && (w.chains > 1) == (w.split > 0));
+        CHECK(cb <= SW_HELD_CB ? w.split == 0 || w.split == cb : w.split <= cb && w.chains <= 2 && w.body == nb);
+        CHECK(skl_wide_part_bytes(w) == (cb <= SW_HELD_CB ? 0ull : 256ull * 8 * w.split * 4 * 64 * 16));
+        std::vector<uint32_t> chains;
+        for (uint32_t i = 0; i < w.chains; ++i) chains.push_back((i + 1) * w.body / w.chains - i * w.body / w.chains);
+        const double one = roundings({nb}, 0, nb), more = roundings(chains, nb - w.body, nb);
+        const uint32_t many = w.chains > 1 ? w.split : cb;
+        // (0.5 / nb of the measure: a chain of l blocks is counted as l^2, not l^2 + l / 2)
+        CHECK((many * more + (cb - many) * one) / cb <= shared_roundings(skl_make_split(out, nb, tokens, true)) + 0.5);
+        divided[cb] += w.chains > 1;
         CHECK(sp.n_col * cb * 32 >= out && (sp.n_col - 1) * cb * 32 < out);
         CHECK(sp.m_tiles * 256 >= tokens && (sp.m_tiles - 1) * 256 < tokens);
         std::vector<uint8_t> done((size_t)sp.n_col * sp.m_tiles, 0);
@@ -43,6 +88,11 @@ int main()
     for (uint32_t cb : {0u, 4u, 6u, 7u, 8u, 10u, 11u})
         if (seen[cb] < 20) {
             printf("width %u chosen %llu times only\n", cb, (unsigned long long)seen[cb]);
+            return 1;
+        }
+    for (uint32_t cb : {4u, 6u, 7u, 8u, 10u, 11u})
+        if (divided[cb] < 20 || (cb == 4 && seen[cb] - divided[cb] < 20)) {
+            printf("width %u in several chains %llu of %llu times\n", cb, (unsigned long long)divided[cb], (unsigned long long)seen[cb]);
             return 1;
         }
     return 0;

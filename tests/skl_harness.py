@@ -3,12 +3,16 @@ called through its C ABI binding, the oracle provides sketches and expected
 values.  Nothing here computes any step of the method."""
 from __future__ import annotations
 
+import os
+import subprocess
+
 import numpy as np
 
 import oracle
 import paper_2506_17255_amd as skl
 import workloads as wk
 
+_ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 DT = {"f16": skl.SKL_F16, "bf16": skl.SKL_BF16, "f32": skl.SKL_F32}
 
 
@@ -227,3 +231,41 @@ def oracle_stack_layer(index: int):
     W_hat = oracle.query(sk)
     y = oracle.linear(W_hat, wk.gen_x(wl, 1))
     return index, sk, hashlib.sha1(np.ascontiguousarray(W_hat).tobytes()).hexdigest(), y
+
+
+# Staged calls of more than 128 tokens on layers of equal widths: in and out features, tokens, type of Y, padding of its rows,
+# and the way they go: whole tiles of 32 x width outputs and the chains of sums in them, shared tiles (with a fix-up pass), or
+# one whole tile of 128 tokens per workgroup.
+STAGED_ROUTES = [
+    (128, 17408, 257, "f16", 0, ("whole", 6, 1)),
+    (128, 19712, 275, "bf16", 0, ("whole", 7, 1)),
+    (128, 19448, 272, "f32", 0, ("whole", 8, 1)),
+    (128, 22217, 524, "bf16", 3, ("whole", 10, 1)),
+    (128, 27513, 517, "f32", 3, ("whole", 11, 1)),
+    (512, 512, 132, "f32", 0, ("whole", 4, 2)),             # added up behind the last block
+    (2048, 600, 550, "f32", 0, ("whole", 4, 7)),            # before it
+    (2048, 600, 1050, "f32", 1, ("whole", 4, 7)),
+    (256, 3122, 4100, "bf16", 0, ("whole", 4, 2)),          # several tiles per workgroup
+    (256, 18062, 260, "f16", 2, ("whole", 6, 2)),
+    (2048, 4868, 1550, "f32", 0, ("whole", 6, 3)),
+    (2048, 7972, 1550, "f32", 0, ("whole", 7, 2)),          # the first chains through memory
+    (2048, 8069, 1550, "f32", 3, ("whole", 8, 2)),
+    (2048, 22528, 546, "f32", 0, ("whole", 10, 2)),
+    (2112, 7681, 4100, "f32", 0, ("whole", 10, 2)),         # several tiles per workgroup
+    (2048, 28362, 516, "f32", 0, ("whole", 11, 2)),
+    (256, 514, 525, "f32", 0, ("shared", 0, 0)),
+    (2112, 600, 150, "f32", 5, ("shared", 0, 0)),
+    (5184, 1140, 155, "bf16", 0, ("shared", 0, 0)),
+    (192, 28672, 300, "f16", 4, ("shared", 0, 0)),
+    (512, 20480, 267, "f32", 0, ("half", 0, 0)),
+    (512, 20477, 267, "bf16", 0, ("half", 0, 0)),
+]
+
+
+def staged_routes(shapes, tmp_path):
+    """(kind, width, chains, measure of rounding of the shared split) of staged calls: 64-channel blocks, outputs, tokens."""
+    exe = tmp_path / "staged_route"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(_ROOT, "paper_2506_17255_amd", "csrc"),
+                           os.path.join(_ROOT, "tests", "sanitize", "staged_route.cpp"), "-o", str(exe)])
+    lines = subprocess.run([str(exe), *[str(v) for s in shapes for v in s]], capture_output=True, text=True, check=True).stdout.splitlines()
+    return [(k, int(cb), int(n), float(m)) for k, cb, n, m in map(str.split, lines)]

@@ -6,7 +6,7 @@ import pytest
 import oracle
 import paper_2506_17255_amd as skl
 import workloads as wk
-from skl_harness import GpuLayer, build_states_on_gpu, matmul_f64, rel_fro, worst_tile_rel_fro
+from skl_harness import STAGED_ROUTES, GpuLayer, build_states_on_gpu, matmul_f64, rel_fro, staged_routes, worst_tile_rel_fro
 
 pytestmark = pytest.mark.gpu
 
@@ -216,6 +216,38 @@ def test_whole_tiles_of_staged_prompts(in_f, out_f, tokens, x_dt, y_dt, ldy_pad)
         assert np.array_equal(y, g.gemm(X, x_dt, y_dt, ldy=out_f + ldy_pad))
     assert np.isfinite(y).all() and worst_tile_rel_fro(y, ref) <= 2 * tol, worst_tile_rel_fro(y, ref)
     assert rel_fro(y, ref) <= tol, rel_fro(y, ref)
+
+
+@pytest.mark.parametrize("in_f,out_f,tokens,y_dt,ldy_pad,way", STAGED_ROUTES)
+def test_ways_of_staged_prompts(in_f, out_f, tokens, y_dt, ldy_pad, way, tmp_path):
+    """Every way of a staged call over a dirty workspace: all outputs against a product in 64 bits, rounded no more than
+    the sums of shared tiles are, whatever the way."""
+    t = __import__("torch")
+    rng = np.random.default_rng(in_f + out_f + tokens)
+    A, C = hash_params(rng, 2)
+    K = np.full(in_f, 9, dtype=np.uint32)
+    sk = oracle.Sketch(in_f, out_f, 1, out_f, 2, A, C, K, (rng.standard_normal(2 * int(K.sum())) * 0.02).astype(np.float16).view(np.uint16))
+    X = wk.f32_to_bf16_bits(rng.standard_normal((tokens, in_f)).astype(np.float32))
+    (kind, cb, chains, measure), = staged_routes([((in_f + 63) // 64, out_f, tokens)], tmp_path)
+    assert (kind, cb, chains) == way
+    with GpuLayer(sk, skl.FLAG_STAGED_PREFILL) as g:
+        ws, _ = g.workspace(1, tokens)
+        ws.fill_(0xFF)
+        y = t.from_numpy(g.gemm(X, "bf16", y_dt, ldy=out_f + ldy_pad)).cuda().double()
+        ws.fill_(0xFF)
+        again = t.from_numpy(g.gemm(X, "bf16", y_dt, ldy=out_f + ldy_pad)).cuda().double()
+        ref = t.from_numpy(wk.bf16_bits_to_f32(X)).cuda().double() @ t.from_numpy(oracle.query(sk).view(np.float16)).cuda().double()
+    assert bool((y == again).all()) and bool(t.isfinite(y).all())
+    # the measure is the variance of the roundings of products of like size over that of one, which is at most 2^-24 of the
+    # sum in root mean square; one more for the rounding of the result, then that to a shorter type
+    tol = 2.0**-24 * (measure + 1) ** 0.5 + {"f32": 0.0, "f16": 2.0**-11, "bf16": 2.0**-8}[y_dt]
+    err = float((y - ref).norm() / ref.norm())
+    assert err <= tol, (err, tol)
+    for t0 in range(0, tokens, 128):                            # no wrong tile hides in the norm of the whole
+        d, r = (y - ref)[t0:t0 + 128], ref[t0:t0 + 128]
+        pad = -out_f % 32
+        d, r = (t.nn.functional.pad(v, (0, pad)).reshape(len(v), -1, 32).square().sum((0, 2)) for v in (d, r))
+        assert float((d / r).max()) <= (2 * tol) ** 2, (t0, int((d / r).argmax()))
 
 
 @pytest.mark.parametrize("batch", [1, 2, 4, 5, 16])

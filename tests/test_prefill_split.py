@@ -13,6 +13,7 @@ import subprocess
 import pytest
 
 import paper_2506_17255_amd as skl
+from skl_harness import STAGED_ROUTES, staged_routes
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -263,6 +264,12 @@ def test_plans_of_one_pass_prompts_and_whole_tiles(name, tmp_path):
                            os.path.join(ROOT, "tests", "sanitize", name + ".cpp"), "-o", str(exe)])
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout
+
+
+def test_ways_of_staged_calls_that_the_gpu_tests_rely_on(tmp_path):
+    got = staged_routes([((n_in + 63) // 64, n_out, tokens) for n_in, n_out, tokens, *_ in STAGED_ROUTES], tmp_path)
+    for case, (kind, cb, chains, _) in zip(STAGED_ROUTES, got):
+        assert (kind, cb, chains) == case[-1], case
 
 
 def test_argument_errors():
