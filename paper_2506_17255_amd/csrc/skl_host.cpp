@@ -360,6 +360,18 @@ static void plan_prefill(const skl_desc_t *d, skl_plan *P)
     // staged kernel: dense 32-entry steps along the channel list, two per 64-channel block (entries past the end of
     // the list are empty: zero activation words), and the windows of X that the packing kernel stages
     L.gemm_kb = (L.n_packed + 63) / 64;
+    // channels of at least twice the median width carry most of the result: the rounding of sums is planned for them
+    // where they are few (at most one in sixteen)
+    const auto width = [&](uint32_t e) { return d->group_width[P->chan[e]]; };
+    uint32_t median = 0, first_wide = L.n_packed, n_wide = 0;
+    for (uint32_t e = 0, n = 0; e < L.n_packed; ++e) {
+        if (P->chan[e] == SKL_NO_CHANNEL) continue;
+        if (n++ == L.in / 2) median = width(e);
+        if (!median || width(e) / 2 < median) continue;
+        first_wide = std::min(first_wide, e);
+        ++n_wide;
+    }
+    L.gemm_tail = n_wide && n_wide <= L.in / 16 && first_wide >= 64 ? L.gemm_kb - first_wide / 64 : 0;
     P->windows.clear();
     for (uint32_t e0 = 0; e0 < 64 * L.gemm_kb; e0 += 32 * PO_STEPS) {
         uint32_t lo = SKL_NO_CHANNEL, hi = 0;

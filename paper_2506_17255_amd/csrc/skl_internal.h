@@ -124,6 +124,7 @@ struct skl_layer {
     // list, and the windows of X that hold the channels of PO_STEPS steps of 32 list entries
     uint32_t gemm_staged_from = 0, gemm_kb = 0;     // calls with at least gemm_staged_from tokens are staged,
     uint32_t gemm_short_to = 0;                     // and those with at most gemm_short_to
+    uint32_t gemm_tail = 0;                         // last 64-channel blocks: those with wide channels, where these are few
     uint64_t off_windows = 0;
     // prompts in one pass: allowed (the library chooses the kernel, and every padded table fits a table buffer); 32-channel
     // steps of all blocks

@@ -465,32 +465,36 @@ uint64_t skl_gemm_workspace_bytes(const skl_layer *L, uint32_t tokens, bool stag
 // Whether a call the library may choose the kernel for takes the one-pass kernel (`plan`) instead of the staged or the
 // fused one, in the room those ask for: by the estimated times.  The other two are lines through measured whole calls: a
 // staged one by the MB of dense weights it writes and reads (dearer beyond the caches) and its tokens, a fused one 44 us +
-// 2.6 us per channel block of the busiest workgroup.  Layers that stay fused at up to SKL_SHORT_TOKENS tokens (workspaces without room for the dense weights,
-// eight-word layers beyond the memory-side cache) stay so.  One pass / the other, us: 4096 x 11008, d = 4: 17 tokens 27 / 45
-// (staged), 64 31 / 46, 100 38 / 50, 256 77 / 88 (fused); 4096 x 4096: 17 / 25, 20 / 25, 24 / 28, 512 tokens 56 / 67; 8192 x
-// 8192: 33 / 76, 38 / 77, 46 / 84; four-word blocks (4096 x 11008, 0.75 bit): 32 / 43, 36 / 44, 48 / 48, 384 tokens 129 /
-// 177; two-word (8192 x 28672, d = 3): 180 / 229, 198 / 233, 320 / 234.  Beside the fused kernel the call takes as many block
-// groups as keep a chain of float32 sums no longer than that kernel's: with fewer, 4096 x 11008 at 256 tokens took 64 us at
-// a relative error of 6.4e-8 (fused 5.6e-8, now 5.5e-8), 4096 x 4096 at 512 42 us.
+// 2.6 us per channel block of the busiest workgroup.  Layers that stay fused at up to SKL_SHORT_TOKENS tokens (workspaces
+// without room for the dense weights, eight-word layers beyond the memory-side cache) stay so.  One pass / the other, us:
+// 4096 x 11008, d = 4: 17 tokens 27 / 45 (staged), 64 31 / 46, 100 38 / 50, 256 77 / 88 (fused); 4096 x 4096: 17 / 25, 20 /
+// 25, 24 / 28, 512 tokens 56 / 67; 8192 x 8192: 33 / 76, 38 / 77, 46 / 84; four-word blocks (4096 x 11008, 0.75 bit): 32 /
+// 43, 36 / 44, 48 / 48, 384 tokens 129 / 177; two-word (8192 x 28672, d = 3): 180 / 229, 198 / 233, 320 / 234.
+// The call takes only as few block groups as keep the rounding of its sums at that of the kernel it replaces (skl_split.h):
+// with fewer, 4096 x 11008 at 256 tokens took 64 us at a relative error of 6.4e-8 (fused 5.6e-8, now 5.5e-8), 4096 x 4096
+// at 512 42 us, and 1048 x 2384, equal 4-bit channels, 473 tokens, 28 us at 1.13e-7 (1.07e-7, now 30 us at 1.05e-7).
 static bool takes_prompt_kernel(const skl_layer *L, uint32_t tokens, bool staged, PromptPlan &plan)
 {
     if (!L->gemm_prompt || tokens > SKL_PROMPT_MAX_TOKENS || (!staged && tokens <= SKL_SHORT_TOKENS)) return false;
     double other;
-    uint32_t least = 1;
+    Rounding most;                                              // of the sums of the kernel it would replace
     if (staged) {
         const double mb = 2e-6 * L->in * L->out;                // dense weights
         other = 13.0 + 0.36 * std::min(mb, 100.0) + 0.5 * std::max(mb - 100.0, 0.0) + 0.03 * std::min(tokens, SKL_SHORT_TOKENS);
         if (tokens > SKL_SHORT_TOKENS) other += 20.0 + 1.25e-4 * tokens * mb;
+        const uint32_t out = std::min(L->out, skl_staged_slab_cols(L->out, L->gemm_kb, tokens) * GM3_NT);
+        most = tokens > SKL_SHORT_TOKENS ? skl_split_rounding(skl_make_split(out, L->gemm_kb, tokens, true), L->gemm_kb)
+                                         : skl_chain_rounding(L->gemm_kb, L->gemm_kb, skl_make_short_split(out, L->gemm_kb).P, 0, false);
     } else {
         const G3Split sp = gemm3_split(L, tokens);
         uint32_t blocks = 0;
         for (uint32_t x = 0; x < 8; ++x) blocks = std::max(blocks, sp.rounds(x) * sp.nb + (sp.units(x) + sp.gx - 1) / sp.gx);
         other = 44.0 + 2.6 * blocks;
-        // no longer chains of sums than the fused kernel's shares of its tiles
-        least = (L->n_blocks + blocks - 1) / blocks;
+        most = skl_split_rounding(sp, L->gemm_kb);
     }
+    if (!L->gemm_tail) most.wide = HUGE_VAL;
     plan = skl_make_prompt_plan(PromptLayer{L->out, L->d, L->n_blocks, L->gemm_kb, L->gemm_steps32, L->table_bytes}, tokens,
-                                gemm_own_bytes(L, tokens, staged), least);
+                                gemm_own_bytes(L, tokens, staged), most);
     if (!plan.P) return false;
     return plan.cost_us * 1.02 < other;
 }

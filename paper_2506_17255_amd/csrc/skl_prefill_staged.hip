@@ -346,7 +346,7 @@ struct WideArgs {
     void *Y;
     float *parts;                       // [workgroup][wavefront][column][64-token quarter][64 lanes] x 4: first chains
     uint32_t KB, tokens, out, y_dt, ldy, rows_aligned;
-    uint32_t chains, split, body;       // of skl_make_wide_split
+    uint32_t chains, split, body, join; // of skl_make_wide_split
     G3Split sp;
 };
 
@@ -460,20 +460,36 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
         } else {
             uint32_t st = 0;
-            for (uint32_t i = 1; i <= p.chains + HELD; ++i) {
+            const uint32_t n = p.chains + (HELD ? p.body < p.KB : 0);
+            for (uint32_t i = 1; i <= n; ++i) {
                 for (const uint32_t end = i <= p.chains ? i * p.body / p.chains * 2 : n_st; st < end; st += 2) {
                     stage(st, c0);
                     stage(st + 1, c1);
                 }
                 if constexpr (HELD) {
+                    if (p.join && i > p.chains) break;          // the sum has gone through the last blocks
+                    const bool go_on = i == n || (p.join && i == p.chains);
+                    const float4v zero = {0.f, 0.f, 0.f, 0.f};
+                    auto each = [&](auto what) {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
+                        for (int r = 0; r < 4; ++r)
 #pragma unroll
-                        for (int c = 0; c < CB; ++c) {
-                            if (i <= p.chains) sum[r][c] = i == 1 ? acc[r][c] : sum[r][c] + acc[r][c];
-                            if (i < p.chains) acc[r][c] = (float4v){0.f, 0.f, 0.f, 0.f};
-                            if (i == p.chains) acc[r][c] = sum[r][c];
-                        }
+                            for (int c = 0; c < CB; ++c) what(sum[r][c], acc[r][c]);
+                    };
+                    // (branches that the empty statements keep: selects one way or the other are 128 instructions more, 0.4 us; 192
+                    // outputs have no registers for both ways of the accumulators)
+                    if constexpr (CB > 4) {
+                        each([&](float4v &s, float4v &a) { s = i == 1 ? a : s + a; a = go_on ? s : zero; });
+                    } else if (go_on) {
+                        asm volatile("");
+                        each([&](float4v &s, float4v &a) { a = s + a; });
+                    } else if (i == 1) {
+                        asm volatile("");
+                        each([&](float4v &s, float4v &a) { s = a; a = zero; });
+                    } else {
+                        asm volatile("");
+                        each([&](float4v &s, float4v &a) { s += a; a = zero; });
+                    }
                 } else if (i < p.chains) {                      // (the stores only make the next waits for copies longer)
                     uint32_t ln = lane;
                     asm volatile("" : "+v"(ln));
@@ -614,7 +630,7 @@ static skl_status_t launch_wide(const WideArgs &g, hipStream_t stream)
         hipLaunchKernelGGL(kernel, dim3(256), dim3(512), lds, stream, g);
         return check_launch("staged gemm, whole tiles");
     };
-    return g.chains > 1 ? launch(k_staged_wide<CB, true>) : launch(k_staged_wide<CB, false>);
+    return g.split ? launch(k_staged_wide<CB, true>) : launch(k_staged_wide<CB, false>);
 }
 
 skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx,
@@ -632,10 +648,7 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
     const skl_pack_window *windows = reinterpret_cast<const skl_pack_window *>(L->dev + L->off_windows);
     const PackArgs k{X, a.chan, windows, Xp, (uint32_t)x_dt, ldx, tokens, L->in, 2 * KB};
     skl_status_t st = SKL_OK;
-    // (all output tiles in one slab; the split is the call's only one then)
-    const uint64_t w_room = staged_part_bytes(L, tokens) + (uint64_t)slab_cols * KB * SG_SLOT_BYTES;
-    WideSplit wide{};
-    if (tokens > SKL_SHORT_TOKENS && slab_cols == n_col) wide = skl_make_wide_split(L->out, KB, tokens, w_room);
+    const WideSplit wide = tokens > SKL_SHORT_TOKENS ? skl_staged_product(L->out, KB, tokens, L->gemm_tail) : WideSplit{};     // (slabs: cb 0)
     const uint32_t wide_cb = wide.cb;
     // no partial tiles: their room holds the first chains and weight words
     if (wide_cb) Wp = reinterpret_cast<uint4 *>(static_cast<char *>(ws) + round256(staged_pack_bytes(L, tokens)) + skl_wide_part_bytes(wide));
@@ -664,7 +677,7 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
 
         if (wide_cb) {
             const WideArgs g{Xp, Wp, Y, parts, KB, tokens, L->out, (uint32_t)y_dt, ldy, ((size_t)ldy * (y_dt == SKL_F32 ? 4 : 2)) % 16 == 0,
-                             wide.chains, wide.split, wide.body, wide.sp};
+                             wide.chains, wide.split, wide.body, wide.join, wide.sp};
             return wide_cb == 6 ? launch_wide<6>(g, stream) : wide_cb == 7 ? launch_wide<7>(g, stream) : wide_cb == 8 ? launch_wide<8>(g, stream)
                  : wide_cb == 10 ? launch_wide<10>(g, stream) : wide_cb == 4 ? launch_wide<4>(g, stream) : launch_wide<11>(g, stream);
         }

@@ -3,6 +3,7 @@
 // by the host compiler alone).
 #pragma once
 
+#include <math.h>
 #include <stdint.h>
 #include <algorithm>
 
@@ -183,6 +184,7 @@ static inline G3Split skl_make_split(uint32_t out, uint32_t nb, uint32_t tokens,
     deal(GM_MT);
     sp.gx = (uint32_t)std::min<uint64_t>(32, std::max<uint64_t>(1, (uint64_t)most() * nb / 4));
     for (uint32_t x = 0; x < 8; ++x) {
+        if (x && sp.left(x) == sp.left(x - 1)) continue;        // (neighbours mostly share alike)
         sp.l_max = std::max(sp.l_max, sp.left(x));
         for (uint32_t l = 0; l < sp.left(x); ++l) sp.p_cap = std::max(sp.p_cap, sp.parts(x, l));
     }
@@ -228,54 +230,66 @@ static inline uint64_t skl_staged_part_floats(uint32_t out, uint32_t kb, uint32_
 }
 
 // ---- rounding of float32 sums ----
-// A chain of l blocks rounds a sum of 1, 2 .. 2 l products (of 32 channels), and adding up chains rounds their sums so far:
-// the variance of an output's error, over that of rounding its last product, is about the sum of l^2 over the chains, plus
-// the blocks summed so far per addition, over the blocks of the tile.  This is the mean over the outputs of a split, for
-// products of like size; its root is within 4 % of the errors measured on channels of equal width.
-static inline double skl_split_chain(const G3Split &sp)
+// The variance of an output's rounding errors for a way of adding up its products, in units of four roundings of the result
+// (a matrix instruction rounds its sums once per eight channels, as the errors of layers of all sizes show): a chain over a
+// fraction f of nb blocks counts nb f^2, adding a chain to the sum of those before it a quarter of the fraction reached.
+//   like:  all channels contribute alike (channels of equal width);
+//   wide:  wide channels, which come last, carry the result (where the layer has such): measured with one percent of them,
+//          the others are 1/40 of its variance.  In units of theirs an addition behind the last block, which rounds the whole
+//          result, counts 15, and 10 where the last blocks are a chain of their own (their products then meet no sum of
+//          others in the matrix cores).
+// Roots of `like` are within 4 % of the errors measured on channels of equal width.
+struct Rounding {
+    double like, wide;
+    bool within(const Rounding &o) const { return like <= o.like * (1 + 1e-9) && wide <= o.wide * (1 + 1e-9); }
+};
+#define SKL_LAST_ADDITION 14.75         // further weight of an addition behind the last block
+#define SKL_LAST_OF_TAIL 9.75
+
+// The mean over the outputs of a split, whose blocks hold the channels of nb (64-channel) blocks.
+static inline Rounding skl_split_rounding(const G3Split &sp, double nb)
 {
-    double total = 0, shared = 0;
+    const double unit = 1.0 / sp.nb;
+    Rounding total{}, shared{};
     for (uint32_t x = 0; x < 8; ++x) {
         const uint32_t left = sp.left(x);
-        total += (double)(sp.tiles_of(x) - left) * sp.nb * sp.nb;
-        if (!x || left != sp.left(x - 1)) {                     // (neighbours mostly share alike)
-            shared = 0;
+        if (!x || left != sp.left(x - 1)) {
+            shared = Rounding{};
             for (uint32_t j = 0; left && j < sp.sharers(x); ++j)
                 for (uint32_t u = sp.share_begin(x, j), end = sp.share_begin(x, j + 1); u < end;) {
                     const uint32_t k = u % sp.nb, n = std::min(end - u, sp.nb - k);
-                    shared += (double)n * n + (k ? k + n : 0);
+                    shared.like += nb * (n * unit) * (n * unit) + (k ? 0.25 * (k + n) * unit : 0);
+                    if (k && k + n == sp.nb) shared.wide += SKL_LAST_ADDITION;
                     u += n;
                 }
         }
-        total += shared;
+        total.like += (double)(sp.tiles_of(x) - left) * nb + shared.like;
+        total.wide += shared.wide;
     }
-    return total / ((double)sp.T * sp.nb);
+    return {total.like / sp.T, (total.like + total.wide) / sp.T};
 }
-// Blocks past the last addition of chains where a whole tile is made of several: the channels of the widest sketches, which
-// carry most of the result, come last, and an addition behind them would round the whole of it.
-static inline uint32_t skl_wide_tail(uint32_t nb) { return (nb + 63) / 64; }
-// The same measure for n equal chains in a row over all but the last blocks, which the sum of them goes through.
-static inline double skl_wide_chain(uint32_t nb, uint32_t n, uint32_t tail)
+// n equal chains in a row over all but the last `tail` of `blocks` blocks, which hold the channels of nb.  The last ones are a
+// chain of their own or (join) go into the sum of the others: behind the last addition, but each of their products rounds it
+// (where wide channels carry the result, those roundings are theirs in any case).
+static inline Rounding skl_chain_rounding(uint32_t blocks, double nb, uint32_t n, uint32_t tail, bool join)
 {
-    const uint32_t body = nb - tail;
-    double total = (double)tail * (2 * body + tail);
-    for (uint32_t i = 0; i < n; ++i) {
-        const uint32_t end = (i + 1) * body / n, l = end - i * body / n;
-        total += (double)l * l + (i ? end : 0);
-    }
-    return total / nb;
+    const uint32_t body = blocks - tail, l = body / n, longer = body % n;       // chain i: blocks [i body / n, (i + 1) body / n)
+    const double unit = 1.0 / blocks, squares = (double)longer * (2 * l + 1) + (double)n * l * l;
+    const double ends = n > 1 ? 0.5 * ((double)(body - 1) * (n - 1)) + body - l : 0;        // of the chains behind the first
+    const double chains = nb * squares * unit * unit + 0.25 * ends * unit, own = tail && !join ? 0.25 : 0;
+    return {chains + own + nb * tail * ((join ? 2.0 * body : 0.0) + tail) * unit * unit,
+            chains + own + (tail ? (join ? 0 : SKL_LAST_OF_TAIL) : n > 1 ? SKL_LAST_ADDITION : 0)};
 }
-
 // Whole tiles of another width instead: 256 tokens x 32 * cb outputs, one tile after another per workgroup (the k-th of XCD
 // x by workgroup k % 32), no partial tiles, no fix-up.  An output of a shared tile is the sum of several chains of products,
 // one of a whole tile would be a single chain with up to three times the rounding error (4096 x 2048, 600 tokens, channels
 // of equal width: 1.4e-7 in eleven chains, 4.1e-7 in one).  So the first `split` of a wavefront's cb columns of outputs
-// go through `chains` chains, one after the other, as many as keep the measure above at that of the shared tiles.
+// go through `chains` chains, one after the other, as many as keep both measures above at those of the shared tiles.
 // Where those are whole as well, one chain does.
 struct WideSplit {
     G3Split sp;
     uint32_t cb, chains, split;         // cb 0: shared tiles
-    uint32_t body;                      // blocks that the chains divide; their sum goes through the rest
+    uint32_t body, join;                // blocks that the chains divide; the rest goes into their sum (join) or is one more
     double us;                          // estimated time of the product
 };
 #define SW_HELD_CB 6u                   // up to this width the sums of the earlier chains are held in registers
@@ -291,17 +305,23 @@ static inline uint64_t skl_wide_part_bytes(const WideSplit &w) { return w.cb > S
 // 4 188, 6 182, 8 198, 11 167, 172 us; 4096 x 4096 81 / 4 76; 2048 x 5632, 1500 tokens, 75 / 6 53, 57; 1024 x 2048 42 / 4 28, 30;
 // 3000 x 7001, 1024 tokens, 95 / 4 60, 64; 8192 x 28672 852 / 4 900, 6 829, 8 835, 10 812, 827, 11 834; 4096 x 11008, 777
 // tokens, 164 / 6 102, 105; 8192 x 3000, 1300 tokens, 136 / 4 110, 111; 4096 x 2048, 600 tokens, 49 / 4 53, 61 in twelve chains.
-static inline WideSplit skl_make_wide_split(uint32_t out, uint32_t nb, uint32_t tokens, uint64_t room)
+// tail: last blocks, those that hold the wide channels of the layer (0: it has none).
+static inline WideSplit skl_make_wide_split(uint32_t out, uint32_t nb, uint32_t tokens, uint64_t room, uint32_t tail)
 {
     const G3Split old = skl_make_split(out, nb, tokens, true);
-    const double longest = skl_split_chain(old) * (1 + 1e-9);
+    Rounding most = skl_split_rounding(old, nb);
+    if (!tail) most.wide = HUGE_VAL;
     double whole = 0, shared = 0;
-    uint32_t slots = 0, rounds = 1;
+    uint32_t slots = 0, rounds = 1, of_x = 0;
     for (uint32_t x = 0; x < 8; ++x) {
         whole = std::max(whole, old.rounds(x) * nb * (old.mt < GM_MT ? 0.6 : 1.0));
         shared = std::max(shared, (double)old.units(x) / old.gx);
         rounds = std::max(rounds, old.rounds(x));
-        for (uint32_t l = 0; l < old.left(x); ++l) slots += old.parts(x, l);
+        if (!x || old.left(x) != old.left(x - 1)) {
+            of_x = 0;
+            for (uint32_t l = 0; l < old.left(x); ++l) of_x += old.parts(x, l);
+        }
+        slots += of_x;
     }
     WideSplit best{};
     best.us = 1.52 * whole + 2.2 * shared + 8.0 * rounds + (slots ? 6.0 + 0.05 * slots : 0.0);
@@ -318,32 +338,33 @@ static inline WideSplit skl_make_wide_split(uint32_t out, uint32_t nb, uint32_t 
         c.chains = 1;
         c.body = nb;
         double more = 0;
-        if (nb <= longest) {
+        const Rounding one = skl_chain_rounding(nb, nb, 1, 0, false);
+        if (one.within(most)) {
         } else if (w.cb <= SW_HELD_CB) {
-            // (where every tile is shared, all outputs have had an addition behind the last block)
-            bool found = false;
-            for (const uint32_t tail : {skl_wide_tail(nb), 0u}) {
-                if (found || (!tail && whole > 0)) break;
-                c.body = nb - tail;
-                double before = nb;
-                for (c.chains = 2; c.chains <= c.body; ++c.chains) {
-                    const double now = skl_wide_chain(nb, c.chains, tail);
-                    found = now <= longest;
-                    if (found || now >= before) break;          // (past the least the additions outweigh what they shorten)
-                    before = now;
+            c.body = nb - tail;
+            c.chains = 0;
+            for (const bool join : {true, false}) {             // the fewest (without a tail both ways are one)
+                double before = 2.0 * nb;
+                for (uint32_t n = join || !tail ? 2 : 1; n <= c.body && (!c.chains || n + !join < c.chains + !c.join); ++n) {
+                    const Rounding now = skl_chain_rounding(nb, nb, n, tail, join);
+                    if (now.within(most)) {
+                        c.chains = n;
+                        c.join = join;
+                    }
+                    if (now.like >= before) break;              // (past the least the additions outweigh what they shorten)
+                    before = now.like;
                 }
             }
-            if (!found) continue;
+            if (!c.chains) continue;
             c.split = w.cb;
-            more = 0.16 * w.cb * c.chains * rounds;
-        } else {
-            // The two chains are added at the end, where that rounds the whole result: counted like five products, and
-            // only where the chains are long (512 x 28672, 2048 tokens, nine blocks, one percent of wide channels: 3.58e-8
-            // in two chains, 3.43e-8 in one; shared tiles 3.54e-8).
-            if (nb < 32) continue;
-            const double one = nb, two = skl_wide_chain(nb, 2, 0) + 4.0;
+            more = 0.16 * w.cb * (c.chains + !c.join) * rounds;
+        } else {                                                // two chains, added behind the last block
+            const Rounding two = skl_chain_rounding(nb, nb, 2, 0, false);
             c.chains = 2;
-            c.split = (uint32_t)(w.cb * (one - longest) / (one - two)) + 1;
+            for (c.split = 1; c.split <= w.cb; ++c.split) {
+                const double f = (double)c.split / w.cb;
+                if (Rounding{one.like + f * (two.like - one.like), one.wide + f * (two.wide - one.wide)}.within(most)) break;
+            }
             if (c.split > w.cb) continue;
             more = (2.0 + c.split) * rounds;
         }
@@ -351,14 +372,24 @@ static inline WideSplit skl_make_wide_split(uint32_t out, uint32_t nb, uint32_t 
         for (uint32_t mu = sp.m_tiles; mu >= 1; mu /= 2) {      // the largest dealing unit that needs no further round
             if (sp.m_tiles % mu) continue;
             sp.mu = mu;
-            uint32_t most = 0;
-            for (uint32_t x = 0; x < 8; ++x) most = std::max(most, sp.tiles_of(x));
-            if ((most + 31) / 32 <= rounds) break;
+            uint32_t tiles = 0;
+            for (uint32_t x = 0; x < 8; ++x) tiles = std::max(tiles, sp.tiles_of(x));
+            if ((tiles + 31) / 32 <= rounds) break;
         }
         c.us = (0.6 * rounds + 0.4 * sp.T / 256.0) * nb * w.cb / 8.0 * w.f + 5.0 * rounds + more;
         if (c.us < best.us) best = c;
     }
     return best;
+}
+
+// The product of a staged call of more than 128 tokens, in the room that such calls ask for.
+static inline WideSplit skl_staged_product(uint32_t out, uint32_t kb, uint32_t tokens, uint32_t tail)
+{
+    const uint32_t n_col = (out + GM3_NT - 1) / GM3_NT, cols = skl_staged_slab_cols(out, kb, tokens);
+    if (cols == n_col) return skl_make_wide_split(out, kb, tokens, skl_staged_part_floats(out, kb, tokens) * sizeof(float) + (uint64_t)cols * kb * SG_SLOT_BYTES, tail);
+    WideSplit w = skl_make_wide_split(cols * GM3_NT, kb, tokens, 0, tail);        // slab by slab, in shared tiles
+    w.us *= (n_col + cols - 1) / cols;
+    return w;
 }
 
 // ---- short prompts in one pass ----
@@ -381,9 +412,16 @@ struct PromptLayer {
 // 13 layer shapes (2 to 8 words per state row, d = 2 to 4) x 10 token counts; 5 % rms, and the plan it picks is 2 % slower
 // than the fastest one measured on average, 12 % at worst.  A block costs the larger of its copy into LDS and its
 // arithmetic plus 0.38 of the smaller; fewer than six wavefronts do not hide each other's latency.
-// least: fewest block groups (the products of a group are one chain of float32 sums).
-static inline PromptPlan skl_make_prompt_plan(const PromptLayer &L, uint32_t tokens, uint64_t room, uint32_t least = 1)
+// most: groups whose sums (a chain per group) are rounded more are not taken.
+static inline PromptPlan skl_make_prompt_plan(const PromptLayer &L, uint32_t tokens, uint64_t room, const Rounding &most)
 {
+    uint64_t groups = 0;                                        // bit P - 1: P groups may be taken
+    uint32_t least = 0;
+    for (uint32_t P = 1; P <= std::min(L.n_blocks, 64u); ++P)
+        if (skl_chain_rounding(L.n_blocks, L.kb, P, 0, false).within(most)) {
+            groups |= 1ull << (P - 1);
+            if (!least) least = P;
+        }
     PromptPlan best{};
     const uint32_t blocks16 = (tokens + 15) / 16;
     const uint32_t M = (blocks16 + 7) / 8, rb = std::max(2u, (blocks16 + 2 * M - 1) / (2 * M) * 2);
@@ -396,7 +434,7 @@ static inline PromptPlan skl_make_prompt_plan(const PromptLayer &L, uint32_t tok
         const uint32_t T = (units + nw - 1) / nw;
         const uint32_t one = 256 / (T * M);                      // groups that fill the chip once
         for (const uint32_t P : {one, one * 2 / 3, one / 8 * 8, 512 / (T * M), 768 / (T * M), least}) {
-            if (P < least || P > std::min(L.n_blocks, 64u)) continue;
+            if (P < 1 || P > 64 || !(groups >> (P - 1) & 1)) continue;
             const uint64_t part = (uint64_t)M * T * P * rows * 2 * nw * 1024;
             if (pack + part > room) continue;
             const uint32_t per_group = (L.n_blocks + P - 1) / P, rounds = (T * M * P + 255) / 256;

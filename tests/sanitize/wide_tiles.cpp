@@ -15,22 +15,26 @@
         }                                                                                                                    \
     } while (0)
 
-// Squares of the roundings' sizes of one output, in products, over the last one's: chains of the given blocks (two products
-// each), added up in order after `tail` further blocks have gone into the last chain, or before them (merged).
-static double roundings(const std::vector<uint32_t> &chains, uint32_t tail, uint32_t nb)
+// The roundings of one output, a quarter each: a matrix instruction rounds its sum once per eight channels, an addition of
+// chains the sum so far.  Sizes are fractions of the result: of all channels alike, or (wide) of the narrow ones alone, whose
+// own roundings are the smaller part there; an addition behind the last block then counts 14.75 more, 9.75 for the tail's own
+// chain.  `join`: the last chain is not added but takes up the sum of those before it.
+static double roundings(const std::vector<uint32_t> &chains, uint32_t nb, bool wide, bool join = false, bool tail = false)
 {
     double sum = 0, so_far = 0;
     for (size_t i = 0; i < chains.size(); ++i) {
-        for (uint32_t k = 1; k <= 2 * chains[i]; ++k) sum += k;
-        so_far += 2 * chains[i];
-        if (i) sum += so_far;
+        const bool last = i + 1 == chains.size(), joins = join && last;
+        if (!(wide && tail && last))
+            for (uint32_t k = 1; k <= 8 * chains[i]; ++k) sum += ((joins ? so_far : 0) + k / 8.0) / nb / 4;
+        so_far += chains[i];
+        if (i && !joins) sum += so_far / nb / 4;
     }
-    for (uint32_t k = 1; k <= 2 * tail; ++k) sum += so_far + k;
-    return sum / (2.0 * nb);
+    if (wide && chains.size() > 1 && !join) sum += tail ? 9.75 : 14.75;
+    return sum;
 }
 
 // The mean over the outputs of the shared-tile split, by walking it as the kernel does.
-static double shared_roundings(const G3Split &sp)
+static double shared_roundings(const G3Split &sp, bool wide)
 {
     std::vector<std::vector<uint32_t>> tiles(sp.T);
     for (uint32_t x = 0; x < 8; ++x)
@@ -44,7 +48,7 @@ static double shared_roundings(const G3Split &sp)
             }
         }
     double sum = 0;
-    for (const auto &t : tiles) sum += roundings(t, 0, sp.nb);
+    for (const auto &t : tiles) sum += roundings(t, sp.nb, wide);
     return sum / sp.T;
 }
 
@@ -52,26 +56,33 @@ int main()
 {
     uint64_t s = 88172645463325252ull, seen[12] = {}, divided[12] = {};
     auto rnd = [&](uint32_t lo, uint32_t hi) { s ^= s << 13; s ^= s >> 7; s ^= s << 17; return lo + (uint32_t)(s % (hi - lo + 1)); };
-    for (uint32_t n = 0; n < 20000; ++n) {
+    for (uint32_t n = 0; n < 8000; ++n) {
         const uint32_t out = rnd(0, 3) ? rnd(1, 12000) : rnd(1, 60000), nb = rnd(1, 200), tokens = rnd(129, 4200);
         const uint64_t room = rnd(0, 3) ? ~0ull : (uint64_t)rnd(1, 60000) << rnd(0, 14);
-        const WideSplit w = skl_make_wide_split(out, nb, tokens, room);
+        const uint32_t tail = std::min(rnd(0, 3), nb - 1);
+        const WideSplit w = skl_make_wide_split(out, nb, tokens, room, tail);
         const G3Split &sp = w.sp;
         const uint32_t cb = w.cb;
         CHECK(cb == 0 || cb == 4 || cb == 6 || cb == 7 || cb == 8 || cb == 10 || cb == 11);
         ++seen[cb];
         if (!cb) continue;
         CHECK((uint64_t)sp.n_col * nb * cb * 4096 + skl_wide_part_bytes(w) <= room);
-        CHECK(w.chains >= 1 && w.chains <= w.body && w.body <= nb && (w.chains > 1) == (w.split > 0));
-        CHECK(cb <= SW_HELD_CB ? w.split == 0 || w.split == cb : w.split <= cb && w.chains <= 2 && w.body == nb);
+        CHECK(w.chains >= 1 && w.chains <= w.body && (w.chains > 1 || w.body < nb) == (w.split > 0));
+        CHECK(w.split ? w.body == (cb <= SW_HELD_CB ? nb - tail : nb) : w.body == nb);
+        CHECK(cb <= SW_HELD_CB ? w.split == 0 || w.split == cb : w.split <= cb && w.chains <= 2);
         CHECK(skl_wide_part_bytes(w) == (cb <= SW_HELD_CB ? 0ull : 256ull * 8 * w.split * 4 * 64 * 16));
         std::vector<uint32_t> chains;
         for (uint32_t i = 0; i < w.chains; ++i) chains.push_back((i + 1) * w.body / w.chains - i * w.body / w.chains);
-        const double one = roundings({nb}, 0, nb), more = roundings(chains, nb - w.body, nb);
-        const uint32_t many = w.chains > 1 ? w.split : cb;
-        // (0.5 / nb of the measure: a chain of l blocks is counted as l^2, not l^2 + l / 2)
-        CHECK((many * more + (cb - many) * one) / cb <= shared_roundings(skl_make_split(out, nb, tokens, true)) + 0.5);
-        divided[cb] += w.chains > 1;
+        if (w.body < nb) chains.push_back(nb - w.body);
+        const G3Split shared = skl_make_split(out, nb, tokens, true);
+        for (const bool wide : {false, true}) {
+            if (wide && !tail) continue;
+            const double one = roundings({nb}, nb, wide), more = roundings(chains, nb, wide, w.body < nb && w.join, w.body < nb);
+            const uint32_t many = w.split ? w.split : cb;
+            // (the planner counts a chain of l blocks as l^2, here it is l^2 + l / 8, and the ends of chains on the mean)
+            CHECK((many * more + (cb - many) * one) / cb <= shared_roundings(shared, wide) + 0.4);
+        }
+        divided[cb] += w.split > 0;
         CHECK(sp.n_col * cb * 32 >= out && (sp.n_col - 1) * cb * 32 < out);
         CHECK(sp.m_tiles * 256 >= tokens && (sp.m_tiles - 1) * 256 < tokens);
         std::vector<uint8_t> done((size_t)sp.n_col * sp.m_tiles, 0);

@@ -233,39 +233,45 @@ def oracle_stack_layer(index: int):
     return index, sk, hashlib.sha1(np.ascontiguousarray(W_hat).tobytes()).hexdigest(), y
 
 
-# Staged calls of more than 128 tokens on layers of equal widths: in and out features, tokens, type of Y, padding of its rows,
-# and the way they go: whole tiles of 32 x width outputs and the chains of sums in them, shared tiles (with a fix-up pass), or
-# one whole tile of 128 tokens per workgroup.
+# Staged calls of more than 128 tokens: in and out features, tokens, wide channels among the former (behind whole blocks of
+# 64), type of Y, padding of its rows, and the way they go: whole tiles of 32 x width outputs and the chains of sums in them,
+# shared tiles (with a fix-up pass), or one whole tile of 128 tokens per workgroup.
 STAGED_ROUTES = [
-    (128, 17408, 257, "f16", 0, ("whole", 6, 1)),
-    (128, 19712, 275, "bf16", 0, ("whole", 7, 1)),
-    (128, 19448, 272, "f32", 0, ("whole", 8, 1)),
-    (128, 22217, 524, "bf16", 3, ("whole", 10, 1)),
-    (128, 27513, 517, "f32", 3, ("whole", 11, 1)),
-    (512, 512, 132, "f32", 0, ("whole", 4, 2)),             # added up behind the last block
-    (2048, 600, 550, "f32", 0, ("whole", 4, 7)),            # before it
-    (2048, 600, 1050, "f32", 1, ("whole", 4, 7)),
-    (256, 3122, 4100, "bf16", 0, ("whole", 4, 2)),          # several tiles per workgroup
-    (256, 18062, 260, "f16", 2, ("whole", 6, 2)),
-    (2048, 4868, 1550, "f32", 0, ("whole", 6, 3)),
-    (2048, 7972, 1550, "f32", 0, ("whole", 7, 2)),          # the first chains through memory
-    (2048, 8069, 1550, "f32", 3, ("whole", 8, 2)),
-    (2048, 22528, 546, "f32", 0, ("whole", 10, 2)),
-    (2112, 7681, 4100, "f32", 0, ("whole", 10, 2)),         # several tiles per workgroup
-    (2048, 28362, 516, "f32", 0, ("whole", 11, 2)),
-    (256, 514, 525, "f32", 0, ("shared", 0, 0)),
-    (2112, 600, 150, "f32", 5, ("shared", 0, 0)),
-    (5184, 1140, 155, "bf16", 0, ("shared", 0, 0)),
-    (192, 28672, 300, "f16", 4, ("shared", 0, 0)),
-    (512, 20480, 267, "f32", 0, ("half", 0, 0)),
-    (512, 20477, 267, "bf16", 0, ("half", 0, 0)),
+    (128, 18432, 268, 0, "f16", 0, ("whole", 6, 1)),
+    (128, 19712, 275, 0, "bf16", 0, ("whole", 7, 1)),
+    (128, 19427, 258, 0, "f32", 0, ("whole", 8, 1)),
+    (128, 8539, 1828, 0, "bf16", 3, ("whole", 10, 1)),
+    (128, 19234, 826, 0, "f32", 3, ("whole", 11, 1)),
+    (512, 512, 132, 0, "f32", 0, ("whole", 4, 2)),
+    (456, 512, 137, 8, "f32", 1, ("whole", 4, 3)),                      # the last block a chain of its own
+    (520, 512, 145, 8, "f32", 0, ("whole", 4, 3)),                      # the last block behind the sum of the chains
+    (712, 6912, 749, 8, "f32", 0, ("whole", 4, 5)),
+    (2048, 600, 1050, 0, "f32", 1, ("whole", 4, 9)),
+    (256, 18062, 260, 0, "f16", 2, ("whole", 6, 2)),
+    (200, 10896, 569, 8, "f32", 0, ("whole", 6, 2)),
+    (136, 16595, 280, 8, "f32", 0, ("whole", 6, 2)),
+    (520, 28672, 600, 8, "bf16", 0, ("whole", 6, 2)),                   # several tiles per workgroup
+    (2048, 4868, 1550, 0, "f32", 0, ("whole", 6, 3)),
+    (2048, 7972, 1550, 0, "f32", 0, ("whole", 7, 2)),                   # the first chains through memory
+    (2048, 8069, 1550, 0, "f32", 3, ("whole", 8, 2)),
+    (1992, 22528, 546, 8, "f32", 0, ("whole", 10, 2)),
+    (2112, 7681, 4100, 0, "f32", 0, ("whole", 10, 2)),                  # several tiles per workgroup
+    (2048, 28362, 516, 0, "f32", 0, ("whole", 11, 2)),
+    (128, 6400, 139, 0, "f32", 0, ("whole", 4, 2)),
+    (2112, 600, 150, 0, "f32", 5, ("shared", 0, 1)),
+    (5184, 1140, 155, 0, "bf16", 0, ("shared", 0, 1)),
+    (72, 17408, 257, 8, "f16", 4, ("shared", 0, 1)),
+    (512, 20992, 314, 0, "f32", 0, ("half", 0, 1)),
+    (512, 20480, 267, 0, "bf16", 5, ("half", 0, 1)),
 ]
 
 
-def staged_routes(shapes, tmp_path):
-    """(kind, width, chains, measure of rounding of the shared split) of staged calls: 64-channel blocks, outputs, tokens."""
+def staged_routes(cases, tmp_path):
+    """(kind, width, chains, measure of rounding of the shared split) of cases as above."""
     exe = tmp_path / "staged_route"
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(_ROOT, "paper_2506_17255_amd", "csrc"),
                            os.path.join(_ROOT, "tests", "sanitize", "staged_route.cpp"), "-o", str(exe)])
-    lines = subprocess.run([str(exe), *[str(v) for s in shapes for v in s]], capture_output=True, text=True, check=True).stdout.splitlines()
+    args = [str(v) for n_in, n_out, tokens, n_wide, *_ in cases
+            for v in ((n_in - n_wide + 63) // 64 + (n_wide > 0), n_out, tokens, int(n_wide > 0))]
+    lines = subprocess.run([str(exe), *args], capture_output=True, text=True, check=True).stdout.splitlines()
     return [(k, int(cb), int(n), float(m)) for k, cb, n, m in map(str.split, lines)]

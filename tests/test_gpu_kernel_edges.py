@@ -218,17 +218,21 @@ def test_whole_tiles_of_staged_prompts(in_f, out_f, tokens, x_dt, y_dt, ldy_pad)
     assert rel_fro(y, ref) <= tol, rel_fro(y, ref)
 
 
-@pytest.mark.parametrize("in_f,out_f,tokens,y_dt,ldy_pad,way", STAGED_ROUTES)
-def test_ways_of_staged_prompts(in_f, out_f, tokens, y_dt, ldy_pad, way, tmp_path):
+@pytest.mark.parametrize("in_f,out_f,tokens,n_wide,y_dt,ldy_pad,way", STAGED_ROUTES)
+def test_ways_of_staged_prompts(in_f, out_f, tokens, n_wide, y_dt, ldy_pad, way, tmp_path):
     """Every way of a staged call over a dirty workspace: all outputs against a product in 64 bits, rounded no more than
     the sums of shared tiles are, whatever the way."""
     t = __import__("torch")
     rng = np.random.default_rng(in_f + out_f + tokens)
     A, C = hash_params(rng, 2)
     K = np.full(in_f, 9, dtype=np.uint32)
-    sk = oracle.Sketch(in_f, out_f, 1, out_f, 2, A, C, K, (rng.standard_normal(2 * int(K.sum())) * 0.02).astype(np.float16).view(np.uint16))
+    K[in_f - n_wide:] = 36
+    scale = np.where(np.arange(in_f) < in_f - n_wide, 0.02, 0.4).repeat(2 * K)
+    order = rng.permutation(in_f)
+    states = np.split((rng.standard_normal(scale.size) * scale).astype(np.float16).view(np.uint16), np.cumsum(2 * K)[:-1])
+    sk = oracle.Sketch(in_f, out_f, 1, out_f, 2, A, C, K[order], np.concatenate([states[j] for j in order]))
     X = wk.f32_to_bf16_bits(rng.standard_normal((tokens, in_f)).astype(np.float32))
-    (kind, cb, chains, measure), = staged_routes([((in_f + 63) // 64, out_f, tokens)], tmp_path)
+    (kind, cb, chains, measure), = staged_routes([(in_f, out_f, tokens, n_wide)], tmp_path)
     assert (kind, cb, chains) == way
     with GpuLayer(sk, skl.FLAG_STAGED_PREFILL) as g:
         ws, _ = g.workspace(1, tokens)
@@ -238,8 +242,8 @@ def test_ways_of_staged_prompts(in_f, out_f, tokens, y_dt, ldy_pad, way, tmp_pat
         again = t.from_numpy(g.gemm(X, "bf16", y_dt, ldy=out_f + ldy_pad)).cuda().double()
         ref = t.from_numpy(wk.bf16_bits_to_f32(X)).cuda().double() @ t.from_numpy(oracle.query(sk).view(np.float16)).cuda().double()
     assert bool((y == again).all()) and bool(t.isfinite(y).all())
-    # the measure is the variance of the roundings of products of like size over that of one, which is at most 2^-24 of the
-    # sum in root mean square; one more for the rounding of the result, then that to a shorter type
+    # the measure counts four roundings of the result, of up to 2^-25 each in root mean square; one more for the result itself,
+    # then that to a shorter type
     tol = 2.0**-24 * (measure + 1) ** 0.5 + {"f32": 0.0, "f16": 2.0**-11, "bf16": 2.0**-8}[y_dt]
     err = float((y - ref).norm() / ref.norm())
     assert err <= tol, (err, tol)

@@ -267,8 +267,7 @@ def test_plans_of_one_pass_prompts_and_whole_tiles(name, tmp_path):
 
 
 def test_ways_of_staged_calls_that_the_gpu_tests_rely_on(tmp_path):
-    got = staged_routes([((n_in + 63) // 64, n_out, tokens) for n_in, n_out, tokens, *_ in STAGED_ROUTES], tmp_path)
-    for case, (kind, cb, chains, _) in zip(STAGED_ROUTES, got):
+    for case, (kind, cb, chains, _) in zip(STAGED_ROUTES, staged_routes(STAGED_ROUTES, tmp_path)):
         assert (kind, cb, chains) == case[-1], case
 
 
