@@ -464,7 +464,7 @@ uint64_t skl_gemm_workspace_bytes(const skl_layer *L, uint32_t tokens, bool stag
 
 // Whether a call the library may choose the kernel for takes the one-pass kernel (`plan`) instead of the staged or the
 // fused one, in the room those ask for: by the estimated times.  The other two are lines through measured whole calls: a
-// staged one by the MB of dense weights it writes and reads (dearer beyond the caches) and its tokens, a fused one 44 us +
+// staged one by the MB of dense weights it writes and reads (dearer beyond the caches) and its product, a fused one 44 us +
 // 2.6 us per channel block of the busiest workgroup.  Layers that stay fused at up to SKL_SHORT_TOKENS tokens (workspaces
 // without room for the dense weights, eight-word layers beyond the memory-side cache) stay so.  One pass / the other, us:
 // 4096 x 11008, d = 4: 17 tokens 27 / 45 (staged), 64 31 / 46, 100 38 / 50, 256 77 / 88 (fused); 4096 x 4096: 17 / 25, 20 /
@@ -480,8 +480,13 @@ static bool takes_prompt_kernel(const skl_layer *L, uint32_t tokens, bool staged
     Rounding most;                                              // of the sums of the kernel it would replace
     if (staged) {
         const double mb = 2e-6 * L->in * L->out;                // dense weights
-        other = 13.0 + 0.36 * std::min(mb, 100.0) + 0.5 * std::max(mb - 100.0, 0.0) + 0.03 * std::min(tokens, SKL_SHORT_TOKENS);
-        if (tokens > SKL_SHORT_TOKENS) other += 20.0 + 1.25e-4 * tokens * mb;
+        if (tokens <= SKL_SHORT_TOKENS)
+            other = 13.0 + 0.36 * std::min(mb, 100.0) + 0.5 * std::max(mb - 100.0, 0.0) + 0.03 * tokens;
+        else
+            // the rebuild launch and the product as it will be split: within 6 us (standard deviation over 47 layers); 688 x
+            // 6104, d = 2, 465 tokens, 25 us, estimated 26 (by a line through calls with shared tiles 40), one pass 35
+            other = 9.0 + 0.19 * std::min(mb, 120.0) + 0.35 * std::max(mb - 120.0, 0.0) + 0.0175 * L->n_blocks +
+                    skl_staged_product(L->out, L->gemm_kb, tokens, L->gemm_tail).us;
         const uint32_t out = std::min(L->out, skl_staged_slab_cols(L->out, L->gemm_kb, tokens) * GM3_NT);
         most = tokens > SKL_SHORT_TOKENS ? skl_split_rounding(skl_make_split(out, L->gemm_kb, tokens, true), L->gemm_kb)
                                          : skl_chain_rounding(L->gemm_kb, L->gemm_kb, skl_make_short_split(out, L->gemm_kb).P, 0, false);

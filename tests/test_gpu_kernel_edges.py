@@ -191,6 +191,21 @@ def test_prompts_in_one_pass(in_f, out_f, d, widths, bits, tokens, x_dt, y_dt, l
         assert np.isfinite(v.astype(np.float32)).all() and rel_fro(v, ref) <= tol, rel_fro(v, ref)
 
 
+@pytest.mark.parametrize("in_f,out_f,d,widths,tokens", [
+    (688, 6104, 2, (95, 381), 465),         # whole tiles are faster than a pass over the tables per token tile
+])
+def test_prompts_that_stay_staged(in_f, out_f, d, widths, tokens):
+    """Layers whose tables the fused kernel cannot hold, where one pass fits the workspace but is slower: the staged kernel's
+    result bit for bit."""
+    rng = np.random.default_rng(in_f + tokens)
+    A, C = hash_params(rng, d)
+    K = np.where(np.arange(in_f) % 100 == 7, widths[1], widths[0]).astype(np.uint32)
+    sk = oracle.Sketch(in_f, out_f, 1, out_f, d, A, C, K, (rng.standard_normal(d * int(K.sum())) * 0.02).astype(np.float16).view(np.uint16))
+    X = wk.f32_to_bf16_bits(rng.standard_normal((tokens, in_f)).astype(np.float32))
+    with GpuLayer(sk) as g, GpuLayer(sk, skl.FLAG_STAGED_PREFILL) as st:
+        assert np.array_equal(g.gemm(X, "bf16", "f32"), st.gemm(X, "bf16", "f32"))
+
+
 @pytest.mark.parametrize("in_f,out_f,tokens,x_dt,y_dt,ldy_pad", [
     (64, 600, 300, "bf16", "f32", 0),           # tiles of 128 outputs; one 64-channel block: fewer stages than the pipeline holds
     (264, 3001, 600, "bf16", "bf16", 0),        # of 128; rows of Y not on 16-byte boundaries, ragged last tile and token tile
