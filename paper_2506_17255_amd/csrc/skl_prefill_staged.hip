@@ -659,11 +659,7 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
         r.out = L->out; r.n_blocks = L->n_blocks; r.KB = KB; r.n_words = L->n_packed / 8;
         r.tile0 = tile0; r.n_col = cols;
         r.tb = wide_cb ? 2 * wide_cb : 16; r.n_tb = wide_cb ? wide.sp.n_col * 2 * wide_cb : 16 * cols;
-        // Output segments per channel block: two, or as many as make 128 workgroups.  More segments stage every table
-        // more often and gain nothing (the activation workgroups behind them fill the rest of the chip): launch time by
-        // segments, 2048 tokens, 4096 x 11008 (67 blocks) 2 28.2 us, 4 29.6, 8 31.5; 8192 x 28672 (518) 2 105.8, 4
-        // 111.8, 8 120.4; 4096 x 4096 (66) 2 15.3, 4 17.1; 2048 x 5632, 1500 tokens (33) 1 19.1, 2 12.6, 4 12.4.
-        r.n_oseg = std::min(cols, std::max(2u, (127 + L->n_blocks) / L->n_blocks));
+        r.n_oseg = skl_rebuild_segments(L->n_blocks, L->n_packed / 8, L->table_bytes, cols);
         const size_t lds = std::max<size_t>(L->max_table_bytes, PO_LDS_BYTES);
         const uint32_t n_pack = tile0 ? 0 : (tokens + 15) / 16 * ((2 * KB + PO_STEPS - 1) / PO_STEPS);     // (with the first slab)
         const uint32_t n_wg = n_pack + L->n_blocks * r.n_oseg, row = std::min(n_wg, 1u << 22);

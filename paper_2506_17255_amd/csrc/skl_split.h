@@ -229,6 +229,28 @@ static inline uint64_t skl_staged_part_floats(uint32_t out, uint32_t kb, uint32_
     return most;
 }
 
+// Output segments per channel block in the rebuild launch, one workgroup each: two, or those that take least by rounds of
+// 256 workgroups, each of which stages its table (3.7 us for 64 KiB) and rebuilds words of 256 outputs (84 us per 1024).
+// Whole calls by segments, 17 tokens (the one chosen in brackets): 4096 x 11008 (67 blocks) 1 53.5, 2 41.7, [3] 40.2, 4 44.0
+// us; 8192 x 8192 (131) 1 55.4, 2 59.1, [3] 51.9, 4 54.5; 2048 x 5632 (33) 4 26.1, 6 25.5, [7] 24.8, 8 25.2; 1024 x 8192 (17),
+// 33 tokens, 8 24.9, 12 23.1, [15] 23.2, 16 25.5; 4096 x 11008 with 4-bit states (two-word blocks) 1 61.3, [2] 59.6, 4 63.7.
+// Long prompts, whose activation workgroups fill the chip beside, hardly differ: 4096 x 11008, 2048 tokens, 2 180.4, [3] 179.9,
+// 8 183.5; 8192 x 8192, 513 tokens, 2 131.9, [3] 127.3.
+static inline uint32_t skl_rebuild_segments(uint32_t n_blocks, uint32_t n_words, uint64_t table_bytes, uint32_t cols)
+{
+    const double stage = 3.7 / 65536 * table_bytes / n_blocks, rebuild = 84.0 / 1024 * n_words / n_blocks * cols;
+    uint32_t best = 1;
+    double least = HUGE_VAL;
+    for (uint32_t n = std::min(cols, 2u); n <= std::min(cols, 32u); ++n) {
+        const double t = (double)(((uint64_t)n_blocks * n + 255) / 256) * (stage + rebuild / n);
+        if (t < least) {
+            least = t;
+            best = n;
+        }
+    }
+    return best;
+}
+
 // ---- rounding of float32 sums ----
 // The variance of an output's rounding errors for a way of adding up its products, in units of four roundings of the result
 // (a matrix instruction rounds its sums once per eight channels, as the errors of layers of all sizes show): a chain over a

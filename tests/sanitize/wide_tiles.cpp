@@ -1,6 +1,6 @@
 // Whole-tile splits of staged calls over random layers, token counts and workspaces: every tile of the call belongs to one
 // workgroup and round, the tiles cover the outputs, their weight words and first chains fit the room, and the float32 sums
-// are rounded no more than those of the shared tiles they replace.  Host only; prints the first violation.
+// are rounded no more than those of the shared tiles they replace; segments of the rebuild launch.  Host only; prints the first violation.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -83,6 +83,10 @@ int main()
             CHECK((many * more + (cb - many) * one) / cb <= shared_roundings(shared, wide) + 0.4);
         }
         divided[cb] += w.split > 0;
+        // the rebuild launch: every segment has outputs; and 131 blocks of 8192 outputs don't start a second round for six of them
+        const uint32_t cols = (out + 255) / 256, seg = skl_rebuild_segments(nb, 8 * nb, 65536ull * nb, cols);
+        CHECK(seg >= 1 && seg <= cols);
+        CHECK(skl_rebuild_segments(131, 8 * 131, 65536ull * 131, 32) == 3);
         CHECK(sp.n_col * cb * 32 >= out && (sp.n_col - 1) * cb * 32 < out);
         CHECK(sp.m_tiles * 256 >= tokens && (sp.m_tiles - 1) * 256 < tokens);
         std::vector<uint8_t> done((size_t)sp.n_col * sp.m_tiles, 0);
