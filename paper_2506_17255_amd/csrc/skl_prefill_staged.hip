@@ -337,9 +337,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // their products, into registers that the column before has left.  A stage's buffer is therefore read until its last
 // column, and the copies issued during a stage go to the buffer of the stage before it.
 // CHAINS: the products of an output go through several chains of float32 sums, one after the other, where shared tiles would
-// have had as many.  Narrow tiles keep the sum of the earlier chains in as many registers as the accumulators, wider ones,
-// which have none left, write the first chain of some columns to the workspace and read it back at the end: 4096 x 11008, 5 of
-// 11 columns, 167 -> 176 us for the whole call, 8192 x 28672, 2 of 10, 812 -> 827.
+// have had as many.  Narrow tiles keep the sum of the earlier chains in as many registers as the accumulators; wider ones,
+// which have none left, write the first chain of some columns to the workspace, a column per 64-channel block, and read it
+// back at the end, where all workgroups do so at once: 4096 x 11008, 5 of 11 columns (42 MB), 177 -> 186 us for the whole call,
+// 8192 x 28672, 2 of 10, 831 -> 837 (847 with all columns written at the same block).
 struct WideArgs {
     const uint4 *Xp;                    // activation words: [256-token tile][32-channel step][SG_STEP_WORDS]
     const uint4 *Wp;                    // weight words: [output tile][32-channel step][2 * CB blocks of 16 outputs][64]
@@ -460,9 +461,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
         } else {
             uint32_t st = 0;
-            const uint32_t n = p.chains + (HELD ? p.body < p.KB : 0);
+            const uint32_t n = HELD ? p.chains + (p.body < p.KB) : p.split + 1;
             for (uint32_t i = 1; i <= n; ++i) {
-                for (const uint32_t end = i <= p.chains ? i * p.body / p.chains * 2 : n_st; st < end; st += 2) {
+                uint32_t end = n_st;
+                if (HELD ? i <= p.chains : i < n) end = 2 * (HELD ? i * p.body / p.chains : skl_first_chain_end(p.KB, p.split, i - 1, wg));
+                for (; st < end; st += 2) {
                     stage(st, c0);
                     stage(st + 1, c1);
                 }
@@ -490,12 +493,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                         asm volatile("");
                         each([&](float4v &s, float4v &a) { s += a; a = zero; });
                     }
-                } else if (i < p.chains) {                      // (the stores only make the next waits for copies longer)
+                } else if (i < n) {                             // (the stores only make the next waits for copies longer)
                     uint32_t ln = lane;
                     asm volatile("" : "+v"(ln));
 #pragma unroll
                     for (int c = 0; c < CB; ++c)
-                        if ((uint32_t)c < p.split) {
+                        if ((uint32_t)c + 1 == i) {
 #pragma unroll
                             for (int r = 0; r < 4; ++r) {
                                 part[(c * 4 + r) * 64 + ln] = acc[r][c];
@@ -505,16 +508,31 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 }
             }
         }
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __syncthreads();                                        // nothing on its way into LDS, nobody reads it: the epilogue may use it
+        // the first chains, two columns at a time into the registers that the operand words have left: the first two are on
+        // their way while the workgroup meets (not at 352 outputs, where they would spill)
+        float4v first[CHAINS && !HELD ? 2 : 1][4];
         uint32_t ln = lane;
         asm volatile("" : "+v"(ln));
+        auto request = [&](int c0) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) first[c][r] = part[(min(c0 + c, (int)p.split - 1) * 4 + r) * 64 + ln];
+        };
+        if constexpr (CHAINS && !HELD && CB < 11) request(0);
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __syncthreads();                                        // nothing on its way into LDS, nobody reads it: the epilogue may use it
         if constexpr (CHAINS && !HELD) {
 #pragma unroll
-            for (int c = 0; c < CB; ++c)
-                if ((uint32_t)c < p.split) {
+            for (int c0 = 0; c0 < CB; c0 += 2)
+                if ((uint32_t)c0 < p.split) {
+                    if (c0 || CB == 11) request(c0);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[r][c] += part[(c * 4 + r) * 64 + ln];
+                    for (int c = 0; c < 2 && c0 + c < CB; ++c)
+                        if ((uint32_t)(c0 + c) < p.split) {
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) acc[r][c0 + c] += first[c][r];
+                        }
                 }
         }
         const uint32_t t0 = tile_m * GM_MT + wm * 64, o0 = tile_n * (CB * 32) + wn * (CB * 16);

@@ -318,15 +318,23 @@ struct WideSplit {
 // Bytes of workspace for the first chains of `split` columns, wider tiles: 256 workgroups x 8 wavefronts x 4 KiB each.
 static inline uint64_t skl_wide_part_bytes(const WideSplit &w) { return w.cb > SW_HELD_CB ? (uint64_t)w.split << 23 : 0; }
 
+// Blocks of the first chain of column c of `split` through memory, in workgroup wg of an XCD: around the middle, but not all at
+// the same time (4096 x 11008, 2048 tokens, 42 MB in one go cost the call 5 us more).
+__host__ __device__ static inline uint32_t skl_first_chain_end(uint32_t nb, uint32_t split, uint32_t c, uint32_t wg)
+{
+    const int end = (int)(nb - split) / 2 + (int)c + ((int)(wg & 7) - 3) * (int)nb / 64;
+    return end < 1 ? 1 : end < (int)nb ? end : nb - 1;
+}
+
 // cb is 0 where the split above is estimated to be no slower, or weight words and first chains do not fit `room`.
 // The estimates of the product, in us: a 64-channel block of a 256 x 256 tile on every CU takes 1.52 (f[cb] per such area;
 // narrow tiles read more operand words from LDS per product), 2.2 in a share of a tile; a round of tiles 5 to 8 more for its
 // start and its stores; a partial tile 0.05 to write and read; a further chain 0.16 per column held in registers, 1 per
 // column and 2 per round through memory; a round that leaves CUs idle runs at a higher clock.
 // Whole calls, shared tiles / whole ones by cb, in one chain, then as they run (2048 tokens unless said): 4096 x 11008 224 /
-// 4 188, 6 182, 8 198, 11 167, 172 us; 4096 x 4096 81 / 4 76; 2048 x 5632, 1500 tokens, 75 / 6 53, 57; 1024 x 2048 42 / 4 28, 30;
-// 3000 x 7001, 1024 tokens, 95 / 4 60, 64; 8192 x 28672 852 / 4 900, 6 829, 8 835, 10 812, 827, 11 834; 4096 x 11008, 777
-// tokens, 164 / 6 102, 105; 8192 x 3000, 1300 tokens, 136 / 4 110, 111; 4096 x 2048, 600 tokens, 49 / 4 53, 61 in twelve chains.
+// 4 188, 6 182, 8 198, 11 171, 180 us; 4096 x 4096 81 / 4 76; 2048 x 5632, 1500 tokens, 76 / 6 51, 57; 1024 x 2048 42 / 4 27, 29;
+// 3000 x 7001, 1024 tokens, 95 / 4 61, 62; 8192 x 28672 845 / 4 900, 6 829, 8 835, 10 803, 811, 11 834; 4096 x 11008, 777
+// tokens, 164 / 6 102, 105; 8192 x 3000, 1300 tokens, 137 / 4 110, 112; 4096 x 2048, 600 tokens, 49 / 4 53, 61 in twelve chains.
 // tail: last blocks, those that hold the wide channels of the layer (0: it has none).
 static inline WideSplit skl_make_wide_split(uint32_t out, uint32_t nb, uint32_t tokens, uint64_t room, uint32_t tail)
 {
@@ -385,7 +393,13 @@ static inline WideSplit skl_make_wide_split(uint32_t out, uint32_t nb, uint32_t 
             c.chains = 2;
             for (c.split = 1; c.split <= w.cb; ++c.split) {
                 const double f = (double)c.split / w.cb;
-                if (Rounding{one.like + f * (two.like - one.like), one.wide + f * (two.wide - one.wide)}.within(most)) break;
+                double unlike = 0;                              // mean square of the ends' distances from the middle
+                for (uint32_t i = 0; i < 8 * c.split; ++i) {
+                    const double off = skl_first_chain_end(nb, c.split, i >> 3, i & 7) - 0.5 * nb;
+                    unlike += off * off / (8 * c.split);
+                }
+                unlike *= 2.0 / nb;
+                if (Rounding{one.like + f * (two.like + unlike - one.like), one.wide + f * (two.wide + unlike - one.wide)}.within(most)) break;
             }
             if (c.split > w.cb) continue;
             more = (2.0 + c.split) * rounds;

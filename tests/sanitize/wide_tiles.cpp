@@ -77,7 +77,17 @@ int main()
         const G3Split shared = skl_make_split(out, nb, tokens, true);
         for (const bool wide : {false, true}) {
             if (wide && !tail) continue;
-            const double one = roundings({nb}, nb, wide), more = roundings(chains, nb, wide, w.body < nb && w.join, w.body < nb);
+            const double one = roundings({nb}, nb, wide);
+            double more = 0;
+            if (cb <= SW_HELD_CB || !w.split)
+                more = roundings(chains, nb, wide, w.body < nb && w.join, w.body < nb);
+            else
+                for (uint32_t c = 0; c < w.split; ++c)
+                    for (uint32_t wg = 0; wg < 32; ++wg) {
+                        const uint32_t end = skl_first_chain_end(nb, w.split, c, wg);
+                        CHECK(end >= 1 && end < nb && (c == 0 || end >= skl_first_chain_end(nb, w.split, c - 1, wg)));
+                        more += roundings({end, nb - end}, nb, wide) / (32 * w.split);
+                    }
             const uint32_t many = w.split ? w.split : cb;
             // (the planner counts a chain of l blocks as l^2, here it is l^2 + l / 8, and the ends of chains on the mean)
             CHECK((many * more + (cb - many) * one) / cb <= shared_roundings(shared, wide) + 0.4);
