@@ -305,7 +305,8 @@ SKL_API skl_status_t sketch_linear_gemm(const skl_layer_t *layer, const void *X,
  * Staged calls of more than 128 tokens in one slab may take whole tiles of another
  * width (256 tokens x 128 to 352 outputs) instead where those fit the chip
  * better; this listing then shows the split that such a call would have with
- * tiles of 256 outputs.
+ * tiles of 256 outputs.  The same holds for calls of up to 512 tokens that run
+ * in one pass (skl_info_t, prefill_kernel): they have no tiles of either kind.
  * *n_segments receives the number of segments (also when it exceeds
  * `capacity`; then only the first `capacity` are written).  `shape` (HOST,
  * 6 words, may be NULL) receives workgroups per XCD, partial tiles per XCD,

@@ -77,28 +77,31 @@ def test_activation_packing_of_the_staged_prefill(in_f, tokens, ldx_pad, wide_sh
 
 @pytest.mark.parametrize("tokens", [1, 16, 17, 64, 65, 100, 128, 129])
 @pytest.mark.parametrize("in_f,out_f,ldy_pad,y_dt", [
-    (256, 300, 0, "f32"),       # shares of fewer than eight blocks: one per tile, stored without partials; ragged outputs
+    # (staged) shares of fewer than eight blocks: one per tile, stored without partials; ragged outputs
+    (256, 300, 0, "f32"),
     (1030, 264, 3, "bf16"),     # four shares per tile, rows of Y not on 16-byte boundaries, ragged last block
     (2048, 1024, 0, "f16"),     # eight shares per tile
     (520, 520, 8, "f32"),       # two shares of four and five blocks
 ])
 def test_short_prompts(in_f, out_f, ldy_pad, y_dt, tokens):
-    """Calls of at most 128 tokens (tiles of 64 and of 128 tokens) against the fused kernel, which other calls of
-    these layers take, and the oracle; 129 tokens: the first call of the other path."""
+    """Calls of at most 128 tokens, the way the library chooses (mostly one pass) and staged (tiles of 64 and of 128 tokens),
+    against the fused kernel, which other calls of these layers may take, and the oracle; 129 tokens: the first call of the
+    other rules."""
     rng = np.random.default_rng(in_f + out_f + tokens)
     sk = row_layer(6, in_f, out_f, 4, np.where(rng.random(in_f) < 0.02, 20, 9))
     X = wk.f32_to_bf16_bits(rng.standard_normal((tokens, in_f)).astype(np.float32))
     ref = oracle.linear(oracle.query(sk), X, x_kind="bf16")
     # one rounding of the result: half a unit of the last place, at most 2^-8 (bf16) and 2^-11 (f16) relative
     tol = {"f32": SUM_TOL, "f16": 2.0**-11, "bf16": 2.0**-8}[y_dt]
-    with GpuLayer(sk) as g, GpuLayer(sk, skl.FLAG_FUSED_PREFILL) as f:
+    with GpuLayer(sk) as g, GpuLayer(sk, skl.FLAG_FUSED_PREFILL) as f, GpuLayer(sk, skl.FLAG_STAGED_PREFILL) as st:
         assert g.info["prefill_kernel"] == skl.SKL_PREFILL_FUSED
         need, fused = (skl.sketch_linear_workspace_bytes(h.handle, 1, tokens) for h in (g, f))
         assert (need != fused) == (tokens <= 128)       # the way the call goes, told by the workspace it asks for
-        y, other = (h.gemm(X, "bf16", y_dt, ldy=out_f + ldy_pad) for h in (g, f))
-        assert np.array_equal(y, g.gemm(X, "bf16", y_dt, ldy=out_f + ldy_pad))
+        y, other, staged = (h.gemm(X, "bf16", y_dt, ldy=out_f + ldy_pad) for h in (g, f, st))
+        for h, v in ((g, y), (st, staged)):
+            assert np.array_equal(v, h.gemm(X, "bf16", y_dt, ldy=out_f + ldy_pad))
     assert y.shape == ref.shape
-    for v in (y, other):
+    for v in (y, other, staged):
         assert rel_fro(v, ref) <= tol, rel_fro(v, ref)
 
 
@@ -164,8 +167,9 @@ def test_short_prompts_in_a_workspace_of_the_fused_kernel(tokens, bits):
     (520, 777, 4, (9, 24), 16, 512, "f16", "f32", 0),               # four, all full
 ])
 def test_prompts_in_one_pass(in_f, out_f, d, widths, bits, tokens, x_dt, y_dt, ldy_pad):
-    """Against the oracle and the staged kernel, twice bit for bit.  Up to 128 tokens the way the call goes shows in the
-    workspace: the weight words that the staged kernel would leave at its end are not written."""
+    """Against the oracle and the staged kernel, twice bit for bit.  The way the call goes shows in the workspace (the weight
+    words that the staged kernel would leave at its end are not written) or, where the workspace is the fused kernel's or ends
+    in expanded tables, in sums that are neither that kernel's nor the staged one's to the last bit."""
     rng = np.random.default_rng(in_f + out_f + tokens)
     A, C = hash_params(rng, d)
     K = np.where(rng.random(in_f) < 0.03, rng.choice(widths[1:], in_f), widths[0]).astype(np.uint32)
@@ -179,12 +183,15 @@ def test_prompts_in_one_pass(in_f, out_f, d, widths, bits, tokens, x_dt, y_dt, l
     ref = matmul_f64(W_hat, X if x_dt == "bf16" else X.view(np.float16), x_dt)
     # float32 sums of in_f exact products, then one rounding to the output type
     tol = SUM_TOL + {"f32": 0.0, "f16": 2.0**-11, "bf16": 2.0**-8}[y_dt]
-    with GpuLayer(sk) as g, GpuLayer(sk, skl.FLAG_STAGED_PREFILL) as st:
+    with GpuLayer(sk) as g, GpuLayer(sk, skl.FLAG_STAGED_PREFILL) as st, GpuLayer(sk, skl.FLAG_FUSED_PREFILL) as fu:
         ws, need = g.workspace(1, tokens)
         ws.fill_(0xA5)
         y = g.gemm(X, x_dt, y_dt, ldy=out_f + ldy_pad)
         if tokens <= 128 and bits == 16:
             assert bool((ws[need - 4096:need] == 0xA5).all())
+        else:
+            exact = g.gemm(X, x_dt, "f32")
+            assert not any(np.array_equal(exact, h.gemm(X, x_dt, "f32")) for h in (st, fu))
         assert np.array_equal(y, g.gemm(X, x_dt, y_dt, ldy=out_f + ldy_pad))
         other = st.gemm(X, x_dt, y_dt, ldy=out_f + ldy_pad)
     for v in (y, other):
@@ -207,17 +214,18 @@ def test_prompts_that_stay_staged(in_f, out_f, d, widths, tokens):
 
 
 @pytest.mark.parametrize("in_f,out_f,tokens,x_dt,y_dt,ldy_pad", [
-    (64, 600, 300, "bf16", "f32", 0),           # tiles of 128 outputs; one 64-channel block: fewer stages than the pipeline holds
-    (264, 3001, 600, "bf16", "bf16", 0),        # of 128; rows of Y not on 16-byte boundaries, ragged last tile and token tile
-    (200, 5700, 2000, "f16", "f16", 4),         # of 192
-    (128, 28672, 300, "bf16", "bf16", 0),       # of 224
-    (100, 20000, 520, "bf16", "f32", 0),        # of 256
-    (200, 8200, 2000, "bf16", "bf16", 0),       # of 320
-    (200, 11008, 2048, "bf16", "f32", 0),       # of 352: every CU one tile
-    (200, 12000, 2048, "f16", "bf16", 8),       # of 192, two tiles per workgroup
+    (64, 600, 300, "bf16", "f32", 0),           # fewer stages than the pipeline holds
+    (264, 3001, 600, "bf16", "bf16", 0),        # rows of Y not on 16-byte boundaries, ragged last tile and token tile
+    (200, 5700, 2000, "f16", "f16", 4),
+    (128, 28672, 300, "bf16", "bf16", 0),
+    (100, 20000, 520, "bf16", "f32", 0),
+    (200, 8200, 2000, "bf16", "bf16", 0),
+    (200, 11008, 2048, "bf16", "f32", 0),
+    (200, 12000, 2048, "f16", "bf16", 8),
 ])
 def test_whole_tiles_of_staged_prompts(in_f, out_f, tokens, x_dt, y_dt, ldy_pad):
-    """Every width of the whole-tile product, twice bit for bit, all outputs against a product in 64 bits."""
+    """Staged products of few channels and all element types, twice bit for bit, all outputs against a product in 64 bits.
+    (Which way such calls go: test_ways_of_staged_prompts.)"""
     rng = np.random.default_rng(in_f + out_f + tokens)
     A, C = hash_params(rng, 3)
     K = np.where(rng.random(in_f) < 0.03, 24, 9).astype(np.uint32)

@@ -278,9 +278,9 @@ def test_gemm_identity_probe_is_exact(name, flags):
 
 @pytest.mark.parametrize("flags", [skl.FLAG_FUSED_PREFILL, skl.FLAG_STAGED_PREFILL])
 def test_gemm_with_fewer_blocks_than_workgroups_and_a_dirty_workspace(flags):
-    """64 input channels (one channel block), 4864 outputs, 768 tokens: 57 tiles, so some XCDs finish a
-    leftover tile with a single share that covers it whole.  The workspace starts full of NaN patterns:
-    whatever the fix-up pass adds must have been written by this call."""
+    """64 input channels (one channel block), 4864 outputs, 768 tokens: 57 tiles of 256 x 256, so in the fused kernel some
+    XCDs finish a leftover tile with a single share that covers it whole (the staged call takes whole tiles of 128 outputs).
+    The workspace starts full of NaN patterns: whatever is added must have been written by this call."""
     W, sk = custom_layer("few_blocks", 64, 4864, 1, 4864, 4, [40] * 64, 21)
     W_hat = oracle.query(sk)
     rng = np.random.default_rng(79)
@@ -298,9 +298,10 @@ def test_gemm_with_fewer_blocks_than_workgroups_and_a_dirty_workspace(flags):
 
 def test_gemm_with_one_half_height_tile_per_workgroup():
     """Calls whose 128-token tiles number between 225 and 256 (here 58 token tiles x 4 output-tile columns,
-    both ragged; 160 channels are three channel blocks, the last one partly filled) take the staged
-    kernel's single-round mode: one whole tile per workgroup, no partials, no fix-up pass.  The workspace
-    starts full of NaN patterns."""
+    both ragged; 160 channels are three channel blocks, the last one partly filled) are listed in the staged
+    kernel's single-round mode: one whole tile per workgroup, no partials, no fix-up pass.  This call runs in
+    whole tiles of 256 tokens x 128 outputs all the same (test_ways_of_staged_prompts has calls that run as listed);
+    the fused kernel shares its tiles.  The workspace starts full of NaN patterns."""
     widths = np.array([30] * 120 + [140] * 40)
     np.random.default_rng(5).shuffle(widths)
     W, sk = custom_layer("half_tiles", 160, 1000, 1, 1000, 4, widths, 23)

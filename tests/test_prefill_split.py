@@ -234,7 +234,8 @@ def test_half_height_tiles_are_used_where_they_fill_the_chip_once():
 @pytest.mark.parametrize("n_tiles_out,n_blocks", [(1, 1), (1, 3), (3, 8), (16, 64), (43, 64), (64, 7), (100, 64), (127, 9), (128, 64),
                                                   (129, 448), (300, 16)])
 def test_short_prompts_are_listed_as_they_run(n_tiles_out, n_blocks, tokens):
-    """One token tile; a tile's blocks in equal shares, one workgroup each, dealt to the XCDs in turn."""
+    """As staged calls run them: one token tile; a tile's blocks in equal shares, one workgroup each, dealt to the XCDs in
+    turn.  (Calls that one pass takes over have no such split.)"""
     segs, (gx, l_max, p_cap, n_tiles, mu, mt) = split(256 * n_tiles_out - 5, n_blocks, tokens, skl.SKL_PREFILL_STAGED)
     assert (n_tiles, mu, mt) == (n_tiles_out, 1, 64 if tokens <= 64 else 128)
     shares = p_cap or 1
