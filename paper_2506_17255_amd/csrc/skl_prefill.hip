@@ -471,8 +471,8 @@ uint64_t skl_gemm_workspace_bytes(const skl_layer *L, uint32_t tokens, bool stag
 // 25, 24 / 28, 512 tokens 56 / 67; 8192 x 8192: 33 / 76, 38 / 77, 46 / 84; four-word blocks (4096 x 11008, 0.75 bit): 32 /
 // 43, 36 / 44, 48 / 48, 384 tokens 129 / 177; two-word (8192 x 28672, d = 3): 180 / 229, 198 / 233, 320 / 234.
 // The call takes only as few block groups as keep the rounding of its sums at that of the kernel it replaces (skl_split.h):
-// with fewer, 4096 x 11008 at 256 tokens took 64 us at a relative error of 6.4e-8 (fused 5.6e-8, now 5.5e-8), 4096 x 4096
-// at 512 42 us, and 1048 x 2384, equal 4-bit channels, 473 tokens, 28 us at 1.13e-7 (1.07e-7, now 30 us at 1.05e-7).
+// with fewer, 4096 x 11008 at 256 tokens took 64 us at a relative error of 6.4e-8 (fused 5.63e-8, now 75 us at 5.51e-8), 4096
+// x 4096 at 512 42 us, and 1048 x 2384, equal 4-bit channels, 473 tokens, 28.7 us at 1.13e-7 (1.07e-7, now 30 us at 9.8e-8).
 static bool takes_prompt_kernel(const skl_layer *L, uint32_t tokens, bool staged, PromptPlan &plan)
 {
     if (!L->gemm_prompt || tokens > SKL_PROMPT_MAX_TOKENS || (!staged && tokens <= SKL_SHORT_TOKENS)) return false;

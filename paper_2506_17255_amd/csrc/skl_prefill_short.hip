@@ -216,7 +216,8 @@ __global__ __launch_bounds__(RB >= 6 ? 512 : 768) void k_prompt_gemm(PromptArgs 
 
 // y = the sum of the P partials of every output, in group order: a wavefront adds one 16 x 16 block, four partials in
 // flight, and the workgroup's 16 x 64 outputs are turned round in LDS to leave as 8- or 16-byte pieces.  Grid (ceil(out /
-// 64), 16-token blocks).
+// 64), 16-token blocks).  The additions are in 64 bits, which the memory-bound kernel does not notice: without roundings of
+// their own fewer groups do (skl_prompt_rounding).
 __global__ __launch_bounds__(256) void k_prompt_reduce(const float *__restrict__ parts, uint32_t T, uint32_t P, uint32_t nw, uint32_t rows, void *Y, uint32_t y_dt,
                                                        uint32_t ldy, uint32_t tokens, uint32_t out)
 {
@@ -224,7 +225,11 @@ __global__ __launch_bounds__(256) void k_prompt_reduce(const float *__restrict__
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, rb = blockIdx.y;
     const uint32_t cb = blockIdx.x * 4 + wave, tile = cb / (2 * nw), c = cb - tile * 2 * nw, tm = rb / rows * T + tile;
     const size_t stride = (size_t)rows * 2 * nw * 64;           // float4v per group
-    float4v s = {0.f, 0.f, 0.f, 0.f};
+    double s[4] = {0, 0, 0, 0};
+    auto add = [&](const float4v &v) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] += (double)v[i];
+    };
     if (cb * 16 < out) {
         const float4v *src = reinterpret_cast<const float4v *>(parts) + (size_t)tm * P * stride + ((size_t)(rb % rows) * 2 * nw + c) * 64 + lane;
         uint32_t g = 0;
@@ -233,12 +238,12 @@ __global__ __launch_bounds__(256) void k_prompt_reduce(const float *__restrict__
 #pragma unroll
             for (int k = 0; k < 4; ++k) v[k] = src[(size_t)(g + k) * stride];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) s += v[k];
+            for (int k = 0; k < 4; ++k) add(v[k]);
         }
-        for (; g < P; ++g) s += src[(size_t)g * stride];
+        for (; g < P; ++g) add(src[(size_t)g * stride]);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) sm[(lane >> 4) * 4 + i][wave * 16 + (lane & 15)] = s[i];
+    for (int i = 0; i < 4; ++i) sm[(lane >> 4) * 4 + i][wave * 16 + (lane & 15)] = (float)s[i];
     __syncthreads();
     const uint32_t row = threadIdx.x >> 4, o = blockIdx.x * 64 + (threadIdx.x & 15) * 4, t = rb * 16 + row;
     if (t >= tokens || o >= out) return;

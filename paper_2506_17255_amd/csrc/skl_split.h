@@ -302,6 +302,14 @@ static inline Rounding skl_chain_rounding(uint32_t blocks, double nb, uint32_t n
     return {chains + own + nb * tail * ((join ? 2.0 * body : 0.0) + tail) * unit * unit,
             chains + own + (tail ? (join ? 0 : SKL_LAST_OF_TAIL) : n > 1 ? SKL_LAST_ADDITION : 0)};
 }
+// n equal chains whose sums are added up without roundings but the last (one pass).
+static inline Rounding skl_prompt_rounding(uint32_t blocks, double nb, uint32_t n)
+{
+    const uint32_t l = blocks / n, longer = blocks % n;
+    const double like = nb * ((double)longer * (2 * l + 1) + (double)n * l * l) / ((double)blocks * blocks) + (n > 1 ? 0.25 : 0);
+    return {like, like + (n > 1 ? SKL_LAST_ADDITION : 0)};
+}
+
 // Whole tiles of another width instead: 256 tokens x 32 * cb outputs, one tile after another per workgroup (the k-th of XCD
 // x by workgroup k % 32), no partial tiles, no fix-up.  An output of a shared tile is the sum of several chains of products,
 // one of a whole tile would be a single chain with up to three times the rounding error (4096 x 2048, 600 tokens, channels
@@ -454,7 +462,7 @@ static inline PromptPlan skl_make_prompt_plan(const PromptLayer &L, uint32_t tok
     uint64_t groups = 0;                                        // bit P - 1: P groups may be taken
     uint32_t least = 0;
     for (uint32_t P = 1; P <= std::min(L.n_blocks, 64u); ++P)
-        if (skl_chain_rounding(L.n_blocks, L.kb, P, 0, false).within(most)) {
+        if (skl_prompt_rounding(L.n_blocks, L.kb, P).within(most)) {
             groups |= 1ull << (P - 1);
             if (!least) least = P;
         }

@@ -33,7 +33,7 @@ int main()
             ++refused;
             continue;
         }
-        const Rounding own = skl_chain_rounding(n_blocks, L.kb, p.P, 0, false);
+        const Rounding own = skl_prompt_rounding(n_blocks, L.kb, p.P);
         CHECK(own.within(most));
 
         bounded += skl_make_prompt_plan(L, tokens, room, any).P != p.P;
