@@ -11,11 +11,11 @@
 // matrix instructions of one wavefront.  The kernel is that of the batched decode with up to 128 tokens instead of 16:
 // lanes are outputs, a wavefront rebuilds the operand words of 32 outputs and multiplies them with all tokens of its
 // tile, whose activation words arrive in LDS beside the table (two buffers each).
-// Bound by none of its units alone: 4096 x 11008, d = 4, 100 tokens, 250 workgroups of seven wavefronts, main kernel 28
-// us; with the copies left out 24, with the arithmetic left out 20, with neither 7 (LDS busy 0.3 of the time, matrix cores
+// Bound by none of its units alone: 4096 x 11008, d = 4, 100 tokens, 250 workgroups of seven wavefronts, main kernel 29
+// us at best (31.5 on inputs that are not in the caches); with the copies left out 24, with the arithmetic left out 20, with neither 7 (LDS busy 0.3 of the time, matrix cores
 // 0.2, vector issue 0.25): two wavefronts per SIMD meet at a barrier per block and wait for LDS together.  What helped:
 // copies issued one by one between the arithmetic instead of as a burst behind the barrier (39 -> 33, it holds the
-// wavefronts up), chunks without bounds checks (33 -> 28), the products of a pair beside the query of the next one.
+// wavefronts up), chunks without bounds checks (33 -> 29), the products of a pair beside the query of the next one.
 // Whole call (packing 4 us, reduction 6): 17 tokens 45 -> 28 us, 64 46 -> 31, 100 50 -> 38 (59 -> 36 on inputs that are
 // not in the caches), 256 88 -> 77; 8192 x 8192 17 tokens 76 -> 34, 64 77 -> 38, 100 84 -> 45; 4096 x 4096 25 -> 18, 26 -> 21,
 // 28 -> 24, 512 tokens 67 -> 56; 1024 x 2048, 300 tokens, 43 -> 20.

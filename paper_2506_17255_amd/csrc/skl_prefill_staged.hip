@@ -8,9 +8,12 @@
 //   1. k_rebuild_operands: one workgroup per (channel block, range of output tiles) stages the block's table
 //      in LDS once, runs select / gather / query / decode for all its outputs and writes the weights as
 //      16-byte matrix-core operand words, already in the order the product kernel's LDS slot has;
-//   2. k_staged_gemm: 256 tokens x 256 outputs per workgroup, a product of operand words that both come from
-//      memory (the workgroups of the first launch that do not rebuild re-order the activations).
-// The work split is that of the fused kernel, dealt by output-tile column; short prompts have one of their own.
+//   2. the product of operand words that both come from memory (the workgroups of the first launch that do not rebuild
+//      re-order the activations): k_staged_wide, whole tiles of 256 tokens x 128 to 352 outputs, for calls of more than
+//      128 tokens where those are estimated faster (skl_make_wide_split); else k_staged_gemm, tiles of 256 tokens x 256 outputs in
+//      the fused kernel's split, dealt by output-tile column, and k_staged_fixup where workgroups share tiles.  That is so for
+//      layers in several slabs, for few tiles of many channels, where a whole tile would need too many chains of sums, and
+//      for calls that fill the chip once with tiles of half the height.  Short prompts have a split of their own.
 #include "skl_prefill_common.h"
 
 namespace SKL_NS {
@@ -173,10 +176,10 @@ __device__ __forceinline__ void staged_store_rows(const float4v (&acc)[RB][CB], 
 // Short prompts (ShortSplit) take it with RB 2 or 4 for one token tile of 64 or 128 tokens: bound by the weight words,
 // each read once, and by the partials; 4096 x 11008 at 100 tokens 22 us (56 us in the fused kernel, which multiplies a
 // 256-token tile and rebuilds its weights beside it).
-// 2048 tokens x 8192 x 28672: 718 to 726 us at best = 1.32 to 1.34 PFLOP/s, 801 us with one wavefront per SIMD in the 32x32x16 form; of the
-// difference to a loop without LDS reads and copies (525 us) the reads are about 80 us and the copies 120, and on
-// all-zero data (clock not held back) the copies alone set the time: 7.6 GB through the L2s, 1.7 GB from behind
-// them, in 570 us.  4096 x 11008: 186 us (200), 4096 x 4096 in half-height tiles: 63 us (74).
+// On layers that take whole tiles now (2048 tokens), 8192 x 28672: 718 to 726 us at best = 1.32 to 1.34 PFLOP/s, 801 us with
+// one wavefront per SIMD in the 32x32x16 form; of the difference to a loop without LDS reads and copies (525 us) the reads
+// are about 80 us and the copies 120, and on all-zero data (clock not held back) the copies alone set the time: 7.6 GB
+// through the L2s, 1.7 GB from behind them, in 570 us.  4096 x 11008: 186 us (200), 4096 x 4096 in half-height tiles: 63 (74).
 #define SG_STAGES(rb) ((rb) == 8 ? 5u : (rb) == 4 ? 6u : 7u)
 #define SG_STAGE_BYTES(rb) ((rb) * 2048u + 16384u)      // (rb * 32) tokens x 32 channels, 32 channels x 256 outputs
 template <int RB, class Split>
@@ -330,8 +333,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // Y = X W on re-ordered operands, whole tiles of 256 tokens x 32 * CB outputs (the split is skl_make_wide_split).  A tile
 // that fits the chip in whole rounds needs no partial tiles: 4096 x 11008 at 2048 tokens is 256 tiles of 352 outputs instead
-// of 344 of 256, 88 of which went through 90 MB of float32 partials and a fix-up launch (product 185 us + fix-up 17 -> 131;
-// whole call 219 -> 172).
+// of 344 of 256, 88 of which went through 90 MB of float32 partials and a fix-up launch (product 186 us + fix-up 16 -> 151,
+// with the chains below 161; 138 and 140 at best).
 // As k_staged_gemm, but the eight wavefronts own 64 tokens x 16 * CB outputs each: up to 176 accumulator registers, so that
 // of a stage only the activation words are held twice; weight words are read two or three columns (of 16 outputs) ahead of
 // their products, into registers that the column before has left.  A stage's buffer is therefore read until its last
