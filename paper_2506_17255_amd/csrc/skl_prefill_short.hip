@@ -11,14 +11,12 @@
 // matrix instructions of one wavefront.  The kernel is that of the batched decode with up to 128 tokens instead of 16:
 // lanes are outputs, a wavefront rebuilds the operand words of 32 outputs and multiplies them with all tokens of its
 // tile, whose activation words arrive in LDS beside the table (two buffers each).
-// Bound by none of its units alone: 4096 x 11008, d = 4, 100 tokens, 250 workgroups of seven wavefronts, main kernel 29
-// us at best (31.5 on inputs that are not in the caches); with the copies left out 24, with the arithmetic left out 20, with neither 7 (LDS busy 0.3 of the time, matrix cores
-// 0.2, vector issue 0.25): two wavefronts per SIMD meet at a barrier per block and wait for LDS together.  What helped:
-// copies issued one by one between the arithmetic instead of as a burst behind the barrier (39 -> 33, it holds the
-// wavefronts up), chunks without bounds checks (33 -> 29), the products of a pair beside the query of the next one.
-// Whole call (packing 4 us, reduction 6): 17 tokens 45 -> 28 us, 64 46 -> 31, 100 50 -> 38 (59 -> 36 on inputs that are
-// not in the caches), 256 88 -> 77; 8192 x 8192 17 tokens 76 -> 34, 64 77 -> 38, 100 84 -> 45; 4096 x 4096 25 -> 18, 26 -> 21,
-// 28 -> 24, 512 tokens 67 -> 56; 1024 x 2048, 300 tokens, 43 -> 20.
+// Bound by none of its units alone: of 36 us for 4096 x 11008, d = 4, 100 tokens on inputs that are not in the caches (250
+// workgroups of seven wavefronts) the packing launch is 5 and the reduction 5.5; without copies the call takes 2 us less,
+// without products 4, without the query 2.4, with gathers free of bank conflicts 2, without any of these 13.  What helped: chunks
+// copied without bounds checks, an even load per stretch of code and no wait at a block's head (prompt_run).
+// Whole call against the kernels it replaces: 17 tokens 45 -> 23 us, 48 46 -> 27, 100 59 -> 35.5, 256 88 -> 71; 8192 x 8192, 128
+// tokens, 84 -> 42; 4096 x 4096, 64 tokens, 26 -> 19; 1024 x 2048, 300 tokens, 43 -> 18.5.
 namespace SKL_NS {
 
 struct PromptArgs {
@@ -46,42 +44,110 @@ __global__ __launch_bounds__(SKL_WG) void k_prompt_pack(PackArgs k, uint32_t n_r
 #define PG_X0 (2u * SKL_PBUF_DIST)      // LDS: two table buffers, two activation buffers
 #define PG_LDS(rb) (PG_X0 + 2u * (rb) * 2048u)
 
+struct PromptBlock {
+    uint32_t table_off16, K, rs, nb, chan_off;
+};
+
+// The metadata of a block, requested from an address the compiler takes to differ between the lanes: left to itself it
+// puts the words into scalar registers at once and waits out the load's latency at the head of every block.
+struct PromptBlockLoad {
+    u32x4v m;
+    uint32_t chan_off;
+    __device__ __forceinline__ void request(const skl_block_meta *bm)
+    {
+        uint32_t none = 0;
+        asm volatile("" : "+v"(none));
+        const char *at = reinterpret_cast<const char *>(bm) + none;
+        m = *reinterpret_cast<const u32x4v *>(at);
+        chan_off = reinterpret_cast<const uint32_t *>(at)[4];
+    }
+    __device__ __forceinline__ PromptBlock block() const
+    {
+        auto u = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane(v); };
+        return PromptBlock{u(m.x), u(m.y), u(m.z), u(m.w), u(chan_off)};
+    }
+};
+
 template <int D, int RB>
 struct PromptWalk {
     uint32_t b, b1, buf;                // next block, end of the group, its buffers
-    skl_block_meta bm, nx;              // metadata of block b and the one after it
+    PromptBlock bm, nx;                 // block b and the one after it
+    PromptBlockLoad ahead;              // the one after those, on its way
     uint32_t lane, wave, nw, o_base, lds0, tile_m;
     float4v acc[RB][2];
 };
 
 template <int D, int RB>
-__device__ __forceinline__ void prompt_copies(const PromptArgs &p, const PromptWalk<D, RB> &w, const skl_block_meta &bm, uint32_t buf, ChunkCopy &tab, ChunkCopy &x)
+__device__ __forceinline__ void prompt_copies(const PromptArgs &p, const PromptWalk<D, RB> &w, const PromptBlock &bm, uint32_t buf, ChunkCopy &tab, ChunkCopy &x)
 {
     tab.start(p.tables + bm.table_off16, D * bm.K * bm.rs, w.lds0 + buf * SKL_PBUF_DIST, w.wave, w.nw, w.lane);
     x.start(p.Xq + ((size_t)w.tile_m * p.n_words + (bm.chan_off >> 3)) * (RB * 16), bm.nb * (RB * 16), w.lds0 + PG_X0 + buf * (RB * 2048), w.wave, w.nw, w.lane);
 }
 
 // A run of consecutive blocks of one width class (NB words per state row): NB / 4 (at least one) steps of 32 channels
-// x two 16-output sub-blocks per block.
+// x two 16-output sub-blocks per block, a "pair" each.  A pair is gathered, queried and multiplied in three successive
+// stretches of the code, and every stretch holds the reads of one pair, the query of the pair before and the products of the
+// one before that, across the blocks: LDS, vector units and matrix cores have an even load, and the barrier that hands
+// the buffers over stands where the last pair of a block is gathered but not yet queried, so that its arithmetic covers
+// the first gathers of the next block.  Against the gathers of three pairs in flight, the first two in one burst behind
+// the barrier, and the metadata of a block waited for at its head: 4096 x 11008, whole call, 17 tokens 25.8 -> 23.4 us, 48
+// 29.1 -> 26.8, 100 37.7 -> 35.7, 256 76.7 -> 71.1; 8192 x 8192, 128 tokens, 47 -> 42.5 (the same with the burst, and the
+// barrier moved all the same: 38.2, 83 and 44.3 on the last three).
 template <int D, int RB, int NB>
 __device__ __forceinline__ void prompt_run(const PromptArgs &p, PromptWalk<D, RB> &w)
 {
     constexpr uint32_t RS = NB == 1 ? 1 : NB + 1;
-    constexpr int NH = NB == 8 ? 2 : 1, NP = 2 * NH, RING = D <= 4 || (D == 5 && RB < 8) ? 3 : 2;      // pairs whose gathers are in registers or on their way
+    constexpr int NH = NB == 8 ? 2 : 1, NP = 2 * NH;
     const uint32_t n = w.lane & 15, kg = w.lane >> 4;
     const uint32_t word = min(kg, (uint32_t)NB - 1);       // classes with fewer than 4 words: lanes past the last word re-read it, their activations count as zero
     const bool x_live = NB >= 4 || kg < (uint32_t)NB;
-    uint32_t off[2][D], K_prev = 0;
-    uint4 q[RING][D], a[NH][RB], wd[2];
-    bool carried = false;
+    const uint4 none = make_uint4(0, 0, 0, 0);
+    uint32_t off[2][D], K_prev = 0, xa = 0;
+    uint4 q[2][D], a[NH][RB], wd[2] = {none, none};
+    auto gather = [&](int pr) {
+#pragma unroll
+        for (int r = 0; r < D; ++r) q[pr & 1][r] = lds_word_at(off[pr & 1][r] + (pr >> 1) * 64);
+    };
+    auto read_a = [&](int h) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i) a[h][i] = lds_word_at(xa + h * (RB * 1024) + i * 256);
+    };
+    auto query = [&](int pr) {
+        uint4 m = q[pr & 1][0];
+#pragma unroll
+        for (int r = 1; r < D; ++r) m = pk_max_u16x8(m, q[pr & 1][r]);
+        wd[pr & 1].x = keys_to_neg_half2_mad(m.x); wd[pr & 1].y = keys_to_neg_half2_mad(m.y);
+        wd[pr & 1].z = keys_to_neg_half2_mad(m.z); wd[pr & 1].w = keys_to_neg_half2_mad(m.w);
+    };
+    auto multiply = [&](int pr) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            const uint4 ai = NB >= 4 ? a[pr >> 1][i] : keep_if(x_live, a[pr >> 1][i]);
+            w.acc[i][pr & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, ai), __builtin_bit_cast(half8v, wd[pr & 1]), w.acc[i][pr & 1], 0, 0, 0);
+        }
+    };
+    auto tail = [&]() {
+        multiply(NP - 2);
+        query(NP - 1);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // nothing is carried into the first block: its predecessor's last pairs are products of zero activations and of keys
+    // that stand for finite weights in either query mode
+#pragma unroll
+    for (int i = 0; i < RB; ++i) a[NH - 1][i] = none;
+#pragma unroll
+    for (int r = 0; r < D; ++r) q[1][r] = make_uint4(0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u);
     do {
-        wait_async_copies();
-        __syncthreads();                                        // block b has arrived, nobody reads the other buffers any more
+        // block b has arrived, nobody reads the other buffers any more
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        w.nx = w.ahead.block();
         const bool more = w.b + 1 < w.b1;
         ChunkCopy ct, cx;
         prompt_copies<D, RB>(p, w, w.nx, w.buf ^ 1, ct, cx);
         if (!more) ct.off = cx.off = 0xFFFFFFFFu;
-        const skl_block_meta n2 = p.bmeta[min(w.b + 2, w.b1 - 1)];
+        w.ahead.request(p.bmeta + min(w.b + 2, w.b1 - 1));
         if (w.bm.K != K_prev) {
             const uint32_t K = w.bm.K, Kq = K << 8;
             uint32_t ob = w.o_base;
@@ -96,73 +162,52 @@ __device__ __forceinline__ void prompt_run(const PromptArgs &p, PromptWalk<D, RB
                 }
             }
             K_prev = K;
-        } else {                                                // the other buffer
-            const uint32_t to = w.buf ? SKL_PBUF_DIST : 0u - SKL_PBUF_DIST;
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int r = 0; r < D; ++r) off[j][r] += to;
         }
-        const uint32_t xa = w.lds0 + PG_X0 + w.buf * (RB * 2048) + word * (RB * 256) + n * 16;
-        auto gather = [&](int pr) {
-#pragma unroll
-            for (int r = 0; r < D; ++r) q[pr % RING][r] = lds_word_at(off[pr & 1][r] + (pr >> 1) * 64);
-        };
-        auto read_a = [&](int h) {
-#pragma unroll
-            for (int i = 0; i < RB; ++i) a[h][i] = lds_word_at(xa + h * (RB * 1024) + i * 256);
-        };
-        auto query = [&](int pr) {
-            uint4 m = q[pr % RING][0];
-#pragma unroll
-            for (int r = 1; r < D; ++r) m = pk_max_u16x8(m, q[pr % RING][r]);
-            wd[pr & 1].x = keys_to_neg_half2_mad(m.x); wd[pr & 1].y = keys_to_neg_half2_mad(m.y);
-            wd[pr & 1].z = keys_to_neg_half2_mad(m.z); wd[pr & 1].w = keys_to_neg_half2_mad(m.w);
-        };
-        auto multiply = [&](int pr) {
-#pragma unroll
-            for (int i = 0; i < RB; ++i) {
-                const uint4 ai = NB >= 4 ? a[pr >> 1][i] : keep_if(x_live, a[pr >> 1][i]);
-                w.acc[i][pr & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, ai), __builtin_bit_cast(half8v, wd[pr & 1]), w.acc[i][pr & 1], 0, 0, 0);
-            }
-        };
+        xa = w.lds0 + PG_X0 + w.buf * (RB * 2048) + word * (RB * 256) + n * 16;
         gather(0);
-        if (RING > 2) gather(1);
-        read_a(0);
         cx.some(1);
         ct.some(2);
         __builtin_amdgcn_sched_barrier(0);
-        if (NH == 2 && carried) multiply(NP - 1);               // of the block before
+        tail();                                                 // of the block before
+        gather(1);
+        if (NH == 2) read_a(0);
+        ct.some(2);
+        cx.some(1);
         __builtin_amdgcn_sched_barrier(0);
+        multiply(NP - 1);
         query(0);
-        if (RING == 2) gather(1);
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int pr = 1; pr < NP; ++pr) {
-            if (RING > 2 && pr + 1 < NP) gather(pr + 1);
-            if (NH == 2 && pr == 1) read_a(1);
-            if (pr == 1) cx.some(1);
+        if (NH == 2) {
+            gather(2);
             ct.some(2);
             __builtin_amdgcn_sched_barrier(0);
-            multiply(pr - 1);
-            query(pr);
-            if (RING == 2 && pr + 1 < NP) gather(pr + 1);
+            multiply(0);
+            query(1);
             __builtin_amdgcn_sched_barrier(0);
+            gather(3);
+            read_a(1);
+            ct.rest();
+            cx.rest();
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(1);
+            query(2);
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
+            read_a(0);
+            ct.rest();
+            cx.rest();
         }
-        ct.rest();
-        cx.rest();
-        if (NH == 1) multiply(NP - 1);
-        carried = true;
+        const uint32_t to = w.buf ? 0u - SKL_PBUF_DIST : SKL_PBUF_DIST;     // to the other buffer
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < D; ++r) off[j][r] += to;
         w.bm = w.nx;
-        w.nx = n2;
         w.buf ^= 1;
         ++w.b;
     } while (w.b < w.b1 && w.bm.rs == RS);
-    if (NH == 2) {
-#pragma unroll
-        for (int i = 0; i < RB; ++i)
-            w.acc[i][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, a[NH - 1][i]), __builtin_bit_cast(half8v, wd[1]), w.acc[i][1], 0, 0, 0);
-    }
+    tail();
+    multiply(NP - 1);
 }
 
 // One workgroup per (block group, token tile, output tile), in that order over the XCDs: the workgroups of an XCD stage
@@ -173,11 +218,11 @@ __global__ __launch_bounds__(RB >= 6 ? 512 : 768) void k_prompt_gemm(PromptArgs 
 {
     const uint32_t q = (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);
     if (q >= p.T * p.M * p.P) return;
-    const uint32_t g = q / (p.T * p.M), tm = q - g * p.T * p.M, tile_m = tm / p.T, tile = tm - tile_m * p.T;
-    const uint32_t b0 = g * p.n_blocks / p.P;
+    const uint32_t g = __builtin_amdgcn_readfirstlane(q / (p.T * p.M)), tm = q - g * p.T * p.M, tile_m = __builtin_amdgcn_readfirstlane(tm / p.T), tile = tm - tile_m * p.T;
+    const uint32_t b0 = __builtin_amdgcn_readfirstlane(g * p.n_blocks / p.P);
     PromptWalk<D, RB> w;
     w.b = b0;
-    w.b1 = (g + 1) * p.n_blocks / p.P;
+    w.b1 = __builtin_amdgcn_readfirstlane((g + 1) * p.n_blocks / p.P);
     w.buf = 0;
     w.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     w.nw = blockDim.x >> 6;
@@ -189,8 +234,9 @@ __global__ __launch_bounds__(RB >= 6 ? 512 : 768) void k_prompt_gemm(PromptArgs 
     for (int i = 0; i < RB; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) w.acc[i][j] = (float4v){0.f, 0.f, 0.f, 0.f};
-    w.bm = p.bmeta[b0];
-    w.nx = p.bmeta[min(b0 + 1, w.b1 - 1)];
+    w.ahead.request(p.bmeta + b0);
+    w.bm = w.ahead.block();
+    w.ahead.request(p.bmeta + min(b0 + 1, w.b1 - 1));
     {
         ChunkCopy ct, cx;
         prompt_copies<D, RB>(p, w, w.bm, 0, ct, cx);

@@ -201,6 +201,31 @@ def test_prompts_in_one_pass(in_f, out_f, d, widths, bits, tokens, x_dt, y_dt, l
         assert np.isfinite(v.astype(np.float32)).all() and rel_fro(v, ref) <= tol, rel_fro(v, ref)
 
 
+@pytest.mark.parametrize("query_mode", [0, 1])
+@pytest.mark.parametrize("in_f,out_f,d,widths,tokens", [
+    (777, 3001, 4, (9, 200, 330, 1000), 30),    # all widths of blocks, a group with one block of each: what a run of blocks
+    (777, 3001, 3, (9, 250, 500, 1300), 60),    # begins with (products of nothing) and ends with, in every tile of tokens
+    (777, 3001, 2, (9, 400, 800, 2000), 90),
+    (777, 3001, 1, (9, 800, 1700, 4000), 120),
+    (1500, 6000, 8, (30, 60, 100, 450), 20),
+])
+def test_one_pass_runs_of_blocks(in_f, out_f, d, widths, tokens, query_mode):
+    """Runs of blocks of one width class begin with an empty pipeline and carry their last products over a barrier."""
+    rng = np.random.default_rng(d + tokens)
+    A, C = hash_params(rng, d)
+    K = np.where(rng.random(in_f) < 0.06, rng.choice(widths[1:], in_f), widths[0]).astype(np.uint32)
+    states = (rng.standard_normal(int(K.sum()) * d) * 0.02).astype(np.float16).view(np.uint16)
+    sk = oracle.Sketch(in_f, out_f, 1, out_f, d, A, C, K, states)
+    x = rng.standard_normal((tokens, in_f)).astype(np.float16).view(np.uint16)
+    ref = matmul_f64(oracle.query(sk, query_mode), x.view(np.float16), "f16")
+    with GpuLayer(sk, query_mode=query_mode) as g:
+        ws, need = g.workspace(1, tokens)
+        ws.fill_(0xA5)
+        y = g.gemm(x, "f16", "f32")
+        assert bool((ws[need - 4096:need] == 0xA5).all())       # (the staged kernel would leave weight words there)
+    assert np.isfinite(y).all() and rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
+
+
 @pytest.mark.parametrize("in_f,out_f,d,widths,tokens", [
     (688, 6104, 2, (95, 381), 465),         # whole tiles are faster than a pass over the tables per token tile
 ])
