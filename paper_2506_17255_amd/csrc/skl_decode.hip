@@ -382,94 +382,109 @@ __device__ __forceinline__ void gn_offsets(const HashArgs &h, uint32_t o_base, u
     }
 }
 
-// one block: NB words = NB/4 (at least one) slabs of 32 channels x 4 output sub-blocks
-template <int D, int NB, uint32_t BUF_OFF>
-__device__ __forceinline__ void gn_block(const uint32_t (&off)[4][D], uint32_t x_addr, bool x_live, float4v (&acc)[4])
-{
-    constexpr int NH = NB == 8 ? 2 : 1;
-    constexpr int NP = 4 * NH;                              // (slab, sub-block) pairs
-    uint4 a[NH];
-#pragma unroll
-    for (int hh = 0; hh < NH; ++hh) a[hh] = keep_if(x_live, lds_word_at(x_addr + hh * 64));
-    constexpr bool PIPE = D <= 5;                           // gathers of the next pair in flight during the arithmetic (registers allowing)
-    uint4 q[PIPE ? 2 : 1][D];
-#pragma unroll
-    for (int r = 0; r < D; ++r) q[0][r] = lds_word_at(off[0][r] + BUF_OFF);
-#pragma unroll
-    for (int pr = 0; pr < NP; ++pr) {
-        if (PIPE && pr + 1 < NP) {
-#pragma unroll
-            for (int r = 0; r < D; ++r) q[(pr + 1) & 1][r] = lds_word_at(off[(pr + 1) & 3][r] + BUF_OFF + ((pr + 1) >> 2) * 64);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        uint4 m = q[PIPE ? pr & 1 : 0][0];
-#pragma unroll
-        for (int r = 1; r < D; ++r) m = pk_max_u16x8(m, q[PIPE ? pr & 1 : 0][r]);
-        uint4 w;
-        w.x = keys_to_neg_half2_mad(m.x); w.y = keys_to_neg_half2_mad(m.y);
-        w.z = keys_to_neg_half2_mad(m.z); w.w = keys_to_neg_half2_mad(m.w);
-        acc[pr & 3] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, a[pr >> 2]), __builtin_bit_cast(half8v, w),
-                                                              acc[pr & 3], 0, 0, 0);
-        if (PIPE && pr + 1 < NP) __builtin_amdgcn_sched_barrier(0);
-        if (!PIPE && pr + 1 < NP) {
-#pragma unroll
-            for (int r = 0; r < D; ++r) q[0][r] = lds_word_at(off[(pr + 1) & 3][r] + BUF_OFF + ((pr + 1) >> 2) * 64);
-        }
-    }
-}
-
 struct GnWalk {
-    const uint4 *sm_meta;    // metadata of the group's blocks in LDS
     uint32_t xs_addr;        // LDS address of this lane's activation row (batch row lane % 16)
     uint32_t nblk, bi;
-    uint32_t K, rs, chan_off;
+    RowBlock cur;            // current block
+    BlockAhead ahead;        // the one after it, on its way
     uint32_t lane, o_base;
     bool wave_live;
 };
 
+// (chunks without a bounds check per lane: gate/up of 4096 x 11008, batch 16, 44.4 -> 43.7 us, 8192 x 28672, batch 8, 116
+// -> 112, 8192 x 8192, batch 16, 28.1 -> 27.0)
+template <int D>
+__device__ __forceinline__ void gn_copy(uint4 *dst, const StreamArgs &p, const RowBlock &b, uint32_t lane)
+{
+    ChunkCopy copy;
+    copy.start(p.r.tables + b.table_off16, D * b.K * b.rs, (uint32_t)(uintptr_t)(lds_void *)dst, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
+               blockDim.x >> 6, lane);
+    copy.rest();
+}
+
+// A run of consecutive blocks of one width class: NB / 4 (at least one) slabs of 32 channels x 4 output sub-blocks per
+// block, a "pair" each.  The gathers of the next pair are on their way during the arithmetic of one, across the blocks: the
+// barrier that hands the buffers over stands where the last pair of a block is gathered but not yet worked off, the
+// metadata of a block arrives a block ahead and its state-row addresses are formed while its table is on its way.  Against
+// a drained wavefront and two LDS reads of metadata at every barrier: 11008 x 4096, batch 8, 19.6 -> 18.6 us, gate/up of
+// 4096 x 11008, batch 16, 40.5 -> 39.5, 8192 x 8192, batch 16, 30.2 -> 27.3, 8192 x 28672, batch 8, 102 -> 88 (two or three pairs
+// ahead, where 8 or 12 wavefronts have the registers: the same or 1 % more).
 template <int D, int NB>
 __device__ __forceinline__ void gn_run(const StreamArgs &p, const StreamCtx &c, GnWalk &w, float4v (&acc)[4])
 {
-    const uint32_t nw = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr int NH = NB == 8 ? 2 : 1, NP = 4 * NH, AHEAD = D <= 4 ? 1 : 0, RING = AHEAD + 1;      // (128 registers per lane: more rows spill)
     uint4 *const buf0 = smem, *const buf1 = smem + SKL_PBUF_DIST / 16;
     uint32_t off[4][D];
     uint32_t K_prev = 0;
-    const uint32_t rs_run = w.rs;
+    const uint32_t rs_run = w.cur.rs;
     const bool x_live = NB >= 4 || (w.lane >> 4) < (uint32_t)NB;
-    // (chunks without a bounds check per lane: gate/up of 4096 x 11008, batch 16, 44.4 -> 43.7 us, 8192 x 28672, batch 8, 116
-    // -> 112, 8192 x 8192, batch 16, 28.1 -> 27.0)
-    auto copy_next = [&](uint4 *dst, const uint4 *src, uint32_t n16) {
-        ChunkCopy copy;
-        copy.start(src, n16, (uint32_t)(uintptr_t)(lds_void *)dst, wave, nw, w.lane);
-        copy.rest();
+    // nothing is carried into the first block: products of zero activations and of keys that stand for finite weights in
+    // either query mode
+    uint4 a[NH], last = make_uint4(0, 0, 0, 0), q[RING][D];
+#pragma unroll
+    for (int i = 0; i < RING; ++i)
+#pragma unroll
+        for (int r = 0; r < D; ++r) q[i][r] = make_uint4(0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u);
+    auto work_off = [&](int pr, const uint4 &x) {
+        uint4 m = q[pr % RING][0];
+#pragma unroll
+        for (int r = 1; r < D; ++r) m = pk_max_u16x8(m, q[pr % RING][r]);
+        uint4 v;
+        v.x = keys_to_neg_half2_mad(m.x); v.y = keys_to_neg_half2_mad(m.y);
+        v.z = keys_to_neg_half2_mad(m.z); v.w = keys_to_neg_half2_mad(m.w);
+        acc[pr & 3] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, x), __builtin_bit_cast(half8v, v), acc[pr & 3], 0, 0, 0);
     };
     auto step = [&](auto bo_tag) {
         constexpr uint32_t BO = decltype(bo_tag)::value;
-        uint4 *nxt = BO || !c.two_bufs ? buf0 : buf1;
-        const bool more = w.bi + 1 < w.nblk;
-        const uint32_t bn = min(w.bi + 1, w.nblk - 1);
-        const uint4 m0 = w.sm_meta[2 * bn];          // {table_off16, K, rs, nb}
-        const uint4 m1 = w.sm_meta[2 * bn + 1];      // {chan_off, ..}
-        if (more && c.two_bufs) copy_next(nxt, p.r.tables + m0.x, D * m0.y * m0.z);
+        // the state-row addresses need no table: they are formed while it is still on its way
+        if (w.wave_live && w.cur.K != K_prev) {
+            gn_offsets<D, NB>(p.r.h, w.o_base, p.r.out, w.cur.K, w.lane, off);
+            K_prev = w.cur.K;
+        }
+        if (!c.two_bufs && w.bi) {                              // (the group's first table is on its way already)
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();                       // everyone is done with the only buffer
+            asm volatile("" ::: "memory");
+            gn_copy<D>(buf0, p, w.cur, w.lane);
+        }
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();                           // the block's table has arrived, nobody reads the other buffer any more
+        asm volatile("" ::: "memory");
+        const RowBlock next = w.ahead.block();
+        w.ahead.request(p.r.bmeta + c.b_lo + min(w.bi + 2, w.nblk - 1));
         if (w.wave_live) {
-            if (w.K != K_prev) {
-                gn_offsets<D, NB>(p.r.h, w.o_base, p.r.out, w.K, w.lane, off);
-                K_prev = w.K;
+            const uint32_t x_addr = w.xs_addr + (w.cur.chan_off - c.c_lo) * 2 + (x_live ? (w.lane >> 4) * 16 : 0);
+            auto gather = [&](int pr) {
+#pragma unroll
+                for (int r = 0; r < D; ++r) q[pr % RING][r] = lds_word_at(off[pr & 3][r] + BO + (pr >> 2) * 64);
+            };
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {                   // the end of the block before
+                gather(i);
+                __builtin_amdgcn_sched_barrier(0);
+                work_off(NP - AHEAD + i, last);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            gn_block<D, NB, BO>(off, w.xs_addr + (w.chan_off - c.c_lo) * 2 + (x_live ? (w.lane >> 4) * 16 : 0), x_live, acc);
+#pragma unroll
+            for (int h = 0; h < NH; ++h) a[h] = keep_if(x_live, lds_word_at(x_addr + h * 64));
+            if (c.two_bufs && w.bi + 1 < w.nblk) gn_copy<D>(BO ? buf0 : buf1, p, next, w.lane);
+#pragma unroll
+            for (int pr = 0; pr < NP - AHEAD; ++pr) {
+                gather(pr + AHEAD);
+                if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+                work_off(pr, a[pr >> 2]);
+                if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+            }
+            last = a[NH - 1];
+        } else if (c.two_bufs && w.bi + 1 < w.nblk) {
+            gn_copy<D>(BO ? buf0 : buf1, p, next, w.lane);
         }
-        if (more && !c.two_bufs) {
-            __syncthreads();                 // everyone is done with the only buffer
-            copy_next(nxt, p.r.tables + m0.x, D * m0.y * m0.z);
-        }
-        wait_async_copies();
-        __syncthreads();
-        w.K = m0.y; w.rs = m0.z; w.chan_off = m1.x;
+        w.cur = next;
         ++w.bi;
     };
     const std::integral_constant<uint32_t, 0> first_buf;
     const std::integral_constant<uint32_t, SKL_PBUF_DIST> second_buf;
-    auto in_run = [&]() { return w.bi < w.nblk && w.rs == rs_run; };
+    auto in_run = [&]() { return w.bi < w.nblk && w.cur.rs == rs_run; };
     if (c.two_bufs) {
         if (w.bi & 1) step(second_buf);
         while (in_run()) {
@@ -480,9 +495,11 @@ __device__ __forceinline__ void gn_run(const StreamArgs &p, const StreamCtx &c, 
     } else {
         while (in_run()) step(first_buf);
     }
+    if (w.wave_live) {
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) work_off(NP - AHEAD + i, last);
+    }
 }
-
-#define SKL_GN_FIXED_LDS (SKL_MAX_GROUP_BLOCKS * 32)
 
 template <int D, bool PAST>
 __device__ __forceinline__ void gemvN_body(const StreamArgs &p, const uint16_t *__restrict__ x, uint32_t ldx, uint32_t batch,
@@ -492,17 +509,14 @@ __device__ __forceinline__ void gemvN_body(const StreamArgs &p, const uint16_t *
     if (!c.live) return;
     char *lds = reinterpret_cast<char *>(smem);
     const uint32_t tab_bytes = p.tab_bytes;
-    uint4 *sm_meta = reinterpret_cast<uint4 *>(lds + tab_bytes);
-    uint16_t *xs = reinterpret_cast<uint16_t *>(lds + tab_bytes + SKL_GN_FIXED_LDS);   // 16 rows of xs_stride halfs
+    uint16_t *xs = reinterpret_cast<uint16_t *>(lds + tab_bytes);      // 16 rows of xs_stride halfs
     GnWalk w;
     w.lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwv = blockDim.x >> 6;
-    w.nblk = min(c.b_hi - c.b_lo, (uint32_t)SKL_MAX_GROUP_BLOCKS);
-    w.sm_meta = sm_meta;
+    w.nblk = c.b_hi - c.b_lo;
     w.xs_addr = (uint32_t)(uintptr_t)(lds_void *)xs + (w.lane & 15) * xs_stride * 2;
-    auto first_table = [&]() { copy_words_to_lds_async(smem, p.r.tables + c.toff0, D * c.K0 * c.rs0, nwv); };
-    first_table();
-    for (uint32_t i = threadIdx.x; i < 2 * w.nblk; i += blockDim.x) sm_meta[i] = reinterpret_cast<const uint4 *>(p.r.bmeta + c.b_lo)[i];
+    const RowBlock first{c.toff0, c.K0, c.rs0, 0, c.chan_off0, 0};
+    gn_copy<D>(smem, p, first, w.lane);
     // activations of the group's channels, 16 rows (rows >= batch are zero): one
     // thread per (channel, half of the rows), so that the channel number is
     // fetched once and the eight activation loads that depend on it go out together
@@ -526,15 +540,19 @@ __device__ __forceinline__ void gemvN_body(const StreamArgs &p, const uint16_t *
         w.o_base = c.o_lo + (pass * nwv + wave) * 64;
         w.wave_live = w.o_base < c.o_hi;
         w.bi = 0;
-        w.K = c.K0; w.rs = c.rs0; w.chan_off = c.chan_off0;
-        if (pass) first_table();             // the last step of the previous pass ended with a barrier: the first buffer is free
-        wait_async_copies();
-        __syncthreads();
+        w.cur = first;
+        w.ahead.request(p.r.bmeta + c.b_lo + min(1u, w.nblk - 1));
+        if (pass) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();    // everyone is done with the last block of the pass before
+            asm volatile("" ::: "memory");
+            gn_copy<D>(smem, p, first, w.lane);
+        }
         float4v acc[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] = (float4v){0.f, 0.f, 0.f, 0.f};
         while (w.bi < w.nblk) {
-            switch (w.rs) {
+            switch (w.cur.rs) {
             case 9: gn_run<D, 8>(p, c, w, acc); break;
             case 5: gn_run<D, 4>(p, c, w, acc); break;
             case 3: gn_run<D, 2>(p, c, w, acc); break;
@@ -849,7 +867,7 @@ skl_status_t skl_launch_gemv(const skl_layer *L, const void *x_, uint32_t ldx, v
             const uint32_t xs_stride = (L->max_group_chan / 8 | 1u) * 8;
             a.tab_bytes = L->tab_bytes;
             a.buf_flag = 2;
-            const size_t lds = (size_t)L->tab_bytes + SKL_GN_FIXED_LDS + (size_t)16 * xs_stride * sizeof(uint16_t);
+            const size_t lds = (size_t)L->tab_bytes + (size_t)16 * xs_stride * sizeof(uint16_t);
             auto launch = [&](auto kernel) {
                 st = allow_lds(kernel, lds);
                 if (st == SKL_OK) hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), lds, stream, a, x, ldx, batch, xs_stride, partial);
@@ -954,7 +972,7 @@ skl_status_t skl_launch_gemv_group(const skl_layer *const *layers, uint32_t n, c
         } else {
             a.tab_bytes = L->tab_bytes;
             a.buf_flag = 2;
-            need = (size_t)L->tab_bytes + SKL_GN_FIXED_LDS + (size_t)16 * xs_stride * sizeof(uint16_t);
+            need = (size_t)L->tab_bytes + (size_t)16 * xs_stride * sizeof(uint16_t);
         }
         gr.y[i] = ys[i < n ? i : 0];
         gr.n_units[i] = L->n_units;

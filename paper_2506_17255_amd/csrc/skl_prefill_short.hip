@@ -44,41 +44,17 @@ __global__ __launch_bounds__(SKL_WG) void k_prompt_pack(PackArgs k, uint32_t n_r
 #define PG_X0 (2u * SKL_PBUF_DIST)      // LDS: two table buffers, two activation buffers
 #define PG_LDS(rb) (PG_X0 + 2u * (rb) * 2048u)
 
-struct PromptBlock {
-    uint32_t table_off16, K, rs, nb, chan_off;
-};
-
-// The metadata of a block, requested from an address the compiler takes to differ between the lanes: left to itself it
-// puts the words into scalar registers at once and waits out the load's latency at the head of every block.
-struct PromptBlockLoad {
-    u32x4v m;
-    uint32_t chan_off;
-    __device__ __forceinline__ void request(const skl_block_meta *bm)
-    {
-        uint32_t none = 0;
-        asm volatile("" : "+v"(none));
-        const char *at = reinterpret_cast<const char *>(bm) + none;
-        m = *reinterpret_cast<const u32x4v *>(at);
-        chan_off = reinterpret_cast<const uint32_t *>(at)[4];
-    }
-    __device__ __forceinline__ PromptBlock block() const
-    {
-        auto u = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane(v); };
-        return PromptBlock{u(m.x), u(m.y), u(m.z), u(m.w), u(chan_off)};
-    }
-};
-
 template <int D, int RB>
 struct PromptWalk {
     uint32_t b, b1, buf;                // next block, end of the group, its buffers
-    PromptBlock bm, nx;                 // block b and the one after it
-    PromptBlockLoad ahead;              // the one after those, on its way
+    RowBlock bm, nx;                 // block b and the one after it
+    BlockAhead ahead;              // the one after those, on its way
     uint32_t lane, wave, nw, o_base, lds0, tile_m;
     float4v acc[RB][2];
 };
 
 template <int D, int RB>
-__device__ __forceinline__ void prompt_copies(const PromptArgs &p, const PromptWalk<D, RB> &w, const PromptBlock &bm, uint32_t buf, ChunkCopy &tab, ChunkCopy &x)
+__device__ __forceinline__ void prompt_copies(const PromptArgs &p, const PromptWalk<D, RB> &w, const RowBlock &bm, uint32_t buf, ChunkCopy &tab, ChunkCopy &x)
 {
     tab.start(p.tables + bm.table_off16, D * bm.K * bm.rs, w.lds0 + buf * SKL_PBUF_DIST, w.wave, w.nw, w.lane);
     x.start(p.Xq + ((size_t)w.tile_m * p.n_words + (bm.chan_off >> 3)) * (RB * 16), bm.nb * (RB * 16), w.lds0 + PG_X0 + buf * (RB * 2048), w.wave, w.nw, w.lane);

@@ -376,6 +376,32 @@ def test_batched_decode_stores(in_f, out_f, batch):
     assert rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
 
 
+@pytest.mark.parametrize("query_mode", [0, 1])
+@pytest.mark.parametrize("in_f,out_f,d,widths,batch", [
+    (777, 1500, 4, (9, 200, 330, 1300), 2),     # blocks of all widths, some groups with one table buffer, some of one block
+    (777, 1500, 4, (9, 200, 330, 1300), 9),     # the second eight rows: one of them
+    (2000, 333, 3, (9, 250, 500, 1800), 5),
+    (520, 2100, 2, (9, 400, 900, 2500), 16),
+    (300, 1200, 1, (3, 1200, 1700, 4060), 8),
+    (900, 1100, 5, (9, 200), 7),                # more than four rows: nothing in flight across the blocks
+    (900, 1100, 8, (9, 120, 450), 12),
+])
+def test_batched_decode_runs_of_blocks(in_f, out_f, d, widths, batch, query_mode):
+    """Runs of blocks of one width class begin with an empty pipeline and carry their last products over a barrier; rows past
+    the batch hold whatever LDS held."""
+    rng = np.random.default_rng(in_f + d + batch)
+    A, C = hash_params(rng, d)
+    K = np.where(rng.random(in_f) < 0.06, rng.choice(widths[1:], in_f), widths[0]).astype(np.uint32)
+    states = (rng.standard_normal(int(K.sum()) * d) * 0.02).astype(np.float16).view(np.uint16)
+    sk = oracle.Sketch(in_f, out_f, 1, out_f, d, A, C, K, states)
+    x = rng.standard_normal((batch, in_f)).astype(np.float16)
+    ref = matmul_f64(oracle.query(sk, query_mode), x, "f16")
+    with GpuLayer(sk, query_mode=query_mode) as g:
+        y = g.gemv(x, "f32")
+        assert np.array_equal(y, g.gemv(x, "f32", ldx=in_f + 8))
+    assert np.isfinite(y).all() and rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
+
+
 @pytest.mark.parametrize("out_f,batch,ldh_pad,h_dt", [
     (4096, 15, 0, "f32"),       # 240 wavefronts of the row reduction: the other one
     (4096, 16, 0, "f16"),       # 256: the first
