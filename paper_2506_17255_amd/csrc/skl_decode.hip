@@ -517,21 +517,21 @@ __device__ __forceinline__ void gemvN_body(const StreamArgs &p, const uint16_t *
     w.xs_addr = (uint32_t)(uintptr_t)(lds_void *)xs + (w.lane & 15) * xs_stride * 2;
     const RowBlock first{c.toff0, c.K0, c.rs0, 0, c.chan_off0, 0};
     gn_copy<D>(smem, p, first, w.lane);
-    // activations of the group's channels, 16 rows (rows >= batch are zero): one
-    // thread per (channel, half of the rows), so that the channel number is
-    // fetched once and the eight activation loads that depend on it go out together
+    // Activations of the group's channels: a thread per channel and eight rows, whose loads all go out together.  (Rows past
+    // the batch repeat the last one or are left as they are: their sums are not stored.  With a branch around every load
+    // the eight went out one after the other, each behind the table: 11008 x 4096, batch 8, 17.4 -> 15.8 us, gate/up of 4096 x 11008,
+    // batch 16, 39.2 -> 36.0.)
     const uint32_t nch = c.c_hi - c.c_lo;
-    for (uint32_t i = threadIdx.x; i < 2 * nch; i += blockDim.x) {
-        const uint32_t cc = i >> 1, b0 = (i & 1) * 8;
+    for (uint32_t i = threadIdx.x; i < (batch > 8 ? 2 * nch : nch); i += blockDim.x) {
+        const uint32_t b0 = i >= nch ? 8 : 0, cc = i >= nch ? i - nch : i;
         const uint32_t ch = p.r.chan[c.c_lo + cc];
+        const bool live = ch != SKL_NO_CHANNEL && skl_in_range(ch, p.r.in, SKL_DBG_CHANNEL);
+        const uint16_t *col = x + (live ? ch : 0);
         uint16_t v[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            v[k] = 0;
-            if (ch != SKL_NO_CHANNEL && b0 + k < batch && skl_in_range(ch, p.r.in, SKL_DBG_CHANNEL)) v[k] = x[(size_t)(b0 + k) * ldx + ch] ^ 0x8000u;
-        }
+        for (uint32_t k = 0; k < 8; ++k) v[k] = col[(size_t)min(b0 + k, batch - 1) * ldx];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) xs[(b0 + k) * xs_stride + cc] = v[k];
+        for (uint32_t k = 0; k < 8; ++k) xs[(b0 + k) * xs_stride + cc] = live ? v[k] ^ 0x8000u : 0;
     }
     // A segment of more than 16 units (plans made for the batch-1 kernel's two units per wavefront) is
     // walked in passes: the wavefronts take units 0 .. nwv - 1, then nwv .. 2 nwv - 1, streaming the group's
