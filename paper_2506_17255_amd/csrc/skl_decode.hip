@@ -72,25 +72,25 @@ __device__ __forceinline__ StreamCtx stream_ctx(const StreamArgs &p)
 // carries twice the arithmetic between its barriers -- what layers with wide sketches (large tables behind
 // few channels) need.
 //
-// LDS: [table buffer 0][table buffer 1 at SKL_PBUF_DIST][1024 x U sums][block
-// metadata][state-row addresses, 1024 x d][activations].  The kernel has no static LDS, so the dynamic region
+// LDS: [table buffer 0][table buffer 1 at SKL_PBUF_DIST][1024 x U sums][state-row addresses, 1024 x d][activations].
+// The kernel has no static LDS, so the dynamic region
 // starts at LDS address 0 and the second buffer is reached through the 16-bit
 // offset field of the read instruction: no address arithmetic per gather.
-#define SKL_G1_FIXED_LDS(d, u) (SKL_SWG * 4 * (u) + SKL_MAX_GROUP_BLOCKS * 32 + SKL_SWG * 4 * (d))
-
-// 16 bytes at an absolute LDS address
+#define SKL_G1_FIXED_LDS(d, u) (SKL_SWG * 4 * (u) + SKL_SWG * 4 * (d))
 
 template <int D, int NB>
 __device__ __forceinline__ void lane_offsets(const HashArgs &h, uint32_t o_base, uint32_t out, uint32_t K, uint32_t lane,
                                              uint32_t *row_addr_w, uint32_t (&off)[NB][D])
 {
     constexpr uint32_t OPI = 64 / NB;               // outputs per instruction
-    const uint32_t sub = lane / NB, cw = lane % NB;
+    typedef __attribute__((address_space(3))) uint32_t lds_u32;
     const uint32_t Kq = K << 8;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void *)smem;
-    // The hash values A*o + C do not depend on K; hide that from the compiler,
-    // which would otherwise keep them in registers across the block loop.
-    asm volatile("" : "+v"(o_base));
+    uint32_t scratch_addr = (uint32_t)(uintptr_t)(lds_void *)row_addr_w;
+    // The hash values A*o + C do not depend on K, nor do the scratch addresses; hide that from the compiler,
+    // which would otherwise keep them (some thirty registers) across the block loop.
+    asm volatile("" : "+v"(o_base), "+v"(scratch_addr), "+v"(lane));
+    const uint32_t sub = lane / NB, cw = lane % NB;
     // every lane hashes one output (Eq. 3 for the D rows) and leaves the LDS
     // addresses of its state rows (first buffer, word cw = 0) in the wavefront's
     // scratch area [64][D] ...
@@ -98,14 +98,14 @@ __device__ __forceinline__ void lane_offsets(const HashArgs &h, uint32_t o_base,
 #pragma unroll
     for (int r = 0; r < D; ++r) {
         const uint32_t t = __umul24(h.A[r], o) + h.C[r];
-        row_addr_w[lane * D + r] = lds0 + (r * K + select_index(t, Kq)) * (NB * 16);
+        *(lds_u32 *)(uintptr_t)(scratch_addr + (lane * D + r) * 4) = lds0 + (r * K + select_index(t, Kq)) * (NB * 16);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     // ... and picks up the rows of the NB outputs it works on
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
 #pragma unroll
-        for (int r = 0; r < D; ++r) off[i][r] = row_addr_w[(sub + OPI * i) * D + r] + cw * 16;
+        for (int r = 0; r < D; ++r) off[i][r] = *(lds_u32 *)(uintptr_t)(scratch_addr + sub * (D * 4) + (OPI * i * D + r) * 4) + cw * 16;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
@@ -123,118 +123,131 @@ __device__ __forceinline__ float sum_over_words(float v)
     return v;
 }
 
-// one block: NB outputs per lane, one 16-byte word (8 channels) of each.
-// The D gathers of the next output are issued before the arithmetic of the
-// current one (the scheduling barriers keep them there); left alone, the
-// compiler waits for every single gather right after issuing it.
-template <int D, int NB, uint32_t BUF_OFF, int MAXW>
-__device__ __forceinline__ void lane_block_dot(const uint32_t (&off)[NB][D], uint4 xv, float (&acc)[NB])
-{
-    // Outputs whose gathers are in flight ahead of the arithmetic, as far as
-    // the registers allow: a workgroup of at most 12 wavefronts may use 168
-    // registers per lane, one of 16 wavefronts 128.
-    constexpr int AHEAD = MAXW <= 12 ? (D <= 4 ? 2 : 1) : (D <= 4 ? 1 : 0);
-    constexpr int RING = AHEAD + 1;
-    uint4 q[RING][D];
-#pragma unroll
-    for (int a = 0; a < AHEAD && a < NB; ++a)
-#pragma unroll
-        for (int r = 0; r < D; ++r) q[a][r] = lds_word_at(off[a][r] + BUF_OFF);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        if (i + AHEAD < NB) {
-#pragma unroll
-            for (int r = 0; r < D; ++r) q[(i + AHEAD) % RING][r] = lds_word_at(off[i + AHEAD][r] + BUF_OFF);
-        }
-        if (AHEAD) __builtin_amdgcn_sched_barrier(0);
-        uint4 m = q[i % RING][0];
-#pragma unroll
-        for (int r = 1; r < D; ++r) m = pk_max_u16x8(m, q[i % RING][r]);
-        acc[i] = dot2_acc(keys_to_neg_half2_mad(m.x), xv.x, acc[i]);
-        acc[i] = dot2_acc(keys_to_neg_half2_mad(m.y), xv.y, acc[i]);
-        acc[i] = dot2_acc(keys_to_neg_half2_mad(m.z), xv.z, acc[i]);
-        acc[i] = dot2_acc(keys_to_neg_half2_mad(m.w), xv.w, acc[i]);
-        if (AHEAD) __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
 // The block loop of one workgroup, shared by all width classes.
 struct G1Walk {
-    const uint4 *sm_meta;    // metadata of the group's blocks in LDS (two 16-byte words each)
     const uint16_t *xs;      // the group's activations (negated binary16) in LDS
     float *yw;               // the wavefront's 64 output sums in LDS
     uint32_t *row_addr_w;    // the wavefront's scratch for state-row addresses, [64][D]
     uint32_t nblk, bi;       // blocks of the group, current block
-    uint32_t K, rs, chan_off;   // current block
+    RowBlock cur;            // current block
+    BlockAhead ahead;        // the one after it, on its way
     uint32_t lane, o_base;   // o_base: first output of the wavefront's unit 0; unit u starts unit_stride outputs further on
     uint32_t unit_stride, o_hi;
     bool wave_live;
-    bool first_wait;         // the first table, the activations and the metadata are still on their way
 };
 
-// A run of consecutive blocks of one width class (NB words per state row).
-// The partial sums and the table offsets of the run live in registers.
+__device__ __forceinline__ void meet_after_lds_reads()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// the same, and the workgroup's copies into LDS have arrived
+__device__ __forceinline__ void meet_after_copies()
+{
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// A run of consecutive blocks of one width class (NB words per state row).  The partial sums and the table offsets of the
+// run live in registers.  A block is U x NB items per lane, an item being one 16-byte word (8 channels) of one output.
+// The D gathers of the next item are issued before the arithmetic of the current one (the scheduling barriers keep them
+// there; left alone, the compiler waits for every single gather right after issuing it), across the blocks: the barrier
+// that hands the buffers over stands where the last item of a block is gathered but not yet worked off.  Against two items
+// ahead and a drained wavefront, two LDS reads of metadata and a wait for them at every barrier: 4096 x 11008 15.3 -> 14.5
+// us, at 0.75 bit per weight 17.3 -> 15.7, 8192 x 28672 57.5 -> 52.3, seven layers of a decoder block 77.9 -> 73.1 (two or
+// three items ahead across the blocks: 1.1 and 0.7 us more than one on 4096 x 11008).
 template <int D, int NB, int MAXW, int U>
 __device__ __forceinline__ void g1_run(const StreamArgs &p, const StreamCtx &c, G1Walk &w)
 {
     const uint32_t nw = blockDim.x >> 6;
     constexpr uint32_t OPI = 64 / NB;
+    // one item ahead as far as the registers allow: a workgroup of at most 12 wavefronts may use 168 registers per lane, one
+    // of 16 wavefronts 128 (a lone item per block would change its registers from block to block)
+    constexpr int N = U * NB, AHEAD = N % 2 == 0 && (MAXW <= 12 || D <= 4) ? 1 : 0, RING = AHEAD + 1;
     uint4 *const buf0 = smem, *const buf1 = smem + SKL_PBUF_DIST / 16;
     float acc[U][NB];
     uint32_t off[U][NB][D];
-    bool live[U];            // wavefront-uniform: unit u of this wavefront lies inside the segment
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        live[u] = w.o_base + u * w.unit_stride < w.o_hi;
+    for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int i = 0; i < NB; ++i) acc[u][i] = 0.f;
-    }
     uint32_t K_prev = 0;
-    const uint32_t rs_run = w.rs;
+    const uint32_t rs_run = w.cur.rs;
+    // nothing is carried into the first block: products of zero activations and of keys that stand for finite weights in
+    // either query mode
+    uint4 last = make_uint4(0, 0, 0, 0), q[RING][D];
+#pragma unroll
+    for (int i = 0; i < RING; ++i)
+#pragma unroll
+        for (int r = 0; r < D; ++r) q[i][r] = make_uint4(0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u);
+    auto work_off = [&](int it, const uint4 &x) {
+        uint4 m = q[it % RING][0];
+#pragma unroll
+        for (int r = 1; r < D; ++r) m = pk_max_u16x8(m, q[it % RING][r]);
+        float &sum = acc[it / NB][it % NB];
+        sum = dot2_acc(keys_to_neg_half2_mad(m.x), x.x, sum);
+        sum = dot2_acc(keys_to_neg_half2_mad(m.y), x.y, sum);
+        sum = dot2_acc(keys_to_neg_half2_mad(m.z), x.z, sum);
+        sum = dot2_acc(keys_to_neg_half2_mad(m.w), x.w, sum);
+    };
     // One block out of the buffer at byte offset BO (a compile-time constant, so that it ends up in the
     // offset field of the LDS reads); with two buffers the next block's table streams into the other one
     // meanwhile, with one it is copied after the block.
     auto step = [&](auto bo_tag, auto bufs_tag) {
         constexpr uint32_t BO = decltype(bo_tag)::value;
         constexpr int BUFS = decltype(bufs_tag)::value;
-        const bool more = w.bi + 1 < w.nblk;
-        const uint32_t bn = min(w.bi + 1, w.nblk - 1);
-        // the state-row addresses need no table: at the start of the workgroup they are computed while
-        // the first table is still arriving
-        if (w.wave_live && w.K != K_prev) {
+        // the state-row addresses need no table: they are formed while it is still on its way
+        if (w.wave_live && w.cur.K != K_prev) {
+            // (outputs past the segment or the layer are the next segment's or the last one: their sums are not kept)
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (live[u]) lane_offsets<D, NB>(p.r.h, w.o_base + u * w.unit_stride, p.r.out, w.K, w.lane, w.row_addr_w, off[u]);
-            K_prev = w.K;
+            for (int u = 0; u < U; ++u) lane_offsets<D, NB>(p.r.h, w.o_base + u * w.unit_stride, p.r.out, w.cur.K, w.lane, w.row_addr_w, off[u]);
+            K_prev = w.cur.K;
         }
-        if (w.first_wait) {
-            wait_async_copies();
-            __syncthreads();
-            w.first_wait = false;
+        if (BUFS == 1 && w.bi) {                                // (the group's first table is on its way already)
+            meet_after_lds_reads();                             // everyone is done with the only buffer
+            copy_chunks_to_lds_async(buf0, p.r.tables + w.cur.ptable_off16, D * w.cur.K * w.cur.nb, nw);
         }
-        const uint4 m0 = w.sm_meta[2 * bn];          // {table_off16, K, rs, nb}
-        const uint4 m1 = w.sm_meta[2 * bn + 1];      // {chan_off, ptable_off16, ..}
-        if (BUFS == 2 && more) copy_chunks_to_lds_async(BO ? buf0 : buf1, p.r.tables + m1.y, D * m0.y * m0.w, nw);
+        meet_after_copies();                                    // the block's table is there, nobody reads the other buffer any more
+        const RowBlock next = w.ahead.block();
+        w.ahead.request(p.r.bmeta + c.b_lo + min(w.bi + 2, w.nblk - 1));
+        const bool more = BUFS == 2 && w.bi + 1 < w.nblk;
+        auto copy_next = [&]() { copy_chunks_to_lds_async(BO ? buf0 : buf1, p.r.tables + next.ptable_off16, D * next.K * next.nb, nw); };
         if (w.wave_live) {
-            const uint4 xv = reinterpret_cast<const uint4 *>(w.xs + (w.chan_off - c.c_lo))[w.lane % NB];
+            auto gather = [&](int it) {
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (live[u]) lane_block_dot<D, NB, BO, MAXW>(off[u], xv, acc[u]);
+                for (int r = 0; r < D; ++r) q[it % RING][r] = lds_word_at(off[it / NB][it % NB][r] + BO);
+            };
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {                   // the end of the block before
+                gather(i);
+                __builtin_amdgcn_sched_barrier(0);
+                work_off(N - AHEAD + i, last);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const uint4 xv = reinterpret_cast<const uint4 *>(w.xs + (w.cur.chan_off - c.c_lo))[w.lane % NB];
+            if (more) copy_next();
+#pragma unroll
+            for (int it = 0; it < N - AHEAD; ++it) {
+                gather(it + AHEAD);
+                if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+                work_off(it, xv);
+                if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+            }
+            last = xv;
+        } else if (more) {
+            copy_next();
         }
-        if (BUFS == 1 && more) {
-            __syncthreads();                 // everyone is done with the only buffer
-            copy_chunks_to_lds_async(buf0, p.r.tables + m1.y, D * m0.y * m0.w, nw);
-        }
-        wait_async_copies();
-        __syncthreads();
-        w.K = m0.y; w.rs = m0.z; w.chan_off = m1.x;
+        w.cur = next;
         ++w.bi;
     };
     const std::integral_constant<uint32_t, 0> at_0;
     const std::integral_constant<uint32_t, SKL_PBUF_DIST> at_dist;
     const std::integral_constant<int, 1> one_buf;
     const std::integral_constant<int, 2> two_bufs;
-    auto in_run = [&]() { return w.bi < w.nblk && w.rs == rs_run; };
+    auto in_run = [&]() { return w.bi < w.nblk && w.cur.rs == rs_run; };
     if (c.two_bufs) {
         // even blocks sit in the first buffer, odd blocks in the second
         if (w.bi & 1) step(at_dist, two_bufs);
@@ -246,10 +259,13 @@ __device__ __forceinline__ void g1_run(const StreamArgs &p, const StreamCtx &c, 
     } else {
         while (in_run()) step(at_0, one_buf);
     }
+    if (!w.wave_live) return;
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) work_off(N - AHEAD + i, last);
     // fold the NB lanes of every output, add the totals to the wavefront's sums
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        if (!live[u]) continue;
+        if (w.o_base + u * w.unit_stride >= w.o_hi) continue;  // (the same for the whole wavefront)
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
             // LDS add without a returned value: nothing to wait for between the NB updates
@@ -269,12 +285,11 @@ __device__ __forceinline__ void gemv1_body(const StreamArgs &p, const uint16_t *
     char *lds = reinterpret_cast<char *>(smem);
     const uint32_t tab_bytes = p.tab_bytes;
     float *ysum = reinterpret_cast<float *>(lds + tab_bytes);
-    uint4 *sm_meta = reinterpret_cast<uint4 *>(lds + tab_bytes + SKL_SWG * 4 * U);
-    uint32_t *row_addr = reinterpret_cast<uint32_t *>(lds + tab_bytes + SKL_SWG * 4 * U + SKL_MAX_GROUP_BLOCKS * 32);
+    uint32_t *row_addr = reinterpret_cast<uint32_t *>(lds + tab_bytes + SKL_SWG * 4 * U);
     uint16_t *xs = reinterpret_cast<uint16_t *>(lds + tab_bytes + SKL_G1_FIXED_LDS(D, U));
     G1Walk w;
     w.lane = threadIdx.x & 63;
-    const uint32_t wave = threadIdx.x >> 6;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
     w.o_base = c.o_lo + wave * 64;
     w.unit_stride = blockDim.x;          // 64 outputs x wavefronts
     w.o_hi = c.o_hi;
@@ -282,22 +297,33 @@ __device__ __forceinline__ void gemv1_body(const StreamArgs &p, const uint16_t *
     w.yw = ysum + wave * 64;
     w.row_addr_w = row_addr + wave * 64 * D;
     w.xs = xs;
-    w.nblk = min(c.b_hi - c.b_lo, (uint32_t)SKL_MAX_GROUP_BLOCKS);
+    w.nblk = c.b_hi - c.b_lo;
     w.bi = 0;
-    w.sm_meta = sm_meta;
-    w.K = c.K0; w.rs = c.rs0; w.chan_off = c.chan_off0;
-    copy_chunks_to_lds_async(smem, p.r.tables + c.ptoff0, D * w.K * (w.rs == 1 ? 1u : w.rs - 1), blockDim.x >> 6);
-    // the plan keeps a group at SKL_MAX_GROUP_BLOCKS blocks or fewer
-    for (uint32_t i = threadIdx.x; i < 2 * w.nblk; i += blockDim.x) sm_meta[i] = reinterpret_cast<const uint4 *>(p.r.bmeta + c.b_lo)[i];
+    w.cur = RowBlock{c.toff0, c.K0, c.rs0, c.rs0 == 1 ? 1u : c.rs0 - 1, c.chan_off0, c.ptoff0};
+    // The last two wavefronts fetch the group's activations (channel numbers, then what they point at) while the others
+    // copy the first table: a wavefront that did both would wait for its share of the table before each of the two.
+    const uint32_t n_x = nw >= 4 ? 2 : 1, n_tab = nw - n_x;
+    if (wave < n_tab) {
+        copy_chunks_to_lds_async(smem, p.r.tables + c.ptoff0, D * w.cur.K * w.cur.nb, n_tab);
+    } else {
+        // four entries of the channel list at a time (block groups begin on multiples of eight)
+        for (uint32_t e = ((wave - n_tab) * 64 + w.lane) * 4; e < c.c_hi - c.c_lo; e += n_x * 256) {
+            const u32x4v ch = *reinterpret_cast<const u32x4v *>(p.r.chan + c.c_lo + e);
+            uint32_t v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const bool live = ch[k] != SKL_NO_CHANNEL && skl_in_range(ch[k], p.r.in, SKL_DBG_CHANNEL);
+                v[k] = x[live ? ch[k] : 0] ^ 0x8000u;
+                if (!live) v[k] = 0;
+            }
+            *reinterpret_cast<uint2 *>(xs + e) = make_uint2(v[0] | v[1] << 16, v[2] | v[3] << 16);
+        }
+    }
+    w.ahead.request(p.r.bmeta + c.b_lo + min(1u, w.nblk - 1));
 #pragma unroll
     for (int u = 0; u < U; ++u) w.yw[u * w.unit_stride + w.lane] = 0.f;
-    for (uint32_t i = threadIdx.x; i < c.c_hi - c.c_lo; i += blockDim.x) {
-        const uint32_t ch = p.r.chan[c.c_lo + i];
-        xs[i] = ch != SKL_NO_CHANNEL && skl_in_range(ch, p.r.in, SKL_DBG_CHANNEL) ? (uint16_t)(x[ch] ^ 0x8000u) : (uint16_t)0;
-    }
-    w.first_wait = true;                 // waited for in the first step of the first run
     while (w.bi < w.nblk) {
-        switch (w.rs) {
+        switch (w.cur.rs) {
         case 9:
             if constexpr (D <= 6 && U == 1) {      // the plan uses 8-word blocks for d <= 6 only,
                 g1_run<D, 8, MAXW, U>(p, c, w);    // and two units per wavefront only for layers of one- and two-word blocks
@@ -311,10 +337,6 @@ __device__ __forceinline__ void gemv1_body(const StreamArgs &p, const uint16_t *
         case 3: g1_run<D, 2, MAXW, U>(p, c, w); break;
         default: g1_run<D, 1, MAXW, U>(p, c, w); break;
         }
-    }
-    if (w.first_wait) {                  // a group without blocks: nothing may stay in flight
-        wait_async_copies();
-        __syncthreads();
     }
     if (w.wave_live) {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -442,14 +464,10 @@ __device__ __forceinline__ void gn_run(const StreamArgs &p, const StreamCtx &c, 
             K_prev = w.cur.K;
         }
         if (!c.two_bufs && w.bi) {                              // (the group's first table is on its way already)
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();                       // everyone is done with the only buffer
-            asm volatile("" ::: "memory");
+            meet_after_lds_reads();                             // everyone is done with the only buffer
             gn_copy<D>(buf0, p, w.cur, w.lane);
         }
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();                           // the block's table has arrived, nobody reads the other buffer any more
-        asm volatile("" ::: "memory");
+        meet_after_copies();                                    // the block's table is there, nobody reads the other buffer any more
         const RowBlock next = w.ahead.block();
         w.ahead.request(p.r.bmeta + c.b_lo + min(w.bi + 2, w.nblk - 1));
         if (w.wave_live) {
@@ -543,9 +561,7 @@ __device__ __forceinline__ void gemvN_body(const StreamArgs &p, const uint16_t *
         w.cur = first;
         w.ahead.request(p.r.bmeta + c.b_lo + min(1u, w.nblk - 1));
         if (pass) {
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();    // everyone is done with the last block of the pass before
-            asm volatile("" ::: "memory");
+            meet_after_lds_reads();          // everyone is done with the last block of the pass before
             gn_copy<D>(smem, p, first, w.lane);
         }
         float4v acc[4];

@@ -234,9 +234,10 @@ static bool plan_decode(const skl_desc_t *d, skl_plan *P)
             const uint32_t c_hi = start[g + 1] < nblk ? P->bmeta[start[g + 1]].chan_off : (uint32_t)P->chan.size();
             o.max_chan = std::max(o.max_chan, c_hi - c_lo);
         }
-        // batch-1 kernel: sums of upw x 1024 outputs, block metadata, state-row addresses, the group's activations
+        // batch-1 kernel: sums of upw x 1024 outputs, state-row addresses, the group's activations
+        // (and 2 KiB in either kernel that held block metadata: a split, and with it the order of a layer's sums, stays what it was)
         const uint64_t g1_rest = 4096ull * upw + SKL_MAX_GROUP_BLOCKS * 32 + 4096ull * d->d + 2ull * (o.max_chan + 64);
-        // batched kernel: block metadata, 16 activation rows of the group
+        // batched kernel: 16 activation rows of the group
         const uint64_t gn_rest = 16ull * (o.max_chan + 16) * 2 + 2048;
         o.ptab = std::max<uint32_t>(any1 ? 2 * SKL_PBUF_DIST : 0, L.max_ptable_bytes);
         o.tab = std::max<uint32_t>(anyN ? 2 * SKL_PBUF_DIST : 0, L.max_table_bytes);
@@ -283,7 +284,7 @@ static bool plan_decode(const skl_desc_t *d, skl_plan *P)
         const DecodeShape sh = decode_shape(units, S);
         if (sh.upw > 1 && (L.block_classes & ~3u)) return -1.0;              // two units per wavefront: one- and two-word blocks only
         price_blocks(sh);
-        if (cut_groups(G, start) > SKL_MAX_GROUP_BLOCKS) return -1.0;       // block metadata of a group sits in LDS
+        if (cut_groups(G, start) > SKL_MAX_GROUP_BLOCKS) return -1.0;
         if (!lds_plan(start, G, sh.upw, lds)) return -1.0;
         return split_cost(start, G, S, sh, lds);
     };

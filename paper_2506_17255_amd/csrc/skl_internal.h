@@ -12,7 +12,7 @@
 #define SKL_SWG 1024          // threads per workgroup of the streaming decode kernels
 #define SKL_N_CU 256          // compute units of the target (MI355X)
 #define SKL_NO_CHANNEL 0xFFFFFFFFu
-#define SKL_MAX_GROUP_BLOCKS 64   // most channel blocks in one block group of the decode plan (metadata kept in LDS)
+#define SKL_MAX_GROUP_BLOCKS 64   // most channel blocks in one block group of the decode plan
 
 // LDS budgets.  A CU of gfx950 has 160 KiB of LDS.  A block takes the most words per state row (8, 4, 2, 1)
 // whose padded table still fits one of the decode kernels' two table buffers.

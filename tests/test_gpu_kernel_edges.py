@@ -378,7 +378,14 @@ def test_batched_decode_stores(in_f, out_f, batch):
 
 @pytest.mark.parametrize("query_mode", [0, 1])
 @pytest.mark.parametrize("in_f,out_f,d,widths,batch", [
-    (777, 1500, 4, (9, 200, 330, 1300), 2),     # blocks of all widths, some groups with one table buffer, some of one block
+    (777, 1500, 4, (9, 200, 330, 1300), 1),     # blocks of all widths, some groups with one table buffer, some of one block
+    (2000, 333, 3, (9, 250, 500, 1800), 1),
+    (300, 1200, 1, (3, 1200, 1700, 4060), 1),
+    (520, 14300, 2, (9, 400, 900, 2500), 1),    # segments of more than 12 wavefronts
+    (150, 9000, 4, (500, 700, 1100), 1),        # two units per wavefront, the last one without outputs
+    (900, 1100, 5, (9, 200), 1),
+    (900, 1100, 8, (9, 120, 450), 1),
+    (777, 1500, 4, (9, 200, 330, 1300), 2),
     (777, 1500, 4, (9, 200, 330, 1300), 9),     # the second eight rows: one of them
     (2000, 333, 3, (9, 250, 500, 1800), 5),
     (520, 2100, 2, (9, 400, 900, 2500), 16),
@@ -386,7 +393,7 @@ def test_batched_decode_stores(in_f, out_f, batch):
     (900, 1100, 5, (9, 200), 7),                # more than four rows: nothing in flight across the blocks
     (900, 1100, 8, (9, 120, 450), 12),
 ])
-def test_batched_decode_runs_of_blocks(in_f, out_f, d, widths, batch, query_mode):
+def test_decode_runs_of_blocks(in_f, out_f, d, widths, batch, query_mode):
     """Runs of blocks of one width class begin with an empty pipeline and carry their last products over a barrier; rows past
     the batch hold whatever LDS held."""
     rng = np.random.default_rng(in_f + d + batch)
