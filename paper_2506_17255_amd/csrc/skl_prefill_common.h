@@ -16,6 +16,8 @@ skl_status_t skl_launch_gemm_prompt(const skl_layer *L, const TableSrc &src, con
 
 typedef float float4v __attribute__((ext_vector_type(4)));
 
+typedef uint32_t u32x4h __attribute__((ext_vector_type(4), aligned(2)));     // eight 16-bit elements on any 2-byte boundary
+
 // two activations -> two binary16 values with inverted sign bits
 __device__ __forceinline__ uint32_t neg_half_pair(uint32_t e, uint32_t x_dt)
 {
@@ -35,6 +37,9 @@ __device__ __forceinline__ uint32_t neg_half_pair(uint32_t e, uint32_t x_dt)
 // spans such a gap channel by channel from memory took 5 of 15 us on layers with one percent of wide channels).
 // Steps whose channels are far apart (the wide channels themselves) have no window and are fetched from memory.
 // 2048 tokens x 4096 channels of such a layer, 16.8 MB in and out: 10 us, 15 before (5.1 TB/s would be 6.6).
+// All loads of a stretch are on their way before the first is needed, and rows on any 2-byte boundary take 16-byte pieces:
+// with a wait after every piece, and by element where rows do not start on 16-byte boundaries, whole calls took 26.8 us
+// (3001 x 7003, 77 tokens; now 22.2), 36.7 (5001 x 3000, 200 tokens; 32.0), 23.4 (4096 x 11008, 17 tokens; 22.8).
 #define PO_STRIDE (PO_WINDOW + 8u)      // halfs per LDS row: 16-byte aligned rows on different banks
 #define PO_LDS_BYTES (16u * PO_STRIDE * 2u)
 struct PackArgs {
@@ -66,39 +71,55 @@ __device__ __forceinline__ void pack_group(const PackArgs &p, uint32_t t0, uint3
         ch[i][1] = c[1];
     }
     if (win.n) {
+        // (every piece is requested before the first is stored; pieces that reach past the row's end are fetched again, by
+        // element: what lies past it is never read from LDS)
         const uint32_t r = threadIdx.x / PER_ROW;               // PER_ROW threads copy one token's row
-        const uint16_t *src = X + (size_t)min(t0 + r, tokens - 1) * ldx + win.base;
-        const bool vec = (ldx & 7u) == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;        // (base is a multiple of 8)
+        const uint16_t *src = X + (size_t)min(t0 + r, tokens - 1) * ldx;
+        constexpr uint32_t PIECES = (PO_WINDOW + 8 * PER_ROW - 1) / (8 * PER_ROW);
+        u32x4v v[PIECES];
 #pragma unroll
-        for (uint32_t i = 0; i < (PO_WINDOW + 8 * PER_ROW - 1) / (8 * PER_ROW); ++i) {
+        for (uint32_t i = 0; i < PIECES; ++i) {
             const uint32_t c = (threadIdx.x % PER_ROW + PER_ROW * i) * 8;
-            if (c < win.n) {
-                u32x4v v = {0, 0, 0, 0};
-                if (vec && win.base + c + 8 <= in) {
-                    v = *reinterpret_cast<const u32x4v *>(src + c);
-                } else {
+            if (c < win.n && in >= 8) v[i] = *reinterpret_cast<const u32x4h *>(src + min(win.base + c, in - 8));
+        }
 #pragma unroll
-                    for (uint32_t k = 0; k < 8; ++k)
-                        if (win.base + c + k < in) v[k >> 1] |= (uint32_t)src[c + k] << ((k & 1) * 16);
-                }
-                *reinterpret_cast<u32x4v *>(rows + r * PO_STRIDE + c) = v;
+        for (uint32_t i = 0; i < PIECES; ++i) {
+            const uint32_t c = (threadIdx.x % PER_ROW + PER_ROW * i) * 8;
+            if (c >= win.n) continue;
+            if (win.base + c + 8 > in) {
+                uint32_t e[8];
+#pragma unroll
+                for (uint32_t k = 0; k < 8; ++k) e[k] = src[min(win.base + c + k, in - 1)];
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) v[i][k] = e[2 * k] | e[2 * k + 1] << 16;
             }
+            *reinterpret_cast<u32x4v *>(rows + r * PO_STRIDE + c) = v[i];
         }
     }
     __syncthreads();
     const uint16_t *far = X + (size_t)min(t0 + row, tokens - 1) * ldx;     // rows past the end repeat the last one: their products are never stored
     const uint16_t *near = rows + row * PO_STRIDE;
+    uint32_t e[N][8];
+    auto fetch = [&](const uint16_t *from, uint32_t base) {     // (all on their way before the first is needed)
+#pragma unroll
+        for (uint32_t i = 0; i < N; ++i)
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k) {
+                const uint32_t c = ch[i][k >> 2][k & 3];
+                if (c != SKL_NO_CHANNEL && skl_in_range(c, in, SKL_DBG_CHANNEL)) e[i][k] = from[c - base];
+            }
+    };
+    if (win.n) fetch(near, win.base);
+    else fetch(far, 0);
 #pragma unroll
     for (uint32_t i = 0; i < N; ++i) {
         const uint32_t step = g * PO_STEPS + wave + WAVES * i;
         if (step >= n_steps) continue;
-        uint32_t w[4] = {0, 0, 0, 0};
+        uint32_t w[4];
 #pragma unroll
         for (uint32_t k = 0; k < 8; ++k) {
-            const uint32_t c = ch[i][k >> 2][k & 3];
-            uint32_t e = 0;
-            if (c != SKL_NO_CHANNEL && skl_in_range(c, in, SKL_DBG_CHANNEL)) e = win.n ? near[c - win.base] : far[c];
-            w[k >> 1] |= e << ((k & 1) * 16);
+            const uint32_t v = ch[i][k >> 2][k & 3] != SKL_NO_CHANNEL ? e[i][k] : 0;
+            w[k >> 1] = k & 1 ? w[k >> 1] | v << 16 : v;
         }
         Xp[place(step)] =
             make_uint4(neg_half_pair(w[0], x_dt), neg_half_pair(w[1], x_dt), neg_half_pair(w[2], x_dt), neg_half_pair(w[3], x_dt));

@@ -75,6 +75,20 @@ def test_activation_packing_of_the_staged_prefill(in_f, tokens, ldx_pad, wide_sh
     assert rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
 
 
+@pytest.mark.parametrize("flags", [0, skl.FLAG_STAGED_PREFILL])
+@pytest.mark.parametrize("in_f,tokens,ldx_pad", [(5, 33, 0), (7, 20, 2), (8, 17, 1), (513, 40, 0), (1029, 100, 6), (391, 16, 1)])
+def test_activation_packing_of_odd_rows(in_f, tokens, ldx_pad, flags):
+    """Rows of fewer than eight channels, and rows that end inside a 16-byte piece, on any 2-byte boundary; the last row of X
+    ends where its buffer does."""
+    rng = np.random.default_rng(in_f + tokens)
+    sk = row_layer(6, in_f, 264, 3, np.where(rng.random(in_f) < 0.02, 20, 9))
+    X = wk.f32_to_bf16_bits(rng.standard_normal((tokens, in_f)).astype(np.float32))
+    ref = oracle.linear(oracle.query(sk), X, x_kind="bf16")
+    with GpuLayer(sk, flags) as g:
+        y = g.gemm(X, "bf16", "f32", ldx=in_f + ldx_pad)
+    assert np.isfinite(y).all() and rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
+
+
 @pytest.mark.parametrize("tokens", [1, 16, 17, 64, 65, 100, 128, 129])
 @pytest.mark.parametrize("in_f,out_f,ldy_pad,y_dt", [
     # (staged) shares of fewer than eight blocks: one per tile, stored without partials; ragged outputs
