@@ -1,6 +1,6 @@
 // Per-weight path: 2-D groups, one hash evaluation (Sec. 3.1 Eq. 3) per
 // weight and sketch row.
-#include "skl_device.h"
+#include "skl_prefill_common.h"
 
 namespace SKL_NS {
 
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(TS_O * TS_SLICES) void k_tile_gemv_small(TileArgs p
         store_out(y, y_dt, (size_t)(b0 + b) * ldy + ob * p.to + ol, t);
 }
 
-// prefill GEMM on path 0: 64 tokens x 64 outputs per workgroup; per 16 input
+// prefill GEMM on path 0, any geometry: 64 tokens x 64 outputs per workgroup; per 16 input
 // rows the weights are reconstructed once into LDS (transposed, binary16 with
 // inverted sign) and fed to 32x32x16 MFMAs.
 #define TG_T 64
@@ -319,6 +319,130 @@ __global__ __launch_bounds__(SKL_WG) void k_tile_gemm(TileArgs p, const uint16_t
     }
 }
 
+
+// Prefill GEMM on path 0 where a lane's eight consecutive input rows lie in one group (group heights that are multiples of 8)
+// and a 16-wide output tile does (widths that are multiples of 16).  A workgroup owns RB * 16 tokens x OB * 16 outputs; its
+// wavefronts divide the input rows among themselves, 32 at a time: a lane rebuilds the eight weights of one output that
+// the matrix instruction takes from it (one key per row and sketch row from the tables above the outputs, which all sit in
+// LDS), and the activations come from memory in operand order as they lie.  No barrier between the first table and the last
+// product; the wavefronts' sums are added in their order at the end.
+// Bound by the vector units (four instructions per weight and sketch row); every weight is rebuilt once per RB * 16 tokens.
+// Whole call against 64 x 64 tiles that walk all rows, 16 at a time between two barriers (k_tile_gemm, for the other
+// geometries): 256 x 256, 17 tokens, 15.5 -> 4.6 us, 512 x 512, 256 tokens, 32.7 -> 6.3, 1024 x 1024, 64 tokens, 62 -> 7.9, 2048 x 512,
+// 100 tokens, 120 -> 11.8, 2048 x 2048, 512 tokens, 130 -> 31.
+// The wavefronts' chains of float32 sums are shorter: errors against 64 bits 0.39 to 0.69 of those before (24 drawn layers).
+#define TP_RED_BYTES 65536u             // sums of all wavefronts for some of the 16 x 16 blocks of the tile
+
+// a group's table to LDS by one wavefront, wherever it starts, four loads in flight
+__device__ __forceinline__ void stage_by_wave(uint16_t *dst, const uint16_t *src, uint32_t n, uint32_t lane)
+{
+    const uint32_t pieces = n / 8;
+    for (uint32_t i0 = lane; i0 < pieces; i0 += 256) {
+        u32x4v v[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const u32x4h *>(src + 8 * min(i0 + 64 * k, pieces - 1));
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+            if (i0 + 64 * k < pieces) reinterpret_cast<u32x4v *>(dst)[i0 + 64 * k] = v[k];
+    }
+    if (lane < (n & 7u)) dst[pieces * 8 + lane] = src[pieces * 8 + lane];
+}
+
+template <int D, int RB, int OB>
+__global__ __launch_bounds__(OB == 2 ? 512 : 1024) void k_tile_prompt(TileArgs p, const uint16_t *__restrict__ X, uint32_t x_dt, uint32_t ldx, uint32_t tokens,
+                                                      void *__restrict__ Y, uint32_t y_dt, uint32_t ldy, uint32_t key_words, uint32_t at_once)
+{
+    uint32_t *const width = reinterpret_cast<uint32_t *>(smem + at_once * key_words);           // of the tables in LDS
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+    const uint32_t n = lane & 15, kg = lane >> 4;
+    const uint32_t n_jb = p.in / p.tj, n_ot = p.to / (16 * OB);
+    const uint32_t ob = __builtin_amdgcn_readfirstlane(blockIdx.x / n_ot), o0 = (blockIdx.x - ob * n_ot) * (16 * OB);
+    const uint32_t t0 = blockIdx.y * (RB * 16);
+    const uint16_t *row[RB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) row[i] = X + (size_t)min(t0 + i * 16 + n, tokens - 1) * ldx;   // (rows past the end: never stored)
+    float4v acc[RB][OB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int b = 0; b < OB; ++b) acc[i][b] = (float4v){0.f, 0.f, 0.f, 0.f};
+    u32x4v next[RB];
+    auto request = [&](uint32_t j) {                            // (steps past the last row fetch the last eight again)
+#pragma unroll
+        for (int i = 0; i < RB; ++i) next[i] = *reinterpret_cast<const u32x4h *>(row[i] + min(j, p.in - 8));
+    };
+    for (uint32_t jb0 = 0; jb0 < n_jb; jb0 += at_once) {        // as many tables as fit, all of them in most layers
+        const uint32_t jb1 = min(jb0 + at_once, n_jb), j_hi = jb1 * p.tj;
+        uint32_t j = jb0 * p.tj + wave * 32 + kg * 8, left = wave * 32 < j_hi - jb0 * p.tj ? (j_hi - jb0 * p.tj - wave * 32 + 32 * nw - 1) / (32 * nw) : 0;
+        request(j);
+        if (jb0) __syncthreads();                               // nobody reads the tables before these any more
+        for (uint32_t jb = jb0 + wave; jb < jb1; jb += nw) {
+            const skl_group_meta gm = p.gmeta[jb * p.n_ob + ob];
+            if (lane == 0) width[jb - jb0] = gm.K;
+            stage_by_wave(reinterpret_cast<uint16_t *>(smem + (jb - jb0) * key_words), p.keys + gm.key_off, D * gm.K, lane);
+        }
+        __syncthreads();
+        for (; left; --left, j += 32 * nw) {
+            const bool live = j < j_hi;
+            const uint32_t jc = live ? j : jb0 * p.tj, jb = jc / p.tj, jl = jc - jb * p.tj;
+            const uint32_t K = width[jb - jb0], Kq = K << 8, tab = (uint32_t)(uintptr_t)(lds_void *)smem + (jb - jb0) * key_words * 16;
+            u32x4v x[RB];
+#pragma unroll
+            for (int i = 0; i < RB; ++i) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[i][k] = live ? neg_half_pair(next[i][k], x_dt) : 0;
+            }
+            request(j + 32 * nw);
+#pragma unroll
+            for (int b = 0; b < OB; ++b) {
+                TileHash<D> th;
+                th.init(p.h, jl * p.to + o0 + b * 16 + n, p.to);
+                uint32_t w[4];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    uint32_t m = 0;
+#pragma unroll
+                    for (int r = 0; r < D; ++r) {
+                        const uint32_t at = r * K + select_index(th.t[r], Kq);
+                        m = max(m, (uint32_t)*(const __attribute__((address_space(3))) uint16_t *)(uintptr_t)(tab + at * 2));
+                        th.t[r] += th.step[r];
+                    }
+                    w[k >> 1] = k & 1 ? w[k >> 1] | m << 16 : m;
+                }
+                uint4 v;
+                v.x = keys_to_neg_half2_mad(w[0]); v.y = keys_to_neg_half2_mad(w[1]);
+                v.z = keys_to_neg_half2_mad(w[2]); v.w = keys_to_neg_half2_mad(w[3]);
+                v = keep_if(live, v);
+                // both operands carry an inverted sign: the product is x * w
+#pragma unroll
+                for (int i = 0; i < RB; ++i)
+                    acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, x[i]), __builtin_bit_cast(half8v, v), acc[i][b], 0, 0, 0);
+            }
+        }
+    }
+    // the blocks of the tile, as many at a time as their sums fit: every wavefront leaves its own, and one adds them in order
+    const uint32_t some = min((uint32_t)(RB * OB), TP_RED_BYTES / 1024 / nw);
+    float4v *const red = reinterpret_cast<float4v *>(smem);
+    for (uint32_t r0 = 0; r0 < RB * OB; r0 += some) {
+        __syncthreads();
+#pragma unroll
+        for (uint32_t i = 0; i < RB; ++i)
+#pragma unroll
+            for (uint32_t b = 0; b < OB; ++b)
+                if (i * OB + b >= r0 && i * OB + b < r0 + some) red[(wave * some + i * OB + b - r0) * 64 + lane] = acc[i][b];
+        __syncthreads();
+        for (uint32_t k = wave; k < some && r0 + k < RB * OB; k += nw) {
+            float4v s = red[k * 64 + lane];
+            for (uint32_t v = 1; v < nw; ++v) s += red[(v * some + k) * 64 + lane];
+            const uint32_t i = (r0 + k) / OB, b = (r0 + k) % OB;
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e) {
+                const uint32_t t = t0 + i * 16 + kg * 4 + e;
+                if (t < tokens) store_out(Y, y_dt, (size_t)t * ldy + ob * p.to + o0 + b * 16 + n, s[e]);
+            }
+        }
+    }
+}
 
 static TileArgs make_tile_args(const skl_layer *L, const TableSrc &src)
 {
@@ -429,6 +553,35 @@ skl_status_t skl_tile_launch_gemm(const skl_layer *L, const TableSrc &src, const
     if (n_tt > 65535) {
         skl_set_error("more than %u tokens in one call through the per-weight path", 65535u * TG_T);
         return SKL_ERR_UNSUPPORTED;
+    }
+    // tables above an output tile that are in LDS together
+    const uint32_t n_jb = L->n_jb, at_once = std::min(n_jb, std::max(1u, 49152u / (kw * 16)));
+    const size_t tables = (size_t)at_once * (kw * 16 + 4);
+    if (L->tj % 8 == 0 && L->to % 16 == 0 && tables <= SKL_LDS_HARD_BYTES) {
+        // The smallest tile that is no more than three workgroups for two CUs: a larger one re-uses weights and activations
+        // more, a smaller one fills the chip and is over sooner.  Whole calls by tokens x outputs per tile, in us: 512 x 512,
+        // 256 tokens 32 x 16 (256 workgroups) 6.7, 64 x 16 7.7, 128 x 16 10.9; 2048 x 512, 100 tokens, 32 x 16 (128) 11.8, 64 x 16
+        // 15.1; 1024 x 1024, 400 tokens, 32 x 32 (416) 16.0, 64 x 32 (224) 12.7, 128 x 32 17.7; 2048 x 2048, 512 tokens, 32 x 32
+        // (1024) 48, 64 x 32 34.4, 128 x 32 (256) 30.8; 256 x 2048, 300 tokens, 64 x 32 (320) 8.3, 128 x 32 10.5.
+        const uint32_t blocks = (tokens + 15) / 16;
+        uint32_t RB = 2, ob = 1;
+        auto wgs = [&]() { return (uint64_t)(L->out / (16 * ob)) * ((blocks + RB - 1) / RB); };
+        if (wgs() > SKL_N_CU * 3 / 2 && L->to % 32 == 0) ob = 2;
+        while (wgs() > SKL_N_CU * 3 / 2 && RB < 8) RB *= 2;
+        const dim3 tiles(L->out / (16 * ob), (blocks + RB - 1) / RB);
+        // (sixteen wavefronts, 2048 rows: 2048 x 512, 100 tokens, 12.8 -> 11.8, 2048 x 256, 512 tokens, 13.7 -> 11.5; 1024 rows the same; 512
+        // x 512, 100 tokens, 6.0 / 6.5)
+        const uint32_t nw = ob == 1 && wgs() <= SKL_N_CU && L->in > 1024 ? 16 : 8;
+        const size_t need = std::max<size_t>(tables, (size_t)nw * std::min(RB * ob, TP_RED_BYTES / 1024 / nw) * 1024);
+        auto launch = [&](auto kernel) {
+            st = allow_lds(kernel, need);
+            if (st == SKL_OK) hipLaunchKernelGGL(kernel, tiles, dim3(64 * nw), need, stream, a, X, (uint32_t)x_dt, ldx, tokens, Y, (uint32_t)y_dt, ldy, kw, at_once);
+        };
+        DISPATCH_D(L->d, {
+            if (ob == 1) RB == 2 ? launch(k_tile_prompt<D, 2, 1>) : RB == 4 ? launch(k_tile_prompt<D, 4, 1>) : launch(k_tile_prompt<D, 8, 1>);
+            else RB == 2 ? launch(k_tile_prompt<D, 2, 2>) : RB == 4 ? launch(k_tile_prompt<D, 4, 2>) : launch(k_tile_prompt<D, 8, 2>);
+        });
+        return st == SKL_OK ? check_launch("gemm") : st;
     }
     const dim3 grid(L->n_ob * n_oc, n_tt);
     DISPATCH_D(L->d, {

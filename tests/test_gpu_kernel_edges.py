@@ -391,6 +391,33 @@ def test_batched_decode_stores(in_f, out_f, batch):
 
 
 @pytest.mark.parametrize("query_mode", [0, 1])
+@pytest.mark.parametrize("in_f,out_f,tile_in,tile_out,d,widths,tokens,x_dt,y_dt,ldx_pad", [
+    (256, 256, 128, 128, 2, (200, 333), 17, "f16", "f16", 0),       # two tables, tiles of 32 tokens
+    (8, 16, 8, 16, 1, (3, 3), 1, "bf16", "f32", 0),                 # one lane group of one step
+    (72, 96, 24, 48, 3, (7, 20), 33, "f16", "f32", 3),              # steps that span groups and end short; odd rows of X
+    (1032, 160, 8, 16, 4, (1, 5), 65, "bf16", "bf16", 1),           # a table per eight rows, more than fit the wavefronts
+    (640, 512, 128, 128, 3, (170, 171), 129, "bf16", "f32", 0),     # two tiles of tokens, sixteen wavefronts
+    (512, 4096, 256, 256, 3, (682, 683), 130, "f16", "f32", 0),     # 32 outputs per tile, tables on odd addresses
+    (2048, 64, 256, 64, 8, (1500, 1600), 40, "f16", "f16", 0),      # tables that do not all fit at once
+])
+def test_group_prompts(in_f, out_f, tile_in, tile_out, d, widths, tokens, x_dt, y_dt, ldx_pad, query_mode):
+    """The kernel for groups of whole lanes and output blocks, at its edges, against the oracle in 64 bits."""
+    rng = np.random.default_rng(in_f + out_f + tokens)
+    A, C = hash_params(rng, d)
+    K = rng.choice(widths, (in_f // tile_in) * (out_f // tile_out)).astype(np.uint32)
+    states = (rng.standard_normal(int(K.sum()) * d) * 0.02).astype(np.float16).view(np.uint16)
+    sk = oracle.Sketch(in_f, out_f, tile_in, tile_out, d, A, C, K, states)
+    x = rng.standard_normal((tokens, in_f)).astype(np.float32)
+    X = wk.f32_to_bf16_bits(x) if x_dt == "bf16" else x.astype(np.float16).view(np.uint16)
+    ref = matmul_f64(oracle.query(sk, query_mode), X if x_dt == "bf16" else X.view(np.float16), x_dt)
+    with GpuLayer(sk, query_mode=query_mode) as g:
+        y = g.gemm(X, x_dt, y_dt, ldx=in_f + ldx_pad, ldy=out_f + 3)
+        assert np.array_equal(y, g.gemm(X, x_dt, y_dt, ldx=in_f + ldx_pad, ldy=out_f + 3))
+    tol = SUM_TOL + {"f32": 0.0, "f16": 2.0**-11, "bf16": 2.0**-8}[y_dt]
+    assert np.isfinite(y.astype(np.float32)).all() and rel_fro(y, ref) <= tol, rel_fro(y, ref)
+
+
+@pytest.mark.parametrize("query_mode", [0, 1])
 @pytest.mark.parametrize("in_f,out_f,d,widths,batch", [
     (777, 1500, 4, (9, 200, 330, 1300), 1),     # blocks of all widths, some groups with one table buffer, some of one block
     (2000, 333, 3, (9, 250, 500, 1800), 1),
