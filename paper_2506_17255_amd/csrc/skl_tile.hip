@@ -541,6 +541,46 @@ skl_status_t skl_tile_launch_gemv_small(const skl_layer *L, const TableSrc &src,
     return st == SKL_OK ? check_launch("gemv") : st;
 }
 
+// tables above an output tile that are in LDS together
+static uint32_t tile_prompt_tables(const skl_layer *L) { return std::min(L->n_jb, std::max(1u, 49152u / (uint32_t)(tile_key_words(L) * 16))); }
+static size_t tile_prompt_table_bytes(const skl_layer *L) { return (size_t)tile_prompt_tables(L) * (tile_key_words(L) * 16 + 4); }
+
+bool skl_tile_prompt_fits(const skl_layer *L) { return L->tj % 8 == 0 && L->to % 16 == 0 && tile_prompt_table_bytes(L) <= SKL_LDS_HARD_BYTES; }
+
+skl_status_t skl_tile_launch_prompt(const skl_layer *L, const TableSrc &src, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx, void *Y,
+                                    skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, hipStream_t stream)
+{
+    skl_status_t st = SKL_OK;
+    const TileArgs a = make_tile_args(L, src);
+    const uint32_t kw = (uint32_t)tile_key_words(L), at_once = tile_prompt_tables(L);
+    const size_t tables = tile_prompt_table_bytes(L);
+    // The smallest tile that is no more than three workgroups for two CUs: a larger one re-uses weights and activations
+    // more, a smaller one fills the chip and is over sooner.  Whole calls by tokens x outputs per tile, in us: 512 x 512,
+    // 256 tokens 32 x 16 (256 workgroups) 6.7, 64 x 16 7.7, 128 x 16 10.9; 2048 x 512, 100 tokens, 32 x 16 (128) 11.8, 64 x 16
+    // 15.1; 1024 x 1024, 400 tokens, 32 x 32 (416) 16.0, 64 x 32 (224) 12.7, 128 x 32 17.7; 2048 x 2048, 512 tokens, 32 x 32
+    // (1024) 48, 64 x 32 34.4, 128 x 32 (256) 30.8; 256 x 2048, 300 tokens, 64 x 32 (320) 8.3, 128 x 32 10.5.
+    const uint32_t blocks = (tokens + 15) / 16;
+    uint32_t RB = blocks == 1 ? 1 : 2, ob = 1;
+    auto wgs = [&]() { return (uint64_t)(L->out / (16 * ob)) * ((blocks + RB - 1) / RB); };
+    if (wgs() > SKL_N_CU * 3 / 2 && L->to % 32 == 0) ob = 2;
+    while (wgs() > SKL_N_CU * 3 / 2 && RB > 1 && RB < 8) RB *= 2;
+    const dim3 tiles(L->out / (16 * ob), (blocks + RB - 1) / RB);
+    // (sixteen wavefronts, 2048 rows: 2048 x 512, 100 tokens, 12.8 -> 11.8, 2048 x 256, 512 tokens, 13.7 -> 11.5; 1024 rows the same; 512
+    // x 512, 100 tokens, 6.0 / 6.5; up to 16 tokens, 1024 x 1024 6.9 -> 6.6, 512 x 512 the same)
+    const uint32_t nw = ob == 1 && wgs() <= SKL_N_CU && L->in > (RB == 1 ? 512u : 1024u) ? 16 : 8;
+    const size_t need = std::max<size_t>(tables, (size_t)nw * std::min(RB * ob, TP_RED_BYTES / 1024 / nw) * 1024);
+    auto launch = [&](auto kernel) {
+        st = allow_lds(kernel, need);
+        if (st == SKL_OK) hipLaunchKernelGGL(kernel, tiles, dim3(64 * nw), need, stream, a, X, (uint32_t)x_dt, ldx, tokens, Y, (uint32_t)y_dt, ldy, kw, at_once);
+    };
+    DISPATCH_D(L->d, {
+        if (RB == 1) ob == 1 ? launch(k_tile_prompt<D, 1, 1>) : launch(k_tile_prompt<D, 1, 2>);
+        else if (ob == 1) RB == 2 ? launch(k_tile_prompt<D, 2, 1>) : RB == 4 ? launch(k_tile_prompt<D, 4, 1>) : launch(k_tile_prompt<D, 8, 1>);
+        else RB == 2 ? launch(k_tile_prompt<D, 2, 2>) : RB == 4 ? launch(k_tile_prompt<D, 4, 2>) : launch(k_tile_prompt<D, 8, 2>);
+    });
+    return st == SKL_OK ? check_launch("gemm") : st;
+}
+
 skl_status_t skl_tile_launch_gemm(const skl_layer *L, const TableSrc &src, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx,
                                   void *Y, skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, hipStream_t stream)
 {
@@ -554,35 +594,7 @@ skl_status_t skl_tile_launch_gemm(const skl_layer *L, const TableSrc &src, const
         skl_set_error("more than %u tokens in one call through the per-weight path", 65535u * TG_T);
         return SKL_ERR_UNSUPPORTED;
     }
-    // tables above an output tile that are in LDS together
-    const uint32_t n_jb = L->n_jb, at_once = std::min(n_jb, std::max(1u, 49152u / (kw * 16)));
-    const size_t tables = (size_t)at_once * (kw * 16 + 4);
-    if (L->tj % 8 == 0 && L->to % 16 == 0 && tables <= SKL_LDS_HARD_BYTES) {
-        // The smallest tile that is no more than three workgroups for two CUs: a larger one re-uses weights and activations
-        // more, a smaller one fills the chip and is over sooner.  Whole calls by tokens x outputs per tile, in us: 512 x 512,
-        // 256 tokens 32 x 16 (256 workgroups) 6.7, 64 x 16 7.7, 128 x 16 10.9; 2048 x 512, 100 tokens, 32 x 16 (128) 11.8, 64 x 16
-        // 15.1; 1024 x 1024, 400 tokens, 32 x 32 (416) 16.0, 64 x 32 (224) 12.7, 128 x 32 17.7; 2048 x 2048, 512 tokens, 32 x 32
-        // (1024) 48, 64 x 32 34.4, 128 x 32 (256) 30.8; 256 x 2048, 300 tokens, 64 x 32 (320) 8.3, 128 x 32 10.5.
-        const uint32_t blocks = (tokens + 15) / 16;
-        uint32_t RB = 2, ob = 1;
-        auto wgs = [&]() { return (uint64_t)(L->out / (16 * ob)) * ((blocks + RB - 1) / RB); };
-        if (wgs() > SKL_N_CU * 3 / 2 && L->to % 32 == 0) ob = 2;
-        while (wgs() > SKL_N_CU * 3 / 2 && RB < 8) RB *= 2;
-        const dim3 tiles(L->out / (16 * ob), (blocks + RB - 1) / RB);
-        // (sixteen wavefronts, 2048 rows: 2048 x 512, 100 tokens, 12.8 -> 11.8, 2048 x 256, 512 tokens, 13.7 -> 11.5; 1024 rows the same; 512
-        // x 512, 100 tokens, 6.0 / 6.5)
-        const uint32_t nw = ob == 1 && wgs() <= SKL_N_CU && L->in > 1024 ? 16 : 8;
-        const size_t need = std::max<size_t>(tables, (size_t)nw * std::min(RB * ob, TP_RED_BYTES / 1024 / nw) * 1024);
-        auto launch = [&](auto kernel) {
-            st = allow_lds(kernel, need);
-            if (st == SKL_OK) hipLaunchKernelGGL(kernel, tiles, dim3(64 * nw), need, stream, a, X, (uint32_t)x_dt, ldx, tokens, Y, (uint32_t)y_dt, ldy, kw, at_once);
-        };
-        DISPATCH_D(L->d, {
-            if (ob == 1) RB == 2 ? launch(k_tile_prompt<D, 2, 1>) : RB == 4 ? launch(k_tile_prompt<D, 4, 1>) : launch(k_tile_prompt<D, 8, 1>);
-            else RB == 2 ? launch(k_tile_prompt<D, 2, 2>) : RB == 4 ? launch(k_tile_prompt<D, 4, 2>) : launch(k_tile_prompt<D, 8, 2>);
-        });
-        return st == SKL_OK ? check_launch("gemm") : st;
-    }
+    if (skl_tile_prompt_fits(L)) return skl_tile_launch_prompt(L, src, X, x_dt, ldx, Y, y_dt, ldy, tokens, stream);
     const dim3 grid(L->n_ob * n_oc, n_tt);
     DISPATCH_D(L->d, {
         st = allow_lds(k_tile_gemm<D>, lds);

@@ -418,6 +418,32 @@ def test_group_prompts(in_f, out_f, tile_in, tile_out, d, widths, tokens, x_dt, 
 
 
 @pytest.mark.parametrize("query_mode", [0, 1])
+@pytest.mark.parametrize("in_f,out_f,tile_in,tile_out,d,widths,batch,one_launch", [
+    (512, 128, 32, 16, 3, (9, 20), 2, True),        # the fewest rows, input rows and outputs that take the prompt kernel
+    (512, 112, 32, 16, 3, (9, 20), 2, False),       # fewer outputs: partial sums
+    (520, 16384, 8, 16, 2, (2, 3), 16, True),       # 32 outputs per tile do not fit the groups
+    (1024, 512, 256, 256, 4, (300, 301), 5, True),
+    (504, 144, 72, 16, 3, (9, 20), 16, True),       # fewer rows: the small kernel, which takes groups of at least 64
+    (1100, 520, 20, 40, 2, (9, 20), 3, False),      # groups that are no whole lanes: partial sums
+])
+def test_group_decode_of_several_rows(in_f, out_f, tile_in, tile_out, d, widths, batch, one_launch, query_mode):
+    rng = np.random.default_rng(in_f + out_f)
+    A, C = hash_params(rng, d)
+    K = rng.choice(widths, (in_f // tile_in) * (out_f // tile_out)).astype(np.uint32)
+    states = (rng.standard_normal(int(K.sum()) * d) * 0.02).astype(np.float16).view(np.uint16)
+    sk = oracle.Sketch(in_f, out_f, tile_in, tile_out, d, A, C, K, states)
+    x = rng.standard_normal((batch, in_f)).astype(np.float16)
+    ref = matmul_f64(oracle.query(sk, query_mode), x, "f16")
+    with GpuLayer(sk, query_mode=query_mode) as g:
+        ws, need = g.workspace(0, batch)
+        ws.fill_(0xA5)
+        y = g.gemv(x, "f32", ldy=out_f + 1)
+        assert bool((ws[:need] == 0xA5).all()) == one_launch
+        assert np.array_equal(y, g.gemv(x, "f32", ldx=in_f + 8))
+    assert np.isfinite(y).all() and rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
+
+
+@pytest.mark.parametrize("query_mode", [0, 1])
 @pytest.mark.parametrize("in_f,out_f,d,widths,batch", [
     (777, 1500, 4, (9, 200, 330, 1300), 1),     # blocks of all widths, some groups with one table buffer, some of one block
     (2000, 333, 3, (9, 250, 500, 1800), 1),
