@@ -39,28 +39,6 @@ __device__ __forceinline__ uint16_t key_of_code(int q, uint16_t scale_bits, uint
     return key_of_code_step(q, half_bits_to_float(scale_bits) * (BITS == 8 ? 1.0f / 127.0f : 1.0f / 7.0f), mode);
 }
 
-// Two codes as binary16 numbers, exactly (a binary16 number between 1024 and 2047 holds an integer in its low bits), and
-// the two order keys they stand for.  step: minus scale / qmax in float32; with -0 added to the product its sign, also that
-// of a zero (code 0 is +0, a negative code with scale 0 is -0), is the inverted sign of the state.
-__device__ __forceinline__ half2v codes_from_biased(uint32_t biased, float bias)
-{
-    return __builtin_bit_cast(half2v, biased) - (half2v){(_Float16)bias, (_Float16)bias};
-}
-
-template <int MODE>
-__device__ __forceinline__ uint32_t keys_of_codes(half2v q, float step0, float step1)
-{
-    half2v neg;
-    neg[0] = (_Float16)__builtin_fmaf((float)q[0], step0, -0.0f);
-    neg[1] = (_Float16)__builtin_fmaf((float)q[1], step1, -0.0f);
-    const uint32_t h = __builtin_bit_cast(uint32_t, neg);
-    const ushort2v u = __builtin_bit_cast(ushort2v, h);
-    if (MODE == 0) return __builtin_bit_cast(uint32_t, (ushort2v)(u * (unsigned short)2 + (u >> 15)));     // magnitude, then the sign bit that is clear in the state
-    // h >= 0 where the state is negative: key = ~state; else state | 0x8000
-    const uint32_t top = __builtin_bit_cast(uint32_t, __builtin_bit_cast(short2v, h) >> 15);
-    return h ^ (~top & 0x7FFF7FFFu);
-}
-
 // Row sketches.  create() keeps the codes in the order of the block tables: word (r, k, c) of a block holds
 // the eight codes of channels 8c .. 8c + 7 for state (r, k) -- 4 bytes (nibble i = channel 8c + i) or
 // 8 bytes per word, at the word's index in the unpadded table -- and the scales as one 16-byte word of
@@ -75,9 +53,7 @@ __global__ __launch_bounds__(SKL_WG) void k_expand_rows(const skl_block_meta *__
 {
     const uint32_t gid = blockIdx.x * SKL_WG + threadIdx.x;     // word of the unpadded tables
     if (gid >= n_words) return;
-    uint2 codes;                                                // on their way while the block is looked up
-    if (BITS == 8) codes = reinterpret_cast<const uint2 *>(tcodes)[gid];
-    else codes = make_uint2(reinterpret_cast<const uint32_t *>(tcodes)[gid], 0);
+    const uint2 codes = codes_of_word<BITS>(tcodes, gid);       // on their way while the block is looked up
     const uint32_t blk = __builtin_amdgcn_readfirstlane(chunk_block[__builtin_amdgcn_readfirstlane(gid >> 6)]);
     const skl_block_meta bm = bmeta[blk];
     const uint32_t K = bm.K, nb = bm.nb;
@@ -88,23 +64,7 @@ __global__ __launch_bounds__(SKL_WG) void k_expand_rows(const skl_block_meta *__
     uint32_t r = 0;
     for (uint32_t i = 1; i < d; ++i) r += rk >= i * K;
     const uint4 sw = tscales[bm.scale_off16 + r * nb + c];
-    const uint32_t sc[4] = {sw.x, sw.y, sw.z, sw.w};
-    uint32_t key[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {                               // channels 8c + 2j, 8c + 2j + 1; a slot without a channel has code 0: +0.0
-        half2v q;
-        if (BITS == 8) {
-            const uint32_t two = (j < 2 ? codes.x : codes.y) >> (j & 1) * 16;
-            q = codes_from_biased((((two & 0xFFFFu) | (two << 8 & 0xFFFF0000u)) & 0x00FF00FFu) ^ 0x64806480u, 1152.0f);
-        } else {
-            const uint32_t two = codes.x >> 8 * j;
-            q = codes_from_biased((((two & 0xFFFFu) | (two << 12 & 0xFFFF0000u)) & 0x000F000Fu) ^ 0x64086408u, 1032.0f);
-        }
-        const half2v s = __builtin_bit_cast(half2v, sc[j]);
-        constexpr float per = BITS == 8 ? -1.0f / 127.0f : -1.0f / 7.0f;
-        key[j] = keys_of_codes<MODE>(q, (float)s[0] * per, (float)s[1] * per);
-    }
-    const uint4 w = make_uint4(key[0], key[1], key[2], key[3]);
+    const uint4 w = keys_of_word<BITS, MODE>(codes, sw);
     if (gid - bm.ptable_off16 >= words) return;
     if (padded) padded[bm.table_off16 + (size_t)rk * bm.rs + c] = w;
     if (unpadded) unpadded[gid] = w;

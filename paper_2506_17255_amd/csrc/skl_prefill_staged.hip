@@ -28,7 +28,9 @@ static_assert(SG_SLOT_BYTES == SG_SLOT_WORDS * 16u, "weight words of a 64-channe
 struct RebuildArgs {
     HashArgs h;
     const skl_block_meta *bmeta;
-    const uint4 *tables;                // padded block tables, [r][k][rs] words
+    const uint4 *tables;                // padded block tables, [r][k][rs] words; low-bit states:
+    const uint8_t *codes;               // codes and scales instead
+    const uint4 *scales;
     uint4 *Wp;                          // [output tile of the slab][64-channel block][SG_SLOT_WORDS]
     uint32_t out, n_blocks, KB, n_words;
     uint32_t tile0, n_col, n_oseg;      // the slab: first output tile (of 256), pieces of 256 outputs, output segments
@@ -62,17 +64,49 @@ __device__ __forceinline__ void rebuild_body(const RebuildArgs &p, uint32_t blk,
     }
 }
 
+// A block's padded table from codes and scales.  The expansion by a launch of its own, which writes all tables to the workspace
+// for this kernel to read back, took 8 to 10 us of a call (4096 x 11008, 4-bit states, 100 tokens, 72.5 -> 65.4; 6784 x 11008, 8-bit,
+// 237 tokens, 123 -> 112; 1024 x 2048, 8-bit, 700 tokens, 24.4 -> 22.4).
+template <int D, int BITS>
+__device__ __forceinline__ void expand_block(const RebuildArgs &p, const skl_block_meta &bm)
+{
+    const uint32_t nb = bm.nb, words = D * bm.K * nb, lg = 31 - __builtin_clz(nb);
+    for (uint32_t i0 = threadIdx.x; i0 < words; i0 += 4 * SG_REBUILD_WG) {
+        uint2 codes[4];
+        uint4 sw[4];
+        uint32_t rk[4], c[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t i = min(i0 + k * SG_REBUILD_WG, words - 1);
+            codes[k] = codes_of_word<BITS>(p.codes, bm.ptable_off16 + i);
+            c[k] = i & (nb - 1);
+            rk[k] = i >> lg;
+            uint32_t r = 0;
+#pragma unroll
+            for (uint32_t j = 1; j < D; ++j) r += rk[k] >= j * bm.K;
+            sw[k] = p.scales[bm.scale_off16 + r * nb + c[k]];
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+            if (i0 + k * SG_REBUILD_WG < words) smem[rk[k] * bm.rs + c[k]] = keys_of_word<BITS, SKL_QM>(codes[k], sw[k]);
+    }
+}
+
 // Workgroup `idx` of n_blocks * n_oseg: channel block idx % n_blocks, output segment idx / n_blocks.
 // LDS: the block's padded table.
-template <int D>
+template <int D, int BITS>
 __device__ __forceinline__ void rebuild_block(const RebuildArgs &p, uint32_t idx)
 {
     const uint32_t blk = idx % p.n_blocks, seg = idx / p.n_blocks;
     if (!skl_in_range(blk, p.n_blocks, SKL_DBG_BLOCK) || !skl_in_range(seg, p.n_oseg, SKL_DBG_OUTPUT)) return;
     const skl_block_meta bm = p.bmeta[blk];
-    // global -> LDS without passing through registers: all of a wavefront's chunks are in flight at once
-    copy_words_to_lds_async(smem, p.tables + bm.table_off16, D * bm.K * bm.rs, SG_REBUILD_WG / 64);
-    wait_async_copies();
+    if constexpr (BITS == 16) {
+        // global -> LDS without passing through registers: all of a wavefront's chunks are in flight at once
+        copy_words_to_lds_async(smem, p.tables + bm.table_off16, D * bm.K * bm.rs, SG_REBUILD_WG / 64);
+        wait_async_copies();
+    } else {
+        expand_block<D, BITS>(p, bm);
+    }
     __syncthreads();
     switch (bm.rs) {
     case 9: rebuild_body<D, 9>(p, blk, seg, bm, smem); break;
@@ -91,12 +125,12 @@ __device__ __forceinline__ void rebuild_block(const RebuildArgs &p, uint32_t idx
 // nothing, without the stores 79); 4096 x 4096 19.7 -> 15.3.
 // Channel blocks x output segments + 16-token rows x step groups workgroups, over two grid dimensions (a dimension holds
 // 2^32 threads)
-template <int D>
+template <int D, int BITS>
 __global__ __launch_bounds__(SG_REBUILD_WG) void k_rebuild_operands(RebuildArgs r, PackArgs k, uint32_t n_pack)
 {
     const uint32_t n_rows = (k.tokens + 15) / 16, idx = blockIdx.y * gridDim.x + blockIdx.x;
     if (idx < r.n_blocks * r.n_oseg) {
-        rebuild_block<D>(r, idx);
+        rebuild_block<D, BITS>(r, idx);
     } else if (idx < r.n_blocks * r.n_oseg + n_pack) {
         // [256-token tile][32-channel step][16-token block][channel group 4][16 tokens]
         const uint32_t i = idx - r.n_blocks * r.n_oseg, t0 = i % n_rows * 16;
@@ -677,6 +711,7 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
         const uint32_t cols = wide_cb ? (wide.sp.n_col * wide_cb + 7) / 8 : std::min(slab_cols, n_col - tile0);
         RebuildArgs r;
         r.h = a.h; r.bmeta = a.bmeta; r.tables = src.tables; r.Wp = Wp;
+        r.codes = L->dev + L->off_codes; r.scales = reinterpret_cast<const uint4 *>(L->dev + L->off_scales);
         r.out = L->out; r.n_blocks = L->n_blocks; r.KB = KB; r.n_words = L->n_packed / 8;
         r.tile0 = tile0; r.n_col = cols;
         r.tb = wide_cb ? 2 * wide_cb : 16; r.n_tb = wide_cb ? wide.sp.n_col * 2 * wide_cb : 16 * cols;
@@ -685,10 +720,11 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
         const uint32_t n_pack = tile0 ? 0 : (tokens + 15) / 16 * ((2 * KB + PO_STEPS - 1) / PO_STEPS);     // (with the first slab)
         const uint32_t n_wg = n_pack + L->n_blocks * r.n_oseg, row = std::min(n_wg, 1u << 22);
         const dim3 grid(row, (n_wg + row - 1) / row);
-        DISPATCH_D(L->d, {
-            st = allow_lds(k_rebuild_operands<D>, lds);
-            if (st == SKL_OK) hipLaunchKernelGGL((k_rebuild_operands<D>), grid, dim3(SG_REBUILD_WG), lds, stream, r, k, n_pack);
-        })
+        auto rebuild = [&](auto kernel) {
+            st = allow_lds(kernel, lds);
+            if (st == SKL_OK) hipLaunchKernelGGL(kernel, grid, dim3(SG_REBUILD_WG), lds, stream, r, k, n_pack);
+        };
+        DISPATCH_D(L->d, { L->qbits == 0 ? rebuild(k_rebuild_operands<D, 16>) : L->qbits == 8 ? rebuild(k_rebuild_operands<D, 8>) : rebuild(k_rebuild_operands<D, 4>); })
         if (st == SKL_OK) st = check_launch("operand rebuild");
         if (st != SKL_OK) return st;
 
