@@ -18,6 +18,28 @@ typedef float float4v __attribute__((ext_vector_type(4)));
 
 typedef uint32_t u32x4h __attribute__((ext_vector_type(4), aligned(2)));     // eight 16-bit elements on any 2-byte boundary
 
+// four neighbouring results of token t, from output o (a multiple of four) on
+__device__ __forceinline__ void store_four(void *Y, uint32_t y_dt, uint32_t ldy, uint32_t t, uint32_t o, uint32_t out, float4 v)
+{
+    const size_t at = (size_t)t * ldy + o;
+    if ((ldy & 3u) == 0 && o + 4 <= out) {                      // (Y starts on a 16-byte boundary)
+        if (y_dt == SKL_F32) {
+            *reinterpret_cast<float4 *>(static_cast<float *>(Y) + at) = v;
+        } else {
+            uint16_t e[4];
+            const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) e[i] = y_dt == SKL_F16 ? float_to_half_bits(f[i]) : float_to_bf16_bits(f[i]);
+            *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(Y) + at) = make_uint2(e[0] | (uint32_t)e[1] << 16, e[2] | (uint32_t)e[3] << 16);
+        }
+        return;
+    }
+    store_out(Y, y_dt, at, v.x);
+    if (o + 1 < out) store_out(Y, y_dt, at + 1, v.y);
+    if (o + 2 < out) store_out(Y, y_dt, at + 2, v.z);
+    if (o + 3 < out) store_out(Y, y_dt, at + 3, v.w);
+}
+
 // two activations -> two binary16 values with inverted sign bits
 __device__ __forceinline__ uint32_t neg_half_pair(uint32_t e, uint32_t x_dt)
 {

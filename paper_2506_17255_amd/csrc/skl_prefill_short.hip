@@ -270,23 +270,7 @@ __global__ __launch_bounds__(256) void k_prompt_reduce(const float *__restrict__
     const uint32_t row = threadIdx.x >> 4, o = blockIdx.x * 64 + (threadIdx.x & 15) * 4, t = rb * 16 + row;
     if (t >= tokens || o >= out) return;
     const float4 v = *reinterpret_cast<const float4 *>(&sm[row][(threadIdx.x & 15) * 4]);
-    const size_t at = (size_t)t * ldy + o;
-    if ((ldy & 3u) == 0 && o + 4 <= out) {                      // (Y starts on a 16-byte boundary)
-        if (y_dt == SKL_F32) {
-            *reinterpret_cast<float4 *>(static_cast<float *>(Y) + at) = v;
-        } else {
-            uint16_t e[4];
-            const float f[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) e[i] = y_dt == SKL_F16 ? float_to_half_bits(f[i]) : float_to_bf16_bits(f[i]);
-            *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(Y) + at) = make_uint2(e[0] | (uint32_t)e[1] << 16, e[2] | (uint32_t)e[3] << 16);
-        }
-        return;
-    }
-    store_out(Y, y_dt, at, v.x);
-    if (o + 1 < out) store_out(Y, y_dt, at + 1, v.y);
-    if (o + 2 < out) store_out(Y, y_dt, at + 2, v.z);
-    if (o + 3 < out) store_out(Y, y_dt, at + 3, v.w);
+    store_four(Y, y_dt, ldy, t, o, out, v);
 }
 
 // ========================================================================
