@@ -222,6 +222,11 @@ def test_prompts_in_one_pass(in_f, out_f, d, widths, bits, tokens, x_dt, y_dt, l
     (777, 3001, 2, (9, 400, 800, 2000), 90),
     (777, 3001, 1, (9, 800, 1700, 4000), 120),
     (1500, 6000, 8, (30, 60, 100, 450), 20),
+    (777, 3001, 4, (9, 200, 330, 1000), 40),    # tiles of three, five and seven 16-token blocks
+    (777, 3001, 3, (9, 250, 500, 1300), 70),
+    (777, 3001, 1, (9, 800, 1700, 4000), 105),
+    (777, 3001, 8, (9, 100, 165, 500), 80),
+    (777, 3001, 6, (9, 130, 220, 660), 97),
 ])
 def test_one_pass_runs_of_blocks(in_f, out_f, d, widths, tokens, query_mode):
     """Runs of blocks of one width class begin with an empty pipeline and carry their last products over a barrier."""
