@@ -74,6 +74,12 @@ __device__ __forceinline__ void prompt_run(const PromptArgs &p, PromptWalk<D, RB
 {
     constexpr uint32_t RS = NB == 1 ? 1 : NB + 1;
     constexpr int NH = NB == 8 ? 2 : 1, NP = 2 * NH;
+    // Gathers a stretch ahead of their query need registers for two pairs.  Where these run out (RB = 4 and 8 have the fewest
+    // per accumulator, query mode 1 has more temporaries) the gathers of a pair stand behind the query of the pair before:
+    // 4096 x 11008, early -> late, mode 0: d = 8, 60 tokens 41.2 -> 39.0 us, 256 102.7 -> 97.4; d = 6, 8192 x 8192, 120 tokens
+    // 48.2 -> 45.3; but d = 4, 100 tokens 33.1 -> 33.9, d = 7, 256 tokens 90.4 -> 93.7.  Mode 1: d = 4, 60 tokens 31.2 -> 27.4,
+    // 256 84.8 -> 72.2; d = 6, 60 tokens 47.4 -> 30.6, 128 46.3 -> 37.6; d = 8, 256 tokens 120 -> 96.5.
+    constexpr bool LATE = SKL_QM == 1 || (D >= 5 && (RB == 4 || RB == 8) && !(D == 7 && RB == 8));
     const uint32_t n = w.lane & 15, kg = w.lane >> 4;
     const uint32_t word = min(kg, (uint32_t)NB - 1);       // classes with fewer than 4 words: lanes past the last word re-read it, their activations count as zero
     const bool x_live = NB >= 4 || kg < (uint32_t)NB;
@@ -102,10 +108,13 @@ __device__ __forceinline__ void prompt_run(const PromptArgs &p, PromptWalk<D, RB
             w.acc[i][pr & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, ai), __builtin_bit_cast(half8v, wd[pr & 1]), w.acc[i][pr & 1], 0, 0, 0);
         }
     };
-    auto tail = [&]() {
-        multiply(NP - 2);
-        query(NP - 1);
+    auto tail = [&]() { multiply(NP - 2); query(NP - 1); };
+    auto stretch = [&](auto read, auto compute) {
+        if (!LATE) read();
         __builtin_amdgcn_sched_barrier(0);
+        compute();
+        __builtin_amdgcn_sched_barrier(0);
+        if (LATE) read();
     };
     // nothing is carried into the first block: its predecessor's last pairs are products of zero activations and of keys
     // that stand for finite weights in either query mode
@@ -140,34 +149,11 @@ __device__ __forceinline__ void prompt_run(const PromptArgs &p, PromptWalk<D, RB
             K_prev = K;
         }
         xa = w.lds0 + PG_X0 + w.buf * (RB * 2048) + word * (RB * 256) + n * 16;
-        gather(0);
-        cx.some(1);
-        ct.some(2);
-        __builtin_amdgcn_sched_barrier(0);
-        tail();                                                 // of the block before
-        gather(1);
-        if (NH == 2) read_a(0);
-        ct.some(2);
-        cx.some(1);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(NP - 1);
-        query(0);
-        __builtin_amdgcn_sched_barrier(0);
+        stretch([&]() { gather(0); cx.some(1); ct.some(2); }, tail);    // the tail of the block before
+        stretch([&]() { gather(1); if (NH == 2) read_a(0); ct.some(2); cx.some(1); }, [&]() { multiply(NP - 1); query(0); });
         if (NH == 2) {
-            gather(2);
-            ct.some(2);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(0);
-            query(1);
-            __builtin_amdgcn_sched_barrier(0);
-            gather(3);
-            read_a(1);
-            ct.rest();
-            cx.rest();
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(1);
-            query(2);
-            __builtin_amdgcn_sched_barrier(0);
+            stretch([&]() { gather(2); ct.some(2); }, [&]() { multiply(0); query(1); });
+            stretch([&]() { gather(3); read_a(1); ct.rest(); cx.rest(); }, [&]() { multiply(1); query(2); });
         } else {
             read_a(0);
             ct.rest();
