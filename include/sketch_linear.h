@@ -119,8 +119,8 @@ typedef struct {
                                       index depends on the output channel only */
     uint32_t n_units;          /* channel blocks (path 1) or group chunks (path 0): the
                                   number of partial sums per output in the split reduction
-                                  (which decode calls through small 2-D groups do without:
-                                  they take one launch) */
+                                  (which decode calls through 2-D groups that take one
+                                  launch do without: small layers, or several rows) */
     uint32_t max_table_bytes;  /* largest LDS-resident table of one workgroup */
     uint64_t table_bytes;      /* bytes of sketch tables (or of codes and scales) resident in dev_buf */
     uint64_t n_weights;        /* in_features * out_features */
@@ -148,7 +148,7 @@ typedef struct {
 #define SKL_INFO_SIZE_V1 40u
 
 /* skl_info_t.prefill_kernel */
-#define SKL_PREFILL_PER_WEIGHT 0u   /* 2-D groups: weights hashed one by one, 64 x 64 tiles */
+#define SKL_PREFILL_PER_WEIGHT 0u   /* 2-D groups: weights hashed one by one */
 #define SKL_PREFILL_FUSED 3u        /* row sketches, tables of two blocks resident in LDS: weights rebuilt
                                        between the matrix instructions of a 256 x 256 tile */
 #define SKL_PREFILL_STAGED 4u       /* row sketches with larger tables, and long calls: weights rebuilt once per
@@ -256,8 +256,9 @@ SKL_API skl_status_t sketch_linear_gemv_gate_up(const skl_layer_t *gate, const s
  * block group left in workspace), without the reduction that produces y.
  * For timing that kernel by itself; same argument rules as gemv.  Calls that
  * sketch_linear_gemv makes in one launch (2-D groups of at least 64 rows in
- * layers of at most 1024, while there are few outputs and batch rows) have no
- * such kernel: here they run the first kernel of the split form. */
+ * layers of at most 1024, while there are few outputs and batch rows; more than
+ * one row through most layers of 512 inputs and more) have no such kernel: here
+ * they run the first kernel of the split form. */
 SKL_API skl_status_t sketch_linear_gemv_partials(const skl_layer_t *layer, const void *x, skl_dtype_t x_dtype,
                                          uint32_t ldx, uint32_t batch, void *workspace,
                                          uint64_t workspace_bytes, void *hip_stream);

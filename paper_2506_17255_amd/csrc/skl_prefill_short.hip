@@ -11,12 +11,13 @@
 // matrix instructions of one wavefront.  The kernel is that of the batched decode with up to 128 tokens instead of 16:
 // lanes are outputs, a wavefront rebuilds the operand words of 32 outputs and multiplies them with all tokens of its
 // tile, whose activation words arrive in LDS beside the table (two buffers each).
-// Bound by none of its units alone: of 36 us for 4096 x 11008, d = 4, 100 tokens on inputs that are not in the caches (250
-// workgroups of seven wavefronts) the packing launch is 5 and the reduction 5.5; without copies the call takes 2 us less,
-// without products 4, without the query 2.4, with gathers free of bank conflicts 2, without any of these 13.  What helped: chunks
-// copied without bounds checks, an even load per stretch of code and no wait at a block's head (prompt_run).
-// Whole call against the kernels it replaces: 17 tokens 45 -> 23 us, 48 46 -> 27, 100 59 -> 35.5, 256 88 -> 71; 8192 x 8192, 128
-// tokens, 84 -> 42; 4096 x 4096, 64 tokens, 26 -> 19; 1024 x 2048, 300 tokens, 43 -> 18.5.
+// Bound by none of its units alone: of the 36 us that 4096 x 11008, d = 4, 100 tokens took before prompt_run's pipeline, on
+// inputs that are not in the caches (250 workgroups of seven wavefronts), the packing launch was 5 and the reduction 5.5;
+// without copies the call took 2 us less, without products 4, without the query 2.4, with gathers free of bank conflicts 2,
+// without any of these 13.  What helped: chunks copied without bounds checks, an even load per stretch of code and no wait at a
+// block's head (prompt_run), packing with all loads in flight.
+// Whole call against the kernels it replaces: 17 tokens 45 -> 22.5 us, 48 46 -> 26, 100 59 -> 33, 256 88 -> 71; 8192 x 8192, 128
+// tokens, 84 -> 42; 4096 x 4096, 64 tokens, 26 -> 18.3; 1024 x 2048, 300 tokens, 43 -> 18.5.
 namespace SKL_NS {
 
 struct PromptArgs {
