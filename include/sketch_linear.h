@@ -257,8 +257,8 @@ SKL_API skl_status_t sketch_linear_gemv_gate_up(const skl_layer_t *gate, const s
  * For timing that kernel by itself; same argument rules as gemv.  Calls that
  * sketch_linear_gemv makes in one launch (2-D groups of at least 64 rows in
  * layers of at most 1024, while there are few outputs and batch rows; more than
- * one row through most layers of 512 inputs and more) have no such kernel: here
- * they run the first kernel of the split form. */
+ * one row through layers of 512 inputs and more where it is faster) have no such
+ * kernel: here they run the first kernel of the split form. */
 SKL_API skl_status_t sketch_linear_gemv_partials(const skl_layer_t *layer, const void *x, skl_dtype_t x_dtype,
                                          uint32_t ldx, uint32_t batch, void *workspace,
                                          uint64_t workspace_bytes, void *hip_stream);

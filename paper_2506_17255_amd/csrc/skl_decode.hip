@@ -892,13 +892,8 @@ skl_status_t skl_launch_gemv(const skl_layer *L, const void *x_, uint32_t ldx, v
             DISPATCH_D(L->d, { past ? launch(k_row_gemvN<D, true>) : launch(k_row_gemvN<D, false>); })
         }
     } else {
-        // Several rows and 512 input rows or more: the prompt kernel, in one launch.  Its time / that of the kernels below, in
-        // us: 512 x 512, batch 2 to 16, 5.2 to 5.4 / 5.3 to 5.6; 1024 x 1024 in groups of 128, batch 2, 6.6 / 7.8; 1024 x 2048, batch 16, 7.3
-        // / 11.7; 2048 x 512, batch 4, 9.5 / 12.6, batch 16 9.7 / 16.9; 2048 x 2048, batch 16, 9.9 / 23.0.  256 input rows, batch 4, 4.9 /
-        // 4.7; one row, 1024 x 1024 6.9 / 6.6, 2048 x 2048 in groups of 128 9.6 / 8.8.  Layers of fewer than 128 outputs would gain as
-        // well (1088 x 64, batch 2, 7.1 / 8.2), but that is fewer than eight workgroups: they stay with the kernels that divide a
-        // group's rows over the chip.
-        if (with_reduction && batch > 1 && L->in >= 512 && L->out >= 128 && skl_tile_prompt_fits(L))
+        // several rows: the prompt kernel, in one launch, where it is faster
+        if (with_reduction && skl_tile_prompt_decodes(L, batch))
             return skl_tile_launch_prompt(L, src, x, SKL_F16, ldx, y, y_dt, ldy, batch, stream);
         if (with_reduction && skl_tile_gemv_is_small(L, batch))
             return skl_tile_launch_gemv_small(L, src, x, ldx, batch, y, y_dt, ldy, stream);

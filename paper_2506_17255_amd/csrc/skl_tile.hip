@@ -547,6 +547,26 @@ static size_t tile_prompt_table_bytes(const skl_layer *L) { return (size_t)tile_
 
 bool skl_tile_prompt_fits(const skl_layer *L) { return L->tj % 8 == 0 && L->to % 16 == 0 && tile_prompt_table_bytes(L) <= SKL_LDS_HARD_BYTES; }
 
+// Whether a decode call takes the prompt kernel.  Its time / that of the kernels it stands in for, in us: 512 x 512, batch 2 to
+// 16, 5.2 to 5.4 / 5.3 to 5.6; 1024 x 1024 in groups of 128, batch 2, 6.6 / 7.8; 1024 x 2048, batch 16, 7.3 / 11.7; 2048 x 512, batch 4,
+// 9.5 / 12.6, batch 16 9.7 / 16.9; 2048 x 2048, batch 16, 9.9 / 23.0.  256 input rows, batch 4, 4.9 / 4.7; one row, 1024 x 1024 6.9 /
+// 6.6, 2048 x 2048 in groups of 128 9.6 / 8.8.  Layers of fewer than 128 outputs would gain as well (1088 x 64, batch 2, 7.1 /
+// 8.2), but that is fewer than eight workgroups: they stay with the kernels that divide a group's rows over the chip.
+// A wavefront walks its share of all input rows, so beyond 1024 the other kernels can be faster: 4096 x 512 in groups of
+// 64, d = 4, batch 2, 18.3 / 10.4, 8192 x 8192 69 / 64; but they rebuild a weight for every four rows (8192 x 8192, batch 5, 69 / 115)
+// and add one partial sum per chunk of rows and output (8192 x 512 in groups of 256, d = 1, batch 16, 18.5 / 24.3).  The two
+// estimates below stand within a tenth of 410 measured calls (1024 to 8192 rows, 128 to 8192 outputs, batch 2 to 16, d = 1
+// to 8, groups of 16 to 256), and choose the slower kernel in none of them by more than 10 %.
+bool skl_tile_prompt_decodes(const skl_layer *L, uint32_t batch)
+{
+    if (batch < 2 || L->in < 512 || L->out < 128 || !skl_tile_prompt_fits(L)) return false;
+    if (L->in <= 1024) return true;
+    const double weights = (double)L->in * L->out / (1u << 26), passes = (batch + 3) / 4;
+    const double prompt_us = std::max(4.0 + L->in * (4.1 + 2.3 * L->d) / 4096 + 0.022 * L->n_jb, weights * (21.0 + 12.0 * L->d));
+    const double split_us = 6.0 + 0.023 * L->n_units + weights * (15.0 + 9.7 * L->d) * passes * std::max(1.0, 64.0 / L->to);
+    return prompt_us < split_us;
+}
+
 skl_status_t skl_tile_launch_prompt(const skl_layer *L, const TableSrc &src, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx, void *Y,
                                     skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, hipStream_t stream)
 {

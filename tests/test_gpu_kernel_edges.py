@@ -430,6 +430,8 @@ def test_group_prompts(in_f, out_f, tile_in, tile_out, d, widths, tokens, x_dt, 
     (1024, 512, 256, 256, 4, (300, 301), 5, True),
     (504, 144, 72, 16, 3, (9, 20), 16, True),       # fewer rows: the small kernel, which takes groups of at least 64
     (1100, 520, 20, 40, 2, (9, 20), 3, False),      # groups that are no whole lanes: partial sums
+    (2048, 512, 256, 256, 2, (99, 300), 2, True),   # more rows than 1024: by estimate
+    (2048, 512, 64, 64, 4, (30, 31), 2, False),
 ])
 def test_group_decode_of_several_rows(in_f, out_f, tile_in, tile_out, d, widths, batch, one_launch, query_mode):
     rng = np.random.default_rng(in_f + out_f)
