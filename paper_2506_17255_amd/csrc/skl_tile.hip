@@ -587,7 +587,14 @@ skl_status_t skl_tile_launch_prompt(const skl_layer *L, const TableSrc &src, con
     const dim3 tiles(L->out / (16 * ob), (blocks + RB - 1) / RB);
     // (sixteen wavefronts, 2048 rows: 2048 x 512, 100 tokens, 12.8 -> 11.8, 2048 x 256, 512 tokens, 13.7 -> 11.5; 1024 rows the same; 512
     // x 512, 100 tokens, 6.0 / 6.5; up to 16 tokens, 1024 x 1024 6.9 -> 6.6, 512 x 512 the same)
-    const uint32_t nw = ob == 1 && wgs() <= SKL_N_CU && L->in > (RB == 1 ? 512u : 1024u) ? 16 : 8;
+    uint32_t nw = ob == 1 && wgs() <= SKL_N_CU && L->in > (RB == 1 ? 512u : 1024u) ? 16 : 8;
+    // With more workgroups than the chip holds at once, fewer wavefronts each: eight per CU hide the latencies, and every one
+    // beyond the first adds its sums to the exchange at the end, which is what a tile of few input rows consists of.  Groups of
+    // 128, d = 3, eight wavefronts / this rule: 256 x 2048, 1024 tokens (512 workgroups, four) 20.7 / 13.7 us, 4096 tokens (2048, one)
+    // 76 / 35; 2048 x 2048, 1024 tokens 53.5 / 48.8, 4096 tokens 205 / 177; with 256 workgroups eight are best (512 tokens, 28.5 against
+    // 41.9 with four).  And none without input rows: 128 x 2048, 512 tokens, 10.3 -> 9.4.
+    while (nw > 1 && nw <= 8 && wgs() * (nw / 2) >= 8 * SKL_N_CU) nw /= 2;
+    nw = std::min(nw, (L->in + 31) / 32);
     const size_t need = std::max<size_t>(tables, (size_t)nw * std::min(RB * ob, TP_RED_BYTES / 1024 / nw) * 1024);
     auto launch = [&](auto kernel) {
         st = allow_lds(kernel, need);
@@ -614,7 +621,11 @@ skl_status_t skl_tile_launch_gemm(const skl_layer *L, const TableSrc &src, const
         skl_set_error("more than %u tokens in one call through the per-weight path", 65535u * TG_T);
         return SKL_ERR_UNSUPPORTED;
     }
-    if (skl_tile_prompt_fits(L)) return skl_tile_launch_prompt(L, src, X, x_dt, ldx, Y, y_dt, ldy, tokens, stream);
+    // (fewer than 128 input rows, groups of 64: 64 x 2048, 128 tokens 5.5 / 7.8 us here, 512 tokens 8.8 to 9.8 / 7.6, 1024 tokens 10.6
+    // / 9.4, 4096 tokens 19.8 / 24)
+    const uint64_t results = (uint64_t)tokens * L->out;
+    const bool few_rows = L->in < 128 && results > 1u << 18 && results <= 1u << 22;
+    if (skl_tile_prompt_fits(L) && !few_rows) return skl_tile_launch_prompt(L, src, X, x_dt, ldx, Y, y_dt, ldy, tokens, stream);
     const dim3 grid(L->n_ob * n_oc, n_tt);
     DISPATCH_D(L->d, {
         st = allow_lds(k_tile_gemm<D>, lds);

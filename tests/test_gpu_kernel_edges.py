@@ -404,6 +404,9 @@ def test_batched_decode_stores(in_f, out_f, batch):
     (640, 512, 128, 128, 3, (170, 171), 129, "bf16", "f32", 0),     # two tiles of tokens, sixteen wavefronts
     (512, 4096, 256, 256, 3, (682, 683), 130, "f16", "f32", 0),     # 32 outputs per tile, tables on odd addresses
     (2048, 64, 256, 64, 8, (1500, 1600), 40, "f16", "f16", 0),      # tables that do not all fit at once
+    (160, 4096, 32, 32, 2, (20, 21), 520, "f16", "f32", 0),         # 640 workgroups of four wavefronts
+    (136, 8192, 8, 32, 1, (2, 3), 1040, "bf16", "f32", 0),          # 2304 of one
+    (64, 2048, 64, 64, 3, (90, 91), 300, "f16", "f32", 0),          # few rows, many outputs: tiles of 64 x 64
 ])
 def test_group_prompts(in_f, out_f, tile_in, tile_out, d, widths, tokens, x_dt, y_dt, ldx_pad, query_mode):
     """The kernel for groups of whole lanes and output blocks, at its edges, against the oracle in 64 bits."""
