@@ -249,7 +249,11 @@ static bool plan_decode(const skl_desc_t *d, skl_plan *P)
             o.tab = L.max_table_bytes;
             for (uint32_t &f : o.flags) f &= ~2u;
         }
-        return o.ptab + g1_rest <= SKL_LDS_HARD_BYTES && o.tab + gn_rest <= SKL_LDS_HARD_BYTES;
+        const bool fits = o.ptab + g1_rest <= SKL_LDS_HARD_BYTES && o.tab + gn_rest <= SKL_LDS_HARD_BYTES;
+        // the batched kernel copies tables in whole chunks of 1 KiB, and its activations lie right behind the only buffer: a
+        // smaller table takes a chunk all the same (out of the 2 KiB of gn_rest that the kernel does not use)
+        o.tab = std::max(o.tab, 1024u);
+        return fits;
     };
     // Cost of a split: rounds x (start-up + a blend of the dearest group's time and the mean load of a CU)
     // + what the number of groups costs in the kernel and in the reduction pass.  The step model gives the

@@ -3,6 +3,8 @@ picks is the cheapest one under its own cost model among its candidates (up to t
 occupied CUs and fewer segments decide), and the plans the measurements in the design notes were taken with are
 still the ones picked."""
 import dataclasses
+import os
+import subprocess
 
 import numpy as np
 import pytest
@@ -98,3 +100,17 @@ def test_layers_of_narrow_blocks_take_two_units_per_wavefront():
     assert 16 < (units + info["decode_segments"] - 1) // info["decode_segments"] <= 32
     other, _ = skl.sketch_linear_plan(desc, 6, 38)          # 29 units per segment: 15 wavefronts of two units
     assert (other["decode_segments"], other["decode_groups"]) == (6, 38)
+
+
+def test_table_areas_hold_whole_chunks_of_small_tables(tmp_path):
+    """The batched kernel copies a table in chunks of 1 KiB, also where it is smaller: what lies behind the table area stays
+    untouched on every layer (tests/sanitize/decode_tables.cpp)."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    csrc = os.path.join(root, "paper_2506_17255_amd", "csrc")
+    exe = tmp_path / "decode_tables"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(root, "include"),
+                           "-I", csrc, os.path.join(root, "tests", "sanitize", "decode_tables.cpp"), os.path.join(csrc, "skl_host.cpp"),
+                           os.path.join(root, "tests", "sanitize", "host_stubs.cpp"), "-o", str(exe), "-L/opt/rocm/lib", "-lamdhip64",
+                           "-Wl,-rpath,/opt/rocm/lib"])
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout

@@ -486,6 +486,26 @@ def test_decode_runs_of_blocks(in_f, out_f, d, widths, batch, query_mode):
     assert np.isfinite(y).all() and rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
 
 
+@pytest.mark.parametrize("in_f,out_f,d,K", [
+    (32768, 4096, 1, 2),        # tables of 288 bytes in the only buffer, groups of 1024 channels
+    (65536, 2048, 4, 1),        # 576 bytes
+])
+def test_batched_decode_through_tables_smaller_than_a_chunk(in_f, out_f, d, K):
+    """A table is copied in whole chunks of 1 KiB; the activations behind the table area stay what they are."""
+    rng = np.random.default_rng(in_f)
+    A, C = hash_params(rng, d)
+    states = (rng.standard_normal(in_f * d * K) * 0.02).astype(np.float16).view(np.uint16)
+    sk = oracle.Sketch(in_f, out_f, 1, out_f, d, A, C, np.full(in_f, K, dtype=np.uint32), states)
+    x = rng.standard_normal((16, in_f)).astype(np.float16)
+    W_hat = oracle.query(sk)
+    ref = np.vstack([matmul_f64(W_hat[j:j + 4096], x[:, j:j + 4096], "f16")[None] for j in range(0, in_f, 4096)]).sum(axis=0)
+    with GpuLayer(sk) as g:
+        for batch in (2, 9, 16):
+            y = g.gemv(x[:batch], "f32")
+            # (a row at a time: one wrong row of sixteen must not hide among the others)
+            assert max(rel_fro(y[b], ref[b]) for b in range(batch)) <= SUM_TOL, batch
+
+
 @pytest.mark.parametrize("out_f,batch,ldh_pad,h_dt", [
     (4096, 15, 0, "f32"),       # 240 wavefronts of the row reduction: the other one
     (4096, 16, 0, "f16"),       # 256: the first
