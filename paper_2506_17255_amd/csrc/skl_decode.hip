@@ -300,6 +300,7 @@ __device__ __forceinline__ void gemv1_body(const StreamArgs &p, const uint16_t *
     w.nblk = c.b_hi - c.b_lo;
     w.bi = 0;
     w.cur = RowBlock{c.toff0, c.K0, c.rs0, c.rs0 == 1 ? 1u : c.rs0 - 1, c.chan_off0, c.ptoff0};
+    w.ahead.request(p.r.bmeta + c.b_lo + min(1u, w.nblk - 1));
     // The last two wavefronts fetch the group's activations (channel numbers, then what they point at) while the others
     // copy the first table: a wavefront that did both would wait for its share of the table before each of the two.
     const uint32_t n_x = nw >= 4 ? 2 : 1, n_tab = nw - n_x;
@@ -319,7 +320,6 @@ __device__ __forceinline__ void gemv1_body(const StreamArgs &p, const uint16_t *
             *reinterpret_cast<uint2 *>(xs + e) = make_uint2(v[0] | v[1] << 16, v[2] | v[3] << 16);
         }
     }
-    w.ahead.request(p.r.bmeta + c.b_lo + min(1u, w.nblk - 1));
 #pragma unroll
     for (int u = 0; u < U; ++u) w.yw[u * w.unit_stride + w.lane] = 0.f;
     while (w.bi < w.nblk) {
@@ -430,11 +430,14 @@ __device__ __forceinline__ void gn_copy(uint4 *dst, const StreamArgs &p, const R
 // metadata of a block arrives a block ahead and its state-row addresses are formed while its table is on its way.  Against
 // a drained wavefront and two LDS reads of metadata at every barrier: 11008 x 4096, batch 8, 19.6 -> 18.6 us, gate/up of
 // 4096 x 11008, batch 16, 40.5 -> 39.5, 8192 x 8192, batch 16, 30.2 -> 27.3, 8192 x 28672, batch 8, 102 -> 88 (two or three pairs
-// ahead, where 8 or 12 wavefronts have the registers: the same or 1 % more).
+// ahead, where 8 or 12 wavefronts have the registers: the same or 1 % more).  More than four rows have no registers for a second
+// pair among the 128 of a lane: d = 5 with one, 4096 x 11008, batch 8, 22.5 -> 22.8, 2048 x 8192 with two-word blocks 18.3 ->
+// 18.0; d = 6 up to a quarter slower.  Without one, d = 5 to 8, both query modes, six shapes, batch 2 to 16, take 0.90 to 1.015 of
+// the time they took drained, whichever had a pair ahead inside the block then (d = 5) or not.
 template <int D, int NB>
 __device__ __forceinline__ void gn_run(const StreamArgs &p, const StreamCtx &c, GnWalk &w, float4v (&acc)[4])
 {
-    constexpr int NH = NB == 8 ? 2 : 1, NP = 4 * NH, AHEAD = D <= 4 ? 1 : 0, RING = AHEAD + 1;      // (128 registers per lane: more rows spill)
+    constexpr int NH = NB == 8 ? 2 : 1, NP = 4 * NH, AHEAD = D <= 4 ? 1 : 0, RING = AHEAD + 1;
     uint4 *const buf0 = smem, *const buf1 = smem + SKL_PBUF_DIST / 16;
     uint32_t off[4][D];
     uint32_t K_prev = 0;
@@ -534,6 +537,8 @@ __device__ __forceinline__ void gemvN_body(const StreamArgs &p, const uint16_t *
     w.nblk = c.b_hi - c.b_lo;
     w.xs_addr = (uint32_t)(uintptr_t)(lds_void *)xs + (w.lane & 15) * xs_stride * 2;
     const RowBlock first{c.toff0, c.K0, c.rs0, 0, c.chan_off0, 0};
+    const skl_block_meta *const second = p.r.bmeta + c.b_lo + min(1u, w.nblk - 1);
+    w.ahead.request(second);
     gn_copy<D>(smem, p, first, w.lane);
     // Activations of the group's channels: a thread per channel and eight rows, whose loads all go out together.  (Rows past
     // the batch repeat the last one or are left as they are: their sums are not stored.  With a branch around every load
@@ -559,8 +564,8 @@ __device__ __forceinline__ void gemvN_body(const StreamArgs &p, const uint16_t *
         w.wave_live = w.o_base < c.o_hi;
         w.bi = 0;
         w.cur = first;
-        w.ahead.request(p.r.bmeta + c.b_lo + min(1u, w.nblk - 1));
         if (pass) {
+            w.ahead.request(second);
             meet_after_lds_reads();          // everyone is done with the last block of the pass before
             gn_copy<D>(smem, p, first, w.lane);
         }
