@@ -302,13 +302,17 @@ __device__ __forceinline__ void gemv1_body(const StreamArgs &p, const uint16_t *
     w.cur = RowBlock{c.toff0, c.K0, c.rs0, c.rs0 == 1 ? 1u : c.rs0 - 1, c.chan_off0, c.ptoff0};
     w.ahead.request(p.r.bmeta + c.b_lo + min(1u, w.nblk - 1));
     // The last two wavefronts fetch the group's activations (channel numbers, then what they point at) while the others
-    // copy the first table: a wavefront that did both would wait for its share of the table before each of the two.
-    const uint32_t n_x = nw >= 4 ? 2 : 1, n_tab = nw - n_x;
-    if (wave < n_tab) {
-        copy_chunks_to_lds_async(smem, p.r.tables + c.ptoff0, D * w.cur.K * w.cur.nb, n_tab);
-    } else {
+    // copy the first table: a wavefront that did both would wait for its share of the table before each of the two.  Where a
+    // few would copy more than eight chunks each, all of them copy, and fetch then.  The kernel before
+    // that division / divided / by this rule: 57 x 3171, d = 3, two bits per weight, 6.7 / 7.2 / 6.85 us, 739 x 438, d = 4, four
+    // bits, 7.05 / 7.5 / 7.15, 113 x 1371, d = 5, 6.8 / 7.15 / 6.95; 4096 x 11008, eleven wavefronts, 16.6 / 15.4 / 15.5.
+    const uint32_t words = D * w.cur.K * w.cur.nb, n_x = nw >= 4 ? 2 : 1;
+    const bool all = nw < 8 && words > 8 * 64 * (nw - n_x);
+    const uint32_t n_tab = all ? nw : nw - n_x, x_from = all ? 0 : nw - n_x;
+    if (wave < n_tab) copy_chunks_to_lds_async(smem, p.r.tables + c.ptoff0, words, n_tab);
+    if (wave >= x_from) {
         // four entries of the channel list at a time (block groups begin on multiples of eight)
-        for (uint32_t e = ((wave - n_tab) * 64 + w.lane) * 4; e < c.c_hi - c.c_lo; e += n_x * 256) {
+        for (uint32_t e = ((wave - x_from) * 64 + w.lane) * 4; e < c.c_hi - c.c_lo; e += (nw - x_from) * 256) {
             const u32x4v ch = *reinterpret_cast<const u32x4v *>(p.r.chan + c.c_lo + e);
             uint32_t v[4];
 #pragma unroll
