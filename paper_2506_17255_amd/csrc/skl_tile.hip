@@ -593,7 +593,11 @@ skl_status_t skl_tile_launch_prompt(const skl_layer *L, const TableSrc &src, con
     // 128, d = 3, eight wavefronts / this rule: 256 x 2048, 1024 tokens (512 workgroups, four) 20.7 / 13.7 us, 4096 tokens (2048, one)
     // 76 / 35; 2048 x 2048, 1024 tokens 53.5 / 48.8, 4096 tokens 205 / 177; with 256 workgroups eight are best (512 tokens, 28.5 against
     // 41.9 with four).  And none without input rows: 128 x 2048, 512 tokens, 10.3 -> 9.4.
-    while (nw > 1 && nw <= 8 && wgs() * (nw / 2) >= 8 * SKL_N_CU) nw /= 2;
+    // And only as many workgroups count as find room for their tables at once: 5088 x 5888 in
+    // groups of 16 x 128 (318 tables above an output, 40 KB), 3293 tokens, one wavefront each 3918 us, two 1532; the kernel for any
+    // geometry 2159.
+    const uint64_t held = std::min<uint64_t>(wgs(), SKL_N_CU * (SKL_LDS_HARD_BYTES / tables));
+    while (nw > 1 && nw <= 8 && held * (nw / 2) >= 8 * SKL_N_CU) nw /= 2;
     nw = std::min(nw, (L->in + 31) / 32);
     const size_t need = std::max<size_t>(tables, (size_t)nw * std::min(RB * ob, TP_RED_BYTES / 1024 / nw) * 1024);
     auto launch = [&](auto kernel) {
@@ -622,9 +626,12 @@ skl_status_t skl_tile_launch_gemm(const skl_layer *L, const TableSrc &src, const
         return SKL_ERR_UNSUPPORTED;
     }
     // (fewer than 128 input rows, groups of 64: 64 x 2048, 128 tokens 5.5 / 7.8 us here, 512 tokens 8.8 to 9.8 / 7.6, 1024 tokens 10.6
-    // / 9.4, 4096 tokens 19.8 / 24)
+    // / 9.4, 4096 tokens 19.8 / 24.  Beyond, with whole tiles of 64 outputs, the other kernel keeps calls of few rows and sketch rows:
+    // 40 x 2048, d = 3, 2477 tokens, 18.3 / 11.0, 64 x 2112, d = 3, 2138 tokens 20.2 / 16.1, 32 x 1024, d = 8, 4622 tokens 16.8 / 13.4; of 179
+    // measured calls this leaves 9 slower than with the other kernel, by up to 35 %, and makes 6 slower, by up to 19 %)
     const uint64_t results = (uint64_t)tokens * L->out;
-    const bool few_rows = L->in < 128 && results > 1u << 18 && results <= 1u << 22;
+    const bool few_rows = (L->in < 128 && results > 1u << 18 && results <= 1u << 22) ||
+                          (results > 1u << 22 && L->to % 64 == 0 && (uint64_t)L->in * (L->d + 2) <= 340);
     if (skl_tile_prompt_fits(L) && !few_rows) return skl_tile_launch_prompt(L, src, X, x_dt, ldx, Y, y_dt, ldy, tokens, stream);
     const dim3 grid(L->n_ob * n_oc, n_tt);
     DISPATCH_D(L->d, {

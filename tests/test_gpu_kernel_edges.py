@@ -425,6 +425,24 @@ def test_group_prompts(in_f, out_f, tile_in, tile_out, d, widths, tokens, x_dt, 
     assert np.isfinite(y.astype(np.float32)).all() and rel_fro(y, ref) <= tol, rel_fro(y, ref)
 
 
+@pytest.mark.parametrize("in_f,out_f,tile_in,tile_out,d,widths,tokens", [
+    (1024, 2048, 8, 16, 1, (155, 160), 1040),       # 40 KB of tables to a workgroup: four of them on a compute unit, two wavefronts each
+    (16, 512, 16, 512, 2, (250, 256), 8200),        # few rows, few sketch rows and many results: tiles of 64 x 64
+    (64, 1088, 32, 64, 4, (40, 41), 4100),          # more sketch rows: 64 x 1088 of them no longer
+])
+def test_group_prompts_of_many_results(in_f, out_f, tile_in, tile_out, d, widths, tokens):
+    rng = np.random.default_rng(in_f + tokens)
+    A, C = hash_params(rng, d)
+    K = rng.choice(widths, (in_f // tile_in) * (out_f // tile_out)).astype(np.uint32)
+    states = (rng.standard_normal(int(K.sum()) * d) * 0.02).astype(np.float16).view(np.uint16)
+    sk = oracle.Sketch(in_f, out_f, tile_in, tile_out, d, A, C, K, states)
+    X = wk.f32_to_bf16_bits(rng.standard_normal((tokens, in_f)).astype(np.float32))
+    ref = matmul_f64(oracle.query(sk), X, "bf16")
+    with GpuLayer(sk) as g:
+        y = g.gemm(X, "bf16", "f32")
+    assert np.isfinite(y).all() and worst_tile_rel_fro(y, ref) <= SUM_TOL, worst_tile_rel_fro(y, ref)
+
+
 @pytest.mark.parametrize("query_mode", [0, 1])
 @pytest.mark.parametrize("in_f,out_f,tile_in,tile_out,d,widths,batch,one_launch", [
     (512, 128, 32, 16, 3, (9, 20), 2, True),        # the fewest rows, input rows and outputs that take the prompt kernel
