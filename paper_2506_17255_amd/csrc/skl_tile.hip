@@ -1,5 +1,7 @@
 // Per-weight path: 2-D groups, one hash evaluation (Sec. 3.1 Eq. 3) per
 // weight and sketch row.
+#include <cmath>
+
 #include "skl_prefill_common.h"
 
 namespace SKL_NS {
@@ -547,33 +549,12 @@ static size_t tile_prompt_table_bytes(const skl_layer *L) { return (size_t)tile_
 
 bool skl_tile_prompt_fits(const skl_layer *L) { return L->tj % 8 == 0 && L->to % 16 == 0 && tile_prompt_table_bytes(L) <= SKL_LDS_HARD_BYTES; }
 
-// Whether a decode call takes the prompt kernel.  Its time / that of the kernels it stands in for, in us: 512 x 512, batch 2 to
-// 16, 5.2 to 5.4 / 5.3 to 5.6; 1024 x 1024 in groups of 128, batch 2, 6.6 / 7.8; 1024 x 2048, batch 16, 7.3 / 11.7; 2048 x 512, batch 4,
-// 9.5 / 12.6, batch 16 9.7 / 16.9; 2048 x 2048, batch 16, 9.9 / 23.0.  256 input rows, batch 4, 4.9 / 4.7; one row, 1024 x 1024 6.9 /
-// 6.6, 2048 x 2048 in groups of 128 9.6 / 8.8.  Layers of fewer than 128 outputs would gain as well (1088 x 64, batch 2, 7.1 /
-// 8.2), but that is fewer than eight workgroups: they stay with the kernels that divide a group's rows over the chip.
-// A wavefront walks its share of all input rows, so beyond 1024 the other kernels can be faster: 4096 x 512 in groups of
-// 64, d = 4, batch 2, 18.3 / 10.4, 8192 x 8192 69 / 64; but they rebuild a weight for every four rows (8192 x 8192, batch 5, 69 / 115)
-// and add one partial sum per chunk of rows and output (8192 x 512 in groups of 256, d = 1, batch 16, 18.5 / 24.3).  The two
-// estimates below stand within a tenth of 410 measured calls (1024 to 8192 rows, 128 to 8192 outputs, batch 2 to 16, d = 1
-// to 8, groups of 16 to 256), and choose the slower kernel in none of them by more than 10 %.
-bool skl_tile_prompt_decodes(const skl_layer *L, uint32_t batch)
-{
-    if (batch < 2 || L->in < 512 || L->out < 128 || !skl_tile_prompt_fits(L)) return false;
-    if (L->in <= 1024) return true;
-    const double weights = (double)L->in * L->out / (1u << 26), passes = (batch + 3) / 4;
-    const double prompt_us = std::max(4.0 + L->in * (4.1 + 2.3 * L->d) / 4096 + 0.022 * L->n_jb, weights * (21.0 + 12.0 * L->d));
-    const double split_us = 6.0 + 0.023 * L->n_units + weights * (15.0 + 9.7 * L->d) * passes * std::max(1.0, 64.0 / L->to);
-    return prompt_us < split_us;
-}
+struct TilePromptShape {
+    uint32_t RB, ob, nw;            // tiles of RB * 16 tokens x ob * 16 outputs, wavefronts to each
+};
 
-skl_status_t skl_tile_launch_prompt(const skl_layer *L, const TableSrc &src, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx, void *Y,
-                                    skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, hipStream_t stream)
+static TilePromptShape tile_prompt_shape(const skl_layer *L, uint32_t tokens)
 {
-    skl_status_t st = SKL_OK;
-    const TileArgs a = make_tile_args(L, src);
-    const uint32_t kw = (uint32_t)tile_key_words(L), at_once = tile_prompt_tables(L);
-    const size_t tables = tile_prompt_table_bytes(L);
     // The smallest tile that is no more than three workgroups for two CUs: a larger one re-uses weights and activations
     // more, a smaller one fills the chip and is over sooner.  Whole calls by tokens x outputs per tile, in us: 512 x 512,
     // 256 tokens 32 x 16 (256 workgroups) 6.7, 64 x 16 7.7, 128 x 16 10.9; 2048 x 512, 100 tokens, 32 x 16 (128) 11.8, 64 x 16
@@ -584,7 +565,6 @@ skl_status_t skl_tile_launch_prompt(const skl_layer *L, const TableSrc &src, con
     auto wgs = [&]() { return (uint64_t)(L->out / (16 * ob)) * ((blocks + RB - 1) / RB); };
     if (wgs() > SKL_N_CU * 3 / 2 && L->to % 32 == 0) ob = 2;
     while (wgs() > SKL_N_CU * 3 / 2 && RB > 1 && RB < 8) RB *= 2;
-    const dim3 tiles(L->out / (16 * ob), (blocks + RB - 1) / RB);
     // (sixteen wavefronts, 2048 rows: 2048 x 512, 100 tokens, 12.8 -> 11.8, 2048 x 256, 512 tokens, 13.7 -> 11.5; 1024 rows the same; 512
     // x 512, 100 tokens, 6.0 / 6.5; up to 16 tokens, 1024 x 1024 6.9 -> 6.6, 512 x 512 the same)
     uint32_t nw = ob == 1 && wgs() <= SKL_N_CU && L->in > (RB == 1 ? 512u : 1024u) ? 16 : 8;
@@ -593,12 +573,63 @@ skl_status_t skl_tile_launch_prompt(const skl_layer *L, const TableSrc &src, con
     // 128, d = 3, eight wavefronts / this rule: 256 x 2048, 1024 tokens (512 workgroups, four) 20.7 / 13.7 us, 4096 tokens (2048, one)
     // 76 / 35; 2048 x 2048, 1024 tokens 53.5 / 48.8, 4096 tokens 205 / 177; with 256 workgroups eight are best (512 tokens, 28.5 against
     // 41.9 with four).  And none without input rows: 128 x 2048, 512 tokens, 10.3 -> 9.4.
-    // And only as many workgroups count as find room for their tables at once: 5088 x 5888 in
-    // groups of 16 x 128 (318 tables above an output, 40 KB), 3293 tokens, one wavefront each 3918 us, two 1532; the kernel for any
-    // geometry 2159.
-    const uint64_t held = std::min<uint64_t>(wgs(), SKL_N_CU * (SKL_LDS_HARD_BYTES / tables));
+    // And only as many workgroups count as find room for their tables at once: 5088 x 5888 in groups of 16 x 128 (318 tables above
+    // an output, 40 KB), 3293 tokens, one wavefront each 3918 us, two 1532; the kernel for any geometry 2159.
+    const uint64_t held = std::min<uint64_t>(wgs(), SKL_N_CU * (SKL_LDS_HARD_BYTES / tile_prompt_table_bytes(L)));
     while (nw > 1 && nw <= 8 && held * (nw / 2) >= 8 * SKL_N_CU) nw /= 2;
     nw = std::min(nw, (L->in + 31) / 32);
+    return {RB, ob, nw};
+}
+
+// Whether a decode call takes the prompt kernel: two estimates in us, of its time and that of the kernels it stands in for (one
+// launch for small layers, or partial sums and their reduction), both fitted to 1213 measured calls (512 to 8192 input rows,
+// 128 to 8192 outputs, groups of 8 to 512 x 16 to 512, d = 1 to 8, both query modes, 8-bit and 16-bit states, batch 2 to 16; 10 %
+// off on average).  What it gains by is one launch and no partial sums (2048 x 2048 in groups of 128, batch 16, 9.9 / 23.0 us) and
+// weights that are rebuilt once for 16 rows instead of for four; what it can lose by is that a wavefront stages whole tables, one
+// after the other, and walks its share of all input rows: 5632 x 512 in groups of 512, d = 4 (tables of 64 KB), batch 9, 54 /
+// 31; 5088 x 4864 in groups of 16 x 128 (318 tables), batch 4, 69 / 43; 944 x 256, d = 8, batch 3, 10.5 / 8.6.  The choice is slower
+// by more than 3 % in 20 of the calls (26 % at most), that of the rule before it, which left the tables out and took every layer of
+// up to 1024 rows, in 107 (76 %).  Layers of fewer than 128 outputs or 512 input rows stay with the other kernels.
+static double tile_prompt_us(const skl_layer *L, uint32_t batch)
+{
+    const TilePromptShape sh = tile_prompt_shape(L, batch);
+    const uint32_t at_once = tile_prompt_tables(L), full = L->n_jb / at_once, rest = L->n_jb % at_once, rows = 32 * sh.nw;
+    auto up = [](uint32_t a, uint32_t b) { return (double)((a + b - 1) / b); };
+    const double table = 0.135 + 0.325 * up((uint32_t)tile_key_words(L), 256);          // one, by a wavefront
+    const double stage = (full * up(at_once, sh.nw) + up(rest, sh.nw)) * table * (L->qbits ? 1.6 : 1.0);      // (expanded ones come from afar)
+    const double steps = (full * up(at_once * L->tj, rows) + up(rest * L->tj, rows)) * (sh.ob == 2 ? 1.15 : 1.0) * (0.644 + 0.257 * L->d);
+    const double alone = 2.02 + stage + steps + 0.437 * (full + (rest > 0));
+    const double filled = (double)L->in * L->out / (1u << 26) * (20.0 + 11.7 * L->d);
+    return std::pow(std::pow(alone, 5) + std::pow(filled, 5), 0.2);
+}
+
+static double tile_gemv_us(const skl_layer *L, uint32_t batch)
+{
+    const uint32_t passes = (batch + 3) / 4;
+    if (skl_tile_gemv_is_small(L, batch)) {
+        const bool two = (uint64_t)L->n_ob * ((L->to + TS_O - 1) / TS_O) * passes > SKL_N_CU;
+        return 3.27 + L->n_jb * (0.175 + 0.0056 * L->d) + L->in / 64.0 * (0.0908 + 0.0344 * L->d) * (two ? 2.28 : 1.0) +
+               0.4386 / 1024 * L->n_jb * tile_key_words(L);
+    }
+    return 5.55 + 0.0214 * L->n_units + (double)L->in * L->out / (1u << 26) * (20.07 + 9.06 * L->d) * passes * std::max(1.0, 64.0 / L->to) +
+           1.69e-6 * L->n_units * L->out * batch;
+}
+
+bool skl_tile_prompt_decodes(const skl_layer *L, uint32_t batch)
+{
+    return batch >= 2 && L->in >= 512 && L->out >= 128 && skl_tile_prompt_fits(L) && tile_prompt_us(L, batch) < tile_gemv_us(L, batch);
+}
+
+skl_status_t skl_tile_launch_prompt(const skl_layer *L, const TableSrc &src, const uint16_t *X, skl_dtype_t x_dt, uint32_t ldx, void *Y,
+                                    skl_dtype_t y_dt, uint32_t ldy, uint32_t tokens, hipStream_t stream)
+{
+    skl_status_t st = SKL_OK;
+    const TileArgs a = make_tile_args(L, src);
+    const uint32_t kw = (uint32_t)tile_key_words(L), at_once = tile_prompt_tables(L);
+    const size_t tables = tile_prompt_table_bytes(L);
+    const TilePromptShape sh = tile_prompt_shape(L, tokens);
+    const uint32_t RB = sh.RB, ob = sh.ob, nw = sh.nw;
+    const dim3 tiles(L->out / (16 * ob), ((tokens + 15) / 16 + RB - 1) / RB);
     const size_t need = std::max<size_t>(tables, (size_t)nw * std::min(RB * ob, TP_RED_BYTES / 1024 / nw) * 1024);
     auto launch = [&](auto kernel) {
         st = allow_lds(kernel, need);

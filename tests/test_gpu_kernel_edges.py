@@ -471,6 +471,30 @@ def test_group_decode_of_several_rows(in_f, out_f, tile_in, tile_out, d, widths,
     assert np.isfinite(y).all() and rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
 
 
+@pytest.mark.parametrize("in_f,out_f,tile_in,tile_out,d,K,batch,one_launch", [
+    (1024, 512, 256, 512, 5, 3276, 4, False),       # tables of 32 KB, one at a time by one wavefront: partial sums
+    (944, 256, 16, 256, 8, 16, 3, False),           # 59 tables above an output and eight sketch rows
+    (2048, 256, 16, 64, 1, 8, 2, True),             # 128 tables, but 256 partial sums per output in the split form
+    (640, 512, 64, 128, 2, 128, 16, True),          # ten small ones
+    (1024, 1024, 128, 128, 3, 170, 9, True),
+])
+def test_group_decode_of_several_rows_by_tables(in_f, out_f, tile_in, tile_out, d, K, batch, one_launch):
+    """Both sides of the rule that prices the tables above an output; only the split form writes to the workspace."""
+    rng = np.random.default_rng(in_f + out_f)
+    A, C = hash_params(rng, d)
+    n = (in_f // tile_in) * (out_f // tile_out)
+    states = (rng.standard_normal(n * K * d) * 0.02).astype(np.float16).view(np.uint16)
+    sk = oracle.Sketch(in_f, out_f, tile_in, tile_out, d, A, C, np.full(n, K, dtype=np.uint32), states)
+    x = rng.standard_normal((batch, in_f)).astype(np.float16)
+    ref = matmul_f64(oracle.query(sk), x, "f16")
+    with GpuLayer(sk) as g:
+        ws, need = g.workspace(0, batch)
+        ws.fill_(0xA5)
+        y = g.gemv(x, "f32")
+        assert bool((ws[:need] == 0xA5).all()) == one_launch
+    assert np.isfinite(y).all() and rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
+
+
 @pytest.mark.parametrize("query_mode", [0, 1])
 @pytest.mark.parametrize("in_f,out_f,d,widths,batch", [
     (777, 1500, 4, (9, 200, 330, 1300), 1),     # blocks of all widths, some groups with one table buffer, some of one block
