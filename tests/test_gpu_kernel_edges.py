@@ -528,6 +528,40 @@ def test_decode_runs_of_blocks(in_f, out_f, d, widths, batch, query_mode):
     assert np.isfinite(y).all() and rel_fro(y, ref) <= SUM_TOL, rel_fro(y, ref)
 
 
+@pytest.mark.parametrize("query_mode", [0, 1])
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("in_f,out_f,d,widths", [
+    (777, 1500, 4, (9, 200, 330, 1300)),        # blocks of all widths
+    (300, 700, 1, (3, 1200, 1700, 4060)),
+    (900, 600, 8, (9, 120, 450)),
+])
+def test_staged_prompts_expand_codes_in_either_query_mode(in_f, out_f, d, widths, bits, query_mode):
+    """The rebuild launch expands codes while it stages a table: zeros of either sign included (a negative code with scale 0 stands
+    for -0, which the signed maximum ranks below +0)."""
+    rng = np.random.default_rng(in_f + bits)
+    A, C = hash_params(rng, d)
+    K = np.where(rng.random(in_f) < 0.1, rng.choice(widths[1:], in_f), widths[0]).astype(np.uint32)
+    qmax = 127 if bits == 8 else 7
+    codes = rng.integers(-qmax, qmax + 1, size=int(K.sum()) * d).astype(np.int8)
+    scales = (rng.random(in_f * d) * 0.1).astype(np.float16)
+    scales[rng.random(in_f * d) < 0.2] = 0
+    scales = scales.view(np.uint16)
+    states = oracle.dequantize_states(in_f, out_f, 1, out_f, d, K, bits, codes, scales)
+    q = oracle.QuantSketch(in_f, out_f, 1, out_f, d, A, C, K, states, bits=bits, codes=codes, scales=scales)
+    X = wk.f32_to_bf16_bits(rng.standard_normal((600, in_f)).astype(np.float32))
+    ref = matmul_f64(oracle.query(q, query_mode), X, "bf16")
+    with GpuLayer(q, skl.FLAG_STAGED_PREFILL, query_mode) as g:
+        for tokens in (40, 200, 600):
+            y = g.gemm(X[:tokens], "bf16", "f32")
+            assert np.isfinite(y).all() and worst_tile_rel_fro(y, ref[:tokens]) <= SUM_TOL, tokens
+        # a call that multiplies by one puts the rebuilt weights out: bit for bit, but for the sign of a zero
+        ones = np.zeros((64, in_f), dtype=np.uint16)
+        rows = rng.choice(in_f, 64, replace=False)
+        ones[np.arange(64), rows] = 0x3F80
+        w = oracle.query(q, query_mode).view(np.float16).astype(np.float32)[rows]
+        assert np.array_equal(g.gemm(ones, "bf16", "f32"), w)
+
+
 @pytest.mark.parametrize("in_f,out_f,d,K", [
     (32768, 4096, 1, 2),        # tables of 288 bytes in the only buffer, groups of 1024 channels
     (65536, 2048, 4, 1),        # 576 bytes
