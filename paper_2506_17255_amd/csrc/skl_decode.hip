@@ -422,6 +422,8 @@ struct GnWalk {
 template <int D>
 __device__ __forceinline__ void gn_copy(uint4 *dst, const StreamArgs &p, const RowBlock &b, uint32_t lane)
 {
+    // (whole chunks, in the table area: behind it lie the activations)
+    if (!skl_in_range((uint32_t)((dst - smem) * 16) + max(1024u, D * b.K * b.rs * 16), p.tab_bytes + 1, SKL_DBG_LDS_COPY)) return;
     ChunkCopy copy;
     copy.start(p.r.tables + b.table_off16, D * b.K * b.rs, (uint32_t)(uintptr_t)(lds_void *)dst, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
                blockDim.x >> 6, lane);

@@ -380,6 +380,7 @@ __global__ __launch_bounds__(OB == 2 ? 512 : 1024) void k_tile_prompt(TileArgs p
         if (jb0) __syncthreads();                               // nobody reads the tables before these any more
         for (uint32_t jb = jb0 + wave; jb < jb1; jb += nw) {
             const skl_group_meta gm = p.gmeta[jb * p.n_ob + ob];
+            if (!skl_in_range(D * gm.K, key_words * 8 + 1, SKL_DBG_LDS_COPY)) continue;
             if (lane == 0) width[jb - jb0] = gm.K;
             stage_by_wave(reinterpret_cast<uint16_t *>(smem + (jb - jb0) * key_words), p.keys + gm.key_off, D * gm.K, lane);
         }
@@ -405,7 +406,8 @@ __global__ __launch_bounds__(OB == 2 ? 512 : 1024) void k_tile_prompt(TileArgs p
                     uint32_t m = 0;
 #pragma unroll
                     for (int r = 0; r < D; ++r) {
-                        const uint32_t at = r * K + select_index(th.t[r], Kq);
+                        uint32_t at = r * K + select_index(th.t[r], Kq);
+                        if (!skl_in_range(at, key_words * 8, SKL_DBG_LDS_READ)) at = 0;
                         m = max(m, (uint32_t)*(const __attribute__((address_space(3))) uint16_t *)(uintptr_t)(tab + at * 2));
                         th.t[r] += th.step[r];
                     }

@@ -35,6 +35,24 @@ def test_parity_suite_on_the_build_with_range_asserts():
     assert " passed" in res.stdout
 
 
+@pytest.mark.gpu
+@pytest.mark.skipif("debug" in os.path.basename(os.environ.get("SKETCH_LINEAR_LIB", "")), reason="already inside the debug run")
+def test_edges_of_kernels_on_the_build_with_range_asserts():
+    """Decode runs, small tables, prompts in one pass and through 2-D groups, expansion while staging."""
+    assert os.path.exists(skl_build.DEBUG_LIB), "build it first: python -m paper_2506_17255_amd.build --debug-bounds"
+    env = dict(os.environ, SKETCH_LINEAR_LIB=skl_build.DEBUG_LIB)
+    res = subprocess.run([sys.executable, "-u", "-m", "pytest", "-x", "-q", "-m", "gpu", "-p", "no:cacheprovider", "--timeout", "300",
+                          "--timeout-method", "thread", "tests/test_gpu_kernel_edges.py", "-k", EDGES], cwd=ROOT, env=env,
+                         capture_output=True, text=True, timeout=1200)
+    report = res.stdout[-3000:] + res.stderr[-2000:]
+    assert res.returncode == 0, report
+    assert "range asserts of the debug build: 0 violation(s)" in res.stdout, report
+    assert " passed" in res.stdout
+
+
+EDGES = "decode_runs or smaller_than_a_chunk or group_prompts or group_decode or expand_codes or one_pass"
+
+
 SELFTEST = """
 import torch, paper_2506_17255_amd as skl
 torch.zeros(1, device="cuda:0")
