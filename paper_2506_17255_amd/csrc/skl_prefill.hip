@@ -527,13 +527,13 @@ skl_status_t skl_launch_gemm(const skl_layer *L, const void *X_, skl_dtype_t x_d
 {
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     const uint16_t *X = static_cast<const uint16_t *>(X_);
-    // the rebuild kernel and the one-pass kernel read the padded tables, the fused kernel the unpadded ones (low-bit states: the
-    // rebuild kernel takes codes and scales, and the tables are not expanded)
+    // the rebuild kernel and the one-pass kernel read the padded tables, the fused kernel the unpadded ones (low-bit states: where the
+    // rebuild kernel takes codes and scales, the tables are not expanded)
     TableSrc src;
     PromptPlan prompt{};
     const bool one_pass = L->path == 1 && takes_prompt_kernel(L, tokens, staged, prompt);
     skl_status_t st = SKL_OK;
-    if (!L->qbits || L->path != 1 || one_pass || !staged)
+    if (!L->qbits || L->path != 1 || one_pass || !staged || !skl_rebuilds_from_codes(L))
         st = skl_table_source(L, static_cast<char *>(ws) + round256(gemm_own_bytes(L, tokens, staged)), L->path == 1 && (staged || one_pass),
                               L->path == 1 && !staged && !one_pass, stream, &src);
     if (st != SKL_OK) return st;

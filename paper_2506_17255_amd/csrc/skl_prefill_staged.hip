@@ -738,7 +738,7 @@ skl_status_t skl_launch_gemm_staged(const skl_layer *L, const TableSrc &src, con
             st = allow_lds(kernel, lds);
             if (st == SKL_OK) hipLaunchKernelGGL(kernel, grid, dim3(SG_REBUILD_WG), lds, stream, r, k, n_pack);
         };
-        DISPATCH_D(L->d, { L->qbits == 0 ? rebuild(k_rebuild_operands<D, 16>) : L->qbits == 8 ? rebuild(k_rebuild_operands<D, 8>) : rebuild(k_rebuild_operands<D, 4>); })
+        DISPATCH_D(L->d, { !skl_rebuilds_from_codes(L) ? rebuild(k_rebuild_operands<D, 16>) : L->qbits == 8 ? rebuild(k_rebuild_operands<D, 8>) : rebuild(k_rebuild_operands<D, 4>); })
         if (st == SKL_OK) st = check_launch("operand rebuild");
         if (st != SKL_OK) return st;
 

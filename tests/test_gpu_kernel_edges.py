@@ -534,6 +534,7 @@ def test_decode_runs_of_blocks(in_f, out_f, d, widths, batch, query_mode):
     (777, 1500, 4, (9, 200, 330, 1300)),        # blocks of all widths
     (300, 700, 1, (3, 1200, 1700, 4060)),
     (900, 600, 8, (9, 120, 450)),
+    (90, 900, 4, (700, 1500)),                  # one-word blocks alone: 8-bit codes are expanded by a launch of their own
 ])
 def test_staged_prompts_expand_codes_in_either_query_mode(in_f, out_f, d, widths, bits, query_mode):
     """The rebuild launch expands codes while it stages a table: zeros of either sign included (a negative code with scale 0 stands
