@@ -33,8 +33,9 @@
  *             [-qmax, qmax], qmax = 127 (8 bit) or 7 (4 bit), in the order of
  *             `states`.  The state a code stands for is q * scale / qmax
  *             rounded once to binary16 (nearest even).  Such a layer keeps
- *             only codes and scales resident in dev_buf; every call expands
- *             them into the kernels' 16-bit tables inside its workspace.
+ *             only codes and scales resident in dev_buf; a call expands them
+ *             into the kernels' 16-bit tables inside its workspace, or block
+ *             by block on chip (most staged prompts).
  *
  * General rules
  *   - Every function returns a status code and never throws, aborts or
@@ -186,7 +187,8 @@ SKL_API skl_status_t sketch_linear_plan(const skl_desc_t *desc, uint32_t segment
  * (op = 1, n = tokens) or reconstruct (op = 2, n ignored).  The workspace
  * holds the partial sums of the split reduction (gemv), the re-ordered fp16
  * activations and partial tiles (gemm) and, for layers with low-bit states,
- * the 16-bit tables expanded for the call; its contents are scratch.
+ * room for the 16-bit tables expanded for the call (asked for in every case,
+ * though not every kernel uses it); its contents are scratch.
  * The need of gemm does not grow with n throughout.  Staged calls
  * (SKL_PREFILL_STAGED) hold the layer's dense weights on top, so that a short
  * prompt (n <= 128) may need more than one of 129 to prefill_staged_from - 1

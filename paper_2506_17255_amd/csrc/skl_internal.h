@@ -131,7 +131,8 @@ struct skl_layer {
     uint32_t gemm_prompt = 0, gemm_steps32 = 0;
 
     // low-bit states: only codes and scales are resident (row sketches: re-ordered into the word order of the
-    // block tables); every call expands them into 16-bit tables at the end of its workspace
+    // block tables); calls expand them into 16-bit tables at the end of their workspace, the rebuild launch of staged prompts in
+    // LDS (skl_rebuilds_from_codes)
     uint32_t qbits = 0;             // 0 (binary16 states), 8 or 4
     uint64_t off_codes = 0, off_scales = 0, code_bytes = 0, scale_bytes = 0;
     uint32_t scale_words = 0;       // row sketches: 16-byte scale words over all blocks
@@ -184,7 +185,7 @@ static inline uint16_t skl_key_of_half(uint16_t b, uint32_t mode)
 skl_status_t skl_launch_reconstruct(const skl_layer *L, uint16_t *W_hat, void *ws, void *stream);
 // the hash-based operator as a comparator: per-weight select, states fetched from device memory (skl_naive.hip)
 skl_status_t skl_launch_reconstruct_naive(const skl_layer *L, uint16_t *W_hat, void *ws, void *stream);
-// bytes of expanded tables at the end of every workspace of a layer with low-bit states (else 0)
+// room for expanded tables at the end of every workspace of a layer with low-bit states (else 0)
 uint64_t skl_dequant_bytes(const skl_layer *L);
 uint64_t skl_reconstruct_workspace_bytes(const skl_layer *L);
 // with_reduction = false: partial sums only (y, y_dt, ldy unused)

@@ -2,9 +2,10 @@
 
 // ========================================================================
 // Low-bit states: codes -> order keys.  A layer with 8- or 4-bit states keeps
-// only codes and one binary16 scale per (group, sketch row) resident; every
-// call first expands them into the 16-bit tables its kernels read (the same
-// layouts create() builds on the host for binary16 states).  The state a code
+// only codes and one binary16 scale per (group, sketch row) resident; a call
+// first expands them into the 16-bit tables its kernels read (the same
+// layouts create() builds on the host for binary16 states), but for staged
+// prompts whose rebuild launch expands a block's table in LDS.  The state a code
 // stands for is q * scale / qmax rounded once to binary16.  It is computed in
 // float32 as |q| * (scale * (1 / qmax)): three roundings, 1.5 * 2^-23 relative
 // in all.  The exact quotient m / qmax (m an integer of at most 18 bits) is

@@ -60,12 +60,13 @@ __device__ __forceinline__ uint32_t neg_half_pair(uint32_t e, uint32_t x_dt)
 // Activations to negated binary16, re-ordered into matrix-core A words, a word being eight entries of the channel list
 // for one token: lane l of a wavefront builds the word of token l % 16 and channel group l / 16 of a 32-channel step,
 // and place(step) says where in the caller's layout it goes.  A workgroup takes 16 tokens x PO_STEPS steps: it copies the window of X that holds
-// the steps' channels into LDS in its own order (whole aligned 16-byte pieces, coalesced) and builds the words from
+// the steps' channels into LDS in its own order (coalesced 16-byte pieces) and builds the words from
 // 2-byte LDS reads, so that the channels which the width order moved away cost nothing (fetching every word that
 // spans such a gap channel by channel from memory took 5 of 15 us on layers with one percent of wide channels).
 // Steps whose channels are far apart (the wide channels themselves) have no window and are fetched from memory.
 // 2048 tokens x 4096 channels of such a layer, 16.8 MB in and out: 10 us, 15 before (5.1 TB/s would be 6.6).
-// All loads of a stretch are on their way before the first is needed, and rows on any 2-byte boundary take 16-byte pieces:
+// All loads of a stretch are on their way before the first is needed, rows on any 2-byte boundary take 16-byte pieces, and a piece
+// that would reach past the end of a row is fetched by element:
 // with a wait after every piece, and by element where rows do not start on 16-byte boundaries, whole calls took 26.8 us
 // (3001 x 7003, 77 tokens; now 22.2), 36.7 (5001 x 3000, 200 tokens; 32.0), 23.4 (4096 x 11008, 17 tokens; 22.8).
 #define PO_STRIDE (PO_WINDOW + 8u)      // halfs per LDS row: 16-byte aligned rows on different banks
