@@ -16,11 +16,14 @@ skl_status_t skl_launch_gemm_prompt(const skl_layer *L, const TableSrc &src, con
 
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-// Whether the rebuild launch of staged calls expands low-bit states itself.  One-word blocks have the most table per weight, and
-// with 8-bit codes a workgroup takes longer to expand one than the two launches differ: 47 x 6454, d = 4, four times the states of
-// 1 bit per weight, 24 tokens 12.5 us with a launch of its own before, 13.6 without, 1816 x 7128, 100 tokens, 35.3 / 36.1 (4-bit codes:
-// 1898 x 5642, d = 3, 33.8 / 31.7).
-inline bool skl_rebuilds_from_codes(const skl_layer *L) { return L->qbits == 4 || (L->qbits == 8 && L->block_classes != 1u); }
+// Whether the rebuild launch of staged calls expands low-bit states itself.  A workgroup takes longer to expand a table than to copy
+// it, and with a handful of channel blocks a table beyond the LDS buffers is the tail of the launch: 47 x 6454, d = 4, four bits
+// per weight as 8-bit codes (tables of 25 KB, one of 100), 24 tokens, 12.5 us with a launch of its own before, 13.6 without, 37 x
+// 26524, d = 6 (103 KB), 14.9 / 15.9; but 54 x 11872 (46 KB) 10.4 / 9.95, 301 x 6206 (38 blocks, one of 100 KB), 786 tokens, 26.0 / 25.0.
+inline bool skl_rebuilds_from_codes(const skl_layer *L)
+{
+    return L->qbits == 4 || (L->qbits == 8 && (L->n_blocks > 8 || L->max_table_bytes <= SKL_LDS_SOFT_TABLE_BYTES));
+}
 
 typedef uint32_t u32x4h __attribute__((ext_vector_type(4), aligned(2)));     // eight 16-bit elements on any 2-byte boundary
 

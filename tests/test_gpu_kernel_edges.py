@@ -534,7 +534,8 @@ def test_decode_runs_of_blocks(in_f, out_f, d, widths, batch, query_mode):
     (777, 1500, 4, (9, 200, 330, 1300)),        # blocks of all widths
     (300, 700, 1, (3, 1200, 1700, 4060)),
     (900, 600, 8, (9, 120, 450)),
-    (90, 900, 4, (700, 1500)),                  # one-word blocks alone: 8-bit codes are expanded by a launch of their own
+    (50, 900, 4, (700, 1500)),                  # eight blocks with a large table among them: 8-bit codes are expanded by a launch of their own
+    (90, 900, 4, (700, 1500)),                  # more blocks
 ])
 def test_staged_prompts_expand_codes_in_either_query_mode(in_f, out_f, d, widths, bits, query_mode):
     """The rebuild launch expands codes while it stages a table: zeros of either sign included (a negative code with scale 0 stands
@@ -557,7 +558,7 @@ def test_staged_prompts_expand_codes_in_either_query_mode(in_f, out_f, d, widths
             assert np.isfinite(y).all() and worst_tile_rel_fro(y, ref[:tokens]) <= SUM_TOL, tokens
         # a call that multiplies by one puts the rebuilt weights out: bit for bit, but for the sign of a zero
         ones = np.zeros((64, in_f), dtype=np.uint16)
-        rows = rng.choice(in_f, 64, replace=False)
+        rows = rng.choice(in_f, 64, replace=in_f < 64)
         ones[np.arange(64), rows] = 0x3F80
         w = oracle.query(q, query_mode).view(np.float16).astype(np.float32)[rows]
         assert np.array_equal(g.gemm(ones, "bf16", "f32"), w)
